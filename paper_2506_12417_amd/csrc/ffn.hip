@@ -151,6 +151,21 @@ extern "C" int moe_ffn_kernel_mode(int mode) {
     return before;
 }
 
+// Whether the few-row kernels (ffn_rows.hip) serve a plan of 128-row tiles.  A product is then the
+// fetch of the active experts' weights; the tile kernels fetch an expert through one XCD, the
+// few-row kernels through the whole chip, but these read the rows again for every 32 weight rows.
+// Measured (both products, few-row against tile kernels): with more experts than XCDs they win up
+// to about three rows per expert (d=2048 F=1408 E=60: 163 : 184 us at 2.2 rows, 197 : 197 at 4.3;
+// d=768 F=3072 E=128: 158 : 171 at 2, 210 : 193 at 4), with one expert per XCD up to two (d=4096
+// F=14336 E=8: 347 : 348 us at 2, 490 : 445 at 4), and with fewer experts than XCDs up to the row
+// count at which the idle XCDs are made up for (d=2048 F=5632, E=4: 98 : 112 us at 32 rows, 141 :
+// 121 at 64; E=1: 64 : 102 us at 64 rows, 124 : 113 at 128).
+static bool few_rows_per_expert(int A, int E) {
+    if (A <= (E >= 16 ? 3 : 2) * E) return true;
+    if (E >= 8) return false;
+    return A <= 64 * E && (long long)A * E <= 32ll * (8 - E) * E;
+}
+
 static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F, int E, moe_act act, moe_dtype dt,
                             const void* const* w_in, const void* const* w_out, const moe_tile* tiles,
                             int32_t* plan_hdr, int tile_m, void* h_scratch, float* y_perm, void* stream,
@@ -190,9 +205,15 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1).
         auto wide = [&](int epi, int K) { return tile_m == 256 && g_kernel_mode != 1 && moe_gemm_wide_supports(epi, K); };
+        const bool rows = tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
         if (phases & 1) {
             const int epi = act == MOE_SWIGLU ? MOE_EPI_SWIGLU : MOE_EPI_RELU;
-            if (gather.on && stream(epi, d))
+            if (rows && gather.on)
+                rc = moe_launch_gemm_rows_gather(epi, x_perm, A, d, n1, E, w_in, tiles, plan_hdr, h_scratch, F, st, gather.perm,
+                                                 gather.k);
+            else if (rows)
+                rc = moe_launch_gemm_rows(epi, x_perm, A, d, n1, E, w_in, tiles, plan_hdr, h_scratch, F, st);
+            else if (gather.on && stream(epi, d))
                 rc = moe_launch_gemm_stream_gather(stream_narrow(n1), x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr,
                                                    h_scratch, F, st, gather.perm, gather.k);
             else if (gather.on && tile_m == 256)
@@ -213,7 +234,10 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         }
         if (phases & 2) {
             const int epi = top1.on ? MOE_EPI_SCATTER : MOE_EPI_STORE;
-            if (stream(epi, F))
+            if (rows)
+                rc = moe_launch_gemm_rows(epi, h_scratch, A, F, d, E, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
+                                          top1.gate_w);
+            else if (stream(epi, F))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(d), h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st,
                                             top1.perm, top1.gate_w, top1.on ? A : 0);
             else if (wide(epi, F))

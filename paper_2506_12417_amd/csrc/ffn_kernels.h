@@ -46,6 +46,16 @@ int moe_launch_gemm_wide_gather(int epi, const void* x, int x_rows, int K, int N
                                 const moe_tile* tiles, const int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div);
 
+// The same products for experts that hold a handful of rows each, by the kernels of ffn_rows.hip
+// (tiles of at most 128 rows; the fetch of the weights is the work and uses the whole chip,
+// whatever the plan's bins).  All four epilogues, and the first product with the row gather folded
+// in (arguments as for the launchers above; A rows in the table).
+int moe_launch_gemm_rows(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
+                         const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_token = nullptr,
+                         const float* row_gate = nullptr);
+int moe_launch_gemm_rows_gather(int epi, const void* x, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
+                                const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div);
+
 // MOE_OK if the current device is the GPU the persistent launches are laid out for (256 compute
 // units in 8 XCDs), else MOE_ERR_UNSUPPORTED.
 int moe_check_gemm_device();

@@ -524,6 +524,70 @@ def test_streaming_kernels_give_the_bits_of_the_lds_ring_kernels(torch_gpu, T, d
     assert max_err_over_rms(to_numpy(out[2][0]), y_o) <= TOL["bf16"]
 
 
+def _few(rows):
+    """rows per expert -> the routed ids, in a fixed shuffled order"""
+    ids = np.repeat(np.arange(len(rows)), rows)
+    return np.random.default_rng(len(ids)).permutation(ids).astype(np.int32)
+
+
+FEW_ROW_CASES = [
+    # rows per expert, k, d, F, act, policy: row groups of 16 (1, 15, 16, 17, 33, 48, 49, 64 rows), more than one pass of
+    # 64 rows and more than one tile, idle wavefronts (K = 64: two slices), four and eight wavefronts per item,
+    # items of one weight block, six and eight slices per round, more tiles than the launch counts on
+    ([1], 1, 64, 64, "relu", 1),
+    ([1, 0, 0, 1], 2, 256, 512, "swiglu", 1),
+    ([16], 1, 768, 3072, "relu", 1),
+    ([17], 1, 2048, 576, "swiglu", 1),
+    ([33], 1, 2048, 4160, "relu", 1),
+    ([48, 49], 1, 192, 320, "relu", 1),
+    ([64], 1, 320, 2112, "swiglu", 1),
+    ([15, 1, 2] + [0] * 5, 2, 1408, 256, "swiglu", 1),
+    ([110] + [0] * 20 + [1] * 39, 1, 256, 512, "relu", 1),
+    ([170] + [0] * 60 + [2] * 3, 4, 320, 192, "swiglu", 1),
+    ([2] * 32, 1, 256, 512, "relu", 3),
+    ([3] * 16, 2, 2048, 2048, "relu", 3),
+]
+
+
+@pytest.mark.parametrize("rows,k,d,F,act,policy", FEW_ROW_CASES)
+def test_few_row_kernels_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, policy):
+    """Decode-sized calls (a handful of rows per expert) run by the few-row kernels: hidden
+    activations and outputs against the oracle that rounds them to half, as for every bf16 layer,
+    and the fused entry points against the separate ones bit for bit."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    assert A % k == 0
+    T = A // k
+    wl = W.WORKLOADS["c2"].scaled(T=T, d=d, F=F, E=E, k=k, act=act, skew="uniform")
+    _note("few rows A=%d E=%d d=%d F=%d k=%d %s policy %d" % (A, E, d, F, k, act, policy))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, inp, tile_m=128, n_bins=8 if policy == 1 else 16, policy=policy)
+    ids = _few(rows).reshape(T, k)
+    gate = np.random.default_rng(3).random((T, k)).astype(np.float32)
+    layer.expert_idx.copy_(to_device(ids, layer.device))
+    layer.gate_w.copy_(to_device(gate, layer.device))
+    for t in (layer.h, layer.y_perm, layer.y):
+        t.fill_(float("nan"))
+    x = layer_x(layer, inp)
+    y = layer.forward(x, routed=True).clone()
+    h = layer.h.clone()
+    layer.permute(x)
+    layer.plan()
+    for t in (layer.h, layer.y_perm):
+        t.fill_(float("nan"))
+    layer.ffn()
+    layer.combine(True)
+    torch.cuda.synchronize()
+    assert torch.equal(h.view(torch.int16), layer.h.view(torch.int16)) and torch.equal(y, layer.y)
+    p = O.permute(ids, E)
+    yp = O.grouped_ffn(O.gather_rows(inp["x"], p["perm"], k), p["offsets"], expert_dict(wl, inp), act, h_round="f16")
+    # as in _stage_check: one-ulp flips of the half rounding of h are what is left
+    assert max_err_over_rms(to_numpy(layer.y_perm), yp) <= 1e-3
+    assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()      # the work counters stay zero
+
+
 WIDE_CASES = [
     # T, d, F, E, k, act, skew, bins: the four-wavefront kernels for 256-row tiles against the LDS-ring kernels
     (3000, 256, 512, 4, 2, "swiglu", "hot", 8),       # full and ragged tiles, several column blocks
