@@ -276,6 +276,11 @@ int dispatch_route(const void* x, const void* wg, const float* bias, int T, int 
 
 }  // namespace
 
+int moe_route_small(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
+                    float* logits, hipStream_t st) {
+    return dispatch_route<uint16_t>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+}
+
 // bf16 inputs: the MFMA kernel of route_mfma.hip
 int moe_route_bf16_mfma(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm,
                         int32_t* idx, float* w, float* logits, hipStream_t st);

@@ -1,17 +1,21 @@
-// moe_route_topk for bf16 inputs: the router product on the matrix cores (Alg. 1 step 1).
+// moe_route_topk and moe_route_topk_packed for bf16 inputs: the router product on the matrix cores
+// (Alg. 1 step 1).
 //
-// One work-group takes TB tokens (64, or 32 when E > 128).  Logits x.W_g are accumulated by
-// v_mfma_f32_32x32x16_bf16 in chunks of 64 terms (bf16 x bf16 products are exact in fp32); each
-// chunk's fp32 result is added into fp64 accumulators, so only the rounding inside a chunk
-// counts: |error| <= c * |x_t| * |w_e| with c = (2*64+6) * 2^-24 (two roundings per term allowed
-// for, since the accumulation order inside the instruction is not specified).  A token whose
-// deciding gaps are all wider than twice that bound keeps its fp32 selection; the others get the
-// logits of every expert that could still reach the top k recomputed in fp64 by a wavefront, so
-// expert indices and their order are those of exact arithmetic (ties to the lower index).
+// One work-group takes 32 tokens.  Logits x.W_g are accumulated by v_mfma_f32_32x32x16_bf16 in
+// chunks of KA terms (bf16 x bf16 products are exact in fp32); each chunk's fp32 result is added
+// into fp64 accumulators, so only the rounding inside a chunk counts: |error| <= c * |x_t| * |w_e|
+// with c = (2*KA+6) * 2^-24 (two roundings per term allowed for, since the accumulation order
+// inside the instruction is not specified).  A token whose deciding gaps are all wider than twice
+// that bound keeps its fp32 selection; the others get the logits of every expert that could still
+// reach the top k recomputed in fp64, so expert indices and their order are those of exact
+// arithmetic (ties to the lower index).
 //
-// W_g arrives as [d,E] (expert index contiguous); the MFMA wants the contraction index
-// contiguous for both operands, so each chunk of W_g is transposed on its way into LDS.
-// Selection: TPT = 256/TB threads scan one token's logits from LDS, keep a sorted top-(k+1)
+// The wavefronts of a work-group split the experts into blocks of 32 (NB blocks) and, when there
+// are fewer than four blocks, also the contraction (KSP parts); the partial sums of the parts are
+// added in a fixed order through LDS.  The two kernels differ in how the operands reach LDS:
+// route_packed_kernel reads a W_g prepared by moe_pack_router, route_plain_kernel W_g as given.
+//
+// Selection: eight or sixteen threads scan one token's logits from LDS, keep a sorted top-(k+1)
 // list in registers, and merge the lists with DPP exchanges inside their group of lanes.
 #include "common.h"
 #include <climits>
@@ -22,22 +26,23 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef u32x4 frag_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-constexpr int NTH = 256;
-constexpr int KC = 64;                 // terms per fp32 chunk (four MFMAs)
+constexpr int KC = 64;                 // terms per chunk (four MFMAs)
 constexpr int KACC = 256;              // prepared-router kernel: terms per fp32 accumulation
-constexpr int PK = KC + 8;             // LDS pitch of a K-row in bf16 elements (144 B: conflict-free 16 B reads)
 constexpr int MAXR = MOE_MAX_TOPK + 1;
 constexpr float NEG_INF = -__builtin_huge_valf();
 
 __device__ __forceinline__ bool beats(float av, int ae, float bv, int be) { return av > bv || (av == bv && ae < be); }
 __device__ __forceinline__ bool beats(double av, int ae, double bv, int be) { return av > bv || (av == bv && ae < be); }
 
-// exchange inside groups of 4 (steps 0,1) or 8 (step 2) neighbouring lanes
+// exchange inside groups of 4 (steps 0, 1), 8 (step 2) and 16 (step 3) neighbouring lanes
 template <int STEP> __device__ __forceinline__ int dpp_xchg(int v) {
     if (STEP == 0) return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false);    // quad_perm [1,0,3,2]
     if (STEP == 1) return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false);    // quad_perm [2,3,0,1]
-    return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false);                  // row_half_mirror
+    if (STEP == 2) return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false);   // row_half_mirror
+    return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false);                  // row_mirror
 }
 template <int STEP> __device__ __forceinline__ float dpp_xchg(float v) {
     return __int_as_float(dpp_xchg<STEP>(__float_as_int(v)));
@@ -45,21 +50,24 @@ template <int STEP> __device__ __forceinline__ float dpp_xchg(float v) {
 template <int TPT> __device__ __forceinline__ float group_max(float v) {
     v = fmaxf(v, dpp_xchg<0>(v));
     v = fmaxf(v, dpp_xchg<1>(v));
-    if (TPT == 8) v = fmaxf(v, dpp_xchg<2>(v));
+    if (TPT >= 8) v = fmaxf(v, dpp_xchg<2>(v));
+    if (TPT == 16) v = fmaxf(v, dpp_xchg<3>(v));
     return v;
 }
 // fixed pairing order, so every lane of the group gets the same bits
 template <int TPT> __device__ __forceinline__ float group_sum(float v) {
     v += dpp_xchg<0>(v);
     v += dpp_xchg<1>(v);
-    if (TPT == 8) v += dpp_xchg<2>(v);
+    if (TPT >= 8) v += dpp_xchg<2>(v);
+    if (TPT == 16) v += dpp_xchg<3>(v);
     return v;
 }
 template <int TPT> __device__ __forceinline__ void group_best(float& v, int& e) {
     float ov; int oe;
     ov = dpp_xchg<0>(v); oe = dpp_xchg<0>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
     ov = dpp_xchg<1>(v); oe = dpp_xchg<1>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
-    if (TPT == 8) { ov = dpp_xchg<2>(v); oe = dpp_xchg<2>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; } }
+    if (TPT >= 8) { ov = dpp_xchg<2>(v); oe = dpp_xchg<2>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; } }
+    if (TPT == 16) { ov = dpp_xchg<3>(v); oe = dpp_xchg<3>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; } }
 }
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
@@ -76,193 +84,149 @@ __device__ __forceinline__ void wave_best_f64(double& v, int& e) {
     }
 }
 
-// MT m-tiles of 32 tokens per work-group, NJ n-tiles of 32 experts per wavefront.
-// wave w: m-tile w % MT, n-tiles w / MT + (4 / MT) * j.
-template <int MT, int NJ>
-__global__ __launch_bounds__(NTH) void route_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
-                                                         const float* __restrict__ bias, int T, int d, int E, int k,
-                                                         int renorm, int32_t* __restrict__ idx_out,
-                                                         float* __restrict__ w_out, float* __restrict__ logits_out) {
-    constexpr int TB = 32 * MT;
-    constexpr int NW = 4 / MT;              // wavefronts along the expert axis
-    constexpr int EP = 32 * NW * NJ;        // padded expert count
-    constexpr int PL = EP + 4;              // pitch of a logit row (floats)
-    constexpr int TPT = NTH / TB;           // threads per token in the selection
-    __shared__ __attribute__((aligned(16))) uint16_t xs[TB * PK];
-    __shared__ __attribute__((aligned(16))) uint16_t wsT[EP * PK];
-    __shared__ float ls[TB * PL];
-    __shared__ float xn2[TB], part[NTH], red_w[4], red_b[4];
-    __shared__ int flag_tok[TB];
-    __shared__ float flag_thr[TB], flag_max[TB], flag_den[TB];
-    __shared__ int n_flag;
-    // the exact path's candidate lists reuse the W_g tile, which is dead by then (48*EP <= 80*EP bytes)
-    double (*cand_v)[EP] = reinterpret_cast<double (*)[EP]>(wsT);
-    int (*cand_e)[EP] = reinterpret_cast<int (*)[EP]>(wsT + 4 * EP * 4);
-    constexpr int CJ = (EP + 63) / 64;
+// LDS of the phases after the product (it reuses the memory of the operand staging).
+template <int NB, int KSP>
+struct RouteLds {
+    static constexpr int NWV = NB * KSP, NTHR = NWV * 64, TB = 32, EPT = 32 * NB;
+    static constexpr int PL = EPT + 4;               // pitch of a logit row (floats)
+    static constexpr int LIST = MOE_MAX_EXPERTS + 32;    // entries of a wavefront's candidate list
+    static constexpr int SLAB = KSP > 1 ? KSP * TB * EPT * 8 : 0;
+    static constexpr int CAND = NWV * LIST * 12;
+    static constexpr int REGION0 = SLAB > CAND ? SLAB : CAND;
+    static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 4 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Logits, softmax, top-k and the exact path, from the wavefronts' fp64 sums: acc64[r] = token
+// 8*(r/4) + 4*lhi + r%4, expert nbi*32 + l32, contraction part ksi.  xsq: this lane's share of the token
+// norms (wavefronts of expert block 0).  w2: this thread's share of the largest squared column
+// norm.  All threads of the work-group arrive with the staging memory no longer in use.
+template <int NB, int KSP, int RMAX, int KA, bool PACKED>
+__device__ __forceinline__ void route_finish(unsigned char* smem, const double (&acc64)[16], float xsq, float w2,
+                                             const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
+                                             const float* __restrict__ bias, int T, int d, int E, int k, int renorm,
+                                             int32_t* __restrict__ idx_out, float* __restrict__ w_out,
+                                             float* __restrict__ logits_out) {
+    typedef RouteLds<NB, KSP> L;
+    constexpr int NWV = L::NWV, NTHR = L::NTHR, TB = L::TB, EPT = L::EPT, PL = L::PL;
+    constexpr int TPT = NTHR / TB >= 16 ? 16 : 8;    // threads per token in the selection
+    double* slab = reinterpret_cast<double*>(smem);  // [KSP][32][EPT], later the candidate lists
+    float* ls = reinterpret_cast<float*>(smem + L::REGION0);     // logits [32][PL]
+    float* xn2p = ls + TB * PL;                      // [KSP][32]
+    int* flag_tok = reinterpret_cast<int*>(xn2p + KSP * TB);
+    float* flag_thr = reinterpret_cast<float*>(flag_tok + TB);
+    float* flag_max = flag_thr + TB;
+    float* flag_den = flag_max + TB;
+    float* red = flag_den + TB;                      // [2 * NWV]
+    int* n_cand = reinterpret_cast<int*>(red + 2 * NWV);         // [NWV]
+    int* n_flag = n_cand + NWV;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int wm = wave % MT, wn0 = wave / MT;
+    const int nbi = wave / KSP, ksi = wave % KSP;
     const int t0 = blockIdx.x * TB;
 
-    if (tid == 0) n_flag = 0;
+    if (tid == 0) *n_flag = 0;
 
-    double acc64[NJ][16];
+    // ---- logits.  acc64[r]: token 8*(r/4) + 4*lhi + r%4, expert nbi*32 + l32.
+    if (KSP > 1) {                                   // the partial sums of the contraction parts, fixed order
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc64[j][r] = 0.0;
-
-    // Register staging, one chunk ahead: the loads of chunk c+1 are in flight while chunk c is
-    // multiplied.  x: piece p = tid + u*NTH is 8 terms of token p / 8 at k offset (p % 8) * 8.
-    // W_g: piece u is element (kk, e) = ((tid + u*NTH) / EP, tid % EP) -- always the same column,
-    // so the column's sum of squares is kept in a register.
-    constexpr int XN = TB * (KC / 8) / NTH;
-    constexpr int WN = KC * EP / NTH;
-    u32x4 xv[XN];
-    uint16_t wv[WN];
-    float xsq[XN], wsq = 0.f;
-#pragma unroll
-    for (int u2 = 0; u2 < XN; ++u2) xsq[u2] = 0.f;
-    const int w_e = tid % EP, w_kk0 = tid / EP;
-    auto load_chunk = [&](int k0) {
-#pragma unroll
-        for (int u2 = 0; u2 < XN; ++u2) {
-            const int p = tid + u2 * NTH, tok = p >> 3, kk = (p & 7) * 8;
-            xv[u2] = (u32x4){0u, 0u, 0u, 0u};
-            if (t0 + tok < T && k0 + kk < d) xv[u2] = *(const u32x4*)(x + (size_t)(t0 + tok) * d + k0 + kk);
-        }
-#pragma unroll
-        for (int u2 = 0; u2 < WN; ++u2) {
-            const int kk = w_kk0 + u2 * (NTH / EP);
-            wv[u2] = (w_e < E && k0 + kk < d) ? wg[(size_t)(k0 + kk) * E + w_e] : (uint16_t)0;
-        }
-    };
-    // Work-groups start at different chunks: all of them reading the same 16 KB of W_g at the same
-    // moment would queue on a few L2 channels.
-    const int n_chunks = (d + KC - 1) / KC;
-    int chunk = blockIdx.x % n_chunks;
-    load_chunk(chunk * KC);
-    __syncthreads();
-
-    for (int c = 0; c < n_chunks; ++c) {
-#pragma unroll
-        for (int u2 = 0; u2 < XN; ++u2) {
-            const int p = tid + u2 * NTH, tok = p >> 3, kk = (p & 7) * 8;
-            *(u32x4*)(xs + tok * PK + kk) = xv[u2];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float lo = __uint_as_float(xv[u2][i] << 16), hi = __uint_as_float(xv[u2][i] & 0xffff0000u);
-                xsq[u2] = fmaf(lo, lo, xsq[u2]);
-                xsq[u2] = fmaf(hi, hi, xsq[u2]);
-            }
-        }
-#pragma unroll
-        for (int u2 = 0; u2 < WN; ++u2) {             // W_g chunk, transposed into LDS
-            wsT[w_e * PK + w_kk0 + u2 * (NTH / EP)] = wv[u2];
-            const float v = bf16_to_f32(wv[u2]);
-            wsq = fmaf(v, v, wsq);
+        for (int r = 0; r < 16; ++r) {
+            const int tok = 8 * (r >> 2) + 4 * lhi + (r & 3);
+            slab[(ksi * TB + tok) * EPT + nbi * 32 + l32] = acc64[r];
         }
         __syncthreads();
-        chunk = chunk + 1 == n_chunks ? 0 : chunk + 1;
-        if (c + 1 < n_chunks) load_chunk(chunk * KC);
-        f32x16 acc[NJ];
+        for (int i = tid; i < TB * EPT; i += NTHR) {
+            const int tok = i / EPT, e = i % EPT;
+            if (e < E) {
+                double v = slab[i];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KC / 16; ++ks) {
-            const bf16x8 a = *(const bf16x8*)(xs + (wm * 32 + l32) * PK + ks * 16 + lhi * 8);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const bf16x8 b = *(const bf16x8*)(wsT + ((wn0 + NW * j) * 32 + l32) * PK + ks * 16 + lhi * 8);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+                for (int p = 1; p < KSP; ++p) v += slab[p * TB * EPT + i];
+                const float l = (float)(v + (bias ? (double)bias[e] : 0.0));
+                ls[tok * PL + e] = l;
+                if (logits_out && t0 + tok < T) logits_out[(size_t)(t0 + tok) * E + e] = l;
             }
         }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc64[j][r] += (double)acc[j][r];
-        __syncthreads();
-    }
-
-    // ---- logits to LDS (fp32), token and column norms
-#pragma unroll
-    for (int u2 = 0; u2 < XN; ++u2) {              // the 8 threads of a token row are neighbours
-        float v = xsq[u2];
-        v += dpp_xchg<0>(v);
-        v += dpp_xchg<1>(v);
-        v += dpp_xchg<2>(v);
-        if ((tid & 7) == 0) xn2[(tid + u2 * NTH) >> 3] = v;
-    }
-    part[tid] = wsq;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int e = (wn0 + NW * j) * 32 + l32;
+    } else {
+        const int e = nbi * 32 + l32;
         const double be = (bias && e < E) ? (double)bias[e] : 0.0;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int tok = wm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-            const float l = (float)(acc64[j][r] + be);
+            const int tok = 8 * (r >> 2) + 4 * lhi + (r & 3);
+            const float l = (float)(acc64[r] + be);
             if (e < E) {
                 ls[tok * PL + e] = l;
                 if (logits_out && t0 + tok < T) logits_out[(size_t)(t0 + tok) * E + e] = l;
             }
         }
     }
-    __syncthreads();
-
-    {   // largest column norm and largest |bias|, reduced in parallel
-        float w2 = 0.f, bm = 0.f;
-        if (tid < E) {
-#pragma unroll
-            for (int j = 0; j < NTH / EP; ++j) w2 += part[tid + j * EP];
-            if (bias) bm = fabsf(bias[tid]);
-        }
+    // token norms: the two k-halves of a token sit in lanes l and l+32; the parts are added in a fixed order
+    xsq += __shfl_xor(xsq, 32);
+    if (nbi == 0 && lhi == 0) xn2p[ksi * TB + l32] = xsq;
+    {   // largest column norm and largest |bias|
+        float bm = 0.f;
+        if (bias)
+            for (int e = tid; e < E; e += NTHR) bm = fmaxf(bm, fabsf(bias[e]));
         w2 = moe_wave_max_nonneg(w2);
         bm = moe_wave_max_nonneg(bm);
-        if (lane == 0) { red_w[wave] = w2; red_b[wave] = bm; }
+        if (lane == 0) { red[wave] = w2; red[NWV + wave] = bm; }
     }
     __syncthreads();
-    const float wmax2 = fmaxf(fmaxf(red_w[0], red_w[1]), fmaxf(red_w[2], red_w[3]));
-    const float bmax = fmaxf(fmaxf(red_b[0], red_b[1]), fmaxf(red_b[2], red_b[3]));
+    float wmax2 = 0.f, bmax = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) { wmax2 = fmaxf(wmax2, red[w]); bmax = fmaxf(bmax, red[NWV + w]); }
     const float wn_max = sqrtf(wmax2) * 1.0001f;
     const int rounds = (k + 1 < E) ? k + 1 : E;
     const float u = 5.9604645e-8f;   // 2^-24
 
-    // ---- selection: TPT threads per token, thread `sub` scans experts sub, sub+TPT, ...
-    {
+    // ---- selection: TPT threads per token; thread `sub` takes the CPT
+    // consecutive experts from sub * CPT on, fetched with four-float reads before the scan (a read
+    // per expert inside the scan made it wait for LDS at every step)
+    if (tid < TB * TPT) {
+        constexpr int CPT = EPT / TPT;
+        static_assert(CPT % 4 == 0 && PL % 4 == 0, "four-float reads of a logit row");
         const int tok = tid / TPT, sub = tid % TPT, t = t0 + tok;
         const float* row = ls + tok * PL;
-        float lv[MAXR];
-        int le[MAXR];
+        float mine[CPT];
 #pragma unroll
-        for (int r = 0; r < MAXR; ++r) { lv[r] = NEG_INF; le[r] = INT_MAX; }
+        for (int j = 0; j < CPT; j += 4) {
+            const float4 q = *reinterpret_cast<const float4*>(row + sub * CPT + j);
+            mine[j] = q.x; mine[j + 1] = q.y; mine[j + 2] = q.z; mine[j + 3] = q.w;
+        }
+        float lv[RMAX];
+        int le[RMAX];
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) { lv[r] = NEG_INF; le[r] = INT_MAX; }
         float m = NEG_INF;
-        for (int e = sub; e < E; e += TPT) {
-            float v = row[e];
-            int ve = e;
-            m = fmaxf(m, v);
-            if (beats(v, ve, lv[MAXR - 1], le[MAXR - 1])) {     // sorted insertion, static indices
 #pragma unroll
-                for (int r = 0; r < MAXR; ++r) {
-                    if (beats(v, ve, lv[r], le[r])) {
-                        float tv = lv[r]; int te = le[r];
-                        lv[r] = v; le[r] = ve;
-                        v = tv; ve = te;
-                    }
+        for (int j = 0; j < CPT; ++j) {
+            int ve = sub * CPT + j;
+            float v = ve < E ? mine[j] : NEG_INF;                // (columns past E hold nothing)
+            mine[j] = v;
+            m = fmaxf(m, v);
+            // sorted insertion, static indices (rising experts: among equals the one before stays ahead;
+            // an entry that holds nothing yet gives way to anything, a logit of -inf included)
+            if (v > lv[RMAX - 1] || (le[RMAX - 1] == INT_MAX && v == v && ve < E)) {
+#pragma unroll
+                for (int r = 0; r < RMAX; ++r) {
+                    const bool ahead = v > lv[r] || le[r] == INT_MAX;
+                    const float tv = lv[r];
+                    const int te = le[r];
+                    lv[r] = ahead ? v : tv;
+                    le[r] = ahead ? ve : te;
+                    v = ahead ? tv : v;
+                    ve = ahead ? te : ve;
                 }
             }
         }
         m = group_max<TPT>(m);
         float s = 0.f;
-        for (int e = sub; e < E; e += TPT) s += __expf(row[e] - m);
-        const float denom = group_sum<TPT>(s);
-        float sel_v[MAXR];
-        int sel_e[MAXR];
 #pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
+        for (int j = 0; j < CPT; ++j) s += sub * CPT + j < E ? __expf(mine[j] - m) : 0.f;
+        const float denom = group_sum<TPT>(s);
+        float sel_v[RMAX];
+        int sel_e[RMAX];
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
             sel_v[r] = NEG_INF; sel_e[r] = INT_MAX;
             if (r < rounds) {
                 float bv = lv[0];
@@ -272,25 +236,28 @@ __global__ __launch_bounds__(NTH) void route_mfma_kernel(const uint16_t* __restr
                 sel_e[r] = be;
                 if (le[0] == be) {                               // the winner's owner pops its head
 #pragma unroll
-                    for (int i = 0; i + 1 < MAXR; ++i) { lv[i] = lv[i + 1]; le[i] = le[i + 1]; }
-                    lv[MAXR - 1] = NEG_INF; le[MAXR - 1] = INT_MAX;
+                    for (int i = 0; i + 1 < RMAX; ++i) { lv[i] = lv[i + 1]; le[i] = le[i + 1]; }
+                    lv[RMAX - 1] = NEG_INF; le[RMAX - 1] = INT_MAX;
                 }
             }
         }
-        const float xn = sqrtf(xn2[tok]) * 1.0001f;
-        const float tau = 2.1f * u * ((2 * KC + 6) * xn * wn_max + bmax);
+        float xs2 = xn2p[tok];
+#pragma unroll
+        for (int p = 1; p < KSP; ++p) xs2 += xn2p[p * TB + tok];
+        const float xn = sqrtf(xs2) * 1.0001f;
+        const float tau = 2.1f * u * ((2 * KA + 6) * xn * wn_max + bmax);
         bool near = false;
 #pragma unroll
-        for (int r = 0; r + 1 < MAXR; ++r)
+        for (int r = 0; r + 1 < RMAX; ++r)
             if (r + 1 < rounds && sel_v[r] - sel_v[r + 1] < tau) near = true;
         if (t < T && sub == 0) {
             if (!near) {
-                float p[MOE_MAX_TOPK], tot = 0.f;
+                float p[RMAX], tot = 0.f;
 #pragma unroll
-                for (int r = 0; r < MOE_MAX_TOPK; ++r)
+                for (int r = 0; r < RMAX; ++r)
                     if (r < k) { p[r] = __expf(sel_v[r] - m) / denom; tot += p[r]; }
 #pragma unroll
-                for (int r = 0; r < MOE_MAX_TOPK; ++r)
+                for (int r = 0; r < RMAX; ++r)
                     if (r < k) {
                         idx_out[(size_t)t * k + r] = sel_e[r];
                         w_out[(size_t)t * k + r] = renorm ? p[r] / tot : p[r];
@@ -298,8 +265,8 @@ __global__ __launch_bounds__(NTH) void route_mfma_kernel(const uint16_t* __restr
             } else {
                 float last = sel_v[0];
 #pragma unroll
-                for (int r = 1; r < MAXR; ++r) if (r < rounds) last = sel_v[r];
-                const int f = atomicAdd(&n_flag, 1);
+                for (int r = 1; r < RMAX; ++r) if (r < rounds) last = sel_v[r];
+                const int f = atomicAdd(n_flag, 1);
                 flag_tok[f] = tok;
                 flag_thr[f] = last - tau;
                 flag_max[f] = m;
@@ -309,73 +276,106 @@ __global__ __launch_bounds__(NTH) void route_mfma_kernel(const uint16_t* __restr
     }
     __syncthreads();
 
-    // ---- exact path for the flagged tokens: one wavefront per token
-    const int nf = n_flag;
-    for (int f = wave; f < nf; f += 4) {
-        const int tok = flag_tok[f], t = t0 + tok;
-        const float thr = flag_thr[f];
-        const uint16_t* xr = x + (size_t)t * d;
+    // ---- exact path for the flagged tokens: every expert whose fp32 logit could still reach the top
+    // k is recomputed in fp64.  A round takes as many flagged tokens as there are wavefronts: each
+    // wavefront lists one token's candidates, then all of them share out the (token, candidate)
+    // pairs -- a work-group has a flagged token or two, and left to one wavefront its nine or ten
+    // candidates follow one another, a memory latency each -- and each selects for its token.
+    constexpr int CJ = (MOE_MAX_EXPERTS + 63) / 64;
+    double* cand_v = slab;                                       // [NWV][LIST]
+    int* cand_e = reinterpret_cast<int*>(slab + NWV * L::LIST);  // [NWV][LIST]
+    const int nf = *n_flag;
+    for (int f0 = 0; f0 < nf; f0 += NWV) {
+        const int f = f0 + wave;
         int nc = 0;
-        for (int e0 = 0; e0 < E; e0 += 64) {
-            const int e = e0 + lane;
-            unsigned long long mask = __ballot(e < E && ls[tok * PL + e] >= thr);
-            while (mask) {
-                const int ce = e0 + (int)__builtin_ctzll(mask);
-                mask &= mask - 1;
+        if (f < nf) {
+            const int tok = flag_tok[f];
+            const float thr = flag_thr[f];
+            for (int e0 = 0; e0 < E; e0 += 64) {
+                const int e = e0 + lane;
+                const bool in = e < E && ls[tok * PL + e] >= thr;
+                const unsigned long long mask = __ballot(in);
+                if (in) cand_e[wave * L::LIST + nc + __popcll(mask & ((1ull << lane) - 1ull))] = e;
+                nc += __popcll(mask);
+            }
+        }
+        if (lane == 0) n_cand[wave] = nc;
+        __syncthreads();
+        for (int s = 0, p = wave; s < NWV; ++s) {
+            const int n = __builtin_amdgcn_readfirstlane(n_cand[s]);
+            for (; p < n; p += NWV) {
+                const int t = t0 + flag_tok[f0 + s], ce = __builtin_amdgcn_readfirstlane(cand_e[s * L::LIST + p]);
+                const uint16_t* xr = x + (size_t)t * d;
                 double psum = 0.0;
-                for (int i0 = lane; i0 < d; i0 += 64 * 8) {      // 16 loads in flight per lane
-                    float xa[8], wa[8];
+                if constexpr (PACKED) {                      // both operand rows are contiguous
+                    const uint16_t* wr = wg + (size_t)ce * d;
+                    for (int i0 = lane * 8; i0 < d; i0 += 64 * 8) {    // 8 terms per lane and step, 16-byte loads
+                        const frag_t xv = *(const frag_t*)(xr + i0), wv = *(const frag_t*)(wr + i0);
 #pragma unroll
-                    for (int u2 = 0; u2 < 8; ++u2) {
-                        const int i = i0 + 64 * u2;
-                        xa[u2] = i < d ? bf16_to_f32(xr[i]) : 0.f;
-                        wa[u2] = i < d ? bf16_to_f32(wg[(size_t)i * E + ce]) : 0.f;
+                        for (int i = 0; i < 4; ++i) {
+                            psum = fma((double)__uint_as_float(xv[i] << 16), (double)__uint_as_float(wv[i] << 16), psum);
+                            psum = fma((double)__uint_as_float(xv[i] & 0xffff0000u), (double)__uint_as_float(wv[i] & 0xffff0000u), psum);
+                        }
                     }
+                } else {
+                    for (int i0 = lane; i0 < d; i0 += 64 * 8) {        // 16 loads in flight per lane
+                        float xa[8], wa[8];
 #pragma unroll
-                    for (int u2 = 0; u2 < 8; ++u2) psum = fma((double)xa[u2], (double)wa[u2], psum);
+                        for (int u2 = 0; u2 < 8; ++u2) {
+                            const int i = i0 + 64 * u2;
+                            xa[u2] = i < d ? bf16_to_f32(xr[i]) : 0.f;
+                            wa[u2] = i < d ? bf16_to_f32(wg[(size_t)i * E + ce]) : 0.f;
+                        }
+#pragma unroll
+                        for (int u2 = 0; u2 < 8; ++u2) psum = fma((double)xa[u2], (double)wa[u2], psum);
+                    }
                 }
                 const double tot = wave_sum_f64(psum) + (bias ? (double)bias[ce] : 0.0);
-                if (lane == 0) { cand_v[wave][nc] = tot; cand_e[wave][nc] = ce; }
-                ++nc;
+                if (lane == 0) cand_v[s * L::LIST + p] = tot;
             }
+            p -= n;
         }
-        // candidates back to lanes (c = lane + 64 j), then k rounds of arg-best in fp64
-        double cv[CJ];
-        int ce_[CJ];
+        __syncthreads();
+        if (f < nf) {
+            const int t = t0 + flag_tok[f];
+            double cv[CJ];
+            int ce_[CJ];
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) {
-            const int c = lane + 64 * j;
-            cv[j] = c < nc ? cand_v[wave][c] : -__builtin_huge_val();
-            ce_[j] = c < nc ? cand_e[wave][c] : INT_MAX;
-        }
-        const double m = (double)flag_max[f], den = (double)flag_den[f];
-        double p[MOE_MAX_TOPK], tot = 0.0;
-        int pe[MOE_MAX_TOPK];
-#pragma unroll
-        for (int r = 0; r < MOE_MAX_TOPK; ++r) {
-            if (r < k) {
-                double bv = -__builtin_huge_val();
-                int be = INT_MAX;
-#pragma unroll
-                for (int j = 0; j < CJ; ++j)
-                    if (beats(cv[j], ce_[j], bv, be)) { bv = cv[j]; be = ce_[j]; }
-                wave_best_f64(bv, be);
-#pragma unroll
-                for (int j = 0; j < CJ; ++j)
-                    if (ce_[j] == be) { cv[j] = -__builtin_huge_val(); ce_[j] = INT_MAX; }
-                p[r] = exp(bv - m) / den;
-                pe[r] = be;
-                tot += p[r];
+            for (int j = 0; j < CJ; ++j) {
+                const int c = lane + 64 * j;
+                cv[j] = c < nc ? cand_v[wave * L::LIST + c] : -__builtin_huge_val();
+                ce_[j] = c < nc ? cand_e[wave * L::LIST + c] : INT_MAX;
             }
-        }
-        if (lane == 0) {
+            const double m = (double)flag_max[f], den = (double)flag_den[f];
+            double p[MOE_MAX_TOPK], tot = 0.0;
+            int pe[MOE_MAX_TOPK];
 #pragma unroll
-            for (int r = 0; r < MOE_MAX_TOPK; ++r)
+            for (int r = 0; r < MOE_MAX_TOPK; ++r) {
                 if (r < k) {
-                    idx_out[(size_t)t * k + r] = pe[r];
-                    w_out[(size_t)t * k + r] = (float)(renorm ? p[r] / tot : p[r]);
+                    double bv = -__builtin_huge_val();
+                    int be = INT_MAX;
+#pragma unroll
+                    for (int j = 0; j < CJ; ++j)
+                        if (beats(cv[j], ce_[j], bv, be)) { bv = cv[j]; be = ce_[j]; }
+                    wave_best_f64(bv, be);
+#pragma unroll
+                    for (int j = 0; j < CJ; ++j)
+                        if (ce_[j] == be) { cv[j] = -__builtin_huge_val(); ce_[j] = INT_MAX; }
+                    p[r] = exp(bv - m) / den;
+                    pe[r] = be;
+                    tot += p[r];
                 }
+            }
+            if (lane == 0) {
+#pragma unroll
+                for (int r = 0; r < MOE_MAX_TOPK; ++r)
+                    if (r < k) {
+                        idx_out[(size_t)t * k + r] = pe[r];
+                        w_out[(size_t)t * k + r] = (float)(renorm ? p[r] / tot : p[r]);
+                    }
+            }
         }
+        __syncthreads();                                     // (the lists are reused)
     }
 }
 
@@ -395,8 +395,6 @@ __global__ __launch_bounds__(NTH) void route_mfma_kernel(const uint16_t* __restr
 // fp32 MFMA accumulator collects up to KACC terms before it is added into fp64 sums (same error
 // model as above, with KACC-term chunks); the KSP partial sums are added in a fixed order
 // through LDS.  The staging ring shares its LDS with the buffers of the later phases.
-typedef __attribute__((ext_vector_type(4))) unsigned int frag_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr int ROUTE_RING = 3;          // stages of the prepared-router kernel's staging ring
 // s_waitcnt on vmcnt only (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[15:14])
@@ -408,24 +406,8 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
                                                   const float* __restrict__ w_norm2, const float* __restrict__ bias,
                                                   int T, int d, int E, int k, int renorm, int32_t* __restrict__ idx_out,
                                                   float* __restrict__ w_out, float* __restrict__ logits_out) {
-    constexpr int NWV = NB * KSP, NTHR = NWV * 64, TB = 32, TPT = 8, EPT = 32 * NB;
-    constexpr int PL = EPT + 4;                      // pitch of a logit row (floats)
-    constexpr int SLAB = KSP > 1 ? KSP * TB * EPT * 8 : 0;
-    constexpr int CAND = NWV * (MOE_MAX_EXPERTS + 32) * 12;
-    constexpr int REGION0 = SLAB > CAND ? SLAB : CAND;
+    constexpr int NWV = NB * KSP, NTHR = NWV * 64, TB = 32, EPT = 32 * NB;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    // LDS: fp64 slabs [KSP][32][EPT] for the sum over the contraction parts (later the exact path's
-    // candidate lists), the fp32 logits [32][PL], partial token norms, flags
-    double* slab = reinterpret_cast<double*>(smem);
-    float* ls = reinterpret_cast<float*>(smem + REGION0);
-    float* xn2p = ls + TB * PL;                      // [KSP][32]
-    int* flag_tok = reinterpret_cast<int*>(xn2p + KSP * TB);
-    float* flag_thr = reinterpret_cast<float*>(flag_tok + TB);
-    float* flag_max = flag_thr + TB;
-    float* flag_den = flag_max + TB;
-    float* red = flag_den + TB;                      // [2 * NWV]
-    int* n_flag = reinterpret_cast<int*>(red + 2 * NWV);
-
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
     const int nbi = wave / KSP, ksi = wave % KSP;    // this wavefront's expert block and contraction part
@@ -539,224 +521,9 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     if (in_acc) flush_acc();
     MOE_WAIT_VMCNT(0);                                       // (the trailing empty loads still target this LDS)
     __syncthreads();                                         // the ring's memory is reused below
-    if (tid == 0) *n_flag = 0;
-
-    // ---- logits.  acc64[r]: token 8*(r/4) + 4*lhi + r%4, expert nbi*32 + l32.
-    if (KSP > 1) {                                   // the partial sums of the contraction parts, fixed order
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int tok = 8 * (r >> 2) + 4 * lhi + (r & 3);
-            slab[(ksi * TB + tok) * EPT + nbi * 32 + l32] = acc64[r];
-        }
-        __syncthreads();
-        for (int i = tid; i < TB * EPT; i += NTHR) {
-            const int tok = i / EPT, e = i % EPT;
-            if (e < E) {
-                double v = slab[i];
-#pragma unroll
-                for (int p = 1; p < KSP; ++p) v += slab[p * TB * EPT + i];
-                const float l = (float)(v + (bias ? (double)bias[e] : 0.0));
-                ls[tok * PL + e] = l;
-                if (logits_out && t0 + tok < T) logits_out[(size_t)(t0 + tok) * E + e] = l;
-            }
-        }
-    } else {
-        const int e = nbi * 32 + l32;
-        const double be = (bias && e < E) ? (double)bias[e] : 0.0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int tok = 8 * (r >> 2) + 4 * lhi + (r & 3);
-            const float l = (float)(acc64[r] + be);
-            if (e < E) {
-                ls[tok * PL + e] = l;
-                if (logits_out && t0 + tok < T) logits_out[(size_t)(t0 + tok) * E + e] = l;
-            }
-        }
-    }
-    // token norms: the two k-halves of a token sit in lanes l and l+32; the parts are added in a fixed order
-    xsq += __shfl_xor(xsq, 32);
-    if (nbi == 0 && lhi == 0) xn2p[ksi * TB + l32] = xsq;
-    {   // largest column norm and largest |bias|
-        float w2 = 0.f, bm = 0.f;
-        for (int e = tid; e < E; e += NTHR) {
-            w2 = fmaxf(w2, w_norm2[e]);
-            if (bias) bm = fmaxf(bm, fabsf(bias[e]));
-        }
-        w2 = moe_wave_max_nonneg(w2);
-        bm = moe_wave_max_nonneg(bm);
-        if (lane == 0) { red[wave] = w2; red[NWV + wave] = bm; }
-    }
-    __syncthreads();
-    float wmax2 = 0.f, bmax = 0.f;
-#pragma unroll
-    for (int w2 = 0; w2 < NWV; ++w2) { wmax2 = fmaxf(wmax2, red[w2]); bmax = fmaxf(bmax, red[NWV + w2]); }
-    const float wn_max = sqrtf(wmax2) * 1.0001f;
-    const int rounds = (k + 1 < E) ? k + 1 : E;
-    const float u = 5.9604645e-8f;   // 2^-24
-
-    // ---- selection: TPT threads per token (the first four wavefronts); thread `sub` takes the CPT
-    // consecutive experts from sub * CPT on, fetched with four-float reads before the scan (a read
-    // per expert inside the scan made it wait for LDS at every step)
-    if (tid < TB * TPT) {
-        constexpr int CPT = EPT / TPT;
-        static_assert(CPT % 4 == 0 && PL % 4 == 0, "four-float reads of a logit row");
-        const int tok = tid / TPT, sub = tid % TPT, t = t0 + tok;
-        const float* row = ls + tok * PL;
-        float mine[CPT];
-#pragma unroll
-        for (int j = 0; j < CPT; j += 4) {
-            const float4 q = *reinterpret_cast<const float4*>(row + sub * CPT + j);
-            mine[j] = q.x; mine[j + 1] = q.y; mine[j + 2] = q.z; mine[j + 3] = q.w;
-        }
-        float lv[RMAX];
-        int le[RMAX];
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) { lv[r] = NEG_INF; le[r] = INT_MAX; }
-        float m = NEG_INF;
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            int ve = sub * CPT + j;
-            float v = ve < E ? mine[j] : NEG_INF;                // (columns past E hold nothing)
-            mine[j] = v;
-            m = fmaxf(m, v);
-            if (ve < E && beats(v, ve, lv[RMAX - 1], le[RMAX - 1])) {     // sorted insertion, static indices
-#pragma unroll
-                for (int r = 0; r < RMAX; ++r) {
-                    if (beats(v, ve, lv[r], le[r])) {
-                        float tv = lv[r]; int te = le[r];
-                        lv[r] = v; le[r] = ve;
-                        v = tv; ve = te;
-                    }
-                }
-            }
-        }
-        m = group_max<TPT>(m);
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) s += sub * CPT + j < E ? __expf(mine[j] - m) : 0.f;
-        const float denom = group_sum<TPT>(s);
-        float sel_v[RMAX];
-        int sel_e[RMAX];
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            sel_v[r] = NEG_INF; sel_e[r] = INT_MAX;
-            if (r < rounds) {
-                float bv = lv[0];
-                int be = le[0];
-                group_best<TPT>(bv, be);
-                sel_v[r] = bv;
-                sel_e[r] = be;
-                if (le[0] == be) {                               // the winner's owner pops its head
-#pragma unroll
-                    for (int i = 0; i + 1 < RMAX; ++i) { lv[i] = lv[i + 1]; le[i] = le[i + 1]; }
-                    lv[RMAX - 1] = NEG_INF; le[RMAX - 1] = INT_MAX;
-                }
-            }
-        }
-        float xs2 = xn2p[tok];
-#pragma unroll
-        for (int p = 1; p < KSP; ++p) xs2 += xn2p[p * TB + tok];
-        const float xn = sqrtf(xs2) * 1.0001f;
-        const float tau = 2.1f * u * ((2 * KACC + 6) * xn * wn_max + bmax);
-        bool near = false;
-#pragma unroll
-        for (int r = 0; r + 1 < RMAX; ++r)
-            if (r + 1 < rounds && sel_v[r] - sel_v[r + 1] < tau) near = true;
-        if (t < T && sub == 0) {
-            if (!near) {
-                float p[RMAX], tot = 0.f;
-#pragma unroll
-                for (int r = 0; r < RMAX; ++r)
-                    if (r < k) { p[r] = __expf(sel_v[r] - m) / denom; tot += p[r]; }
-#pragma unroll
-                for (int r = 0; r < RMAX; ++r)
-                    if (r < k) {
-                        idx_out[(size_t)t * k + r] = sel_e[r];
-                        w_out[(size_t)t * k + r] = renorm ? p[r] / tot : p[r];
-                    }
-            } else {
-                float last = sel_v[0];
-#pragma unroll
-                for (int r = 1; r < RMAX; ++r) if (r < rounds) last = sel_v[r];
-                const int f = atomicAdd(n_flag, 1);
-                flag_tok[f] = tok;
-                flag_thr[f] = last - tau;
-                flag_max[f] = m;
-                flag_den[f] = denom;
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- exact path for the flagged tokens: one wavefront per token; every expert whose fp32
-    // logit could still reach the top k is recomputed in fp64 (both operand rows are contiguous)
-    double* cand_v = slab + wave * (MOE_MAX_EXPERTS + 32);                       // [NWV][288] doubles ...
-    int* cand_e = reinterpret_cast<int*>(slab + NWV * (MOE_MAX_EXPERTS + 32)) + wave * (MOE_MAX_EXPERTS + 32);   // ... then ints
-    constexpr int CJ = (MOE_MAX_EXPERTS + 63) / 64;
-    const int nf = *n_flag;
-    for (int f = wave; f < nf; f += NWV) {
-        const int tok = flag_tok[f], t = t0 + tok;
-        const float thr = flag_thr[f];
-        const uint16_t* xr = x + (size_t)t * d;
-        int nc = 0;
-        for (int e0 = 0; e0 < E; e0 += 64) {
-            const int e = e0 + lane;
-            unsigned long long mask = __ballot(e < E && ls[tok * PL + e] >= thr);
-            while (mask) {
-                const int ce = e0 + (int)__builtin_ctzll(mask);
-                mask &= mask - 1;
-                const uint16_t* wr = wgt + (size_t)ce * d;
-                double psum = 0.0;
-                for (int i0 = lane * 8; i0 < d; i0 += 64 * 8) {    // 8 terms per lane and step, 16-byte loads
-                    const frag_t xv = *(const frag_t*)(xr + i0), wv = *(const frag_t*)(wr + i0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        psum = fma((double)__uint_as_float(xv[i] << 16), (double)__uint_as_float(wv[i] << 16), psum);
-                        psum = fma((double)__uint_as_float(xv[i] & 0xffff0000u), (double)__uint_as_float(wv[i] & 0xffff0000u), psum);
-                    }
-                }
-                const double tot = wave_sum_f64(psum) + (bias ? (double)bias[ce] : 0.0);
-                if (lane == 0) { cand_v[nc] = tot; cand_e[nc] = ce; }
-                ++nc;
-            }
-        }
-        double cv[CJ];
-        int ce_[CJ];
-#pragma unroll
-        for (int j = 0; j < CJ; ++j) {
-            const int c = lane + 64 * j;
-            cv[j] = c < nc ? cand_v[c] : -__builtin_huge_val();
-            ce_[j] = c < nc ? cand_e[c] : INT_MAX;
-        }
-        const double m = (double)flag_max[f], den = (double)flag_den[f];
-        double p[MOE_MAX_TOPK], tot = 0.0;
-        int pe[MOE_MAX_TOPK];
-#pragma unroll
-        for (int r = 0; r < MOE_MAX_TOPK; ++r) {
-            if (r < k) {
-                double bv = -__builtin_huge_val();
-                int be = INT_MAX;
-#pragma unroll
-                for (int j = 0; j < CJ; ++j)
-                    if (beats(cv[j], ce_[j], bv, be)) { bv = cv[j]; be = ce_[j]; }
-                wave_best_f64(bv, be);
-#pragma unroll
-                for (int j = 0; j < CJ; ++j)
-                    if (ce_[j] == be) { cv[j] = -__builtin_huge_val(); ce_[j] = INT_MAX; }
-                p[r] = exp(bv - m) / den;
-                pe[r] = be;
-                tot += p[r];
-            }
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int r = 0; r < MOE_MAX_TOPK; ++r)
-                if (r < k) {
-                    idx_out[(size_t)t * k + r] = pe[r];
-                    w_out[(size_t)t * k + r] = (float)(renorm ? p[r] / tot : p[r]);
-                }
-        }
-    }
+    float w2 = 0.f;
+    for (int e = tid; e < E; e += NTHR) w2 = fmaxf(w2, w_norm2[e]);
+    route_finish<NB, KSP, RMAX, KACC, true>(smem, acc64, xsq, w2, x, wgt, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
 }
 
 template <int NB, int KSP, int RMAX>
@@ -768,12 +535,158 @@ __global__ __launch_bounds__(NB * KSP * 64, 2) void route_packed_kernel(const ui
     route_packed_body<NB, KSP, RMAX>(x, wgt, w_norm2, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
 }
 
+// =========================================================================================
+// Router with W_g as given, [d,E]: the expert index is contiguous, the matrix instruction wants the
+// contraction index contiguous for both operands.  W_g is transposed on its way into LDS: a
+// thread fetches eight terms of eight neighbouring experts (eight 16-byte loads), swaps them into
+// eight runs of eight terms with byte permutes, and writes those as 16-byte pieces.  (Two-byte
+// loads and LDS writes, one term of one expert each, kept the kernel at 1257 us for 20011 tokens x
+// 1032, E = 256; this takes 137 us, half of it the selection.)  A stage is 128 terms per contraction part of the 32 tokens and
+// all experts; its loads are in flight while the previous stage is multiplied.
+//
+// LDS rows hold 16 pieces (128 terms); piece p of row r sits at position p ^ swz(r), chosen so that
+// both the fragment reads (16 consecutive rows, one piece) and the transposed writes (every
+// eighth row, one piece) touch all banks once.
+constexpr int KPLAIN = 128;            // terms per stage and contraction part
+constexpr int KA_PLAIN = 64;           // terms per fp32 accumulation: recomputing a column of W_g is dear here
+
+__device__ __forceinline__ int plain_swz(int r) { return (((r & 7) << 1) ^ (r >> 3)) & 15; }
+
+template <int NB, int KSP, int RMAX>
+__global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void route_plain_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
+                                                                       const float* __restrict__ bias, int T, int d, int E, int k,
+                                                                       int renorm, int32_t* __restrict__ idx_out,
+                                                                       float* __restrict__ w_out, float* __restrict__ logits_out) {
+    constexpr int NWV = NB * KSP, NTHR = NWV * 64, TB = 32, EPT = 32 * NB;
+    constexpr int PART = (TB + EPT) * KPLAIN * 2;            // bytes of one contraction part of a stage: token rows, expert rows
+    constexpr int XN = TB * 16 * KSP / NTHR;                 // 16-byte pieces of x per thread
+    constexpr int GROUPS = EPT / 8;                          // groups of eight experts
+    static_assert(GROUPS * 16 * KSP == NTHR, "one block of 8 experts x 8 terms per thread and stage");
+    static_assert(XN >= 1 && TB * 16 * KSP % NTHR == 0, "x pieces");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const int nbi = wave / KSP, ksi = wave % KSP;
+    const int t0 = blockIdx.x * TB;
+
+    // This thread's block of W_g: experts 8 g .. 8 g + 7, terms 8 kg .. 8 kg + 7 of the stage.  The loads
+    // carry no conditions: groups past E, tokens past T and terms past d fetch the last ones again
+    // (columns and tokens that do not exist are never looked at, terms past d are cleared below).
+    // Rows are 2-byte aligned only when E is odd: the copies state no alignment.
+    const int g = tid % GROUPS, kg = tid / GROUPS;
+    const int g_in = g * 8 < E ? g : (E - 1) / 8;
+    // Entries of this group past its row's end belong to the next row; the last row has none: there
+    // the eight last entries of the matrix are read and moved into place (E >= 8).
+    const int over = g_in * 8 + 8 > E ? g_in * 8 + 8 - E : 0;
+    u32x4 wv[8], xv[XN];
+    auto load_stage = [&](int st) {
+        const int k0 = st * (KPLAIN * KSP);
+#pragma unroll
+        for (int u2 = 0; u2 < XN; ++u2) {
+            const int p = tid + u2 * NTHR, kk = k0 + (p % (16 * KSP)) * 8, tok = t0 + p / (16 * KSP);
+            xv[u2] = *(const u32x4*)(x + (size_t)(tok < T ? tok : T - 1) * d + (kk < d ? kk : d - 8));
+        }
+        const int kk = k0 + kg * 8 < d ? k0 + kg * 8 : d - 8;    // (d is a multiple of 8)
+        const uint16_t* src = wg + (size_t)kk * E + g_in * 8;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) __builtin_memcpy(&wv[j], src + (size_t)j * E, 16);
+        __builtin_memcpy(&wv[7], src + (size_t)7 * E - (kk + 8 == d ? over : 0), 16);
+    };
+    auto mend_last_stage = [&](int st) {
+        const int k0 = st * (KPLAIN * KSP);
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u2 = 0; u2 < XN; ++u2)
+            if (k0 + ((tid + u2 * NTHR) % (16 * KSP)) * 8 >= d) xv[u2] = zero;
+        if (k0 + kg * 8 + 8 >= d)
+            wv[7] = __builtin_bit_cast(u32x4, __builtin_bit_cast(unsigned __int128, wv[7]) >> (16 * over));
+        if (k0 + kg * 8 >= d) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) wv[j] = zero;
+        }
+    };
+
+    double acc64[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc64[r] = 0.0;
+    float xsq = 0.f, wsq[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) wsq[e] = 0.f;
+    const int n_stages = (d + KPLAIN * KSP - 1) / (KPLAIN * KSP);
+    // Swizzled LDS offsets: piece c * 2 + lhi of a fragment row, and expert e of this thread's block, are
+    // the offset of piece lhi / expert 0 with bits flipped.
+    int xb_at = ksi * PART + l32 * 256 + ((lhi ^ plain_swz(l32)) << 4);
+    int wb_at = ksi * PART + (TB + nbi * 32 + l32) * 256 + ((lhi ^ plain_swz(nbi * 32 + l32)) << 4);
+    int wr_at = (kg >> 4) * PART + (TB + g * 8) * 256 + (((kg ^ g) & 15) << 4);
+    load_stage(0);
+    for (int st = 0; st < n_stages; ++st) {
+        if (st) __syncthreads();                             // the previous stage has been read
+        // (the empty asm keeps the compiler from forming all flipped offsets once, outside the loop)
+        asm volatile("" : "+v"(xb_at), "+v"(wb_at), "+v"(wr_at));
+        if (st + 1 == n_stages) mend_last_stage(st);
+#pragma unroll
+        for (int u2 = 0; u2 < XN; ++u2) {
+            const int p = tid + u2 * NTHR, tok = p / (16 * KSP), pc = p % (16 * KSP);
+            *(u32x4*)(smem + (pc >> 4) * PART + tok * 256 + (((pc & 15) ^ plain_swz(tok)) << 4)) = xv[u2];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {                        // expert g * 8 + e: its eight terms
+            u32x4 piece;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                piece[m] = __builtin_amdgcn_perm(wv[2 * m + 1][e >> 1], wv[2 * m][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+                const bf16x2 p2 = __builtin_bit_cast(bf16x2, piece[m]);
+                wsq[e] = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, wsq[e], false);
+            }
+            *(u32x4*)(smem + (wr_at ^ (e << 5)) + e * 256) = piece;
+        }
+        __syncthreads();
+        if (st + 1 < n_stages) load_stage(st + 1);
+#pragma unroll
+        for (int h = 0; h < KPLAIN / KA_PLAIN; ++h) {
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KA_PLAIN / 16; ++ks) {
+                const int flip = (h * (KA_PLAIN / 16) + ks) << 5;
+                const frag_t xa = *(const frag_t*)(smem + (xb_at ^ flip)), wa = *(const frag_t*)(smem + (wb_at ^ flip));
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa), __builtin_bit_cast(bf16x8, wa), acc, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {                // the token norms (those of expert block 0 are used)
+                    const bf16x2 p2 = __builtin_bit_cast(bf16x2, xa[i]);
+                    xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
+                }
+                if (ks & 1) __builtin_amdgcn_sched_barrier(0);     // (two slices' fragments in registers at a time)
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // squared column norms (a little rounded up): the parts of the threads that share an expert
+    __syncthreads();
+    float* wn = reinterpret_cast<float*>(smem);              // [16 * KSP][EPT]
+#pragma unroll
+    for (int e = 0; e < 8; e += 4)
+        *(float4*)(wn + kg * EPT + g * 8 + e) = make_float4(wsq[e], wsq[e + 1], wsq[e + 2], wsq[e + 3]);
+    __syncthreads();
+    float w2 = 0.f;
+    for (int e = tid; e < E; e += NTHR) {
+        float v = 0.f;
+#pragma unroll
+        for (int p = 0; p < 16 * KSP; ++p) v += wn[p * EPT + e];
+        w2 = fmaxf(w2, v * 1.002f);
+    }
+    __syncthreads();                                         // the staging memory is free now
+    route_finish<NB, KSP, RMAX, KA_PLAIN, false>(smem, acc64, xsq, w2, x, wg, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
+}
+
 template <int NB, int KSP, int RMAX>
 int launch_packed_r(const void* x, const void* wgt, const float* w_norm2, const float* bias, int T, int d, int E, int k,
                     int renorm, int32_t* idx, float* w, float* logits, hipStream_t st) {
     constexpr int NWV = NB * KSP, EPT = 32 * NB;
-    constexpr size_t slab = KSP > 1 ? (size_t)KSP * 32 * EPT * 8 : 0, cand = (size_t)NWV * (MOE_MAX_EXPERTS + 32) * 12;
-    const size_t later = (slab > cand ? slab : cand) + (size_t)32 * (EPT + 4) * 4 + KSP * 32 * 4 + 4 * 32 * 4 + 2 * NWV * 4 + 16;
+    const size_t later = RouteLds<NB, KSP>::BYTES;
     const size_t ring = (size_t)ROUTE_RING * (32 + EPT) * KSP * 128 + 1024;       // the staging ring and the later buffers share LDS
     const size_t smem = ring > later ? ring : later;
     auto kern = route_packed_kernel<NB, KSP, RMAX>;
@@ -797,25 +710,44 @@ int launch_packed(const void* x, const void* wgt, const float* w_norm2, const fl
     return launch_packed_r<NB, KSP, MAXR>(x, wgt, w_norm2, bias, T, d, E, k, renorm, idx, w, logits, st);
 }
 
-template <int MT, int NJ>
-int launch(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx,
-           float* w, float* logits, hipStream_t st) {
-    constexpr int TB = 32 * MT;
-    hipLaunchKernelGGL((route_mfma_kernel<MT, NJ>), dim3((T + TB - 1) / TB), dim3(NTH), 0, st, (const uint16_t*)x,
-                       (const uint16_t*)wg, bias, T, d, E, k, renorm, idx, w, logits);
+template <int NB, int KSP, int RMAX>
+int launch_plain_r(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
+                   float* logits, hipStream_t st) {
+    constexpr size_t stage = (size_t)KSP * (32 + 32 * NB) * KPLAIN * 2, later = RouteLds<NB, KSP>::BYTES;
+    constexpr size_t smem = stage > later ? stage : later;
+    auto kern = route_plain_kernel<NB, KSP, RMAX>;
+    if (smem > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return moe_fail(MOE_ERR_HIP, "moe_route_topk: shared memory attribute: %s", hipGetErrorString(e));
+    }
+    hipLaunchKernelGGL(kern, dim3((T + 31) / 32), dim3(NB * KSP * 64), smem, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, d, E,
+                       k, renorm, idx, w, logits);
     MOE_CHECK_LAUNCH("moe_route_topk");
     return MOE_OK;
 }
 
+template <int NB, int KSP>
+int launch_plain(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
+                 float* logits, hipStream_t st) {
+    // (two depths of the per-thread top list: the selection is a small part of this kernel)
+    if (k <= 2) return launch_plain_r<NB, KSP, 3>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    return launch_plain_r<NB, KSP, MAXR>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+}
+
 }  // namespace
+
+// the general kernel of route.hip (fewer than eight experts: a row of W_g is shorter than a 16-byte load)
+int moe_route_small(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
+                    float* logits, hipStream_t st);
 
 // bf16 path of moe_route_topk (arguments already validated by the caller)
 int moe_route_bf16_mfma(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm,
                         int32_t* idx, float* w, float* logits, hipStream_t st) {
-    // 32 tokens per work-group: twice the work-groups, so that two or three share a CU and hide
-    // each other's load latency
-    if (E <= 128) return launch<1, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    return launch<1, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E < 8) return moe_route_small(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 32) return launch_plain<1, 4>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 64) return launch_plain<2, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 128) return launch_plain<4, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    return launch_plain<8, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
 }
 
 // bf16 path of moe_route_topk_packed (arguments already validated by the caller)

@@ -113,6 +113,57 @@ def test_route_near_ties_bf16_both_entry_points(torch_gpu):
         assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
 
 
+# (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
+# of the stage; every block and contraction split; E < 8: the general kernel)
+@pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
+                                     (31, 264, 33, 1), (97, 72, 129, 2), (5, 72, 7, 2), (130, 520, 128, 5)])
+def test_route_topk_on_weights_as_given(torch_gpu, T, d, E, k):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import to_device
+    _note("route plain T=%d d=%d E=%d k=%d" % (T, d, E, k))
+    r = np.random.default_rng(T + E)
+    x = W.f32_to_bf16_bits(r.standard_normal((T, d)).astype(np.float32))
+    Wf = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    Wf[:, E - 1] = Wf[:, 0]                    # the first and the last column tie exactly
+    Wg = W.f32_to_bf16_bits(Wf)
+    b = r.standard_normal(E).astype(np.float32) * 0.1
+    b[E - 1] = b[0]
+    idx_o, w_o, l_o = O.route_topk(x, Wg, b, k, 0)
+    dev = torch.device("cuda:0")
+    idx = torch.full((T, k), -1, dtype=torch.int32, device=dev)
+    gate = torch.full((T, k), float("nan"), device=dev)
+    logits = torch.full((T, E), float("nan"), device=dev)
+    B.moe_route_topk(to_device(x, dev), to_device(Wg, dev), to_device(b, dev), T, d, E, k, 0, B.MOE_BF16, idx, gate, logits)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_numpy(idx), idx_o)
+    assert np.abs(to_numpy(gate).astype(np.float64) - w_o).max() <= 2e-6
+    assert np.abs(to_numpy(logits) - l_o).max() <= 1e-5 * max(1.0, np.abs(l_o).max())
+
+
+@pytest.mark.parametrize("E,k", [(8, 4), (60, 8), (256, 8)])
+def test_route_with_experts_masked_by_an_infinite_bias(torch_gpu, E, k):
+    """A bias of -inf takes an expert out of the softmax; with fewer than k experts left the masked
+    ones follow by rising index, with weight zero, through both entry points."""
+    torch = torch_gpu
+    T, d = 40, 128
+    r = np.random.default_rng(E)
+    x = W.f32_to_bf16_bits(r.standard_normal((T, d)).astype(np.float32))
+    Wg = W.f32_to_bf16_bits((r.standard_normal((d, E)) / 11).astype(np.float32))
+    b = np.full(E, -np.inf, dtype=np.float32)
+    b[[2, E - 1]] = 0.0
+    wl = W.WORKLOADS["c2"].scaled(T=T, d=d, E=E, k=k)
+    idx_o, w_o, _ = O.route_topk(x, Wg, b, k, 0)
+    from paper_2506_12417_amd.layer import to_device
+    for packed in (False, True):
+        layer = make_layer(wl, {})
+        layer.load_router(Wg, b, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), packed
+        assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
+
+
 PERMUTE_CASES = [(1, 1, 1, 8), (256, 2, 8, 64), (1000, 1, 128, 32), (5000, 4, 60, 16), (3, 2, 256, 8),
                  (4097, 1, 7, 128), (16384, 1, 128, 768), (35000, 2, 200, 8)]   # the last: more than 64 blocks
 
