@@ -3,17 +3,18 @@
 //
 // Four launches, no float atomics, no ordering left to chance:
 //   1. per-block histogram of expert ids (1024 assignments per work-group, LDS integer adds)
-//   2. one work-group: per-expert exclusive prefix over the blocks -> counts, offsets
+//   2. one wavefront per expert: exclusive prefix over the blocks -> counts
 //   3. per-block stable rank: inside a wavefront the peers of an assignment (same expert) are
 //      found with one ballot per bit of the expert id; popcount of the lower lanes is the rank;
-//      per-64-chunk counts are prefix-summed in LDS -> perm, inv_perm
-//   4. row gather x_perm[r] = x[perm[r] / k], 16 bytes per lane, fully coalesced
+//      per-64-chunk counts are prefix-summed in LDS -> offsets, perm, inv_perm
+//   4. rows x_perm[inv_perm[t*k+j]] = x[t]: every row of x is read once and written k times
 #include "common.h"
 #include "permute_rank.h"
 #include <mutex>
 
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 using moe_rank::CHUNKS;
 using moe_rank::NTH;
 using moe_rank::PB;   // assignments per work-group in steps 1 and 3
@@ -37,31 +38,41 @@ __global__ __launch_bounds__(NTH) void hist_kernel(const int32_t* __restrict__ i
     for (int e = threadIdx.x; e < E; e += NTH) block_hist[(size_t)blockIdx.x * E + e] = h[e];
 }
 
-// One work-group.  block_hist[b][e] becomes the number of assignments of expert e in blocks < b.
-__global__ __launch_bounds__(NTH) void scan_kernel(int32_t* __restrict__ block_hist, int nb, int E,
+// One wavefront per expert: block_hist[b][e] becomes the number of assignments of expert e in
+// blocks < b.  (One work-group for all experts, each thread walking its expert's blocks, took 18 us
+// for 157 blocks and 256 experts; this takes 5.)
+__global__ __launch_bounds__(NTH) void scan_kernel(int32_t* __restrict__ block_hist, int nb, int A, int E,
                                                    int32_t* __restrict__ counts, int32_t* __restrict__ offsets) {
-    __shared__ int tot[MOE_MAX_EXPERTS];
-    for (int e = threadIdx.x; e < E; e += NTH) {
-        int run = 0;
-        for (int b0 = 0; b0 < nb; b0 += 8) {               // eight loads in flight at a time
-            int v[8];
+    constexpr int NB = 4;                                  // 64-block groups whose loads are in flight together
+    const int e = blockIdx.x * (NTH / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (e >= E) return;
+    int run = 0;
+    for (int b0 = 0; b0 < nb; b0 += 64 * NB) {
+        int v[NB];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = b0 + j < nb ? block_hist[(size_t)(b0 + j) * E + e] : 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (b0 + j < nb) {
-                    block_hist[(size_t)(b0 + j) * E + e] = run;
-                    run += v[j];
-                }
+        for (int j = 0; j < NB; ++j) {
+            const int b = b0 + j * 64 + lane;
+            v[j] = b < nb ? block_hist[(size_t)b * E + e] : 0;
         }
-        tot[e] = run;
-        counts[e] = run;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int b = b0 + j * 64 + lane;
+            int incl = v[j];
+#pragma unroll
+            for (int step = 1; step < 64; step <<= 1) {
+                const int o = __shfl_up(incl, step);
+                incl += lane >= step ? o : 0;
+            }
+            if (b < nb) block_hist[(size_t)b * E + e] = run + incl - v[j];
+            run += __shfl(incl, 63);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int e = 0; e < E; ++e) { offsets[e] = run; run += tot[e]; }
-        offsets[E] = run;
+    if (lane == 0) {
+        counts[e] = run;
+        if (A == 0) {                                      // (otherwise the rank kernel writes them)
+            offsets[e] = 0;
+            if (e == E - 1) offsets[E] = 0;
+        }
     }
 }
 
@@ -73,14 +84,25 @@ __global__ __launch_bounds__(NTH) void rank_kernel(const int32_t* __restrict__ i
     moe_rank::rank_body<MODE>(idx, A, E, nbits, nb, block_hist, counts, offsets, perm, inv_perm);
 }
 
-// x_perm row r <- x row perm[r] / k, in 16-byte pieces (vpr pieces per row)
-__global__ __launch_bounds__(NTH) void gather_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ perm,
-                                                          int A, int k, int vpr, uint4* __restrict__ x_perm) {
-    const size_t total = (size_t)A * vpr;
-    for (size_t i = (size_t)blockIdx.x * NTH + threadIdx.x; i < total; i += (size_t)gridDim.x * NTH) {
-        int r = (int)(i / vpr), v = (int)(i - (size_t)r * vpr);
-        int t = perm[r] / k;
-        x_perm[i] = x[(size_t)t * vpr + v];
+// x_perm row inv_perm[t*k+j] <- x row t, in 16-byte pieces (vpr pieces per row), one piece of one
+// token per thread.  HBM bound: x is read once (gathering through perm read it k times through the
+// L2 and the row's address at the end of a chain of two loads: 95 us for 20011 x 8 rows of 2064
+// bytes, now 65, 5.7 TB/s.  Nontemporal stores: 106 us, the rows' ends share lines).
+__global__ __launch_bounds__(NTH) void spread_rows_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ inv_perm,
+                                                          unsigned total, unsigned A, unsigned k, unsigned vpr,
+                                                          u32x4* __restrict__ x_perm) {
+    const unsigned i = blockIdx.x * NTH + threadIdx.x;
+    if (i >= total) return;
+    const unsigned t = i / vpr, v = i - t * vpr;
+    const u32x4 piece = x[i];
+    const int32_t* to = inv_perm + (size_t)t * k;
+    for (unsigned j0 = 0; j0 < k; j0 += 4) {
+        unsigned row[4];
+#pragma unroll
+        for (unsigned j = 0; j < 4; ++j) row[j] = j0 + j < k ? (unsigned)to[j0 + j] : A;
+#pragma unroll
+        for (unsigned j = 0; j < 4; ++j)
+            if (row[j] < A) x_perm[(size_t)row[j] * vpr + v] = piece;
     }
 }
 
@@ -141,7 +163,7 @@ static int permute_launch(const void* x, const int32_t* expert_idx, int T, int d
     // blocks, or nothing to rank, the scan is a launch of its own.
     const bool fused_scan = A > 0 && nb <= 64;
     if (!fused_scan) {
-        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(NTH), 0, st, block_hist, nb, E, counts, offsets);
+        hipLaunchKernelGGL(scan_kernel, dim3((E + NTH / 64 - 1) / (NTH / 64)), dim3(NTH), 0, st, block_hist, nb, A, E, counts, offsets);
         MOE_CHECK_LAUNCH("moe_permute/scan");
     }
     if (A == 0) return MOE_OK;
@@ -153,13 +175,16 @@ static int permute_launch(const void* x, const int32_t* expert_idx, int T, int d
                            block_hist, counts, offsets, perm, inv_perm);
     MOE_CHECK_LAUNCH("moe_permute/rank");
     if (x) {
-        const int vpr = (int)((size_t)d * moe_elem_size(dt) / 16);
-        size_t total = (size_t)A * vpr;
-        size_t blocks = (total + NTH - 1) / NTH;
-        if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)blocks), dim3(NTH), 0, st, (const uint4*)x, perm, A, k,
-                           vpr, (uint4*)x_perm);
-        MOE_CHECK_LAUNCH("moe_permute/gather");
+        // (slices of whole tokens whose pieces a 32-bit index counts)
+        const unsigned vpr = (unsigned)((size_t)d * moe_elem_size(dt) / 16);
+        const long long slice = (1ll << 31) / vpr;
+        for (long long t0 = 0; t0 < T; t0 += slice) {
+            const unsigned total = (unsigned)((T - t0 < slice ? T - t0 : slice) * vpr);
+            hipLaunchKernelGGL(spread_rows_kernel, dim3((total + NTH - 1) / NTH), dim3(NTH), 0, st,
+                               (const u32x4*)x + (size_t)t0 * vpr, inv_perm + (size_t)t0 * k, total, (unsigned)A, (unsigned)k, vpr,
+                               (u32x4*)x_perm);
+        }
+        MOE_CHECK_LAUNCH("moe_permute/rows");
     }
     return MOE_OK;
 }

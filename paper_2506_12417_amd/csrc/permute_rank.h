@@ -10,8 +10,9 @@ constexpr int PB = 1024;   // assignments per work-group
 constexpr int NTH = 256;
 constexpr int CHUNKS = PB / 64;
 
-// MODE 0: offsets[] holds the experts' first positions and block_hist[b][e] the number of
-//         assignments of expert e in the blocks before b (a scan launch has run).
+// MODE 0: counts[] holds the experts' totals and block_hist[b][e] the number of assignments of
+//         expert e in the blocks before b (a scan launch has run); the experts' first positions
+//         are scanned here (the first work-group writes offsets).
 // MODE 1: block_hist holds the raw per-block histograms and this work-group does the scan itself
 //         (it sums the histograms of the blocks before it and of all blocks, and scans the
 //         totals; the first one also writes counts and offsets): one launch less.
@@ -70,11 +71,16 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
         const int a = base + (ci * 4 + wave) * 64 + lane;
         my_e[ci] = a < A ? idx[a] : -1;
     }
-    if (MODE >= 1) {
+    {
         static_assert(NTH >= MOE_MAX_EXPERTS, "one thread per expert");
         const int e = threadIdx.x;
         int before = 0, total = 0;
-        if (MODE == 2) {
+        if (MODE == 0) {
+            if (e < E) {
+                before = block_hist[(size_t)blockIdx.x * E + e];
+                total = counts[e];
+            }
+        } else if (MODE == 2) {
             // counters in LDS (scan_buf is free until the scan below): [0] before this block, [1] all
             scan_buf[0][e] = 0;
             scan_buf[1][e] = 0;
@@ -109,13 +115,11 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
         if (e < E) {
             start_of[e] = incl - total + before;
             if (blockIdx.x == 0) {
-                counts[e] = total;
+                if (MODE != 0) counts[e] = total;
                 offsets[e] = incl - total;
                 if (e == E - 1) offsets[E] = incl;
             }
         }
-    } else {
-        for (int e = threadIdx.x; e < E; e += NTH) start_of[e] = offsets[e] + block_hist[(size_t)blockIdx.x * E + e];
     }
     __syncthreads();
 #pragma unroll

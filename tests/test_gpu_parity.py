@@ -734,6 +734,29 @@ def test_forward_in_two_timed_halves_gives_the_same_output(torch_gpu, name, over
     assert marks[0].elapsed_time(marks[1]) > 0 and marks[1].elapsed_time(marks[2]) > 0
 
 
+@pytest.mark.parametrize("T,d,k,gated,with_shared", [(1, 4, 1, True, False), (77, 1032, 3, False, True), (300, 260, 8, True, False),
+                                                     (45, 64, 9, True, True), (20, 516, 17, False, False)])
+def test_combine_any_number_of_experts(torch_gpu, T, d, k, gated, with_shared):
+    """The weighted sum in fp32, j ascending, for every unrolled k and for k beyond them."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    r = np.random.default_rng(T + k)
+    yp = r.standard_normal((T * k, d)).astype(np.float32)
+    inv = r.permutation(T * k).astype(np.int32)
+    gate = r.random((T, k)).astype(np.float32) if gated else None
+    sh = r.standard_normal((T, d)).astype(np.float32) if with_shared else None
+    ref = np.zeros((T, d))
+    for j in range(k):
+        ref += (gate[:, j, None].astype(np.float64) if gated else 1.0) * yp[inv.reshape(T, k)[:, j]]
+    ref += sh if with_shared else 0.0
+    up = lambda a: None if a is None else torch.from_numpy(a).cuda()  # noqa: E731
+    y = torch.full((T, d), float("nan"), device="cuda:0")
+    B.moe_unpermute_combine(up(yp), up(inv), up(gate), up(sh), T, d, k, y)
+    torch.cuda.synchronize()
+    # k + 1 fp32 roundings of partial sums that stay below sum |terms| (about (k + 1) * 4)
+    assert np.abs(to_numpy(y) - ref).max() <= (k + 1) * 2.0 ** -24 * (k + 1) * 6
+
+
 def test_combine_identity_and_error_paths(torch_gpu):
     torch = torch_gpu
     from paper_2506_12417_amd import binding as B
