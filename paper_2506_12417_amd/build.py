@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe.so")
-SOURCES = ["common.hip", "route.hip", "route_mfma.hip", "permute.hip", "plan.hip", "ffn.hip", "ffn_bf16.hip", "ffn_stream.hip", "ffn_wide.hip", "ffn_rows.hip", "combine.hip", "pack.hip", "prefetch.hip"]
+SOURCES = ["common.hip", "route.hip", "route_mfma.hip", "permute.hip", "plan.hip", "ffn.hip", "ffn_bf16.hip", "ffn_stream.hip", "ffn_wide.hip", "ffn_rows.hip", "ffn_f32.hip", "combine.hip", "pack.hip", "prefetch.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -224,7 +224,7 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     objs = []
     # the device assembly of the GEMM kernels, for check_ticket_register (same flags, same code)
     asm_paths = []
-    for src in ("ffn_bf16.hip", "ffn_stream.hip", "ffn_wide.hip", "ffn_rows.hip"):
+    for src in ("ffn_bf16.hip", "ffn_stream.hip", "ffn_wide.hip", "ffn_rows.hip", "ffn_f32.hip"):
         asm_path = os.path.join(obj_dir, src.replace(".hip", ".s"))
         asm_paths.append(asm_path)
         asm_cmd = [HIPCC, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", asm_path]

@@ -4,118 +4,14 @@
 // Two grouped GEMMs, each one persistent launch driven by the tile table of moe_plan_tiles:
 //   G1  H = act(x_perm . W_in^T)     (ReLU, or SiLU(gate)*up on interleaved gate/up rows)
 //   G2  y_perm = H . W_out^T         (fp32 out)
-// bf16 runs on the matrix cores (ffn_bf16.hip); this file holds the entry points and the fp32
-// kernel, a plain FMA tile kernel used by the small fp32 configuration.
+// This file holds the entry points and the choice of the kernel family (ffn_bf16.hip, ffn_wide.hip,
+// ffn_rows.hip, ffn_stream.hip for 16 bits, ffn_f32.hip for fp32).
 #include "common.h"
 #include "ffn_kernels.h"
 
 namespace {
 
-constexpr int EPI_RELU = MOE_EPI_RELU, EPI_SWIGLU = MOE_EPI_SWIGLU, EPI_STORE = MOE_EPI_STORE;
-
-struct WorkList {
-    int bin_start, n_tiles, stride, first;
-};
-__device__ __forceinline__ WorkList work_list(const int32_t* __restrict__ hdr) {
-    WorkList w;
-    const int G = hdr[1];
-    const int bin = blockIdx.x % G;
-    w.first = blockIdx.x / G;
-    w.stride = ((int)gridDim.x - bin + G - 1) / G;
-    w.bin_start = hdr[4 + bin];
-    w.n_tiles = hdr[4 + bin + 1] - w.bin_start;
-    return w;
-}
-
-__device__ __forceinline__ float silu_f(float z) { return z / (1.f + __expf(-z)); }
-
-// =============================================================================== fp32 / FMA
-constexpr int FM = 64, FN = 64, FK = 16;
-
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ a_mat, int K, int N,
-                                                       const void* const* __restrict__ w_ptrs,
-                                                       const moe_tile* __restrict__ tiles,
-                                                       const int32_t* __restrict__ hdr, float* __restrict__ out,
-                                                       int ld_out) {
-    __shared__ float As[FK][FM + 4];
-    __shared__ float Bs[FK][FN + 4];
-    __shared__ float Cs[EPI == EPI_SWIGLU ? FM : 1][FN + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int ld_row = tid >> 2, ld_k = (tid & 3) * 4;
-    const int n_col_blocks = (N + FN - 1) / FN;
-
-    const WorkList wl = work_list(hdr);
-    const int n_items = wl.n_tiles * n_col_blocks;
-    for (int item = wl.first; item < n_items; item += wl.stride) {
-        const int cb = item / wl.n_tiles;
-        const moe_tile tile = tiles[wl.bin_start + (item - cb * wl.n_tiles)];
-        const int rc = tile.row_count;
-        if (rc <= 0) continue;
-        const int n0 = cb * FN;
-        const float* __restrict__ wmat = (const float*)w_ptrs[tile.expert];
-        const float* a_src = a_mat + (size_t)(tile.row_begin + (ld_row < rc ? ld_row : rc - 1)) * K;
-        const float* b_src = wmat + (size_t)(n0 + ld_row < N ? n0 + ld_row : N - 1) * K;
-        float acc[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-        for (int k0 = 0; k0 < K; k0 += FK) {
-            float4 av = make_float4(0.f, 0.f, 0.f, 0.f), bv = av;
-            if (k0 + ld_k < K) {
-                av = *(const float4*)(a_src + k0 + ld_k);
-                bv = *(const float4*)(b_src + k0 + ld_k);
-            }
-            __syncthreads();
-            As[ld_k + 0][ld_row] = av.x; As[ld_k + 1][ld_row] = av.y; As[ld_k + 2][ld_row] = av.z; As[ld_k + 3][ld_row] = av.w;
-            Bs[ld_k + 0][ld_row] = bv.x; Bs[ld_k + 1][ld_row] = bv.y; Bs[ld_k + 2][ld_row] = bv.z; Bs[ld_k + 3][ld_row] = bv.w;
-            __syncthreads();
-#pragma unroll
-            for (int kk = 0; kk < FK; ++kk) {
-                float a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-        }
-        if (EPI == EPI_SWIGLU) {
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) Cs[ty * 4 + i][tx * 4 + j] = acc[i][j];
-            __syncthreads();
-            // packed columns [0,32) of the block are gate, [32,64) the matching up columns
-            for (int i = tid; i < FM * 32; i += 256) {
-                int row = i >> 5, c = i & 31;
-                if (row < rc && n0 + c < N)
-                    out[(size_t)(tile.row_begin + row) * ld_out + n0 / 2 + c] = silu_f(Cs[row][c]) * Cs[row][32 + c];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int row = ty * 4 + i;
-                if (row >= rc) continue;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    int col = n0 + tx * 4 + j;
-                    if (col < N) {
-                        float v = acc[i][j];
-                        out[(size_t)(tile.row_begin + row) * ld_out + col] = (EPI == EPI_RELU) ? fmaxf(v, 0.f) : v;
-                    }
-                }
-            }
-        }
-    }
-}
-
-constexpr int GRID_F32 = 512;
+constexpr int FM = 64;         // tile height of the fp32 kernel (ffn_f32.hip)
 
 }  // namespace
 
@@ -253,18 +149,13 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         }
     } else {
         if (phases & 1) {
-            if (act == MOE_SWIGLU)
-                hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, dim3(GRID_F32), dim3(256), 0, st, (const float*)x_perm, d,
-                                   n1, w_in, tiles, plan_hdr, (float*)h_scratch, F);
-            else
-                hipLaunchKernelGGL(gemm_f32_kernel<EPI_RELU>, dim3(GRID_F32), dim3(256), 0, st, (const float*)x_perm, d,
-                                   n1, w_in, tiles, plan_hdr, (float*)h_scratch, F);
-            MOE_CHECK_LAUNCH("moe_grouped_ffn/G1");
+            rc = moe_launch_gemm_f32(act == MOE_SWIGLU ? MOE_EPI_SWIGLU : MOE_EPI_RELU, x_perm, A, d, n1, E, w_in, tiles, plan_hdr,
+                                     h_scratch, F, st);
+            if (rc != MOE_OK) return rc;
         }
         if (phases & 2) {
-            hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, dim3(GRID_F32), dim3(256), 0, st, (const float*)h_scratch, F,
-                               d, w_out, tiles, plan_hdr, y_perm, d);
-            MOE_CHECK_LAUNCH("moe_grouped_ffn/G2");
+            rc = moe_launch_gemm_f32(MOE_EPI_STORE, h_scratch, A, F, d, E, w_out, tiles, plan_hdr, y_perm, d, st);
+            if (rc != MOE_OK) return rc;
         }
     }
     return MOE_OK;

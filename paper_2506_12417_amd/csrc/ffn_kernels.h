@@ -56,6 +56,10 @@ int moe_launch_gemm_rows(int epi, const void* a, int A, int K, int N, int E, con
 int moe_launch_gemm_rows_gather(int epi, const void* x, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                                 const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div);
 
+// The fp32 products (ffn_f32.hip; tiles of at most 64 rows, RELU / SWIGLU / STORE, all of fp32).
+int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
+                        const int32_t* hdr, void* out, int ld_out, hipStream_t st);
+
 // MOE_OK if the current device is the GPU the persistent launches are laid out for (256 compute
 // units in 8 XCDs), else MOE_ERR_UNSUPPORTED.
 int moe_check_gemm_device();

@@ -1,265 +1,181 @@
 // moe_route_topk: router logits, softmax, top-k selection (Alg. 1 step 1; section 2).
-// This file: argument checks, and the fp32-input kernel (plain FMAs); bf16 inputs go to the MFMA
-// kernel in route_mfma.hip, which follows the same scheme.
+// This file: argument checks, and the kernel for fp32 inputs (and for bf16 with fewer than eight
+// experts); other bf16 inputs go to route_mfma.hip.
 //
-// One work-group takes 64 tokens.  The logits x.W_g are accumulated with fp32 FMAs in chunks of
-// 32 terms; every chunk's partial sum is then added into an fp64 accumulator, so the only
-// rounding that matters is the one inside a chunk: |error| <= 32u * |x_t| * |w_e| (u = 2^-24,
-// Cauchy-Schwarz on the sum of |products|).  The top-k decision of a token is final when all
-// its deciding gaps are wider than twice that bound; the few tokens that fail the test get
-// their logits recomputed entirely in fp64 by their wavefront, so the selected experts and
-// their order are those of exact arithmetic.  HBM traffic: x once, W_g once per work-group
-// (L2-resident), k*(4+4) bytes out per token.
+// The logits are computed in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64, 79 TFLOP/s: products
+// of two fp32 values are exact in fp64), so the selection needs no error bound and no second
+// look.  A work-group takes 16 tokens; its eight wavefronts split the experts into groups of two 16-column blocks and the contraction
+// into 8 / GROUPS parts, whose sums are added in a fixed order through LDS.  Operands go straight
+// from global memory to registers: a lane reads four consecutive terms of its token and the four
+// matching entries of its expert's column (16 neighbouring columns per load), and gives one of
+// the four to each of four matrix instructions.
+// (fp32 fma tiles whose column norms were summed by an LDS atomic per entry of W_g took 111 us for
+// 1501 tokens x 768, E = 16; this takes 11.  64
+// tokens per work-group, which fetch W_g a quarter as often, were no faster at any size: 33000
+// tokens x 768, E = 128 219 against 166 us.)
 #include "common.h"
 #include <climits>
 
 namespace {
 
-constexpr int TB = 64;    // tokens per work-group
-constexpr int KC = 32;    // terms accumulated in fp32 before the partial sum goes to fp64
-constexpr int NTH = 256;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 
-template <typename V> __device__ __forceinline__ bool beats(V av, int ae, V bv, int be) {
-    return av > bv || (av == bv && ae < be);
-}
-template <typename V> __device__ __forceinline__ void wave_best(V& v, int& e) {
+__device__ __forceinline__ bool beats(double av, int ae, double bv, int be) { return av > bv || (av == bv && ae < be); }
+__device__ __forceinline__ void wave_best(double& v, int& e) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-        V ov = __shfl_xor(v, off);
-        int oe = __shfl_xor(e, off);
+        const double ov = __shfl_xor(v, off);
+        const int oe = __shfl_xor(e, off);
         if (beats(ov, oe, v, e)) { v = ov; e = oe; }
     }
 }
-template <typename V> __device__ __forceinline__ V wave_sum(V v) {
+__device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
-template <typename V> __device__ __forceinline__ V wave_max(V v) {
+__device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) { V o = __shfl_xor(v, off); v = o > v ? o : v; }
+    for (int off = 32; off >= 1; off >>= 1) { const double o = __shfl_xor(v, off); v = o > v ? o : v; }
     return v;
 }
-template <typename V> __device__ __forceinline__ V neg_inf();
-template <> __device__ __forceinline__ float neg_inf<float>() { return -__builtin_huge_valf(); }
-template <> __device__ __forceinline__ double neg_inf<double>() { return -__builtin_huge_val(); }
-__device__ __forceinline__ float exp_v(float z) { return __expf(z) ; }
-__device__ __forceinline__ double exp_v(double z) { return exp(z); }
+constexpr double NEG_INF = -__builtin_huge_val();
 
-constexpr int MAXR = MOE_MAX_TOPK + 1;
-
-// A wavefront holds one token's logits, lane l owning experts l, l+64, l+128, l+192.
-// Picks the `rounds` largest (ties to the lower expert id), and the softmax denominator.
-template <typename V>
-__device__ __forceinline__ void select_topk(V (&v)[4], int lane, int E, int rounds,
-                                            V (&sel_v)[MAXR], int (&sel_e)[MAXR], V& denom) {
-    V m = neg_inf<V>();
+// A wavefront holds one token's logits, lane l owning experts l, l+64, l+128, l+192.  Picks the k
+// largest (ties to the lower expert id), forms their softmax values and writes the choice.
+__device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, int renorm, int32_t* idx_row, float* w_row) {
+    double m = NEG_INF, s = 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) m = v[j] > m ? v[j] : m;
     m = wave_max(m);
-    V s = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) s += exp_v(v[j] - m);
-    denom = wave_sum(s);
+    for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) s += exp(v[j] - m);
+    const double denom = wave_sum(s);
+    double p[MOE_MAX_TOPK], tot = 0.0, first = 0.0;
+    int sel[MOE_MAX_TOPK];
 #pragma unroll
-    for (int r = 0; r < MAXR; ++r) {
-        if (r < rounds) {
-            V bv = neg_inf<V>();
+    for (int r = 0; r < MOE_MAX_TOPK; ++r) {
+        if (r < k) {
+            double bv = NEG_INF;
             int be = INT_MAX;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                int e = lane + 64 * j;
+                const int e = lane + 64 * j;
                 if (e < E && beats(v[j], e, bv, be)) { bv = v[j]; be = e; }
             }
             wave_best(bv, be);
-            sel_v[r] = bv;
-            sel_e[r] = be;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) if (lane + 64 * j == be) v[j] = neg_inf<V>();
+            for (int j = 0; j < 4; ++j) if (lane + 64 * j == be) v[j] = NEG_INF;
+            if (r == 0) first = bv;
+            sel[r] = be;
+            p[r] = exp(bv - first) / denom;
+            tot += p[r];
         }
-    }
-}
-
-template <typename V>
-__device__ __forceinline__ void write_choice(const V (&sel_v)[MAXR], const int (&sel_e)[MAXR], V denom,
-                                             int k, int renorm, int lane, int32_t* idx_row, float* w_row) {
-    V p[MOE_MAX_TOPK];
-    V tot = 0;
-#pragma unroll
-    for (int r = 0; r < MOE_MAX_TOPK; ++r) {
-        if (r < k) { p[r] = exp_v(sel_v[r] - sel_v[0]) / denom; tot += p[r]; }
     }
 #pragma unroll
     for (int r = 0; r < MOE_MAX_TOPK; ++r) {
         if (r < k && lane == r) {
-            idx_row[r] = sel_e[r];
+            idx_row[r] = sel[r];
             w_row[r] = (float)(renorm ? p[r] / tot : p[r]);
         }
     }
 }
 
-template <typename XT, int NE>
-__global__ __launch_bounds__(NTH) void route_kernel(const XT* __restrict__ x, const XT* __restrict__ wg,
-                                                    const float* __restrict__ bias, int T, int d, int E,
-                                                    int k, int renorm, int32_t* __restrict__ idx_out,
-                                                    float* __restrict__ w_out, float* __restrict__ logits_out) {
-    constexpr int EP = 16 * NE;
-    extern __shared__ float smem[];
-    float (*xs)[KC + 1] = reinterpret_cast<float (*)[KC + 1]>(smem);
-    float (*ws)[EP] = reinterpret_cast<float (*)[EP]>(smem + TB * (KC + 1));
-    float (*ls)[EP + 1] = reinterpret_cast<float (*)[EP + 1]>(smem + TB * (KC + 1) + KC * EP);
-    float* xn2 = smem + TB * (KC + 1) + KC * EP + TB * (EP + 1);
-    float* wn2 = xn2 + TB;
+__device__ __forceinline__ void load4(const float* p, double (&v)[4]) {
+    const float4 f = *reinterpret_cast<const float4*>(p);
+    v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+}
+__device__ __forceinline__ void load4(const uint16_t* p, double (&v)[4]) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
+    v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+}
 
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
+// GROUPS expert groups of NT blocks of 16 columns
+template <typename XT, int GROUPS, int NT>
+__global__ __launch_bounds__(512) void route_kernel(const XT* __restrict__ x, const XT* __restrict__ wg,
+                                                    const float* __restrict__ bias, int T, int d, int E, int k, int renorm,
+                                                    int32_t* __restrict__ idx_out, float* __restrict__ w_out,
+                                                    float* __restrict__ logits_out) {
+    constexpr int KSP = 8 / GROUPS, EP = GROUPS * NT * 16, TB = 16, NC = 2;
+    __shared__ double part[KSP * TB * EP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int grp = wave / KSP, ks = wave % KSP;
     const int t0 = blockIdx.x * TB;
-
-    for (int i = tid; i < KC * EP; i += NTH) (&ws[0][0])[i] = 0.f;
-    for (int i = tid; i < EP; i += NTH) wn2[i] = 0.f;
-    __syncthreads();
-
-    double acc64[4][NE];
+    f64x4 acc[NT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int j = 0; j < NE; ++j) acc64[i][j] = 0.0;
-    float xsq = 0.f;
-
-    const int s_tok = tid >> 2, s_kk = (tid & 3) * 8;
-    const int s_t = t0 + s_tok;
-
-    for (int k0 = 0; k0 < d; k0 += KC) {
-        {   // x tile: 64 tokens x 32 terms, 8 consecutive terms per thread
-            float v[8];
-            if (s_t < T && k0 + s_kk < d) {
-                const XT* p = x + (size_t)s_t * d + k0 + s_kk;
+        for (int r = 0; r < 4; ++r) acc[n][r] = 0.0;
+    // (tokens past T and columns past E are the last ones again: never looked at)
+    const XT* xr = x + (size_t)(t0 + l16 < T ? t0 + l16 : T - 1) * d;
+    int col[NT];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = load_as_f32<XT>(p + i);
-            } else {
+    for (int n = 0; n < NT; ++n) col[n] = (grp * NT + n) * 16 + l16 < E ? (grp * NT + n) * 16 + l16 : E - 1;
+    // chunks of 16 terms, NC of a wavefront's chunks in flight together
+    for (int k0 = ks * 16; k0 < d; k0 += KSP * 16 * NC) {
+        double xv[NC][4];
+        float wv[NC][NT][4];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = 0.f;
-            }
+        for (int c = 0; c < NC; ++c) {
+            // (d is a multiple of 8: a lane's four terms are all inside or all past the end, where x counts
+            // as zero and W_g's last entries stand in)
+            const int at = k0 + c * KSP * 16 + lq * 4, in = at < d ? at : d - 4;
+            load4(xr + in, xv[c]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { xs[s_tok][s_kk + i] = v[i]; xsq = fmaf(v[i], v[i], xsq); }
-        }
-        for (int i = tid; i < KC * E; i += NTH) {   // W_g chunk: 32 rows x E
-            int kk = i / E, e = i - kk * E;
-            float v = (k0 + kk < d) ? load_as_f32<XT>(wg + (size_t)(k0 + kk) * E + e) : 0.f;
-            ws[kk][e] = v;
-            atomicAdd(&wn2[e], v * v);
-        }
-        __syncthreads();
-        float acc[4][NE];
+            for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < NE; ++j) acc[i][j] = 0.f;
-#pragma unroll 8
-        for (int kk = 0; kk < KC; ++kk) {
-            float xv[4], wv[NE];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) xv[i] = xs[ty * 4 + i][kk];
-#pragma unroll
-            for (int j = 0; j < NE; ++j) wv[j] = ws[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < NE; ++j) acc[i][j] = fmaf(xv[i], wv[j], acc[i][j]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < NE; ++j) acc64[i][j] += (double)acc[i][j];
-        __syncthreads();
-    }
-
-    xsq += __shfl_xor(xsq, 1);
-    xsq += __shfl_xor(xsq, 2);
-    if ((tid & 3) == 0) xn2[s_tok] = xsq;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int tok = ty * 4 + i, t = t0 + tok;
-#pragma unroll
-        for (int j = 0; j < NE; ++j) {
-            int e = tx + 16 * j;
-            if (e < E) {
-                float l = (float)(acc64[i][j] + (bias ? (double)bias[e] : 0.0));
-                ls[tok][e] = l;
-                if (logits_out && t < T) logits_out[(size_t)t * E + e] = l;
-            }
-        }
-    }
-    __syncthreads();
-
-    const int lane = tid & 63, wave = tid >> 6;
-    float wmax2 = 0.f, bmax = 0.f;
-    for (int e = lane; e < E; e += 64) {
-        wmax2 = fmaxf(wmax2, wn2[e]);
-        if (bias) bmax = fmaxf(bmax, fabsf(bias[e]));
-    }
-    const float wn_max = sqrtf(wave_max(wmax2)) * 1.0001f;
-    bmax = wave_max(bmax);
-    const int rounds = (k + 1 < E) ? k + 1 : E;
-    const float u = 5.9604645e-8f;   // 2^-24
-
-    for (int tt = 0; tt < TB / 4; ++tt) {
-        const int tok = wave * (TB / 4) + tt, t = t0 + tok;
-        if (t >= T) break;
-        float v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (lane + 64 * j < E) ? ls[tok][lane + 64 * j] : 0.f;
-        float sel_v[MAXR];
-        int sel_e[MAXR];
-        float denom;
-        select_topk<float>(v, lane, E, rounds, sel_v, sel_e, denom);
-        // twice the bound on a logit's error: chunk rounding (KC terms, +2 for the conversions)
-        // plus the final rounding of the logit itself to fp32
-        const float xn = sqrtf(xn2[tok]) * 1.0001f;
-        const float tau = 2.1f * u * ((KC + 3) * xn * wn_max + bmax);
-        bool near = false;
-#pragma unroll
-        for (int r = 0; r + 1 < MAXR; ++r)
-            if (r + 1 < rounds && sel_v[r] - sel_v[r + 1] < tau) near = true;
-        if (!near) {
-            write_choice<float>(sel_v, sel_e, denom, k, renorm, lane, idx_out + (size_t)t * k, w_out + (size_t)t * k);
-        } else {
-            // exact path: this token's logits in fp64, lane l owning experts l + 64 j
-            double v64[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v64[j] = (bias && lane + 64 * j < E) ? (double)bias[lane + 64 * j] : 0.0;
-            const XT* xr = x + (size_t)t * d;
-#pragma unroll 4
-            for (int i = 0; i < d; ++i) {
-                double xv = (double)load_as_f32<XT>(xr + i);
+                for (int j = 0; j < 4; ++j) wv[c][n][j] = load_as_f32<XT>(wg + (size_t)(in + j) * E + col[n]);
+            if (at >= d) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    int e = lane + 64 * j;
-                    if (e < E) v64[j] = fma(xv, (double)load_as_f32<XT>(wg + (size_t)i * E + e), v64[j]);
+                    xv[c][j] = 0.0;
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) wv[c][n][j] = 0.f;
                 }
             }
-            double sv[MAXR], dn;
-            int se[MAXR];
-            select_topk<double>(v64, lane, E, rounds, sv, se, dn);
-            write_choice<double>(sv, se, dn, k, renorm, lane, idx_out + (size_t)t * k, w_out + (size_t)t * k);
         }
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+                    acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[c][j], (double)wv[c][n][j], acc[n], 0, 0, 0);
+    }
+    // acc[n][r]: token 4 r + lq, column l16 of the block
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(ks * TB + 4 * r + lq) * EP + (grp * NT + n) * 16 + l16] = acc[n][r];
+    __syncthreads();
+    // one wavefront per token, lane l owning experts l, l + 64, ...
+    for (int tok = wave; tok < TB; tok += 8) {
+        const int t = t0 + tok;
+        if (t >= T) break;
+        double v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = lane + 64 * j;
+            v[j] = 0.0;
+            if (e < E) {
+                double s = part[tok * EP + e];
+#pragma unroll
+                for (int p = 1; p < KSP; ++p) s += part[(p * TB + tok) * EP + e];
+                v[j] = s + (bias ? (double)bias[e] : 0.0);
+                if (logits_out) logits_out[(size_t)t * E + e] = (float)v[j];
+            }
+        }
+        choose(v, lane, E, k, renorm, idx_out + (size_t)t * k, w_out + (size_t)t * k);
     }
 }
 
-template <typename XT, int NE>
+template <typename XT, int GROUPS, int NT>
 int launch_route(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm,
                  int32_t* idx, float* w, float* logits, hipStream_t st) {
-    constexpr int EP = 16 * NE;
-    size_t smem = sizeof(float) * (size_t)(TB * (KC + 1) + KC * EP + TB * (EP + 1) + TB + EP);
-    auto kern = route_kernel<XT, NE>;
-    if (smem > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return moe_fail(MOE_ERR_HIP, "route: shared memory attribute: %s", hipGetErrorString(e));
-    }
-    int grid = (T + TB - 1) / TB;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NTH), smem, st, (const XT*)x, (const XT*)wg, bias, T, d, E, k,
-                       renorm, idx, w, logits);
+    hipLaunchKernelGGL((route_kernel<XT, GROUPS, NT>), dim3((T + 15) / 16), dim3(512), 0, st, (const XT*)x, (const XT*)wg, bias, T, d, E,
+                       k, renorm, idx, w, logits);
     MOE_CHECK_LAUNCH("moe_route_topk");
     return MOE_OK;
 }
@@ -267,15 +183,16 @@ int launch_route(const void* x, const void* wg, const float* bias, int T, int d,
 template <typename XT>
 int dispatch_route(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm,
                    int32_t* idx, float* w, float* logits, hipStream_t st) {
-    if (E <= 16) return launch_route<XT, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 32) return launch_route<XT, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 64) return launch_route<XT, 4>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 128) return launch_route<XT, 8>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    return launch_route<XT, 16>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 16) return launch_route<XT, 1, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 32) return launch_route<XT, 1, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 64) return launch_route<XT, 2, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 128) return launch_route<XT, 4, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    return launch_route<XT, 8, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
 }
 
 }  // namespace
 
+// fewer than eight experts in bf16: a row of W_g is shorter than a 16-byte load
 int moe_route_small(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
                     float* logits, hipStream_t st) {
     return dispatch_route<uint16_t>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);

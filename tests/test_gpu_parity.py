@@ -141,6 +141,36 @@ def test_route_topk_on_weights_as_given(torch_gpu, T, d, E, k):
     assert np.abs(to_numpy(logits) - l_o).max() <= 1e-5 * max(1.0, np.abs(l_o).max())
 
 
+# (fp32: every split of experts and contraction over the wavefronts, contractions shorter than it)
+@pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (17, 24, 17, 8), (33, 40, 65, 2), (16, 72, 129, 3), (50, 264, 256, 8), (20, 520, 16, 4)])
+def test_route_topk_in_fp32(torch_gpu, T, d, E, k):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    r = np.random.default_rng(T + E)
+    x = r.standard_normal((T, d)).astype(np.float32)
+    Wg = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    Wg[:, E - 1] = Wg[:, 0]                    # the first and the last column tie exactly
+    b = r.standard_normal(E).astype(np.float32) * 0.1
+    b[E - 1] = b[0]
+    # float64 logits summed term by term, column by column: equal columns get equal sums (a BLAS product
+    # may add the two planted columns in different orders and so break their tie)
+    l_o = (x.astype(np.float64)[:, :, None] * Wg.astype(np.float64)[None]).sum(axis=1) + b.astype(np.float64)
+    idx_o = np.argsort(-l_o, axis=1, kind="stable")[:, :k].astype(np.int32)
+    p_o = np.exp(l_o - l_o.max(axis=1, keepdims=True))
+    w_o = np.take_along_axis(p_o, idx_o, axis=1)
+    w_o /= w_o.sum(axis=1, keepdims=True)
+    dev = torch.device("cuda:0")
+    idx = torch.full((T, k), -1, dtype=torch.int32, device=dev)
+    gate = torch.full((T, k), float("nan"), device=dev)
+    logits = torch.full((T, E), float("nan"), device=dev)
+    up = lambda a: torch.from_numpy(a).to(dev)  # noqa: E731
+    B.moe_route_topk(up(x), up(Wg), up(b), T, d, E, k, 1, B.MOE_F32, idx, gate, logits)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_numpy(idx), idx_o)
+    assert np.abs(to_numpy(gate).astype(np.float64) - w_o).max() <= 2.0 ** -23
+    assert np.abs(to_numpy(logits) - l_o).max() <= 2.0 ** -23 * max(1.0, np.abs(l_o).max())
+
+
 @pytest.mark.parametrize("E,k", [(8, 4), (60, 8), (256, 8)])
 def test_route_with_experts_masked_by_an_infinite_bias(torch_gpu, E, k):
     """A bias of -inf takes an expert out of the softmax; with fewer than k experts left the masked
@@ -637,6 +667,47 @@ def test_few_row_kernels_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, po
     # as in _stage_check: one-ulp flips of the half rounding of h are what is left
     assert max_err_over_rms(to_numpy(layer.y_perm), yp) <= 1e-3
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()      # the work counters stay zero
+
+
+F32_CASES = [
+    # rows per expert, k, d, F, act, policy: tiles of 1, 32, 33, 64 and 65 rows, contractions shorter than a stage and
+    # not a multiple of it, column blocks cut short, both widths of the column block, more tiles than the launch counts on
+    ([1], 1, 4, 4, "relu", 1),
+    ([32, 33, 0, 64], 1, 36, 132, "relu", 1),
+    ([65, 1], 2, 68, 32, "swiglu", 1),
+    ([130, 2, 0], 3, 100, 160, "swiglu", 1),
+    ([400, 300, 500, 77], 1, 128, 4100, "relu", 1),
+    ([900, 31, 600], 1, 64, 4096, "swiglu", 1),
+    ([9] * 24, 1, 32, 64, "relu", 3),
+]
+
+
+@pytest.mark.parametrize("rows,k,d,F,act,policy", F32_CASES)
+def test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, policy):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    assert A % k == 0
+    wl = W.WORKLOADS["c1"].scaled(T=A // k, d=d, F=F, E=E, k=k, act=act, skew="uniform")
+    _note("fp32 products A=%d E=%d d=%d F=%d %s policy %d" % (A, E, d, F, act, policy))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, {n: v for n, v in inp.items() if n != "W_g"}, n_bins=8 if policy == 1 else 16, policy=policy)
+    ids = _few(rows).reshape(A // k, k)
+    layer.expert_idx.copy_(to_device(ids, layer.device))
+    p = O.permute(ids, E)
+    xp = O.gather_rows(inp["x"], p["perm"], k)
+    layer.x_perm.copy_(to_device(xp, layer.device))
+    layer.counts.copy_(to_device(p["counts"], layer.device))
+    layer.offsets.copy_(to_device(p["offsets"], layer.device))
+    for t in (layer.h, layer.y_perm):
+        t.fill_(float("nan"))
+    layer.plan()
+    layer.ffn()
+    torch.cuda.synchronize()
+    yp = O.grouped_ffn(xp, p["offsets"], expert_dict(wl, inp), act)
+    assert max_err_over_rms(to_numpy(layer.y_perm), yp) <= TOL["f32"]
+    assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
 
 
 WIDE_CASES = [
