@@ -416,6 +416,30 @@ def test_pack_weights(torch_gpu, dtype, n, K, N, inter):
     assert np.array_equal(to_numpy(out), ref)
 
 
+@pytest.mark.parametrize("dtype,K,N", [("bf16", 72, 32), ("bf16", 264, 96), ("f32", 132, 68), ("f32", 4, 4)])
+def test_pack_weights_at_any_alignment(torch_gpu, dtype, K, N):
+    """The register transpose (16-byte pieces on both sides) and, from the same matrix one element
+    further on, the LDS transpose: the same bytes, nothing written past them."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    n, dt = 3, B.MOE_F32 if dtype == "f32" else B.MOE_BF16
+    it = torch.int32 if dtype == "f32" else torch.int16
+    w = torch.from_numpy(np.random.default_rng(K).integers(-2 ** 15, 2 ** 15, n * K * N)).to(it).cuda()
+    outs = []
+    for off in (0, 1):
+        src = torch.zeros(n * K * N + 8, dtype=it, device="cuda:0")
+        src[off:off + n * K * N] = w
+        out = torch.full((n * K * N + 16,), -7, dtype=it, device="cuda:0")
+        B.moe_pack_weights(src[off:], None, n, K, N, dt, out[off:])
+        torch.cuda.synchronize()
+        assert (out[:off] == -7).all() and (out[off + n * K * N:] == -7).all()
+        outs.append(out[off:off + n * K * N].clone())
+    assert torch.equal(outs[0], outs[1])
+    ref = to_numpy(w).reshape(n, K, N).transpose(0, 2, 1)
+    ref = _bf16_row_order(ref) if dtype == "bf16" else ref
+    assert np.array_equal(to_numpy(outs[0]).reshape(n, N, K), ref)
+
+
 @pytest.mark.parametrize("dtype,n,F,d", [("bf16", 2, 96, 160), ("bf16", 1, 50, 64), ("f32", 2, 40, 70)])
 def test_pack_w_out(torch_gpu, dtype, n, F, d):
     """Output-major and in the row order of moe_pack_weights; bf16 values become the nearest IEEE
