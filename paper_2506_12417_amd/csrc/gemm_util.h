@@ -17,6 +17,9 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // s_waitcnt on lgkmcnt only
 #define MOE_WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (((n) & 0xF) << 8))
 
+// cache policy of a buffer access: nontemporal
+constexpr int CACHE_NT = 2;
+
 __device__ __forceinline__ float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
 // raw buffer descriptor over [p, p + bytes): offsets beyond `bytes` read 0 / are not written
