@@ -2,9 +2,9 @@
 // (Alg. 1 step 1).
 //
 // One work-group takes 32 tokens.  Logits x.W_g are accumulated by v_mfma_f32_32x32x16_bf16 in
-// chunks of KA terms (bf16 x bf16 products are exact in fp32); each chunk's fp32 result is added
+// chunks of KACC terms (bf16 x bf16 products are exact in fp32); each chunk's fp32 result is added
 // into fp64 accumulators, so only the rounding inside a chunk counts: |error| <= c * |x_t| * |w_e|
-// with c = (2*KA+6) * 2^-24 (two roundings per term allowed for, since the accumulation order
+// with c = (2*KACC+6) * 2^-24 (two roundings per term allowed for, since the accumulation order
 // inside the instruction is not specified).  A token whose deciding gaps are all wider than twice
 // that bound keeps its fp32 selection; the others get the logits of every expert that could still
 // reach the top k recomputed in fp64, so expert indices and their order are those of exact
@@ -30,7 +30,10 @@ typedef u32x4 frag_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 constexpr int KC = 64;                 // terms per chunk (four MFMAs)
-constexpr int KACC = 256;              // prepared-router kernel: terms per fp32 accumulation
+// Terms per fp32 accumulation.  Fewer make the bound on a logit's error tighter, and with it the share
+// of tokens that the exact path has to look at again (which is what a work-group then waits for):
+// 256 terms: 34.3 us for 8192 tokens x 2048, E = 60, k = 4, 51 us at E = 256, k = 8; 64 terms: 26.7 and 38.
+constexpr int KACC = 64;
 constexpr int MAXR = MOE_MAX_TOPK + 1;
 constexpr float NEG_INF = -__builtin_huge_valf();
 
@@ -96,19 +99,36 @@ struct RouteLds {
     static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 4 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
 };
 
+// What a thread needs of the bias: fetched before the product, so that its latency passes under it.
+struct RouteBias {
+    float column;          // of the logits that this thread forms
+    float largest;         // |bias| of expert `tid`: this thread's share of the largest one
+};
+template <int NB, int KSP>
+__device__ __forceinline__ RouteBias route_bias(const float* __restrict__ bias, int E) {
+    typedef RouteLds<NB, KSP> L;
+    static_assert(L::NTHR % L::EPT == 0, "one thread per expert at least, and one column per thread");
+    const int tid = threadIdx.x;
+    const int e = KSP > 1 ? tid % L::EPT : (tid >> 6) * 32 + (tid & 31);
+    RouteBias b = {0.f, 0.f};
+    if (bias && e < E) b.column = bias[e];
+    if (bias && tid < E) b.largest = fmaxf(0.f, fabsf(bias[tid]));       // (a NaN does not count)
+    return b;
+}
+
 // Logits, softmax, top-k and the exact path, from the wavefronts' fp64 sums: acc64[r] = token
 // 8*(r/4) + 4*lhi + r%4, expert nbi*32 + l32, contraction part ksi.  xsq: this lane's share of the token
 // norms (wavefronts of expert block 0).  w2: this thread's share of the largest squared column
 // norm.  All threads of the work-group arrive with the staging memory no longer in use.
-template <int NB, int KSP, int RMAX, int KA, bool PACKED>
-__device__ __forceinline__ void route_finish(unsigned char* smem, const double (&acc64)[16], float xsq, float w2,
+template <int NB, int KSP, int RMAX, bool PACKED>
+__device__ __forceinline__ void route_finish(unsigned char* smem, const double (&acc64)[16], float xsq, float w2, const RouteBias& mine_b,
                                              const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
                                              const float* __restrict__ bias, int T, int d, int E, int k, int renorm,
                                              int32_t* __restrict__ idx_out, float* __restrict__ w_out,
                                              float* __restrict__ logits_out) {
     typedef RouteLds<NB, KSP> L;
     constexpr int NWV = L::NWV, NTHR = L::NTHR, TB = L::TB, EPT = L::EPT, PL = L::PL;
-    constexpr int TPT = NTHR / TB >= 16 ? 16 : 8;    // threads per token in the selection
+    constexpr int TPT = NTHR / TB >= 16 && EPT >= 64 ? 16 : 8;    // threads per token in the selection
     double* slab = reinterpret_cast<double*>(smem);  // [KSP][32][EPT], later the candidate lists
     float* ls = reinterpret_cast<float*>(smem + L::REGION0);     // logits [32][PL]
     float* xn2p = ls + TB * PL;                      // [KSP][32]
@@ -141,14 +161,14 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 double v = slab[i];
 #pragma unroll
                 for (int p = 1; p < KSP; ++p) v += slab[p * TB * EPT + i];
-                const float l = (float)(v + (bias ? (double)bias[e] : 0.0));
+                const float l = (float)(v + (double)mine_b.column);
                 ls[tok * PL + e] = l;
                 if (logits_out && t0 + tok < T) logits_out[(size_t)(t0 + tok) * E + e] = l;
             }
         }
     } else {
         const int e = nbi * 32 + l32;
-        const double be = (bias && e < E) ? (double)bias[e] : 0.0;
+        const double be = (double)mine_b.column;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int tok = 8 * (r >> 2) + 4 * lhi + (r & 3);
@@ -163,11 +183,8 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     xsq += __shfl_xor(xsq, 32);
     if (nbi == 0 && lhi == 0) xn2p[ksi * TB + l32] = xsq;
     {   // largest column norm and largest |bias|
-        float bm = 0.f;
-        if (bias)
-            for (int e = tid; e < E; e += NTHR) bm = fmaxf(bm, fabsf(bias[e]));
         w2 = moe_wave_max_nonneg(w2);
-        bm = moe_wave_max_nonneg(bm);
+        const float bm = moe_wave_max_nonneg(mine_b.largest);
         if (lane == 0) { red[wave] = w2; red[NWV + wave] = bm; }
     }
     __syncthreads();
@@ -245,7 +262,7 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
 #pragma unroll
         for (int p = 1; p < KSP; ++p) xs2 += xn2p[p * TB + tok];
         const float xn = sqrtf(xs2) * 1.0001f;
-        const float tau = 2.1f * u * ((2 * KA + 6) * xn * wn_max + bmax);
+        const float tau = 2.1f * u * ((2 * KACC + 6) * xn * wn_max + bmax);
         bool near = false;
 #pragma unroll
         for (int r = 0; r + 1 < RMAX; ++r)
@@ -406,7 +423,7 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
                                                   const float* __restrict__ w_norm2, const float* __restrict__ bias,
                                                   int T, int d, int E, int k, int renorm, int32_t* __restrict__ idx_out,
                                                   float* __restrict__ w_out, float* __restrict__ logits_out) {
-    constexpr int NWV = NB * KSP, NTHR = NWV * 64, TB = 32, EPT = 32 * NB;
+    constexpr int NWV = NB * KSP, TB = 32, EPT = 32 * NB;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -415,23 +432,13 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     const int n_chunks = d / KC;
     const int rows = T - t0 < TB ? T - t0 : TB;
     float xsq = 0.f;
+    const RouteBias mine = route_bias<NB, KSP>(bias, E);
+    const float w2 = tid < E ? fmaxf(0.f, w_norm2[tid]) : 0.f;           // this thread's share of the largest column norm
 
     double acc64[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc64[r] = 0.0;
-    f32x16 acc;
-    int in_acc = 0;
-    auto clear_acc = [&]() {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        in_acc = 0;
-    };
-    auto flush_acc = [&]() {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
-        clear_acc();
-    };
-    clear_acc();
+    static_assert(KACC == KC, "a chunk is what one fp32 accumulation holds");
 
     // ---- staging.  Stage s holds the chunks s*KSP ... s*KSP+KSP-1: for each, 32 token rows, then
     // for each EPT expert rows, every row one 128-byte line (64 terms) in eight 16-byte pieces,
@@ -497,6 +504,9 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
             const unsigned char* xb = ring + (st % RING) * STAGE + ksi * (TB + EPT) * 128;
             const unsigned char* wb_ = xb + (TB + nbi * 32) * 128;
             frag_t xa[KC / 16], wb[KC / 16];
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KC / 16; ++ks) {
                 const int pos = ((ks * 2 + lhi) ^ frag_sw) << 4;
@@ -515,15 +525,13 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
                     }
                 }
             }
-            if (++in_acc == KACC / KC) flush_acc();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
         }
     }
-    if (in_acc) flush_acc();
     MOE_WAIT_VMCNT(0);                                       // (the trailing empty loads still target this LDS)
     __syncthreads();                                         // the ring's memory is reused below
-    float w2 = 0.f;
-    for (int e = tid; e < E; e += NTHR) w2 = fmaxf(w2, w_norm2[e]);
-    route_finish<NB, KSP, RMAX, KACC, true>(smem, acc64, xsq, w2, x, wgt, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
+    route_finish<NB, KSP, RMAX, true>(smem, acc64, xsq, w2, mine, x, wgt, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
 }
 
 template <int NB, int KSP, int RMAX>
@@ -548,7 +556,6 @@ __global__ __launch_bounds__(NB * KSP * 64, 2) void route_packed_kernel(const ui
 // both the fragment reads (16 consecutive rows, one piece) and the transposed writes (every
 // eighth row, one piece) touch all banks once.
 constexpr int KPLAIN = 128;            // terms per stage and contraction part
-constexpr int KA_PLAIN = 64;           // terms per fp32 accumulation: recomputing a column of W_g is dear here
 
 __device__ __forceinline__ int plain_swz(int r) { return (((r & 7) << 1) ^ (r >> 3)) & 15; }
 
@@ -606,6 +613,7 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
         }
     };
 
+    const RouteBias mine = route_bias<NB, KSP>(bias, E);
     double acc64[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc64[r] = 0.0;
@@ -643,13 +651,13 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
         __syncthreads();
         if (st + 1 < n_stages) load_stage(st + 1);
 #pragma unroll
-        for (int h = 0; h < KPLAIN / KA_PLAIN; ++h) {
+        for (int h = 0; h < KPLAIN / KACC; ++h) {
             f32x16 acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < KA_PLAIN / 16; ++ks) {
-                const int flip = (h * (KA_PLAIN / 16) + ks) << 5;
+            for (int ks = 0; ks < KACC / 16; ++ks) {
+                const int flip = (h * (KACC / 16) + ks) << 5;
                 const frag_t xa = *(const frag_t*)(smem + (xb_at ^ flip)), wa = *(const frag_t*)(smem + (wb_at ^ flip));
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa), __builtin_bit_cast(bf16x8, wa), acc, 0, 0, 0);
 #pragma unroll
@@ -679,7 +687,7 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
         w2 = fmaxf(w2, v * 1.002f);
     }
     __syncthreads();                                         // the staging memory is free now
-    route_finish<NB, KSP, RMAX, KA_PLAIN, false>(smem, acc64, xsq, w2, x, wg, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
+    route_finish<NB, KSP, RMAX, false>(smem, acc64, xsq, w2, mine, x, wg, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
 }
 
 template <int NB, int KSP, int RMAX>
