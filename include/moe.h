@@ -269,7 +269,9 @@ MOE_API int moe_pack_w_out(const void* w, int n, int F, int d, moe_dtype dt, voi
  *   MOE_RELU    y_perm[r] = max(0, x_perm[r] W1_e) W2_e
  *   MOE_SWIGLU  y_perm[r] = (silu(x_perm[r] Wgate_e) * (x_perm[r] Wup_e)) Wdown_e,  silu(z) = z/(1+exp(-z))
  *
- * The work is taken from the tile table of moe_plan_tiles: each XCD runs the tiles of its bin.
+ * The work is taken from the tile table of moe_plan_tiles: each XCD runs the tiles of its bin, except
+ * in calls so small that most XCDs would idle (and in fp32, where arithmetic alone counts): there
+ * all work-groups share all tiles.
  *
  *   x_perm [A,d] dt
  *   w_in  : device array of E device pointers; w_in[e] = packed [F,d] (ReLU) or [2F,d] (SwiGLU,

@@ -65,8 +65,9 @@ static bool few_rows_per_expert(int A, int E) {
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
 // Measured with and without the hint (both products): 128 experts of 768 x 3072, Zipf 1.0: 8 rows
 // each 213 : 228 us, 16 rows 257 : 267, 32 rows 284 : 278; 60 of 2048 x 1408, Zipf 1.2: 13 rows 203 :
-// 219, 27 rows 234 : 245, 53 rows 261 : 251.
-static bool moe_weights_once(int A, int E) { return A <= 24ll * E; }
+// 219, 27 rows 234 : 245, 53 rows 261 : 251.  Only where the matrices are larger than the memory-side
+// cache (256 MB): smaller ones may be found there by the next call (16 of 1024 x 2048: 46 : 43 us).
+static bool moe_weights_once(int A, int E, long long weights_bytes) { return A <= 24ll * E && weights_bytes > (256ll << 20); }
 
 static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F, int E, moe_act act, moe_dtype dt,
                             const void* const* w_in, const void* const* w_out, const moe_tile* tiles,
@@ -108,7 +109,13 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1).
         auto wide = [&](int epi, int K) { return tile_m == 256 && g_kernel_mode != 1 && moe_gemm_wide_supports(epi, K); };
         const bool rows = tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
-        const bool once = moe_weights_once(A, E);
+        // (the eight XCDs' L2s hold 32 MB)
+        auto cache = [&](long long weights, size_t out_bytes) {
+            return moe_weights_once(A, E, weights * E * 2) ? MOE_CACHE_WEIGHTS_ONCE
+                   : out_bytes > (32u << 20)               ? MOE_CACHE_LARGE_OUT
+                                                           : MOE_CACHE_PLAIN;
+        };
+        const int cache_h = cache((long long)d * n1, (size_t)A * F * 2), cache_y = cache((long long)F * d, (size_t)A * d * 4);
         if (phases & 1) {
             const int epi = act == MOE_SWIGLU ? MOE_EPI_SWIGLU : MOE_EPI_RELU;
             if (rows && gather.on)
@@ -124,14 +131,14 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                 rc = moe_launch_gemm_wide_gather(epi, x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
                                                  gather.perm, gather.k);
             else if (gather.on)
-                rc = moe_launch_gemm_bf16_gather(epi, once, x_perm, gather.x_rows, d, n1,
+                rc = moe_launch_gemm_bf16_gather(epi, cache_h, x_perm, gather.x_rows, d, n1,
                                                  w_in, tiles, plan_hdr, h_scratch, F, st, gather.perm, gather.k);
             else if (stream(epi, d))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(n1), x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else if (wide(epi, d))
                 rc = moe_launch_gemm_wide(epi, x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else
-                rc = moe_launch_gemm_bf16(epi, tile_m, narrow(n1), once, x_perm, d, n1,
+                rc = moe_launch_gemm_bf16(epi, tile_m, narrow(n1), cache_h, x_perm, d, n1,
                                           w_in, tiles, plan_hdr, h_scratch, F, st);
             if (rc != MOE_OK) return rc;
         }
@@ -147,10 +154,10 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                 rc = moe_launch_gemm_wide(epi, h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
                                           top1.gate_w, top1.on ? A : 0);
             else if (top1.on)
-                rc = moe_launch_gemm_bf16(MOE_EPI_SCATTER, tile_m, narrow(d), once, h_scratch, F, d, w_out, tiles, plan_hdr,
+                rc = moe_launch_gemm_bf16(MOE_EPI_SCATTER, tile_m, narrow(d), cache_y, h_scratch, F, d, w_out, tiles, plan_hdr,
                                           (void*)y_perm, d, st, top1.perm, top1.gate_w, A);
             else
-                rc = moe_launch_gemm_bf16(MOE_EPI_STORE, tile_m, narrow(d), once, h_scratch, F, d, w_out, tiles, plan_hdr,
+                rc = moe_launch_gemm_bf16(MOE_EPI_STORE, tile_m, narrow(d), cache_y, h_scratch, F, d, w_out, tiles, plan_hdr,
                                           (void*)y_perm, d, st);
             if (rc != MOE_OK) return rc;
         }

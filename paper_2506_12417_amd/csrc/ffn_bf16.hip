@@ -88,7 +88,7 @@ struct Cfg {
 // (Every lambda of the body is force-inlined: one that the compiler leaves as a call takes its
 // captures through memory, and with them go the LDS address space of the ring and the
 // wave-uniformity of the item bookkeeping -- flat loads and vector loads with full waits.)
-template <int EPI, int BM, int BN, int BK, int RING, int WM, int WN, int CS, bool GATHER, bool ONCE>
+template <int EPI, int BM, int BN, int BK, int RING, int WM, int WN, int CS, bool GATHER, int CACHE>
 __device__ __forceinline__ void gemm_bf16_body(const uint16_t* __restrict__ a_mat, int K, int N,
                                                const void* const* __restrict__ w_ptrs,
                                                const moe_tile* __restrict__ tiles, int32_t* __restrict__ hdr,
@@ -118,13 +118,10 @@ __device__ __forceinline__ void gemm_bf16_body(const uint16_t* __restrict__ a_ma
     const int n_col_blocks = (N + BN - 1) / BN;
     const int KT = K / BK;
 
-    // the bin's work list and this work-group's share of it
+    // the work list (a bin's, or in small calls everybody's) and this work-group's share of it
     const int G = hdr[1];
-    const int bin = blockIdx.x % G;
-    const int stride = ((int)gridDim.x - bin + G - 1) / G;
-    const int first = blockIdx.x / G;
-    const int bin_start = hdr[4 + bin];
-    const int n_tiles = hdr[4 + bin + 1] - bin_start;
+    const WorkShare ws = work_share(hdr, n_col_blocks);
+    const int bin = ws.bin, stride = ws.stride, first = ws.first, bin_start = ws.bin_start, n_tiles = ws.n_tiles;
     const int n_items = n_tiles * n_col_blocks;
 
     // ---- who takes which item.  The first round is fixed: work-group j of the bin starts with
@@ -253,10 +250,10 @@ __device__ __forceinline__ void gemm_bf16_body(const uint16_t* __restrict__ a_ma
         l_rb = make_rsrc(wmat + (size_t)n0 * K, (unsigned)nr * (unsigned)K * 2u);
     };
     // load q of a stage (the A passes first, then the B passes), and the bookkeeping once all are out
-    // (ONCE: nearly every tile is its expert's only one, so its weights are read once: they are marked
-    // nontemporal and leave the L2 to the rows.  768 x 3072, 128 experts, 1000 rows: 110 + 118 ->
-    // 103 + 110 us; with weights that other work-groups share it costs as much, see moe_weights_once.)
-    constexpr int W_POLICY = ONCE ? CACHE_NT : 0;
+    // (weights nontemporal: nearly every tile is its expert's only one, so its weights are read once and
+    // leave the L2 to the rows.  768 x 3072, 128 experts, 1000 rows: 110 + 118 -> 103 + 110 us; with
+    // weights that other work-groups share it costs as much, see moe_weights_once.)
+    constexpr int W_POLICY = CACHE == MOE_CACHE_WEIGHTS_ONCE ? CACHE_NT : 0;
     auto issue_load = [&](int q) __attribute__((always_inline)) {
         unsigned char* st = ring + l_buf * C::STAGE_BYTES + wave * 1024;
         const unsigned k_off = (unsigned)l_kt * (BK * 2);
@@ -411,18 +408,20 @@ __device__ __forceinline__ void gemm_bf16_body(const uint16_t* __restrict__ a_ma
     constexpr int ES = HALF_IN ? 4 : 2;
     const unsigned ld_bytes = (unsigned)ld_out * ES;
     const unsigned st_voff = (unsigned)(wm * 32 + 4 * lq) * ld_bytes + (unsigned)(2 * l16) * ES;
-    // (Nontemporal: neither the hidden activations nor the outputs are read again by this launch, and kept
-    // in the L2 they displace weights that are.  16384 rows of 768 x 3072, 128 experts: second
-    // product 187 -> 174 us.)
+    // (Outputs nontemporal: where they are larger than the L2s, keeping them there displaces weights
+    // that this launch reads again.  16384 rows of 768 x 3072, 128 experts: second product 187 ->
+    // 174 us.  Smaller ones the next launch finds in the L2: one expert of 2048 x 5632 with 128 rows,
+    // second product 62 us after nontemporal stores, 54 after plain ones.)
+    constexpr int O_POLICY = CACHE == MOE_CACHE_LARGE_OUT ? CACHE_NT : 0;
     auto store_pair = [&](__amdgpu_buffer_rsrc_t ro, float lo, float hi, unsigned voff, unsigned soff) __attribute__((always_inline)) {
         if (HALF_IN) {
             u32x2 v = {__float_as_uint(lo), __float_as_uint(hi)};
-            __builtin_amdgcn_raw_buffer_store_b64(v, ro, voff, soff, CACHE_NT);
+            __builtin_amdgcn_raw_buffer_store_b64(v, ro, voff, soff, O_POLICY);
         } else {
             // hidden activations saturate at the largest half value instead of becoming infinite
             const f32x2 f = {__builtin_amdgcn_fmed3f(lo, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(hi, -65504.f, 65504.f)};
             const f16x2 b = __builtin_convertvector(f, f16x2);            // nearest-even
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, b), ro, voff, soff, CACHE_NT);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, b), ro, voff, soff, O_POLICY);
         }
     };
     auto epilogue = [&](__amdgpu_buffer_rsrc_t ro, int mi_on, int n0) __attribute__((always_inline)) {
@@ -627,7 +626,7 @@ __device__ __forceinline__ void gemm_bf16_body(const uint16_t* __restrict__ a_ma
     MOE_WAIT_VMCNT(0);                                      // (the trailing empty loads still target this LDS)
 }
 
-template <int EPI, int BM, int BN, int BK, int RING, int WM, int WN, int CS, bool GATHER, bool ONCE>
+template <int EPI, int BM, int BN, int BK, int RING, int WM, int WN, int CS, bool GATHER, int CACHE>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(const uint16_t* __restrict__ a_mat, int K, int N,
                                                                   const void* const* __restrict__ w_ptrs,
                                                                   const moe_tile* __restrict__ tiles,
@@ -635,7 +634,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(const uint16_t*
                                                                   int ld_out, const int32_t* __restrict__ row_token,
                                                                   const float* __restrict__ row_gate, int out_rows,
                                                                   int a_div) {
-    gemm_bf16_body<EPI, BM, BN, BK, RING, WM, WN, CS, GATHER, ONCE>(a_mat, K, N, w_ptrs, tiles, hdr, out, ld_out, row_token,
+    gemm_bf16_body<EPI, BM, BN, BK, RING, WM, WN, CS, GATHER, CACHE>(a_mat, K, N, w_ptrs, tiles, hdr, out, ld_out, row_token,
                                                               row_gate, out_rows, a_div);
 }
 
@@ -646,13 +645,13 @@ struct ScatterArgs {             // MOE_EPI_SCATTER: output row and gate value o
     int a_div = 1;
 };
 
-template <int EPI, class C, bool GATHER = false, bool ONCE = false>
-int launch(const void* a, int K, int N, const void* const* w, const moe_tile* tiles, int32_t* hdr, void* out,
+template <int EPI, class C, bool GATHER, int CACHE>
+int launch_policy(const void* a, int K, int N, const void* const* w, const moe_tile* tiles, int32_t* hdr, void* out,
            int ld_out, const ScatterArgs& sc, hipStream_t st) {
     static_assert(C::SMEM <= 160 * 1024, "LDS ring too large");
     const int dev_ok = moe_check_gemm_device();
     if (dev_ok != MOE_OK) return dev_ok;
-    auto kern = gemm_bf16_kernel<EPI, C::BM, C::BN, C::BK, C::RING, C::WM, C::WN, C::CS, GATHER, ONCE>;
+    auto kern = gemm_bf16_kernel<EPI, C::BM, C::BN, C::BK, C::RING, C::WM, C::WN, C::CS, GATHER, CACHE>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)C::SMEM);
     if (e != hipSuccess) return moe_fail(MOE_ERR_HIP, "moe_grouped_ffn: shared memory attribute: %s", hipGetErrorString(e));
@@ -662,22 +661,31 @@ int launch(const void* a, int K, int N, const void* const* w, const moe_tile* ti
     return MOE_OK;
 }
 
+template <int EPI, class C, bool GATHER = false>
+int launch(int cache, const void* a, int K, int N, const void* const* w, const moe_tile* tiles, int32_t* hdr, void* out, int ld_out,
+           const ScatterArgs& sc, hipStream_t st) {
+    if constexpr (C::BM == 128) {
+        if (cache == MOE_CACHE_WEIGHTS_ONCE)
+            return launch_policy<EPI, C, GATHER, MOE_CACHE_WEIGHTS_ONCE>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+        if (cache == MOE_CACHE_LARGE_OUT)
+            return launch_policy<EPI, C, GATHER, MOE_CACHE_LARGE_OUT>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    }
+    return launch_policy<EPI, C, GATHER, MOE_CACHE_PLAIN>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+}
+
 //          BM   BN  BK RING WM WN CS
 typedef Cfg<256, 256, 64, 2, 2, 4, 2> Tall;     // wavefront tile 128 x 64, two phases pairs per K-step
 typedef Cfg<128, 256, 64, 3, 2, 4, 4> Short;    // wavefront tile  64 x 64, one phase pair per K-step
 typedef Cfg<128, 128, 64, 4, 2, 4, 4> Narrow;   // wavefront tile  64 x 32: twice the items, for few column blocks
 
 template <int EPI>
-int launch_tile(int tile_m, int narrow, bool once, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
+int launch_tile(int tile_m, int narrow, int cache, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
                 int32_t* hdr, void* out, int ld_out, const ScatterArgs& sc, hipStream_t st) {
-    if (tile_m == 256) return launch<EPI, Tall>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    if (tile_m == 256) return launch<EPI, Tall>(cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
     if constexpr (EPI != MOE_EPI_SWIGLU) {          // (the SwiGLU epilogue needs a gate and an up block per wavefront)
-        if (narrow)
-            return once ? launch<EPI, Narrow, false, true>(a, K, N, w, tiles, hdr, out, ld_out, sc, st)
-                        : launch<EPI, Narrow>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+        if (narrow) return launch<EPI, Narrow>(cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
     }
-    return once ? launch<EPI, Short, false, true>(a, K, N, w, tiles, hdr, out, ld_out, sc, st)
-                : launch<EPI, Short>(a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    return launch<EPI, Short>(cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
 }
 
 }  // namespace
@@ -702,32 +710,28 @@ int moe_check_gemm_device() {
     return MOE_OK;
 }
 
-int moe_launch_gemm_bf16(int epi, int tile_m, int narrow, bool once, const void* a, int K, int N, const void* const* w,
+int moe_launch_gemm_bf16(int epi, int tile_m, int narrow, int cache, const void* a, int K, int N, const void* const* w,
                          const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                          const int32_t* row_token, const float* row_gate, int out_rows) {
     ScatterArgs sc;
-    if (epi == MOE_EPI_RELU) return launch_tile<MOE_EPI_RELU>(tile_m, narrow, once, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
-    if (epi == MOE_EPI_SWIGLU) return launch_tile<MOE_EPI_SWIGLU>(tile_m, narrow, once, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    if (epi == MOE_EPI_RELU) return launch_tile<MOE_EPI_RELU>(tile_m, narrow, cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    if (epi == MOE_EPI_SWIGLU) return launch_tile<MOE_EPI_SWIGLU>(tile_m, narrow, cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
     if (epi == MOE_EPI_SCATTER) {
         sc.row_token = row_token;
         sc.row_gate = row_gate;
         sc.out_rows = out_rows;
-        return launch_tile<MOE_EPI_SCATTER>(tile_m, narrow, once, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+        return launch_tile<MOE_EPI_SCATTER>(tile_m, narrow, cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
     }
-    return launch_tile<MOE_EPI_STORE>(tile_m, narrow, once, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    return launch_tile<MOE_EPI_STORE>(tile_m, narrow, cache, a, K, N, w, tiles, hdr, out, ld_out, sc, st);
 }
 
-int moe_launch_gemm_bf16_gather(int epi, bool once, const void* x, int x_rows, int K, int N, const void* const* w,
+int moe_launch_gemm_bf16_gather(int epi, int cache, const void* x, int x_rows, int K, int N, const void* const* w,
                                 const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div) {
     ScatterArgs sc;
     sc.row_token = row_src;
     sc.out_rows = x_rows;
     sc.a_div = src_div;
-    auto go = [&](auto glu, auto nt) {
-        return launch<decltype(glu)::value ? MOE_EPI_SWIGLU : MOE_EPI_RELU, Short, true, decltype(nt)::value>(x, K, N, w, tiles, hdr, out,
-                                                                                                             ld_out, sc, st);
-    };
-    if (epi == MOE_EPI_SWIGLU) return once ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
-    return once ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+    if (epi == MOE_EPI_SWIGLU) return launch<MOE_EPI_SWIGLU, Short, true>(cache, x, K, N, w, tiles, hdr, out, ld_out, sc, st);
+    return launch<MOE_EPI_RELU, Short, true>(cache, x, K, N, w, tiles, hdr, out, ld_out, sc, st);
 }

@@ -11,15 +11,19 @@ constexpr int MOE_GEMM_GRID = 256;
 // SCATTER writes fp32 row r to out[row_token[r]] times row_gate[row_token[r]] (row_gate may be null;
 // out has out_rows rows).
 // tile_m: 128 or 256 (the tile height the table was planned with).  narrow: with tile_m = 128,
-// use column blocks of 128 instead of 256 outputs (ignored for SWIGLU).  once: an expert's weights are
-// hardly shared between work items (a cache hint; 128-row tiles).
-int moe_launch_gemm_bf16(int epi, int tile_m, int narrow, bool once, const void* a, int K, int N, const void* const* w,
+// use column blocks of 128 instead of 256 outputs (ignored for SWIGLU).  cache: a hint for 128-row tiles.
+enum {
+    MOE_CACHE_PLAIN = 0,
+    MOE_CACHE_WEIGHTS_ONCE = 1,    // an expert's weights are hardly shared between work items
+    MOE_CACHE_LARGE_OUT = 2        // the output is larger than the L2s
+};
+int moe_launch_gemm_bf16(int epi, int tile_m, int narrow, int cache, const void* a, int K, int N, const void* const* w,
                          const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                          const int32_t* row_token = nullptr, const float* row_gate = nullptr, int out_rows = 0);
 
 // The first product with the row gather folded in (128-row tiles, RELU or SWIGLU; K / 64 >= 4):
 // row r of the table's row space is row row_src[r] / src_div of x [x_rows, K].
-int moe_launch_gemm_bf16_gather(int epi, bool once, const void* x, int x_rows, int K, int N, const void* const* w,
+int moe_launch_gemm_bf16_gather(int epi, int cache, const void* x, int x_rows, int K, int N, const void* const* w,
                                 const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div);
 

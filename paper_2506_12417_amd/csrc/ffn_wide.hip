@@ -432,12 +432,11 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.N = N;
     g.KT = K / C::BK;                                        // (even: K is a multiple of 64)
     g.n_col_blocks = (N + C::BN - 1) / C::BN;
-    const int G = hdr[1];
-    const int bin = blockIdx.x % G;
-    g.stride = ((int)gridDim.x - bin + G - 1) / G;
-    const int first = blockIdx.x / G;
-    g.bin_start = hdr[4 + bin];
-    g.n_tiles = hdr[4 + bin + 1] - g.bin_start;
+    const WorkShare ws = work_share(hdr, g.n_col_blocks);
+    const int first = ws.first;
+    g.stride = ws.stride;
+    g.bin_start = ws.bin_start;
+    g.n_tiles = ws.n_tiles;
     g.n_items = g.n_tiles * g.n_col_blocks;
     if (first >= g.n_items) return;
 

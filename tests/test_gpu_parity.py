@@ -734,6 +734,35 @@ def test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, polic
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
 
 
+@pytest.mark.parametrize("rows,d,F,tile_m,bins", [([300], 256, 1024, 128, 8), ([700, 10], 256, 512, 128, 8), ([900], 256, 512, 256, 8),
+                                                  ([520, 33, 260], 320, 704, 128, 3), ([300, 0, 40], 512, 256, 256, 16)])
+def test_small_calls_shared_by_all_work_groups(torch_gpu, rows, d, F, tile_m, bins):
+    """Few experts and blocks below q: the plan leaves the work on one or two bins, and the tile
+    kernels give it to all work-groups instead; twice in a row (the work counters), against the
+    oracle and with every row written."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    wl = W.WORKLOADS["c2"].scaled(T=A, d=d, F=F, E=E, k=1, skew="uniform")
+    _note("small calls rows %s d=%d F=%d tile_m=%d" % (rows, d, F, tile_m))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, inp, tile_m=tile_m, n_bins=bins, policy=B.MOE_PLAN_STATIC)
+    ids = _few(rows).reshape(A, 1)
+    layer.expert_idx.copy_(to_device(ids, layer.device))
+    x = layer_x(layer, inp)
+    p = O.permute(ids, E)
+    yp = O.grouped_ffn(O.gather_rows(inp["x"], p["perm"], 1), p["offsets"], expert_dict(wl, inp), wl.act, h_round="f16")
+    layer.permute(x)
+    layer.plan()
+    for _ in range(2):
+        layer.y_perm.fill_(float("nan"))
+        layer.ffn()
+        torch.cuda.synchronize()
+        assert max_err_over_rms(to_numpy(layer.y_perm), yp) <= 1e-3      # (as in _stage_check)
+        assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
+
+
 WIDE_CASES = [
     # T, d, F, E, k, act, skew, bins: the four-wavefront kernels for 256-row tiles against the LDS-ring kernels
     (3000, 256, 512, 4, 2, "swiglu", "hot", 8),       # full and ragged tiles, several column blocks
