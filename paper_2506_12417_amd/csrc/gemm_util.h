@@ -47,10 +47,13 @@ struct WorkShare {
     int bin, first, stride, bin_start, n_tiles;   // bin: whose work counter hands out the items
 };
 __device__ __forceinline__ WorkShare work_share(const int32_t* __restrict__ hdr, int n_col_blocks) {
-    const int G = hdr[1], grid = (int)gridDim.x, lane = threadIdx.x & 63;
-    const unsigned mine = lane < G ? (unsigned)(hdr[5 + lane] - hdr[4 + lane]) : 0u;
-    const int fullest = (int)moe_wave_max_u32(mine);
-    const int all = sgpr(hdr[4 + G] - hdr[4]);
+    // (the bins' starts are fetched with the number of bins, not after it: one memory latency)
+    const int grid = (int)gridDim.x, lane = threadIdx.x & 63;
+    const int at = lane < MOE_MAX_BINS ? lane : MOE_MAX_BINS - 1;
+    const int start = hdr[4 + at], end = hdr[5 + at];
+    const int G = hdr[1];
+    const int fullest = (int)moe_wave_max_u32(lane < G ? (unsigned)(end - start) : 0u);
+    const int first_tile = __builtin_amdgcn_readlane(start, 0), all = __builtin_amdgcn_readlane(end, G - 1) - first_tile;
     const int rounds_flat = (all * n_col_blocks + grid - 1) / grid;
     const int per_bin = grid / G, rounds_bin = (fullest * n_col_blocks + per_bin - 1) / per_bin;
     WorkShare w;
@@ -58,14 +61,14 @@ __device__ __forceinline__ WorkShare work_share(const int32_t* __restrict__ hdr,
         w.bin = 0;
         w.first = (int)blockIdx.x;
         w.stride = grid;
-        w.bin_start = hdr[4];
+        w.bin_start = first_tile;
         w.n_tiles = all;
     } else {
         w.bin = (int)blockIdx.x % G;
         w.first = (int)blockIdx.x / G;
         w.stride = (grid - w.bin + G - 1) / G;
-        w.bin_start = hdr[4 + w.bin];
-        w.n_tiles = hdr[4 + w.bin + 1] - w.bin_start;
+        w.bin_start = __builtin_amdgcn_readlane(start, w.bin);
+        w.n_tiles = __builtin_amdgcn_readlane(end, w.bin) - w.bin_start;
     }
     return w;
 }
