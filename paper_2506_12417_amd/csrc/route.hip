@@ -81,12 +81,15 @@ __device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, i
     }
 }
 
+// (the copies state no alignment beyond the element's: x may be a view that starts anywhere)
 __device__ __forceinline__ void load4(const float* p, double (&v)[4]) {
-    const float4 f = *reinterpret_cast<const float4*>(p);
+    float4 f;
+    __builtin_memcpy(&f, p, sizeof f);
     v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
 }
 __device__ __forceinline__ void load4(const uint16_t* p, double (&v)[4]) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    uint2 u;
+    __builtin_memcpy(&u, p, sizeof u);
     v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
     v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
 }
