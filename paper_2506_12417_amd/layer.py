@@ -25,7 +25,7 @@ def to_device(a: np.ndarray, device) -> torch.Tensor:
 def default_q_tokens(dt: int) -> int:
     """Eq. 4 with one XCD as the unit and the rates this library reaches on an MI355X: phi = its
     share of the sustained grouped-GEMM rate (about 1.0 PFLOP/s in bf16: the matrix cores run
-    near 1.55 GHz under load; 100 TFLOP/s for the fp32 FMA kernel), beta = its share of the HBM
+    near 1.55 GHz under load; 100 TFLOP/s in fp32), beta = its share of the HBM
     streaming rate (about 6.0 TB/s), d_type = bytes per weight.  With the chip's nominal peaks
     (2.5 PFLOP/s, 8 TB/s) q would be 313 rows, which overstates what a cold expert costs here
     and leaves the bins with unequal numbers of tiles."""
