@@ -216,22 +216,21 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
         float m = NEG_INF;
 #pragma unroll
         for (int j = 0; j < CPT; ++j) {
-            int ve = sub * CPT + j;
-            float v = ve < E ? mine[j] : NEG_INF;                // (columns past E hold nothing)
+            const int ve = sub * CPT + j;
+            const float v = ve < E ? mine[j] : NEG_INF;          // (columns past E hold nothing)
             mine[j] = v;
             m = fmaxf(m, v);
             // sorted insertion, static indices (rising experts: among equals the one before stays ahead;
-            // an entry that holds nothing yet gives way to anything, a logit of -inf included)
+            // an entry that holds nothing yet gives way to anything, a logit of -inf included).  The
+            // entries behind its place all move down one, equal ones too: every place compares the new
+            // logit with its own entry and the one above it, from the last place up.
             if (v > lv[RMAX - 1] || (le[RMAX - 1] == INT_MAX && v == v && ve < E)) {
 #pragma unroll
-                for (int r = 0; r < RMAX; ++r) {
-                    const bool ahead = v > lv[r] || le[r] == INT_MAX;
-                    const float tv = lv[r];
-                    const int te = le[r];
-                    lv[r] = ahead ? v : tv;
-                    le[r] = ahead ? ve : te;
-                    v = ahead ? tv : v;
-                    ve = ahead ? te : ve;
+                for (int r = RMAX - 1; r >= 0; --r) {
+                    const bool here = v > lv[r] || le[r] == INT_MAX;
+                    const bool above = r > 0 && (v > lv[r > 0 ? r - 1 : 0] || le[r > 0 ? r - 1 : 0] == INT_MAX);
+                    lv[r] = above ? lv[r > 0 ? r - 1 : 0] : here ? v : lv[r];
+                    le[r] = above ? le[r > 0 ? r - 1 : 0] : here ? ve : le[r];
                 }
             }
         }

@@ -194,6 +194,38 @@ def test_route_with_experts_masked_by_an_infinite_bias(torch_gpu, E, k):
         assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
 
 
+@pytest.mark.parametrize("E,k", [(8, 2), (8, 8), (60, 2), (60, 4), (128, 1), (128, 8), (256, 4)])
+def test_equal_logits_stay_in_order_where_the_error_bound_vanishes(torch_gpu, E, k):
+    """Activations whose squares underflow make the norms, and with them the bound on a logit's error,
+    zero: no token is looked at again and the sorted lists alone decide.  A row of x holds one
+    entry 2^-100, so its logits are a row of W_g (small integers, many equal) exactly."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    T = d = 64
+    r = np.random.default_rng(E * 16 + k)
+    Wg = r.integers(0, 6, (d, E)).astype(np.float32)
+    Wg[0, :4] = [3, 3, 4, 1]
+    Wg[1, :5] = [5, 3, 3, 3, 4]
+    x = W.f32_to_bf16_bits(np.eye(T, d, dtype=np.float32) * np.float32(2.0 ** -100))
+    Wg = W.f32_to_bf16_bits(Wg)
+    idx_o, _, _ = O.route_topk(x, Wg, None, k, 0)
+    wl = W.WORKLOADS["c2"].scaled(T=T, d=d, E=E, k=k, renorm=0)
+    for packed in (False, True):
+        layer = make_layer(wl, {})
+        layer.load_router(Wg, None, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), packed
+    # the same among experts masked by an infinite bias (infinite gaps are not looked at again either)
+    b = np.full(E, -np.inf, dtype=np.float32)
+    b[2] = 0.0
+    idx_o, _, _ = O.route_topk(x, Wg, b, k, 0)
+    layer.load_router(Wg, b, packed=True)
+    layer.route(to_device(x, layer.device))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_numpy(layer.expert_idx), idx_o)
+
+
 PERMUTE_CASES = [(1, 1, 1, 8), (256, 2, 8, 64), (1000, 1, 128, 32), (5000, 4, 60, 16), (3, 2, 256, 8),
                  (4097, 1, 7, 128), (16384, 1, 128, 768), (35000, 2, 200, 8)]   # the last: more than 64 blocks
 
