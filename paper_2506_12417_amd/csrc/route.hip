@@ -43,10 +43,16 @@ constexpr double NEG_INF = -__builtin_huge_val();
 
 // A wavefront holds one token's logits, lane l owning experts l, l+64, l+128, l+192.  Picks the k
 // largest (ties to the lower expert id), forms their softmax values and writes the choice.
+// A chosen expert gives up its id, not only its logit: -inf is a logit that others may hold (experts
+// masked by their bias), and the chosen one must not come up among those again.
 __device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, int renorm, int32_t* idx_row, float* w_row) {
     double m = NEG_INF, s = 0.0;
+    int id[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) m = v[j] > m ? v[j] : m;
+    for (int j = 0; j < 4; ++j) {
+        id[j] = lane + 64 * j < E ? lane + 64 * j : INT_MAX;
+        if (id[j] != INT_MAX) m = v[j] > m ? v[j] : m;
+    }
     m = wave_max(m);
 #pragma unroll
     for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) s += exp(v[j] - m);
@@ -59,13 +65,11 @@ __device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, i
             double bv = NEG_INF;
             int be = INT_MAX;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = lane + 64 * j;
-                if (e < E && beats(v[j], e, bv, be)) { bv = v[j]; be = e; }
-            }
+            for (int j = 0; j < 4; ++j)
+                if (id[j] != INT_MAX && beats(v[j], id[j], bv, be)) { bv = v[j]; be = id[j]; }
             wave_best(bv, be);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) if (lane + 64 * j == be) v[j] = NEG_INF;
+            for (int j = 0; j < 4; ++j) if (id[j] == be) id[j] = INT_MAX;
             if (r == 0) first = bv;
             sel[r] = be;
             p[r] = exp(bv - first) / denom;

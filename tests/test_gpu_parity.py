@@ -226,6 +226,32 @@ def test_equal_logits_stay_in_order_where_the_error_bound_vanishes(torch_gpu, E,
     assert np.array_equal(to_numpy(layer.expert_idx), idx_o)
 
 
+# (fewer experts left than k, one of them not the lowest: the masked ones must follow by rising index,
+# each once.  bf16 below eight experts and fp32 with one and with several experts per lane)
+@pytest.mark.parametrize("dtype,E,k,left", [("bf16", 4, 3, [0]), ("bf16", 4, 3, [2]), ("bf16", 7, 6, [1, 5]), ("bf16", 2, 2, [1]),
+                                            ("bf16", 8, 8, [7]), ("f32", 4, 3, [2]), ("f32", 16, 8, [3, 9]), ("f32", 128, 5, [70]),
+                                            ("f32", 256, 8, [0, 64, 255])])
+def test_masked_experts_are_chosen_once_and_by_rising_index(torch_gpu, dtype, E, k, left):
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    T, d = 33, 128
+    r = np.random.default_rng(E + k)
+    x, Wg = r.standard_normal((T, d)).astype(np.float32), (r.standard_normal((d, E)) / 11).astype(np.float32)
+    if dtype == "bf16":
+        x, Wg = W.f32_to_bf16_bits(x), W.f32_to_bf16_bits(Wg)
+    b = np.full(E, -np.inf, dtype=np.float32)
+    b[left] = 0.0
+    wl = W.WORKLOADS["c2" if dtype == "bf16" else "c1"].scaled(T=T, d=d, E=E, k=k, renorm=0)
+    idx_o, w_o, _ = O.route_topk(x, Wg, b, k, 0)
+    for packed in (False, True) if dtype == "bf16" else (False,):
+        layer = make_layer(wl, {})
+        layer.load_router(Wg, b, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), packed
+        assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
+
+
 PERMUTE_CASES = [(1, 1, 1, 8), (256, 2, 8, 64), (1000, 1, 128, 32), (5000, 4, 60, 16), (3, 2, 256, 8),
                  (4097, 1, 7, 128), (16384, 1, 128, 768), (35000, 2, 200, 8)]   # the last: more than 64 blocks
 
