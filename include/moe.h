@@ -101,7 +101,9 @@ MOE_API int moe_route_topk_packed(const void* x, const void* w_gate_t, const flo
  *   perm[pos(a)] = a      inv_perm[a] = pos(a)      x_perm[pos(a),:] = x[a div k,:] (bit copy)
  *
  *   x [T,d] dt (may be NULL together with x_perm: indices only)
- *   expert_idx [T,k] int32, every entry in [0,E) (entries outside are not detected)
+ *   expert_idx [T,k] int32.  An entry outside [0,E) (the routers write one for a token whose logits
+ *           are NaN) belongs to no expert: it is not counted, inv_perm is -1 there, and the rows of the
+ *           others are not touched by it; perm and x_perm end after the rows that there are
  *   ws / ws_bytes: scratch of at least moe_workspace_bytes(MOE_OP_PERMUTE, ...)
  */
 MOE_API int moe_permute(const void* x, const int32_t* expert_idx, int T, int d, int E, int k, moe_dtype dt,
@@ -398,6 +400,7 @@ MOE_API int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int d, 
  *   y[t] = sum_{j<k} gate_w[t,j] * y_perm[inv_perm[t*k+j]]  (+ shared[t]),  j ascending, fp32
  *
  *   y_perm [A,d] fp32   inv_perm [A] int32   gate_w [T,k] fp32 (NULL = all ones)
+ *           (a negative inv_perm entry has no row: it adds nothing if its weight is 0, otherwise y[t] is NaN)
  *   shared [T,d] fp32 or NULL (output of an always-on shared expert)      y [T,d] fp32 out
  */
 MOE_API int moe_unpermute_combine(const float* y_perm, const int32_t* inv_perm, const float* gate_w,

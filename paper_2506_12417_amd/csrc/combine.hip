@@ -4,6 +4,8 @@
 // HBM bound: A*d*4 bytes read (+ T*d*4 for the shared expert), T*d*4 written, every byte once: all
 // of it bypasses the caches' keeping (nontemporal), and a thread asks for its k rows together.
 // 20011 x 8 rows of 1032: 4.3 -> 5.7 TB/s; 8192 x 2 rows of 4096 alone: 5.4 -> 6.3 TB/s.
+// An assignment without a row (inv_perm negative) adds nothing if its weight is zero and makes its
+// token NaN otherwise; the first row is fetched in its place and not used.
 #include "common.h"
 
 namespace {
@@ -25,17 +27,20 @@ __global__ __launch_bounds__(NTH) void combine_kernel(const f32x4* __restrict__ 
     for (int j0 = 0; j0 < k; j0 += G) {
         f32x4 r[G];
         float w[G];
+        int row[G];
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const int jj = K ? j : (j0 + j < k ? j0 + j : k - 1);
             w[j] = gate_w ? gate_w[a0 + jj] : 1.f;
-            r[j] = __builtin_nontemporal_load(y_perm + (size_t)inv_perm[a0 + jj] * vpr + v);
+            row[j] = inv_perm[a0 + jj];
+            r[j] = __builtin_nontemporal_load(y_perm + (size_t)(row[j] < 0 ? 0 : row[j]) * vpr + v);
         }
 #pragma unroll
         for (int j = 0; j < G; ++j)
             if (K || j0 + j < k) {
+                const float none = w[j] == 0.f ? 0.f : __builtin_nanf("");
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[c] = fmaf(w[j], r[j][c], acc[c]);
+                for (int c = 0; c < 4; ++c) acc[c] = fmaf(w[j], row[j] < 0 ? none : r[j][c], acc[c]);
             }
     }
     if (shared) {

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(NTH) void rank_kernel(const int32_t* __restrict__ i
 }
 
 // x_perm row inv_perm[t*k+j] <- x row t, in 16-byte pieces (vpr pieces per row), one piece of one
-// token per thread.  HBM bound: x is read once (gathering through perm read it k times through the
+// token per thread; an assignment without a row (inv_perm -1) is skipped.  HBM bound: x is read once (gathering through perm read it k times through the
 // L2 and the row's address at the end of a chain of two loads: 95 us for 20011 x 8 rows of 2064
 // bytes, now 65, 5.7 TB/s.  Nontemporal stores: 106 us, the rows' ends share lines).
 __global__ __launch_bounds__(NTH) void spread_rows_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ inv_perm,
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(NTH) void spread_rows_kernel(const u32x4* __restric
     for (unsigned j0 = 0; j0 < k; j0 += 4) {
         unsigned row[4];
 #pragma unroll
-        for (unsigned j = 0; j < 4; ++j) row[j] = j0 + j < k ? (unsigned)to[j0 + j] : A;
+        for (unsigned j = 0; j < 4; ++j) row[j] = j0 + j < k ? (unsigned)to[j0 + j] : A;       // (-1 is past A)
 #pragma unroll
         for (unsigned j = 0; j < 4; ++j)
             if (row[j] < A) x_perm[(size_t)row[j] * vpr + v] = piece;

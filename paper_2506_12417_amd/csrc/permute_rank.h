@@ -155,6 +155,8 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
             int pos = chunk_hist[c * E + my_e[ci]] + my_rank[ci];
             perm[pos] = a;
             inv_perm[a] = pos;
+        } else if (a < A) {
+            inv_perm[a] = -1;                  // no such expert (a router's token of NaN logits): no row
         }
     }
 }

@@ -278,6 +278,88 @@ def test_permute(torch_gpu, T, k, E, d):
     assert np.array_equal(to_numpy(layer.x_perm), O.gather_rows(x, ref["perm"], k))
 
 
+@pytest.mark.parametrize("name,over", [("c1", dict(T=200, d=64, F=128, E=8, k=2)), ("c1", dict(T=2100, d=64, F=128, E=8, k=1)),
+                                       ("c2", dict(T=200, d=128, F=512, E=8, k=2)), ("c2", dict(T=6, d=128, F=512, E=8, k=2)),
+                                       ("c2", dict(T=300, d=256, F=512, E=16, k=4))])
+def test_a_token_of_nans_leaves_the_others_alone(torch_gpu, name, over):
+    """After a clean pass on the same buffers (so that stale permutation entries are in range): the
+    NaN token's output is NaN, every other token's is the clean pass's, bit for bit."""
+    torch = torch_gpu
+    wl = W.WORKLOADS[name].scaled(skew="uniform", renorm=1, **over)
+    _note("nan token %s %s" % (name, over))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, inp)
+    x = layer_x(layer, inp)
+    clean = layer.forward(x).clone()
+    for bad in (0, wl.T // 2, wl.T - 1):
+        xb = x.clone()
+        xb[bad] = float("nan")
+        y = layer.forward(xb).clone()
+        torch.cuda.synchronize()
+        assert torch.isnan(y[bad]).all()
+        rest = torch.arange(wl.T, device=y.device) != bad
+        assert torch.equal(y[rest].view(torch.int32), clean[rest].view(torch.int32)), bad
+        assert (layer.inv_perm.view(wl.T, wl.k)[bad] == -1).all()
+
+
+# (one to two blocks: counted in the rank kernel; up to 64; more: a scan launch of its own)
+@pytest.mark.parametrize("entry,T,k,E,d", [(entry,) + size for size in [(50, 2, 5, 16), (1500, 1, 100, 8), (3000, 3, 60, 24), (70000, 1, 9, 8)]
+                                           for entry in ("moe_permute", "moe_permute_static", "moe_permute_plan")
+                                           if not (entry == "moe_permute_plan" and size[0] > 32768)])
+def test_ids_outside_the_experts_have_no_row(torch_gpu, entry, T, k, E, d):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    A = T * k
+    _note("%s with ids outside T=%d k=%d E=%d" % (entry, T, k, E))
+    r = np.random.default_rng(A)
+    idx = r.integers(0, E, A).astype(np.int32)
+    out = r.random(A) < 0.1
+    out[[0, A - 1]] = True
+    idx[out] = r.choice(np.array([-1, E, 2 ** 31 - 1, -2 ** 31], dtype=np.int64), out.sum()).astype(np.int32)
+    a = np.flatnonzero(~out)
+    perm_o = a[np.argsort(idx[a], kind="stable")].astype(np.int32)
+    inv_o = np.full(A, -1, dtype=np.int32)
+    inv_o[perm_o] = np.arange(len(perm_o))
+    counts_o = np.bincount(idx[a], minlength=E).astype(np.int32)
+    x = torch.from_numpy(r.integers(-2 ** 15, 2 ** 15, (T, d)).astype(np.int16)).cuda()
+    new = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda:0")     # noqa: E731  (zeros: a row that belongs to somebody)
+    counts, offsets, perm, inv = new(E), new(E + 1), new(A), new(A)
+    x_perm = torch.full((A, d), -7, dtype=torch.int16, device="cuda:0")
+    ids = torch.from_numpy(idx).cuda()
+    if entry == "moe_permute":
+        ws = torch.empty(B.moe_workspace_bytes(B.MOE_OP_PERMUTE, T, d, 0, E, k, B.MOE_BF16), dtype=torch.uint8, device="cuda:0")
+        B.moe_permute(x, ids, T, d, E, k, B.MOE_BF16, counts, offsets, perm, inv, x_perm, ws, ws.numel())
+    elif entry == "moe_permute_static":
+        B.moe_permute_static(x, ids, T, d, E, k, B.MOE_BF16, counts, offsets, perm, inv, x_perm)
+    else:
+        cap = B.moe_plan_capacity(A, E, 128, 8)
+        B.moe_permute_plan(ids, T, E, k, counts, offsets, perm, inv, 128, 8, 50, 1, new((cap, 4)), cap, new(B.MOE_PLAN_HDR_INTS), None)
+    torch.cuda.synchronize()
+    n = len(perm_o)
+    assert np.array_equal(to_numpy(counts), counts_o) and np.array_equal(to_numpy(inv), inv_o)
+    assert np.array_equal(to_numpy(offsets), np.concatenate([[0], np.cumsum(counts_o)]))
+    assert np.array_equal(to_numpy(perm)[:n], perm_o)
+    if entry != "moe_permute_plan":
+        assert np.array_equal(to_numpy(x_perm)[:n], to_numpy(x)[perm_o // k]) and (to_numpy(x_perm)[n:] == -7).all()
+    # the combine: nothing from such an assignment if its weight is zero, NaN otherwise
+    y_perm = torch.from_numpy(r.standard_normal((A, d)).astype(np.float32)).cuda()
+    y_perm[0] = float("inf")                                               # (not to be picked up in its place)
+    first = perm_o[0] // k
+    gate = r.random((T, k)).astype(np.float32) + 0.5
+    drop = (r.random(T) < 0.5)[:, None] & out.reshape(T, k)
+    gate[drop] = 0.0
+    y = torch.empty((T, d), dtype=torch.float32, device="cuda:0")
+    B.moe_unpermute_combine(y_perm, inv, torch.from_numpy(gate).cuda(), None, T, d, k, y)
+    torch.cuda.synchronize()
+    bad = (out.reshape(T, k) & (gate != 0)).any(axis=1)
+    ref = np.where(inv_o[:, None] >= 0, to_numpy(y_perm)[np.maximum(inv_o, 0)], 0.0).reshape(T, k, d).astype(np.float64)
+    ref = (ref * gate[:, :, None]).sum(axis=1)
+    got = to_numpy(y)
+    good = ~bad & (np.arange(T) != first)
+    assert np.isnan(got[bad]).all() and not np.isnan(got[~bad]).any()
+    assert np.abs(got[good] - ref[good]).max(initial=0.0) <= (k + 1) * 2.0 ** -24 * (k + 1) * 9      # as below, weights up to 1.5
+
+
 @pytest.mark.parametrize("T,k,E", [(1, 1, 1), (256, 2, 8), (1000, 1, 128), (5000, 4, 60), (3, 2, 256), (4097, 1, 7),
                                    (16384, 1, 128), (16384, 2, 200), (8192, 4, 60)])
 def test_permute_plan_in_one_launch(torch_gpu, T, k, E):
