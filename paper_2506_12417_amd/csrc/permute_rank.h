@@ -22,7 +22,7 @@ constexpr int CHUNKS = PB / 64;
 // Adds, for every assignment i < A, one to all_[idx[i]] and -- if i < upto -- to before[idx[i]] (LDS
 // counters; before may be null).  Every thread fetches its ids four at a time and sixteen
 // fetches at once: the ids are few (A <= 32768), what counts is that the work-group pays one
-// memory latency, not one per fetch.
+// memory latency, not one per fetch.  (The copy states no alignment beyond an id's: idx may be a view.)
 __device__ __forceinline__ void count_experts(const int32_t* __restrict__ idx, int A, int E, int upto, int* before, int* all_) {
     constexpr int NV = 16;
     for (int i0 = 0; i0 < A; i0 += NV * NTH * 4) {
@@ -31,7 +31,7 @@ __device__ __forceinline__ void count_experts(const int32_t* __restrict__ idx, i
         for (int j = 0; j < NV; ++j) {
             const int i = i0 + (j * NTH + (int)threadIdx.x) * 4;
             if (i + 3 < A) {
-                v[j] = *reinterpret_cast<const int4*>(idx + i);
+                __builtin_memcpy(&v[j], idx + i, sizeof v[j]);
             } else {
                 v[j].x = i < A ? idx[i] : -1;
                 v[j].y = i + 1 < A ? idx[i + 1] : -1;

@@ -360,6 +360,31 @@ def test_ids_outside_the_experts_have_no_row(torch_gpu, entry, T, k, E, d):
     assert np.abs(got[good] - ref[good]).max(initial=0.0) <= (k + 1) * 2.0 ** -24 * (k + 1) * 9      # as below, weights up to 1.5
 
 
+# (ids that start one, two and three elements into a 16-byte piece; one block, two, and more)
+@pytest.mark.parametrize("T,k,E", [(5, 1, 3), (700, 1, 128), (1025, 1, 60), (1011, 2, 7), (4099, 1, 256)])
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_sort_of_ids_at_any_alignment(torch_gpu, T, k, E, off):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    A, dev = T * k, torch.device("cuda:0")
+    _note("ids view T=%d k=%d E=%d off=%d" % (T, k, E, off))
+    idx = np.random.default_rng(A + off).integers(0, E, (T, k)).astype(np.int32)
+    ref = O.permute(idx, E)
+    view = torch.zeros(A + 8, dtype=torch.int32, device=dev)[off:off + A]
+    view.copy_(torch.from_numpy(idx.reshape(-1)))
+    cap = B.moe_plan_capacity(A, E, 128, 8)
+    tiles, hdr = torch.empty((cap, 4), dtype=torch.int32, device=dev), torch.empty(B.MOE_PLAN_HDR_INTS, dtype=torch.int32, device=dev)
+    for entry in ("static", "plan"):
+        out = {n: torch.full((m,), -3, dtype=torch.int32, device=dev) for n, m in (("counts", E), ("offsets", E + 1), ("perm", A), ("inv_perm", A))}
+        if entry == "static":
+            B.moe_permute_static(None, view, T, 8, E, k, B.MOE_BF16, out["counts"], out["offsets"], out["perm"], out["inv_perm"], None)
+        else:
+            B.moe_permute_plan(view, T, E, k, out["counts"], out["offsets"], out["perm"], out["inv_perm"], 128, 8, 50, 1, tiles, cap, hdr, None)
+        torch.cuda.synchronize()
+        for n in out:
+            assert np.array_equal(to_numpy(out[n]), ref[n]), (entry, n)
+
+
 @pytest.mark.parametrize("T,k,E", [(1, 1, 1), (256, 2, 8), (1000, 1, 128), (5000, 4, 60), (3, 2, 256), (4097, 1, 7),
                                    (16384, 1, 128), (16384, 2, 200), (8192, 4, 60)])
 def test_permute_plan_in_one_launch(torch_gpu, T, k, E):
