@@ -187,14 +187,13 @@ int launch_route(const void* x, const void* wg, const float* bias, int T, int d,
     return MOE_OK;
 }
 
-template <typename XT>
-int dispatch_route(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm,
-                   int32_t* idx, float* w, float* logits, hipStream_t st) {
-    if (E <= 16) return launch_route<XT, 1, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 32) return launch_route<XT, 1, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 64) return launch_route<XT, 2, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    if (E <= 128) return launch_route<XT, 4, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
-    return launch_route<XT, 8, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+int route_f32(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
+              float* logits, hipStream_t st) {
+    if (E <= 16) return launch_route<float, 1, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 32) return launch_route<float, 1, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 64) return launch_route<float, 2, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    if (E <= 128) return launch_route<float, 4, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    return launch_route<float, 8, 2>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
 }
 
 }  // namespace
@@ -202,7 +201,7 @@ int dispatch_route(const void* x, const void* wg, const float* bias, int T, int 
 // fewer than eight experts in bf16: a row of W_g is shorter than a 16-byte load
 int moe_route_small(const void* x, const void* wg, const float* bias, int T, int d, int E, int k, int renorm, int32_t* idx, float* w,
                     float* logits, hipStream_t st) {
-    return dispatch_route<uint16_t>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
+    return launch_route<uint16_t, 1, 1>(x, wg, bias, T, d, E, k, renorm, idx, w, logits, st);
 }
 
 // bf16 inputs: the MFMA kernel of route_mfma.hip
@@ -242,5 +241,5 @@ extern "C" int moe_route_topk(const void* x, const void* w_gate, const float* bi
     hipStream_t st = (hipStream_t)stream;
     if (dt == MOE_BF16)
         return moe_route_bf16_mfma(x, w_gate, bias, T, d, E, k, renorm, expert_idx, gate_w, logits_out, st);
-    return dispatch_route<float>(x, w_gate, bias, T, d, E, k, renorm, expert_idx, gate_w, logits_out, st);
+    return route_f32(x, w_gate, bias, T, d, E, k, renorm, expert_idx, gate_w, logits_out, st);
 }
