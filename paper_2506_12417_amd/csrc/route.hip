@@ -4,15 +4,15 @@
 //
 // The logits are computed in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64, 79 TFLOP/s: products
 // of two fp32 values are exact in fp64), so the selection needs no error bound and no second
-// look.  A work-group takes 16 tokens; its eight wavefronts split the experts into groups of two 16-column blocks and the contraction
-// into 8 / GROUPS parts, whose sums are added in a fixed order through LDS.  Operands go straight
+// look.  A work-group takes 16 tokens; its eight wavefronts split the experts into groups of up to two
+// 16-column blocks and the contraction into 8 / GROUPS parts, whose sums are added in a fixed order
+// through LDS.  Operands go straight
 // from global memory to registers: a lane reads four consecutive terms of its token and the four
 // matching entries of its expert's column (16 neighbouring columns per load), and gives one of
 // the four to each of four matrix instructions.
 // (fp32 fma tiles whose column norms were summed by an LDS atomic per entry of W_g took 111 us for
-// 1501 tokens x 768, E = 16; this takes 11.  64
-// tokens per work-group, which fetch W_g a quarter as often, were no faster at any size: 33000
-// tokens x 768, E = 128 219 against 166 us.)
+// 1501 tokens x 768, E = 16; this takes 8.  64 tokens per work-group, which fetch W_g a quarter as
+// often, were no faster at any size: 33000 tokens x 768, E = 128 219 against 166 us.)
 #include "common.h"
 #include <climits>
 
@@ -21,42 +21,45 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 __device__ __forceinline__ bool beats(double av, int ae, double bv, int be) { return av > bv || (av == bv && ae < be); }
-__device__ __forceinline__ void wave_best(double& v, int& e) {
+// reductions over a group of SPAN neighbouring lanes
+template <int SPAN> __device__ __forceinline__ void group_best(double& v, int& e) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
+    for (int off = SPAN / 2; off >= 1; off >>= 1) {
         const double ov = __shfl_xor(v, off);
         const int oe = __shfl_xor(e, off);
         if (beats(ov, oe, v, e)) { v = ov; e = oe; }
     }
 }
-__device__ __forceinline__ double wave_sum(double v) {
+template <int SPAN> __device__ __forceinline__ double group_sum(double v) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+    for (int off = SPAN / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
-__device__ __forceinline__ double wave_max(double v) {
+template <int SPAN> __device__ __forceinline__ double group_max(double v) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) { const double o = __shfl_xor(v, off); v = o > v ? o : v; }
+    for (int off = SPAN / 2; off >= 1; off >>= 1) { const double o = __shfl_xor(v, off); v = o > v ? o : v; }
     return v;
 }
 constexpr double NEG_INF = -__builtin_huge_val();
 
-// A wavefront holds one token's logits, lane l owning experts l, l+64, l+128, l+192.  Picks the k
-// largest (ties to the lower expert id), forms their softmax values and writes the choice.
+// SPAN neighbouring lanes hold one token's logits, lane l of them owning experts l, l + SPAN, ...  Picks
+// the k largest (ties to the lower expert id), forms their softmax values and writes the choice.
 // A chosen expert gives up its id, not only its logit: -inf is a logit that others may hold (experts
 // masked by their bias), and the chosen one must not come up among those again.
-__device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, int renorm, int32_t* idx_row, float* w_row) {
+template <int SPAN, int NE>
+__device__ __forceinline__ void choose(const double (&v)[NE], int l, int E, int k, int renorm, int32_t* idx_row, float* w_row) {
+    static_assert(SPAN >= MOE_MAX_TOPK, "lane r writes choice r");
     double m = NEG_INF, s = 0.0;
-    int id[4];
+    int id[NE];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        id[j] = lane + 64 * j < E ? lane + 64 * j : INT_MAX;
+    for (int j = 0; j < NE; ++j) {
+        id[j] = l + SPAN * j < E ? l + SPAN * j : INT_MAX;
         if (id[j] != INT_MAX) m = v[j] > m ? v[j] : m;
     }
-    m = wave_max(m);
+    m = group_max<SPAN>(m);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) if (lane + 64 * j < E) s += exp(v[j] - m);
-    const double denom = wave_sum(s);
+    for (int j = 0; j < NE; ++j) if (id[j] != INT_MAX) s += exp(v[j] - m);
+    const double denom = group_sum<SPAN>(s);
     double p[MOE_MAX_TOPK], tot = 0.0, first = 0.0;
     int sel[MOE_MAX_TOPK];
 #pragma unroll
@@ -65,11 +68,11 @@ __device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, i
             double bv = NEG_INF;
             int be = INT_MAX;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NE; ++j)
                 if (id[j] != INT_MAX && beats(v[j], id[j], bv, be)) { bv = v[j]; be = id[j]; }
-            wave_best(bv, be);
+            group_best<SPAN>(bv, be);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) if (id[j] == be) id[j] = INT_MAX;
+            for (int j = 0; j < NE; ++j) if (id[j] == be) id[j] = INT_MAX;
             if (r == 0) first = bv;
             sel[r] = be;
             p[r] = exp(bv - first) / denom;
@@ -78,7 +81,7 @@ __device__ __forceinline__ void choose(double (&v)[4], int lane, int E, int k, i
     }
 #pragma unroll
     for (int r = 0; r < MOE_MAX_TOPK; ++r) {
-        if (r < k && lane == r) {
+        if (r < k && l == r) {
             idx_row[r] = sel[r];
             w_row[r] = (float)(renorm ? p[r] / tot : p[r]);
         }
@@ -157,14 +160,18 @@ __global__ __launch_bounds__(512) void route_kernel(const XT* __restrict__ x, co
 #pragma unroll
         for (int r = 0; r < 4; ++r) part[(ks * TB + 4 * r + lq) * EP + (grp * NT + n) * 16 + l16] = acc[n][r];
     __syncthreads();
-    // one wavefront per token, lane l owning experts l, l + 64, ...
-    for (int tok = wave; tok < TB; tok += 8) {
+    // A token's experts lie across SPAN lanes; with few experts a wavefront takes several tokens at once
+    // (the selection is a chain of exchanges and 64-bit exponentials: with one token per wavefront,
+    // two in turn, 16384 tokens x 64, E = 4 took 22 us, with four at once 9).
+    constexpr int SPAN = EP < 64 ? EP : 64, NE = EP / SPAN, PER = 64 / SPAN;
+    const int l = lane % SPAN;
+    for (int tok = wave * PER + lane / SPAN; tok < TB; tok += 8 * PER) {
         const int t = t0 + tok;
         if (t >= T) break;
-        double v[4];
+        double v[NE];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = lane + 64 * j;
+        for (int j = 0; j < NE; ++j) {
+            const int e = l + SPAN * j;
             v[j] = 0.0;
             if (e < E) {
                 double s = part[tok * EP + e];
@@ -174,7 +181,7 @@ __global__ __launch_bounds__(512) void route_kernel(const XT* __restrict__ x, co
                 if (logits_out) logits_out[(size_t)t * E + e] = (float)v[j];
             }
         }
-        choose(v, lane, E, k, renorm, idx_out + (size_t)t * k, w_out + (size_t)t * k);
+        choose<SPAN, NE>(v, l, E, k, renorm, idx_out + (size_t)t * k, w_out + (size_t)t * k);
     }
 }
 
