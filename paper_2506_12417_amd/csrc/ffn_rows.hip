@@ -99,15 +99,13 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* _
     const int s0 = wave * per < n_slices ? wave * per : n_slices, s1 = s0 + per < n_slices ? s0 + per : n_slices;
     const unsigned w_off = ((unsigned)l16 * (unsigned)K + (unsigned)lq * 8u) * 2u;
 
-    // (The first item's tile is fetched together with the number of tiles: one memory latency less
-    // before the weights can be asked for.  The grid stays below the table's capacity, so the entry
-    // exists; past the last tile it holds nothing and is not used.)
-    int item = blockIdx.x, ti = item / n_cb;
-    moe_tile t = tiles[ti];
-    int rc = sgpr(t.row_count), row0 = sgpr(t.row_begin), expert = sgpr(t.expert);
+    // (The tile is read after the number of tiles, although both latencies pass before the weights can
+    // be asked for: a table kept by its owner may end with its last tile.)
     const int n_items = sgpr(hdr[0]) * n_cb;
-    while (item < n_items) {
-        const int cb = item - ti * n_cb;
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int ti = item / n_cb, cb = item - ti * n_cb;
+        const moe_tile t = tiles[ti];
+        const int rc = sgpr(t.row_count), row0 = sgpr(t.row_begin), expert = sgpr(t.expert);
         // The item's blocks of 16 packed weight rows.  Packed rows 16 h + j of a block of 32 are outputs
         // 2 j + h (moe_pack_weights): an item of two blocks gives 32 adjacent outputs, an item of one
         // block the h-th of each pair.  With SwiGLU blocks of 32 gate and 32 up rows alternate, and the
@@ -178,14 +176,6 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* _
                 }
             }
             __syncthreads();
-        }
-        item += gridDim.x;
-        if (item < n_items) {
-            ti = item / n_cb;
-            t = tiles[ti];
-            rc = sgpr(t.row_count);
-            row0 = sgpr(t.row_begin);
-            expert = sgpr(t.expert);
         }
     }
 }

@@ -858,6 +858,32 @@ def test_few_row_kernels_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, po
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()      # the work counters stay zero
 
 
+@pytest.mark.parametrize("dtype,T,E,d,F", [("bf16", 8, 128, 128, 512), ("bf16", 600, 8, 128, 512), ("f32", 60, 8, 64, 128)])
+def test_a_kept_plan_may_end_with_its_last_tile(torch_gpu, dtype, T, E, d, F):
+    """The products on a copy of the table cut off after its last tile, what follows in memory being
+    tiles that name rows and experts that do not exist."""
+    torch = torch_gpu
+    wl = W.WORKLOADS["c2" if dtype == "bf16" else "c1"].scaled(T=T, d=d, F=F, E=E, k=1, skew="uniform")
+    _note("kept plan %s T=%d E=%d" % (dtype, T, E))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, inp)
+    x = layer_x(layer, inp)
+    layer.route(x)
+    layer.permute(x)
+    layer.plan()
+    layer.ffn()
+    want = layer.y_perm.clone()
+    n = int(to_numpy(layer.plan_hdr)[0])
+    assert 0 < n < layer.tile_capacity
+    kept = torch.full((layer.tile_capacity + 64, 4), 2 ** 30, dtype=torch.int32, device=layer.device)
+    kept[:n] = layer.tiles[:n]
+    layer.tiles = kept
+    layer.y_perm.fill_(float("nan"))
+    layer.ffn()
+    torch.cuda.synchronize()
+    assert torch.equal(layer.y_perm, want)
+
+
 F32_CASES = [
     # rows per expert, k, d, F, act, policy: tiles of 1, 32, 33, 64 and 65 rows, contractions shorter than a stage and
     # not a multiple of it, column blocks cut short, both widths of the column block, more tiles than the launch counts on
