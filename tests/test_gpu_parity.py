@@ -360,6 +360,30 @@ def test_ids_outside_the_experts_have_no_row(torch_gpu, entry, T, k, E, d):
     assert np.abs(got[good] - ref[good]).max(initial=0.0) <= (k + 1) * 2.0 ** -24 * (k + 1) * 9      # as below, weights up to 1.5
 
 
+# (two blocks, counted in the rank kernel; more than 256, where the scan over the blocks' histograms takes
+# a second round and carries the first one's sums into it)
+@pytest.mark.parametrize("T,k,E,d", [(1025, 1, 128, 8), (1023, 2, 9, 16), (70001, 4, 37, 8), (300001, 1, 256, 8)])
+def test_permute_at_the_block_counts_where_its_launches_change(torch_gpu, T, k, E, d):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    A = T * k
+    _note("permute blocks T=%d k=%d E=%d" % (T, k, E))
+    r = np.random.default_rng(A)
+    p = 1.0 / np.arange(1, E + 1)
+    idx = r.choice(E, size=(T, k), p=p / p.sum()).astype(np.int32)
+    ref = O.permute(idx, E)
+    x = torch.from_numpy(r.integers(-2 ** 15, 2 ** 15, (T, d)).astype(np.int16)).cuda()
+    out = {n: torch.full((m,), -3, dtype=torch.int32, device="cuda:0") for n, m in (("counts", E), ("offsets", E + 1), ("perm", A), ("inv_perm", A))}
+    x_perm = torch.full((A, d), -7, dtype=torch.int16, device="cuda:0")
+    ws = torch.empty(B.moe_workspace_bytes(B.MOE_OP_PERMUTE, T, d, 0, E, k, B.MOE_BF16), dtype=torch.uint8, device="cuda:0")
+    B.moe_permute(x, torch.from_numpy(idx).cuda(), T, d, E, k, B.MOE_BF16, out["counts"], out["offsets"], out["perm"], out["inv_perm"],
+                  x_perm, ws, ws.numel())
+    torch.cuda.synchronize()
+    for n in out:
+        assert np.array_equal(to_numpy(out[n]), ref[n]), n
+    assert np.array_equal(to_numpy(x_perm), to_numpy(x)[ref["perm"] // k])
+
+
 # (ids that start one, two and three elements into a 16-byte piece; one block, two, and more)
 @pytest.mark.parametrize("T,k,E", [(5, 1, 3), (700, 1, 128), (1025, 1, 60), (1011, 2, 7), (4099, 1, 256)])
 @pytest.mark.parametrize("off", [1, 2, 3])
