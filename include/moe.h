@@ -314,7 +314,8 @@ MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
  * they offer the row gather of moe_grouped_ffn_fused at this height.
  * Calls with a handful of rows per expert (decode steps) go, by default and with 128-row tiles, to
  * a third family that shares an expert's weights out over the whole chip whatever the plan's bins;
- * it sums the contraction in parts, so its last bits differ from the other two.
+ * it sums the contraction in parts, so its last bits differ from the other two: a row's last bits
+ * depend on whether the call it is in has that few rows.  (Modes 1 and 2 do not use this family.)
  * moe_ffn_kernel_mode sets the choice for the process -- 0 default, 1 the LDS ring with eight
  * wavefronts at both heights, 2 the streaming kernels wherever they cover the call, -1 leaves
  * it -- and returns the previous setting (a negative moe_status on a bad argument).  For

@@ -36,8 +36,9 @@ struct Gather {
     bool on = false;
 };
 
-// which 16-bit kernels run the 128-row configuration: 0 the default (the LDS-ring kernels), 1 the
-// LDS-ring kernels, 2 the register-streaming kernels wherever they cover the call
+// which 16-bit kernels run: 0 the default (128-row tiles: the few-row kernels where they serve the
+// call, else the LDS-ring kernels; 256-row tiles: the four-wavefront kernels), 1 the LDS-ring
+// kernels, 2 the default with 128-row tiles by the register-streaming kernels wherever they cover the call
 static int g_kernel_mode = 0;
 
 extern "C" int moe_ffn_kernel_mode(int mode) {
@@ -102,8 +103,8 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // (moe_ffn_kernel_mode 2): on the workloads measured so far the LDS-ring kernels are faster.
         // They take items of 128 weight rows, two work-groups per CU, unless there are four wide
         // items per CU.
-        const bool few_rows = tile_m == 128 && g_kernel_mode == 2;
-        auto stream = [&](int epi, int K) { return few_rows && moe_gemm_stream_supports(epi, K); };
+        const bool streaming = tile_m == 128 && g_kernel_mode == 2;
+        auto stream = [&](int epi, int K) { return streaming && moe_gemm_stream_supports(epi, K); };
         auto stream_narrow = [&](int N) { return tiles_est * ((N + 255) / 256) < 4 * MOE_GEMM_GRID; };
         // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1).

@@ -28,7 +28,8 @@ def default_q_tokens(dt: int) -> int:
     near 1.55 GHz under load; 100 TFLOP/s in fp32), beta = its share of the HBM
     streaming rate (about 6.0 TB/s), d_type = bytes per weight.  With the chip's nominal peaks
     (2.5 PFLOP/s, 8 TB/s) q would be 313 rows, which overstates what a cold expert costs here
-    and leaves the bins with unequal numbers of tiles."""
+    and leaves the bins with unequal numbers of tiles.  (The fp32 kernels take all tiles with all
+    work-groups, whatever their bins: there q only decides how the schedule and its tiles are cut.)"""
     if dt == B.MOE_BF16:
         return B.moe_token_threshold(1.0e15 / XCDS, 2, 6.0e12 / XCDS)
     return B.moe_token_threshold(100e12 / XCDS, 4, 6.0e12 / XCDS)
@@ -196,6 +197,9 @@ class MoELayer:
 
     def forward(self, x: torch.Tensor, stream=None, marks=None, routed: bool = False, stages=None) -> torch.Tensor:
         """Enqueues the whole layer on the current (or given) stream; returns the output buffer.
+        A bf16 token's last bits depend on the number of tokens the layer is made for: calls with a
+        handful of rows per expert run by kernels that add the contraction in another order
+        (moe_ffn_kernel_mode 1 keeps to one order; it also gives up the four-wavefront kernels).
         marks: optional list of 3 torch.cuda.Event recorded before / between / after the two
         grouped GEMMs (for per-kernel timing).  routed: expert_idx and gate_w are already set
         (a router that samples ids, section 5.1's synthetic skew): step 1 is skipped.
