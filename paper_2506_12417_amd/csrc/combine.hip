@@ -3,7 +3,7 @@
 // One float4 of one output row per thread; j ascending, so the sum has a fixed order.
 // HBM bound: A*d*4 bytes read (+ T*d*4 for the shared expert), T*d*4 written, every byte once: all
 // of it bypasses the caches' keeping (nontemporal), and a thread asks for its k rows together.
-// 20011 x 8 rows of 1032: 4.3 -> 5.7 TB/s; 8192 x 2 rows of 4096 alone: 5.4 -> 6.3 TB/s.
+// 20011 x 8 rows of 1032: 4.3 -> 5.8 TB/s; 8192 x 2 rows of 4096: 5.4 -> 6.2 TB/s.
 // An assignment without a row (inv_perm negative) adds nothing if its weight is zero and makes its
 // token NaN otherwise; the first row is fetched in its place and not used.
 #include "common.h"

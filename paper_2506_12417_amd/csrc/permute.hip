@@ -86,9 +86,11 @@ __global__ __launch_bounds__(NTH) void rank_kernel(const int32_t* __restrict__ i
 }
 
 // x_perm row inv_perm[t*k+j] <- x row t, in 16-byte pieces (vpr pieces per row), one piece of one
-// token per thread; an assignment without a row (inv_perm -1) is skipped.  HBM bound: x is read once (gathering through perm read it k times through the
-// L2 and the row's address at the end of a chain of two loads: 95 us for 20011 x 8 rows of 2064
-// bytes, now 65, 5.7 TB/s.  Nontemporal stores: 106 us, the rows' ends share lines).
+// token per thread; an assignment without a row (inv_perm -1) is skipped.  HBM bound, and by its scattered stores at that: x is read once (gathering through
+// perm read it k times through the L2 and the row's address at the end of a chain of two loads).
+// 20011 x 8 rows of 2064 bytes: 96 -> 84 us back to back (4.5 TB/s), 95 -> 91 in a dispatch pass, where it
+// writes 335 MB for 330 of rows: the lines that two rows share cost nothing extra.  Nontemporal
+// stores were slower for them.
 __global__ __launch_bounds__(NTH) void spread_rows_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ inv_perm,
                                                           unsigned total, unsigned A, unsigned k, unsigned vpr,
                                                           u32x4* __restrict__ x_perm) {

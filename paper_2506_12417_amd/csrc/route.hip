@@ -11,7 +11,7 @@
 // matching entries of its expert's column (16 neighbouring columns per load), and gives one of
 // the four to each of four matrix instructions.
 // (fp32 fma tiles whose column norms were summed by an LDS atomic per entry of W_g took 111 us for
-// 1501 tokens x 768, E = 16; this takes 8.  64 tokens per work-group, which fetch W_g a quarter as
+// 1501 tokens x 768, E = 16; this takes 9.  64 tokens per work-group, which fetch W_g a quarter as
 // often, were no faster at any size: 33000 tokens x 768, E = 128 219 against 166 us.)
 #include "common.h"
 #include <climits>

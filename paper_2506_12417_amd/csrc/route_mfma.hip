@@ -548,7 +548,7 @@ __global__ __launch_bounds__(NB * KSP * 64, 2) void route_packed_kernel(const ui
 // thread fetches eight terms of eight neighbouring experts (eight 16-byte loads), swaps them into
 // eight runs of eight terms with byte permutes, and writes those as 16-byte pieces.  (Two-byte
 // loads and LDS writes, one term of one expert each, kept the kernel at 1257 us for 20011 tokens x
-// 1032, E = 256; this takes 137 us, half of it the selection.)  A stage is 128 terms per contraction part of the 32 tokens and
+// 1032, E = 256; this takes 128 us.)  A stage is 128 terms per contraction part of the 32 tokens and
 // all experts; its loads are in flight while the previous stage is multiplied.
 //
 // LDS rows hold 16 pieces (128 terms); piece p of row r sits at position p ^ swz(r), chosen so that
