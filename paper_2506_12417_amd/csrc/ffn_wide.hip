@@ -12,16 +12,24 @@
 // wavefront per SIMD -- so a wavefront overlaps its own memory work with its own matrix
 // instructions instead of alternating with a partner.
 //
-// Schedule.  The contraction advances in stages of 32 terms (one matrix-instruction slice; a
-// stage is 16 KB of rows + 16 KB of weight rows).  The LDS ring holds RING = 4 stages.  In step
-// s a wavefront
-//   * multiplies the fragments of stage s, which are in registers (64 matrix instructions),
-//   * reads the fragments of stage s + 1 from LDS into the other half of its fragment registers,
-//   * issues its share of the loads of stage s + RING into the buffer stage s has left,
-// the three interleaved instruction by instruction, and one work-group barrier ends the step
-// (everyone has read stage s + 1, everyone's part of stage s + 2 has landed).  Loads therefore
-// have between two and three steps to arrive.  A work-group's items form one stream of stages:
-// the loads cross item boundaries, and past the last item they go on with empty descriptors.
+// Schedule.  The contraction advances in stages of 64 terms -- a row of a stage is one whole
+// 128-byte line: stages of 32 terms fetched every line in two halves, twice the requests for the same bytes --
+// and the LDS ring holds two of them (32 KB of rows + 32 KB of weight rows each).  A stage is two steps
+// of 32 terms (one matrix-instruction slice); the fragments of a step are in registers when it starts:
+//   step 0 of stage s  multiplies the first half (64 matrix instructions) and reads the second half's
+//                      fragments; then everybody has read all of stage s and waits for stage s + 1: the
+//                      only work-group barrier of a stage
+//   step 1             multiplies the second half, reads the first half's fragments of stage s + 1 and
+//                      issues the loads of stage s + 2 into the buffer that stage s has left, one behind every
+//                      four matrix instructions (which is what the vector cache accepts: two at a time, 8 % slower;
+//                      spread over the next step as well they land too late, 2 - 8 % slower)
+// A work-group's items form one stream of stages: the loads cross item boundaries, and past the last
+// item they go on with empty descriptors.
+// Measured (16384 rows, 4096 x 14336, stages of 32 terms in a ring of four with a barrier per step -> this):
+// one expert 2850 -> 2620 us (1470 TFLOP/s) and 1590 -> 1470, eight Zipf(2) experts 3290 -> 2990 and 1825 -> 1740;
+// 8192 rows, 2048 x 5632: 320 -> 292 and 151 -> 134.  What is left: a power limit (the clock falls with the
+// energy of a multiply-add), loads that miss the L2 (second product with every load hitting: 1290 us), and
+// ragged tiles, which cost nearly a full one (their weights' loads take as long).
 // An item's results are converted and stored between its last step and the next item's first.
 // As in ffn_bf16.hip the first product can fetch its rows from x through the sort's permutation
 // (Alg. 1's step 4 done by the operand loads) and, for top-1 routing, the second can write every
@@ -40,7 +48,7 @@
 namespace {
 
 struct WCfg {
-    static constexpr int BM = 256, BN = 256, BK = 32, RING = 4;
+    static constexpr int BM = 256, BN = 256, BK = 64, RING = 2;
     static constexpr int NW = 4, NTH = NW * 64;
     static constexpr int PPR = BK / 8;                    // 16-byte pieces per row
     static constexpr int ROW_BYTES = BK * 2;
@@ -55,9 +63,8 @@ struct WCfg {
     static constexpr int MAX_BLK_TILES = 3068;            // tiles of a bin the block table can hold
     static constexpr int ROWINFO_BYTES = 2 * 2 * BM * 4;  // (token, gate) of a tile's rows, for two items
     static constexpr size_t SMEM = (size_t)RING_BYTES + (size_t)MAX_BLK_TILES * 4 + 16 + ROWINFO_BYTES;
-    static constexpr int WAIT_BASE = (RING - 2) * LPS;    // loads younger than the stage a step waits for
     static_assert(ROWS_PER_PASS % (WRAP * PPR) == 0 && 16 % (WRAP * PPR) == 0, "swizzle period");
-    static_assert(WAIT_BASE + 47 <= 63 && RING >= 3, "vmcnt range");
+    static_assert(RING == 2 && 2 * LPS <= 63, "vmcnt range");
     static_assert(SMEM <= 160 * 1024, "LDS ring too large");
     static_assert(MI == NI, "one fragment array shape for both operands");
     __device__ static __forceinline__ int swz(int r) { return (r / WRAP) & (PPR - 1); }
@@ -186,9 +193,9 @@ __device__ __forceinline__ void issue_done(const Geo& g, Loader& L, int wave, in
     }
 }
 
-// Fragment read j (0..15) of a stage into set S: the B fragments first.  Lane (l16, lq) supplies
-// row l16 of a 16-row block, terms 8 lq .. 8 lq + 7 of the stage's 32: piece lq of the row, stored at
-// position lq ^ swz(row); the swizzle repeats every 16 rows.
+// Fragment read j (0..15) of one half (32 terms) of a stage into set S: the B fragments first.  Lane
+// (l16, lq) supplies row l16 of a 16-row block, terms 8 lq .. 8 lq + 7 of the half's 32: piece 4 half + lq
+// of the row, stored at that position ^ swz(row); the swizzle repeats every 16 rows.
 template <int S>
 __device__ __forceinline__ void read_frag(FragSet (&fr)[2], const unsigned char* ring, int j, unsigned a_at, unsigned b_at) {
     if (j < 2 * C::NI)
@@ -227,23 +234,13 @@ __device__ __forceinline__ void wg_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// The stage two steps ahead has landed once only the stages issued after it are outstanding
-// (loads complete in issue order).  Stores count like loads: for the two steps after an item
-// has been stored, its store instructions (at least `n` of them) are younger than the stage
-// waited for too.
-struct StoreCredit {
-    int left, n;
-};
-__device__ __forceinline__ void wait_landed(StoreCredit& sc) {
-    if (sc.left > 0) {
-        --sc.left;
-        if (sc.n >= 47) MOE_WAIT_VMCNT(C::WAIT_BASE + 47);
-        else if (sc.n >= 32) MOE_WAIT_VMCNT(C::WAIT_BASE + 32);
-        else if (sc.n >= 16) MOE_WAIT_VMCNT(C::WAIT_BASE + 16);
-        else MOE_WAIT_VMCNT(C::WAIT_BASE);
-    } else {
-        MOE_WAIT_VMCNT(C::WAIT_BASE);
-    }
+// The next stage has landed once only what was issued after it is outstanding: the stores of the
+// item before (at least `stores` of them; the counter falls in issue order).
+__device__ __forceinline__ void wait_landed(int stores) {
+    if (stores >= 63) MOE_WAIT_VMCNT(63);
+    else if (stores >= 32) MOE_WAIT_VMCNT(32);
+    else if (stores >= 16) MOE_WAIT_VMCNT(16);
+    else MOE_WAIT_VMCNT(0);
 }
 
 // What a lane needs to find its fragments and its loads.
@@ -252,15 +249,13 @@ struct Lane {
     unsigned ld_voff0, ld_pass, ld_piece;
 };
 
-// One step: multiply set S (stage s), read stage s + 1 from buffer rd_buf into the other set,
-// issue the loads of stage s + RING.  Sixteen groups of four matrix instructions; the reads go
-// with the first twelve groups (their data is due at the next step's start), a load with every
-// other group: the path that takes the loads accepts one per wavefront every few tens of
-// cycles, so they are spread over the whole step.
-template <int S, bool FULL, bool HALF_IN, bool GATHER>
+// Step S (0 or 1) of a stage in buffer `buf`, see above; FIRST: of an item.  Sixteen groups of four matrix
+// instructions; the reads go with the first twelve (their data is due at the next step's start).
+template <int S, bool FIRST, bool FULL, bool HALF_IN, bool GATHER>
 __device__ __forceinline__ void step(const Geo& g, Loader& L, const Lane& ln, unsigned char* ring, Acc& acc,
-                                     FragSet (&fr)[2], int& rd_buf, StoreCredit& sc, int mi_on) {
-    const unsigned a_at = (unsigned)(rd_buf * C::STAGE_BYTES) + (unsigned)ln.a_rd0;
+                                     FragSet (&fr)[2], int& buf, int stores, int mi_on) {
+    if (S == 1) buf ^= 1;
+    const unsigned a_at = (unsigned)(buf * C::STAGE_BYTES) + ((unsigned)ln.a_rd0 ^ (S == 0 ? 64u : 0u));
     const unsigned b_at = a_at + (unsigned)ln.b_delta;
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -277,14 +272,49 @@ __device__ __forceinline__ void step(const Geo& g, Loader& L, const Lane& ln, un
         } else if (t < 12) {
             read_frag<S ^ 1>(fr, ring, t + 4, a_at, b_at);
         }
-        if (t & 1) issue_load<GATHER>(L, ring, ln.wave, ln.ld_voff0, ln.ld_pass, t >> 1);
+        if (S == 1) issue_load<GATHER>(L, ring, ln.wave, ln.ld_voff0, ln.ld_pass, t);
         __builtin_amdgcn_sched_barrier(0);
     }
-    issue_done<GATHER>(g, L, ln.wave, ln.lane, ln.ld_row, ln.ld_piece);
-    rd_buf = rd_buf + 1 == C::RING ? 0 : rd_buf + 1;
-    MOE_WAIT_LGKMCNT(0);
-    wait_landed(sc);
-    wg_barrier();
+    if (S == 0) {
+        MOE_WAIT_LGKMCNT(0);
+        if (FIRST) wait_landed(stores);
+        else MOE_WAIT_VMCNT(0);
+        issue_done<GATHER>(g, L, ln.wave, ln.lane, ln.ld_row, ln.ld_piece);
+        wg_barrier();
+    }
+}
+
+// Scatter epilogue (top-1 routing: Alg. 1's step 6 folded into the second product).  The token and
+// the gate value of every row of a tile wait in LDS (rinfo[parity of the item][tokens | gates][row]);
+// they are fetched there by two small global -> LDS loads per wavefront during the item's first
+// steps: first the tokens of the tile's rows, then, indexed by them, the gate values.
+__device__ __forceinline__ void fetch_tokens(const Geo& g, int par, int row_begin, int rc, int wave, int lane) {
+    const __amdgpu_buffer_rsrc_t rt = make_rsrc(g.row_token + row_begin, (unsigned)(rc > 0 ? rc : 0) * 4u);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_void_t*)(g.rinfo + par * 2 * C::BM + wave * 64), 4,
+                                             (unsigned)(wave * 64 + lane) * 4u, 0, 0, 0);
+    if (!g.row_gate) ((float*)g.rinfo)[par * 2 * C::BM + C::BM + wave * 64 + lane] = 1.f;
+}
+__device__ __forceinline__ void fetch_gates(const Geo& g, int par, int wave, int lane) {
+    if (g.row_gate) {
+        const unsigned tok = (unsigned)g.rinfo[par * 2 * C::BM + wave * 64 + lane];
+        const __amdgpu_buffer_rsrc_t rg = make_rsrc(g.row_gate, (unsigned)g.out_rows * 4u);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (lds_void_t*)(g.rinfo + par * 2 * C::BM + C::BM + wave * 64), 4, tok * 4u, 0, 0, 0);
+    }
+}
+// The contraction of one item.  (The first stage is written out: it alone allows for stores in flight.  With
+// the stores as a variable of the loop the compiler peels the loop by itself, and moves accumulators
+// between registers in every step.)
+template <bool FULL, bool HALF_IN, bool GATHER, bool SCAT>
+__device__ __forceinline__ void contraction(const Geo& g, Loader& L, const Lane& ln, unsigned char* ring, Acc& acc,
+                                            FragSet (&fr)[2], int& buf, int stores, int mi_on, int par) {
+    step<0, true, FULL, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, buf, stores, mi_on);
+    step<1, false, FULL, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, buf, 0, mi_on);
+#pragma clang loop unroll(disable)
+    for (int kt = 1; kt < g.KT; ++kt) {
+        if constexpr (SCAT) { if (kt == 2) fetch_gates(g, par, ln.wave, ln.lane); }
+        step<0, false, FULL, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, buf, 0, mi_on);
+        step<1, false, FULL, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, buf, 0, mi_on);
+    }
 }
 
 template <bool HALF_IN>
@@ -343,23 +373,6 @@ __device__ __forceinline__ void epilogue(const Acc& acc, __amdgpu_buffer_rsrc_t 
     }
 }
 
-// Scatter epilogue (top-1 routing: Alg. 1's step 6 folded into the second product).  The token and
-// the gate value of every row of a tile wait in LDS (rinfo[parity of the item][tokens | gates][row]);
-// they are fetched there by two small global -> LDS loads per wavefront during the item's first
-// steps: first the tokens of the tile's rows, then, indexed by them, the gate values.
-__device__ __forceinline__ void fetch_tokens(const Geo& g, int par, int row_begin, int rc, int wave, int lane) {
-    const __amdgpu_buffer_rsrc_t rt = make_rsrc(g.row_token + row_begin, (unsigned)(rc > 0 ? rc : 0) * 4u);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_void_t*)(g.rinfo + par * 2 * C::BM + wave * 64), 4,
-                                             (unsigned)(wave * 64 + lane) * 4u, 0, 0, 0);
-    if (!g.row_gate) ((float*)g.rinfo)[par * 2 * C::BM + C::BM + wave * 64 + lane] = 1.f;
-}
-__device__ __forceinline__ void fetch_gates(const Geo& g, int par, int wave, int lane) {
-    if (g.row_gate) {
-        const unsigned tok = (unsigned)g.rinfo[par * 2 * C::BM + wave * 64 + lane];
-        const __amdgpu_buffer_rsrc_t rg = make_rsrc(g.row_gate, (unsigned)g.out_rows * 4u);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (lds_void_t*)(g.rinfo + par * 2 * C::BM + C::BM + wave * 64), 4, tok * 4u, 0, 0, 0);
-    }
-}
 __device__ __forceinline__ void epilogue_scatter(const Acc& acc, const Geo& g, __amdgpu_buffer_rsrc_t ry, int par, int rc,
                                                  int lane_row, unsigned col_off, unsigned ld_bytes, int col0, int mi_on) {
     // The tokens and gates of two row blocks are read before the first of their stores goes out:
@@ -430,7 +443,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.rinfo = (int*)(ring + C::SMEM - C::ROWINFO_BYTES);
     g.K = K;
     g.N = N;
-    g.KT = K / C::BK;                                        // (even: K is a multiple of 64)
+    g.KT = K / C::BK;                                        // (K is a multiple of 64)
     g.n_col_blocks = (N + C::BN - 1) / C::BN;
     const WorkShare ws = work_share(hdr, g.n_col_blocks);
     const int first = ws.first;
@@ -473,7 +486,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
 
     FragSet fr[2];                                          // two sets: the one multiplied, the one being read
     Acc acc;
-    StoreCredit sc = {0, 0};
+    int stores = 0;
 
     // ---- prologue: all RING stages on their way; stage 0 read into set 0; stage 1 landed
     Loader L;
@@ -490,7 +503,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     for (int s = 0; s < C::RING; ++s) {
 #pragma unroll
         for (int q = 0; q < C::LPS; ++q) issue_load<GATHER>(L, ring, wave, ln.ld_voff0, ln.ld_pass, q);
-        issue_done<GATHER>(g, L, wave, lane, ld_row, ln.ld_piece);
+        if (s + 1 < C::RING) issue_done<GATHER>(g, L, wave, lane, ld_row, ln.ld_piece);
     }
     MOE_WAIT_VMCNT((C::RING - 1) * C::LPS);
     wg_barrier();
@@ -498,10 +511,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     for (int j = 0; j < 16; ++j) read_frag<0>(fr, ring, j, (unsigned)ln.a_rd0, (unsigned)(ln.a_rd0 + ln.b_delta));
     zero_acc(acc);
     MOE_WAIT_LGKMCNT(0);
-    MOE_WAIT_VMCNT(C::WAIT_BASE);
-    wg_barrier();
-    // (from here on step s issues the loads of stage s + RING into buffer s % RING: L.buf is back at 0)
-    int rd_buf = 1;
+    int buf = 0;
 
     const unsigned ld_bytes = (unsigned)ld_out * ES;
     const unsigned st_voff = (unsigned)(wm * 32 + 4 * lq) * ld_bytes + (unsigned)(2 * l16) * ES;
@@ -516,23 +526,11 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
         // 32-row blocks of this wavefront that hold real rows (wave-uniform)
         int mi_on = ((rc + 31) / 32 - wm + 1) / 2;
         mi_on = mi_on < 0 ? 0 : (mi_on > C::MI ? C::MI : mi_on);
-        // (scatter: the token load is covered by the waits of the first two steps -- every step
-        // issues a stage of operand loads behind it -- and the barriers after them; the gate load
-        // likewise by the steps that follow it, long before the item ends: K / 32 >= 8 steps)
+        // (scatter: the token load is covered by the wait of the second stage, the gate load, issued
+        // after the second, by the wait of the third and the barrier behind it: K / 64 >= 4 stages)
         if constexpr (SCAT) fetch_tokens(g, c_seq & 1, tile.row_begin, rc, wave, lane);
-        if (mi_on == C::MI) {
-            for (int kt = 0; kt < g.KT; kt += 2) {
-                if constexpr (SCAT) { if (kt == 4) fetch_gates(g, c_seq & 1, wave, lane); }
-                step<0, true, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, rd_buf, sc, mi_on);
-                step<1, true, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, rd_buf, sc, mi_on);
-            }
-        } else {
-            for (int kt = 0; kt < g.KT; kt += 2) {
-                if constexpr (SCAT) { if (kt == 4) fetch_gates(g, c_seq & 1, wave, lane); }
-                step<0, false, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, rd_buf, sc, mi_on);
-                step<1, false, HALF_IN, GATHER>(g, L, ln, ring, acc, fr, rd_buf, sc, mi_on);
-            }
-        }
+        if (mi_on == C::MI) contraction<true, HALF_IN, GATHER, SCAT>(g, L, ln, ring, acc, fr, buf, stores, mi_on, c_seq & 1);
+        else contraction<false, HALF_IN, GATHER, SCAT>(g, L, ln, ring, acc, fr, buf, stores, mi_on, c_seq & 1);
         if constexpr (SCAT) {
             epilogue_scatter(acc, g, ry, c_seq & 1, rc, wm * 32 + 4 * lq, (unsigned)(2 * l16) * 4u, ld_bytes, col0, mi_on);
         } else {
@@ -544,8 +542,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
         // store instructions just issued (a lower bound is what the waits need)
         int cols = (N - col0 + 31) / 32;
         cols = cols < 0 ? 0 : (cols > C::NI ? C::NI : cols);
-        sc.n = mi_on * 8 * (EPI == MOE_EPI_SWIGLU ? (cols + 1) / 2 : cols);
-        sc.left = 2;
+        stores = mi_on * 8 * (EPI == MOE_EPI_SWIGLU ? (cols + 1) / 2 : cols);
     }
     MOE_WAIT_VMCNT(0);                                      // (the trailing empty loads still target this LDS)
 }
