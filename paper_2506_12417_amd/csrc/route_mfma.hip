@@ -29,6 +29,10 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef u32x4 frag_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
+// the two bf16 values of a 32-bit word.  (A value, not an expression: __builtin_bit_cast of a vector's
+// element written in place, `v[i]`, takes the vector's first element whatever i is.)
+__device__ __forceinline__ bf16x2 bf16_pair(unsigned word) { return __builtin_bit_cast(bf16x2, word); }
+
 constexpr int KC = 64;                 // terms per chunk (four MFMAs)
 // Terms per fp32 accumulation.  Fewer make the bound on a logit's error tighter, and with it the share
 // of tokens that the exact path has to look at again (which is what a work-group then waits for):
@@ -519,7 +523,7 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
                 if (nbi == 0) {                              // the token norms, once per contraction part
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const bf16x2 p2 = __builtin_bit_cast(bf16x2, xa[ks][i]);
+                        const bf16x2 p2 = bf16_pair(xa[ks][i]);
                         xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
                     }
                 }
@@ -642,7 +646,7 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 piece[m] = __builtin_amdgcn_perm(wv[2 * m + 1][e >> 1], wv[2 * m][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
-                const bf16x2 p2 = __builtin_bit_cast(bf16x2, piece[m]);
+                const bf16x2 p2 = bf16_pair(piece[m]);
                 wsq[e] = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, wsq[e], false);
             }
             *(u32x4*)(smem + (wr_at ^ (e << 5)) + e * 256) = piece;
@@ -661,7 +665,7 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa), __builtin_bit_cast(bf16x8, wa), acc, 0, 0, 0);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {                // the token norms (those of expert block 0 are used)
-                    const bf16x2 p2 = __builtin_bit_cast(bf16x2, xa[i]);
+                    const bf16x2 p2 = bf16_pair(xa[i]);
                     xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
                 }
                 if (ks & 1) __builtin_amdgcn_sched_barrier(0);     // (two slices' fragments in registers at a time)

@@ -113,6 +113,36 @@ def test_route_near_ties_bf16_both_entry_points(torch_gpu):
         assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
 
 
+@pytest.mark.parametrize("E", [20, 40, 100, 200])
+def test_route_error_bound_covers_every_term(torch_gpu, E):
+    """Tokens that are zero in the first two of every eight terms, and two columns that hold the same
+    coefficients at other terms of equal value: equal logits, summed in another order.  The bound on the
+    rounding has to come from the norms over all terms for the lower index to win every time."""
+    torch = torch_gpu
+    T, d, k = 200, 1024, 2
+    r = np.random.default_rng(E)
+    xf = r.standard_normal((T, d)).astype(np.float32)
+    xf = np.tile(xf[:, :d // 64].reshape(T, d // 64, 1), (1, 1, 64)).reshape(T, d)     # one value per 64 terms
+    xf[:, 0::8] = 0.0
+    xf[:, 1::8] = 0.0
+    x = W.f32_to_bf16_bits(xf)
+    Wf = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    Wf[:, 7] *= 8.0
+    Wf[:, 18] = np.roll(Wf[:, 7].reshape(-1, 64), 16, axis=1).reshape(-1)
+    Wg = W.f32_to_bf16_bits(Wf)
+    wl = W.WORKLOADS["c2"].scaled(T=T, d=d, E=E, k=k, renorm=1)
+    idx_o, w_o, _ = O.route_topk(x, Wg, None, k, 1)
+    assert (idx_o[:, 0] == 7).sum() > T // 5 and np.array_equal(idx_o[:, 0] == 7, (idx_o[:, 0] == 7) & (idx_o[:, 1] == 18))
+    from paper_2506_12417_amd.layer import to_device
+    for packed in (False, True):
+        layer = make_layer(wl, {})
+        layer.load_router(Wg, None, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), "packed=%s" % packed
+        assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
+
+
 # (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
 # of the stage; every block and contraction split; E < 8: the general kernel)
 @pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
