@@ -77,17 +77,43 @@ template <int TPT> __device__ __forceinline__ void group_best(float& v, int& e) 
     if (TPT == 16) { ov = dpp_xchg<3>(v); oe = dpp_xchg<3>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; } }
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+// the same for doubles: exchanges inside a row of 16 lanes stay in the vector unit (a __shfl goes through
+// LDS and takes ten times as long)
+template <int STEP> __device__ __forceinline__ double dpp_xchg(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)dpp_xchg<STEP>((int)(unsigned)u), hi = (unsigned)dpp_xchg<STEP>((int)(unsigned)(u >> 32));
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double row_sum_f64(double v) {
+    v += dpp_xchg<0>(v);
+    v += dpp_xchg<1>(v);
+    v += dpp_xchg<2>(v);
+    v += dpp_xchg<3>(v);
     return v;
 }
-__device__ __forceinline__ void wave_best_f64(double& v, int& e) {
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    v = row_sum_f64(v);
+    return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+// the best of each row of 16 lanes, or (all) of the wavefront
+__device__ __forceinline__ void row_best_f64(double& v, int& e, bool all) {
+    double ov; int oe;
+    ov = dpp_xchg<0>(v); oe = dpp_xchg<0>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+    ov = dpp_xchg<1>(v); oe = dpp_xchg<1>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+    ov = dpp_xchg<2>(v); oe = dpp_xchg<2>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+    ov = dpp_xchg<3>(v); oe = dpp_xchg<3>(e); if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+    if (all) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        double ov = __shfl_xor(v, off);
-        int oe = __shfl_xor(e, off);
-        if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+        for (int off = 16; off <= 32; off <<= 1) {
+            ov = __shfl_xor(v, off);
+            oe = __shfl_xor(e, off);
+            if (beats(ov, oe, v, e)) { v = ov; e = oe; }
+        }
     }
 }
 
@@ -300,7 +326,10 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     // k is recomputed in fp64.  A round takes as many flagged tokens as there are wavefronts: each
     // wavefront lists one token's candidates, then all of them share out the (token, candidate)
     // pairs -- a work-group has a flagged token or two, and left to one wavefront its nine or ten
-    // candidates follow one another, a memory latency each -- and each selects for its token.
+    // candidates follow one another, a memory latency each -- and each selects for its token.  What it costs
+    // is a chain of latencies (256 experts, k = 8: 16 - 20 us of a work-group's 45 when a token is flagged), so the
+    // sums and the choices go through the vector unit's lane exchanges (through LDS: 8 us more).  Sharing a
+    // candidate's terms out over the wavefronts as well was slower (44 -> 57 us: 64-lane sums for everybody).
     constexpr int CJ = (MOE_MAX_EXPERTS + 63) / 64;
     double* cand_v = slab;                                       // [NWV][LIST]
     int* cand_e = reinterpret_cast<int*>(slab + NWV * L::LIST);  // [NWV][LIST]
@@ -326,16 +355,27 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
             for (; p < n; p += NWV) {
                 const int t = t0 + flag_tok[f0 + s], ce = __builtin_amdgcn_readfirstlane(cand_e[s * L::LIST + p]);
                 const uint16_t* xr = x + (size_t)t * d;
-                double psum = 0.0;
+                double psum = 0.0, psum1 = 0.0;
                 if constexpr (PACKED) {                      // both operand rows are contiguous
                     const uint16_t* wr = wg + (size_t)ce * d;
-                    for (int i0 = lane * 8; i0 < d; i0 += 64 * 8) {    // 8 terms per lane and step, 16-byte loads
-                        const frag_t xv = *(const frag_t*)(xr + i0), wv = *(const frag_t*)(wr + i0);
+                    for (int i0 = lane * 8; i0 < d; i0 += 4 * 64 * 8) {   // 8 terms per lane and 16-byte load, eight loads in flight
+                        frag_t xv[4], wv[4];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            psum = fma((double)__uint_as_float(xv[i] << 16), (double)__uint_as_float(wv[i] << 16), psum);
-                            psum = fma((double)__uint_as_float(xv[i] & 0xffff0000u), (double)__uint_as_float(wv[i] & 0xffff0000u), psum);
+                        for (int u2 = 0; u2 < 4; ++u2) {
+                            xv[u2] = wv[u2] = frag_t{0u, 0u, 0u, 0u};
+                            if (i0 + u2 * 512 < d) {
+                                xv[u2] = *(const frag_t*)(xr + i0 + u2 * 512);
+                                wv[u2] = *(const frag_t*)(wr + i0 + u2 * 512);
+                            }
                         }
+#pragma unroll
+                        for (int u2 = 0; u2 < 4; ++u2)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const unsigned xw = xv[u2][i], ww = wv[u2][i];
+                                psum = fma((double)__uint_as_float(xw << 16), (double)__uint_as_float(ww << 16), psum);
+                                psum1 = fma((double)__uint_as_float(xw & 0xffff0000u), (double)__uint_as_float(ww & 0xffff0000u), psum1);
+                            }
                     }
                 } else {
                     for (int i0 = lane; i0 < d; i0 += 64 * 8) {        // 16 loads in flight per lane
@@ -350,7 +390,7 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                         for (int u2 = 0; u2 < 8; ++u2) psum = fma((double)xa[u2], (double)wa[u2], psum);
                     }
                 }
-                const double tot = wave_sum_f64(psum) + (bias ? (double)bias[ce] : 0.0);
+                const double tot = wave_sum_f64(psum + psum1) + (bias ? (double)bias[ce] : 0.0);
                 if (lane == 0) cand_v[s * L::LIST + p] = tot;
             }
             p -= n;
@@ -366,33 +406,27 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 cv[j] = c < nc ? cand_v[wave * L::LIST + c] : -__builtin_huge_val();
                 ce_[j] = c < nc ? cand_e[wave * L::LIST + c] : INT_MAX;
             }
-            const double m = (double)flag_max[f], den = (double)flag_den[f];
-            double p[MOE_MAX_TOPK], tot = 0.0;
-            int pe[MOE_MAX_TOPK];
+            // (lane r < k of the first row keeps the r-th choice: one exponential for all of them)
+            double mine = 0.0;
+            int mine_e = 0;
+            for (int r = 0; r < k; ++r) {
+                double bv = -__builtin_huge_val();
+                int be = INT_MAX;
 #pragma unroll
-            for (int r = 0; r < MOE_MAX_TOPK; ++r) {
-                if (r < k) {
-                    double bv = -__builtin_huge_val();
-                    int be = INT_MAX;
+                for (int j = 0; j < CJ; ++j)
+                    if (beats(cv[j], ce_[j], bv, be)) { bv = cv[j]; be = ce_[j]; }
+                row_best_f64(bv, be, nc > 16);               // (up to 16 candidates sit in the first row)
 #pragma unroll
-                    for (int j = 0; j < CJ; ++j)
-                        if (beats(cv[j], ce_[j], bv, be)) { bv = cv[j]; be = ce_[j]; }
-                    wave_best_f64(bv, be);
-#pragma unroll
-                    for (int j = 0; j < CJ; ++j)
-                        if (ce_[j] == be) { cv[j] = -__builtin_huge_val(); ce_[j] = INT_MAX; }
-                    p[r] = exp(bv - m) / den;
-                    pe[r] = be;
-                    tot += p[r];
-                }
+                for (int j = 0; j < CJ; ++j)
+                    if (ce_[j] == be) { cv[j] = -__builtin_huge_val(); ce_[j] = INT_MAX; }
+                if (lane == r) { mine = bv; mine_e = be; }
             }
-            if (lane == 0) {
-#pragma unroll
-                for (int r = 0; r < MOE_MAX_TOPK; ++r)
-                    if (r < k) {
-                        idx_out[(size_t)t * k + r] = pe[r];
-                        w_out[(size_t)t * k + r] = (float)(renorm ? p[r] / tot : p[r]);
-                    }
+            const double p = exp(mine - (double)flag_max[f]) / (double)flag_den[f];
+            double tot = 0.0;
+            for (int r = 0; r < k; ++r) tot += lane_f64(p, r);
+            if (lane < k) {
+                idx_out[(size_t)t * k + lane] = mine_e;
+                w_out[(size_t)t * k + lane] = (float)(renorm ? p / tot : p);
             }
         }
         __syncthreads();                                     // (the lists are reused)
@@ -439,50 +473,52 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     const float w2 = tid < E ? fmaxf(0.f, w_norm2[tid]) : 0.f;           // this thread's share of the largest column norm
 
     double acc64[16];
+    f32x16 acc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc64[r] = 0.0;
+    for (int r = 0; r < 16; ++r) { acc64[r] = 0.0; acc[r] = 0.f; }
     static_assert(KACC == KC, "a chunk is what one fp32 accumulation holds");
 
     // ---- staging.  Stage s holds the chunks s*KSP ... s*KSP+KSP-1: for each, 32 token rows, then
     // for each EPT expert rows, every row one 128-byte line (64 terms) in eight 16-byte pieces,
     // piece p of row r at position p ^ ((r / 2) & 7) (conflict-free fragment reads).  A load moves
-    // eight rows (lane = row * 8 + position); the loads of a stage are dealt to the wavefronts,
-    // every wavefront issues the same number (LPW) per stage -- the surplus ones, and all loads
-    // past the last stage, with an empty descriptor -- so the count of outstanding loads that
-    // guarantees a stage is a constant.
-    constexpr int SROWS = (TB + EPT) * KSP, NL = SROWS / 8, LPW = (NL + NWV - 1) / NWV;
-    constexpr int STAGE = SROWS * 128;
+    // eight rows (lane = row * 8 + position).  With one or two wavefronts on a SIMD the loop is bound by
+    // the instructions a wavefront issues (one every five cycles), so a wavefront's loads are the
+    // same in every stage: XL of token rows and WL of expert rows, their per-lane offsets formed once,
+    // the stage only in the scalar offset.  (Deciding in every stage which rows a load brings took
+    // 0.6 us a stage.)  Chunks past the end bring the following terms, or zeros past the end of the
+    // matrix, and are not multiplied; past the last stage its loads go out again, so that the count of
+    // outstanding loads that guarantees a stage is a constant.
+    constexpr int SROWS = (TB + EPT) * KSP, STAGE = SROWS * 128;
+    constexpr int XL = (TB / 8 * KSP + NWV - 1) / NWV, WL = EPT / 8 * KSP / NWV, LPW = XL + WL;
     constexpr int RING = ROUTE_RING;
+    static_assert(EPT / 8 * KSP % NWV == 0 && (TB / 8 * KSP % NWV == 0 || XL == 1), "loads dealt to the wavefronts");
     static_assert(LPW * (RING - 1) < 64 && RING * STAGE + 1024 <= 150 * 1024, "staging ring");
     unsigned char* ring = smem;
-    unsigned char* dump = smem + RING * STAGE;               // 1 KB where the surplus loads' zeros go
     const int n_stages = (n_chunks + KSP - 1) / KSP;
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wgt), 0, E * d * 2, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rnull = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), 0, 0, 0x00020000);
     const int ld_r = lane >> 3, ld_p = lane & 7;
+    unsigned voff[LPW], to[LPW];                             // byte offsets: in the matrix, and (scalar) in the stage
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int per_chunk = i < XL ? TB / 8 : EPT / 8;     // loads of a chunk's token (expert) rows
+        const int L = wave + (i < XL ? i : i - XL) * NWV, sub = L / per_chunk, row = (L - sub * per_chunk) * 8;
+        const int rr = (i < XL ? 0 : TB) + row;              // row inside the chunk: tokens, then experts
+        const bool none = i < XL && L >= TB / 8 * KSP;       // (more wavefronts than loads of token rows)
+        voff[i] = (unsigned)(row + ld_r) * (unsigned)d * 2u + (unsigned)(sub * 128) + (unsigned)((ld_p ^ (((rr + ld_r) >> 1) & 7)) << 4);
+        to[i] = (unsigned)__builtin_amdgcn_readfirstlane((sub * (TB + EPT) + rr) * 128);
+        if (none) { voff[i] = 0x80000000u; to[i] = RING * STAGE; }   // (zeros to the 1 KB behind the ring)
+    }
     auto issue_stage = [&](int st) {
-        unsigned char* buf = ring + (st % RING) * STAGE;
+        const unsigned buf = (unsigned)(st % RING) * STAGE, soff = (unsigned)(st < n_stages ? st : n_stages - 1) * (KSP * 128u);
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const int L = wave + i * NWV;                    // (wave-uniform)
-            const int R = L * 8;                             // first stage row of this load
-            const int sub = R / (TB + EPT);                  // chunk of the stage
-            const int rr = R - sub * (TB + EPT);             // row inside the chunk: tokens, then experts
-            const int c = st * KSP + sub;
-            const bool live = L < NL && st < n_stages && c < n_chunks;
-            const bool is_x = rr < TB;
-            const int row = (is_x ? rr : rr - TB) + ld_r;    // token of the tile / expert
-            const unsigned voff = (unsigned)row * (unsigned)d * 2u + (unsigned)((ld_p ^ (((rr + ld_r) >> 1) & 7)) << 4);
-            lds_void_t* to = (lds_void_t*)(L < NL ? buf + R * 128 : dump);
-            const unsigned soff = (unsigned)c * 128u;
-            // (three calls under wave-uniform branches: a descriptor chosen by a conditional
-            // expression is kept in memory by the compiler and reloaded, with a full wait, per load)
-            if (live && is_x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, to, 16, voff, soff, 0, 0);
-            else if (live) __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, to, 16, voff, soff, 0, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rnull, to, 16, voff, soff, 0, 0);
+            const bool spare = XL * NWV > TB / 8 * KSP && i < XL;      // (its place does not move with the stage)
+            lds_void_t* at = (lds_void_t*)(ring + (spare && to[i] == (unsigned)(RING * STAGE) ? to[i] : buf + to[i]));
+            if (i < XL) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, at, 16, voff[i], soff, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, at, 16, voff[i], soff, 0, 0);
         }
     };
 #pragma unroll
@@ -491,9 +527,7 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     const int frag_sw = (l32 >> 1) & 7;
     for (int st = 0; st < n_stages; ++st) {
         // stage st has landed once only the RING-2 younger stages are outstanding
-        if (RING == 4) MOE_WAIT_VMCNT(2 * LPW);
-        else if (RING == 3) MOE_WAIT_VMCNT(LPW);
-        else MOE_WAIT_VMCNT(0);
+        MOE_WAIT_VMCNT((RING - 2) * LPW);
         // ... for every wavefront after the barrier; and stage st-1 has been read by all.  (A bare
         // barrier: __syncthreads would first wait for every load in flight, the prefetched stages too.)
         asm volatile("" ::: "memory");
@@ -501,37 +535,39 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
-        issue_stage(st + RING - 1);                          // into the buffer of stage st-1
         const int c = st * KSP + ksi;
-        if (c < n_chunks) {
-            const unsigned char* xb = ring + (st % RING) * STAGE + ksi * (TB + EPT) * 128;
-            const unsigned char* wb_ = xb + (TB + nbi * 32) * 128;
-            frag_t xa[KC / 16], wb[KC / 16];
-            f32x16 acc;
+        const unsigned char* xb = ring + (st % RING) * STAGE + ksi * (TB + EPT) * 128;
+        const unsigned char* wb_ = xb + (TB + nbi * 32) * 128;
+        frag_t xa[KC / 16], wb[KC / 16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int ks = 0; ks < KC / 16; ++ks) {
+            const int pos = ((ks * 2 + lhi) ^ frag_sw) << 4;
+            xa[ks] = *(const frag_t*)(xb + frag_at + pos);
+            wb[ks] = *(const frag_t*)(wb_ + frag_at + pos);
+        }
+        issue_stage(st + RING - 1);                          // into the buffer of stage st-1
+        // (the sums of the chunk before: they pass while this one's fragments arrive)
 #pragma unroll
-            for (int ks = 0; ks < KC / 16; ++ks) {
-                const int pos = ((ks * 2 + lhi) ^ frag_sw) << 4;
-                xa[ks] = *(const frag_t*)(xb + frag_at + pos);
-                wb[ks] = *(const frag_t*)(wb_ + frag_at + pos);
-            }
+        for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
+        const frag_t none = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int ks = 0; ks < KC / 16; ++ks) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[ks]),
-                                                              __builtin_bit_cast(bf16x8, wb[ks]), acc, 0, 0, 0);
-                if (nbi == 0) {                              // the token norms, once per contraction part
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bf16x2 p2 = bf16_pair(xa[ks][i]);
-                        xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
-                    }
+        for (int ks = 0; ks < KC / 16; ++ks) {
+            if (c >= n_chunks) xa[ks] = none;                // (a stage's last chunks may be past the end)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[ks]),
+                                                          __builtin_bit_cast(bf16x8, c < n_chunks ? wb[ks] : none), acc, 0, 0, 0);
+            if (nbi == 0) {                                  // the token norms, once per contraction part
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bf16x2 p2 = bf16_pair(xa[ks][i]);
+                    xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
         }
     }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
     MOE_WAIT_VMCNT(0);                                       // (the trailing empty loads still target this LDS)
     __syncthreads();                                         // the ring's memory is reused below
     route_finish<NB, KSP, RMAX, true>(smem, acc64, xsq, w2, mine, x, wgt, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
@@ -620,9 +656,7 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
     double acc64[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc64[r] = 0.0;
-    float xsq = 0.f, wsq[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) wsq[e] = 0.f;
+    float xsq = 0.f, wsq = 0.f;                              // this lane's share of the norm of its token row and expert row
     const int n_stages = (d + KPLAIN * KSP - 1) / (KPLAIN * KSP);
     // Swizzled LDS offsets: piece c * 2 + lhi of a fragment row, and expert e of this thread's block, are
     // the offset of piece lhi / expert 0 with bits flipped.
@@ -644,11 +678,8 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
         for (int e = 0; e < 8; ++e) {                        // expert g * 8 + e: its eight terms
             u32x4 piece;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < 4; ++m)
                 piece[m] = __builtin_amdgcn_perm(wv[2 * m + 1][e >> 1], wv[2 * m][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
-                const bf16x2 p2 = bf16_pair(piece[m]);
-                wsq[e] = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, wsq[e], false);
-            }
             *(u32x4*)(smem + (wr_at ^ (e << 5)) + e * 256) = piece;
         }
         __syncthreads();
@@ -664,9 +695,13 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
                 const frag_t xa = *(const frag_t*)(smem + (xb_at ^ flip)), wa = *(const frag_t*)(smem + (wb_at ^ flip));
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa), __builtin_bit_cast(bf16x8, wa), acc, 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {                // the token norms (those of expert block 0 are used)
-                    const bf16x2 p2 = bf16_pair(xa[i]);
-                    xsq = __builtin_amdgcn_fdot2_f32_bf16(p2, p2, xsq, false);
+                for (int i = 0; i < 4; ++i) {
+                    const bf16x2 w2 = bf16_pair(wa[i]);
+                    wsq = __builtin_amdgcn_fdot2_f32_bf16(w2, w2, wsq, false);
+                    if (nbi == 0) {                          // (wave-uniform)
+                        const bf16x2 x2 = bf16_pair(xa[i]);
+                        xsq = __builtin_amdgcn_fdot2_f32_bf16(x2, x2, xsq, false);
+                    }
                 }
                 if (ks & 1) __builtin_amdgcn_sched_barrier(0);     // (two slices' fragments in registers at a time)
             }
@@ -675,18 +710,18 @@ __global__ __launch_bounds__(NB * KSP * 64, NB >= 4 ? 4 : NB == 2 ? 3 : 2) void 
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // squared column norms (a little rounded up): the parts of the threads that share an expert
+    // squared column norms (a little rounded up): the halves of a row's terms sit in lanes l and l + 32, the
+    // contraction parts in the wavefronts that share an expert block
+    wsq += __shfl_xor(wsq, 32);
     __syncthreads();
-    float* wn = reinterpret_cast<float*>(smem);              // [16 * KSP][EPT]
-#pragma unroll
-    for (int e = 0; e < 8; e += 4)
-        *(float4*)(wn + kg * EPT + g * 8 + e) = make_float4(wsq[e], wsq[e + 1], wsq[e + 2], wsq[e + 3]);
+    float* wn = reinterpret_cast<float*>(smem);              // [KSP][EPT]
+    if (lhi == 0) wn[ksi * EPT + nbi * 32 + l32] = wsq;
     __syncthreads();
     float w2 = 0.f;
     for (int e = tid; e < E; e += NTHR) {
-        float v = 0.f;
+        float v = wn[e];
 #pragma unroll
-        for (int p = 0; p < 16 * KSP; ++p) v += wn[p * EPT + e];
+        for (int p = 1; p < KSP; ++p) v += wn[p * EPT + e];
         w2 = fmaxf(w2, v * 1.002f);
     }
     __syncthreads();                                         // the staging memory is free now
