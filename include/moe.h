@@ -394,6 +394,23 @@ MOE_API int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int d, 
                                         void* h_scratch, const int32_t* perm, const float* gate_w,
                                         float* y_out, void* stream);
 
+/* moe_grouped_ffn_fused for k >= 2 and, for the same tokens, the always-on shared expert:
+ *
+ *   moe_grouped_ffn_fused(x, ..., y_perm)
+ *   moe_grouped_ffn(x, T, d, shared_F, 1, MOE_SWIGLU, ..., s_y)        (rows in place, one expert)
+ *
+ * s_tiles / s_plan_hdr: the shared expert's plan (one expert of T rows, made with s_tile_m);
+ * s_h_scratch [T, shared_F], s_y [T,d] fp32.  Where both hold few rows their products share
+ * launches, and the last bits of s_y may differ from those of the separate call.
+ */
+MOE_API int moe_grouped_ffn_shared(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                   const void* const* w_in, const void* const* w_out,
+                                   const moe_tile* tiles, int32_t* plan_hdr, int tile_m,
+                                   void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
+                                   const void* const* s_w_in, const void* const* s_w_out,
+                                   const moe_tile* s_tiles, int32_t* s_plan_hdr, int s_tile_m,
+                                   void* s_h_scratch, float* s_y, void* stream);
+
 /* ------------------------------------------------------------------------------------------
  * Step 6 (Alg. 1 "reconstruct"; section 2: the experts' outputs are weighted by the router's
  * values and combined):

@@ -63,6 +63,10 @@ static bool few_rows_per_expert(int A, int E) {
     return A <= 64 * E && (long long)A * E <= 32ll * (8 - E) * E;
 }
 
+static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
+    return tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
+}
+
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
 // Measured with and without the hint (both products): 128 experts of 768 x 3072, Zipf 1.0: 8 rows
 // each 213 : 228 us, 16 rows 257 : 267, 32 rows 284 : 278; 60 of 2048 x 1408, Zipf 1.2: 13 rows 203 :
@@ -109,7 +113,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1).
         auto wide = [&](int epi, int K) { return tile_m == 256 && g_kernel_mode != 1 && moe_gemm_wide_supports(epi, K); };
-        const bool rows = tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
+        const bool rows = few_rows_call(A, d, F, E, tile_m);
         // (the eight XCDs' L2s hold 32 MB)
         auto cache = [&](long long weights, size_t out_bytes) {
             return moe_weights_once(A, E, weights * E * 2) ? MOE_CACHE_WEIGHTS_ONCE
@@ -263,4 +267,36 @@ extern "C" int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int 
                                            const int32_t* perm, const float* gate_w, float* y_out, void* stream) {
     MOE_REQUIRE(phase == 1 || phase == 2, MOE_ERR_ARG, "moe_grouped_ffn_fused_phase: phase %d", phase);
     return fused_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, gate_w, y_out, stream);
+}
+
+// moe_grouped_ffn_fused and the shared expert's moe_grouped_ffn.  Where the few-row kernels serve both, each
+// product of the shared expert shares the launch of the routed experts' one (33 rows of 2048 x 1408, E = 60, and
+// 5632: 94 + 56 + 25 + 26 us in four launches, SHARED_US in two): one expert's product has too few items to keep
+// the memory busy by itself.  Everywhere else the calls follow one another.
+extern "C" int moe_grouped_ffn_shared(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                      const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                                      int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
+                                      const void* const* s_w_in, const void* const* s_w_out, const moe_tile* s_tiles,
+                                      int32_t* s_plan_hdr, int s_tile_m, void* s_h_scratch, float* s_y, void* stream) {
+    MOE_REQUIRE(k >= 2, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_shared: needs k >= 2 (k=%d)", k);
+    const bool rows = dt == MOE_BF16 && act == MOE_SWIGLU && T >= 1 && E >= 1 && k >= 2 && (long long)T * k < (1ll << 30) &&
+                      few_rows_call(T * k, d, F, E, tile_m) && few_rows_call(T, d, shared_F, 1, s_tile_m);
+    MOE_REQUIRE(T <= 0 || (x && w_in && w_out && y_perm && s_w_in && s_w_out && s_y), MOE_ERR_ARG, "moe_grouped_ffn_shared: null pointer");
+    // (phase 0 checks the other arguments and enqueues nothing)
+    for (int phase = 0; phase <= 3; phase += 3) {
+        if (phase && rows) break;
+        int rc = fused_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, nullptr, y_perm, stream);
+        if (rc == MOE_OK)
+            rc = grouped_ffn_impl(phase, x, T, d, shared_F, 1, MOE_SWIGLU, dt, s_w_in, s_w_out, s_tiles, s_plan_hdr, s_tile_m,
+                                  s_h_scratch, s_y, stream);
+        if (rc != MOE_OK) return rc;
+    }
+    if (!rows) return MOE_OK;
+    for (int phase = 1; phase <= 2; ++phase) {
+        const int rc = moe_launch_gemm_rows_shared(phase, x, T, d, F, E, k, phase == 1 ? w_in : w_out, tiles, plan_hdr, h_scratch, y_perm,
+                                                   perm, shared_F, phase == 1 ? s_w_in : s_w_out, s_tiles, s_plan_hdr, s_h_scratch,
+                                                   s_y, (hipStream_t)stream);
+        if (rc != MOE_OK) return rc;
+    }
+    return MOE_OK;
 }

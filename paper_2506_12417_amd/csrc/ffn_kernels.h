@@ -61,6 +61,14 @@ int moe_launch_gemm_rows(int epi, const void* a, int A, int K, int N, int E, con
 int moe_launch_gemm_rows_gather(int epi, const void* x, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                                 const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div);
 
+// The same for the routed SwiGLU experts (rows gathered from x, k > 1) and a shared SwiGLU expert over all
+// T rows of x (one expert's plan) in one launch per product (phase 1, 2); the shared expert has
+// the same d and holds at most 128 rows.
+int moe_launch_gemm_rows_shared(int phase, const void* x, int T, int d, int F, int E, int k, const void* const* w, const moe_tile* tiles,
+                                const int32_t* hdr, void* h, float* y_perm, const int32_t* perm, int shared_F,
+                                const void* const* s_w, const moe_tile* s_tiles, const int32_t* s_hdr, void* s_h, float* s_y,
+                                hipStream_t st);
+
 // The fp32 products (ffn_f32.hip; tiles of at most 64 rows, RELU / SWIGLU / STORE, all of fp32).
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                         const int32_t* hdr, void* out, int ld_out, hipStream_t st);

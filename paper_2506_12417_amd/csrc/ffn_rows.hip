@@ -79,13 +79,22 @@ __device__ __forceinline__ uint16_t half_bits(float v) {     // saturating, near
     return __builtin_bit_cast(uint16_t, (_Float16)__builtin_amdgcn_fmed3f(v, -65504.f, 65504.f));
 }
 
+// One product: what a launch is given for it (moe_launch_gemm_rows).
+struct Job {
+    const uint16_t* a_mat;
+    const void* const* w_ptrs;
+    const moe_tile* tiles;
+    const int32_t* hdr;
+    void* out;
+    const int32_t* row_token;
+    const float* row_gate;
+    int K, N, ld_out, a_div;
+};
+
+// Two products can share a launch: the first n_other work-groups serve `other`, the rest `main`.  (The
+// shared expert beside the routed ones, whose own two launches leave the chip half idle.)
 template <int EPI, bool GATHER, int KS, int NSUB, int UNROLL>
-__global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* __restrict__ a_mat, int K, int N,
-                                                               const void* const* __restrict__ w_ptrs,
-                                                               const moe_tile* __restrict__ tiles,
-                                                               const int32_t* __restrict__ hdr, void* __restrict__ out, int ld_out,
-                                                               const int32_t* __restrict__ row_token,
-                                                               const float* __restrict__ row_gate, int a_div) {
+__global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(Job main, Job other, unsigned n_other) {
     constexpr bool SCAT = EPI == MOE_EPI_SCATTER, HALF_IN = SCAT || EPI == MOE_EPI_STORE, GLU = EPI == MOE_EPI_SWIGLU;
     constexpr int NTH = KS * 64, RGMAX = 4, COLS = 16 * NSUB;
     static_assert(NSUB == 2 || (NSUB == 1 && !GLU), "SwiGLU needs a gate and an up block");
@@ -94,15 +103,27 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* _
     __shared__ __attribute__((aligned(16))) float part[KS][RGMAX * 16][COLS + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = sgpr(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
+    const bool second = blockIdx.x < n_other;
+    const uint16_t* __restrict__ a_mat = second ? other.a_mat : main.a_mat;
+    const void* const* __restrict__ w_ptrs = second ? other.w_ptrs : main.w_ptrs;
+    const moe_tile* __restrict__ tiles = second ? other.tiles : main.tiles;
+    const int32_t* __restrict__ hdr = second ? other.hdr : main.hdr;
+    void* __restrict__ out = second ? other.out : main.out;
+    const int32_t* __restrict__ row_token = second ? other.row_token : main.row_token;
+    const float* __restrict__ row_gate = second ? other.row_gate : main.row_gate;
+    const int K = second ? other.K : main.K, N = second ? other.N : main.N, ld_out = second ? other.ld_out : main.ld_out;
+    const int a_div = second ? other.a_div : main.a_div;
     const int n_cb = N / COLS;                   // (N is a multiple of 64)
-    const int n_slices = K / 32, per = (n_slices + KS - 1) / KS;
+    // (whole lines: a wavefront's part is an even number of 64-byte slices, K being a multiple of 64.  K = 1408 by
+    // four wavefronts in parts of 11 slices read 20 % more than the weights.)
+    const int n_slices = K / 32, per = (n_slices / 2 + KS - 1) / KS * 2;
     const int s0 = wave * per < n_slices ? wave * per : n_slices, s1 = s0 + per < n_slices ? s0 + per : n_slices;
     const unsigned w_off = ((unsigned)l16 * (unsigned)K + (unsigned)lq * 8u) * 2u;
 
     // (The tile is read after the number of tiles, although both latencies pass before the weights can
     // be asked for: a table kept by its owner may end with its last tile.)
-    const int n_items = sgpr(hdr[0]) * n_cb;
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    const int n_items = sgpr(hdr[0]) * n_cb, step = (int)(second ? n_other : gridDim.x - n_other);
+    for (int item = (int)(second ? blockIdx.x : blockIdx.x - n_other); item < n_items; item += step) {
         const int ti = item / n_cb, cb = item - ti * n_cb;
         const moe_tile t = tiles[ti];
         const int rc = sgpr(t.row_count), row0 = sgpr(t.row_begin), expert = sgpr(t.expert);
@@ -123,7 +144,9 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* _
                 for (int g = 0; g < RG; ++g) {
                     const int r = g * 16 + l16 < left ? g * 16 + l16 : left - 1;
                     unsigned src = (unsigned)(row0 + r0 + r);
-                    if constexpr (GATHER) src = (unsigned)row_token[src] / (unsigned)a_div;
+                    if constexpr (GATHER) {
+                        if (row_token) src = (unsigned)row_token[src] / (unsigned)a_div;
+                    }
                     a_off[g] = (src * (unsigned)K + (unsigned)lq * 8u) * 2u;
                 }
                 f32x4 acc[RG][NSUB];
@@ -180,25 +203,28 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(const uint16_t* _
     }
 }
 
+// The number of tiles is known on the device only: at most one per row, about one per expert.
+// A table with more tiles makes the work-groups loop, a shorter one lets some leave at once.
+long long tiles_estimate(int A, int E) { return A < E + A / 128 ? A : E + A / 128; }
+
 template <int EPI, bool GATHER>
-int launch(const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
-           int ld_out, hipStream_t st, const int32_t* row_token, const float* row_gate, int a_div) {
+int launch(const Job& main, int A, int E, hipStream_t st, const Job* other = nullptr, int other_A = 0) {
     const int dev_ok = moe_check_gemm_device();
     if (dev_ok != MOE_OK) return dev_ok;
-    // The number of tiles is known on the device only: at most one per row, about one per expert.
-    // A table with more tiles makes the work-groups loop, a shorter one lets some leave at once.
-    const long long tiles_est = A < E + A / 128 ? A : E + A / 128;
+    const int K = main.K, N = main.N;
+    const long long tiles_est = tiles_estimate(A, E);
     const long long items = tiles_est * (N / 32);
     auto go = [&](auto ks, auto nsub, auto unroll) {
         constexpr int KS = decltype(ks)::value, NSUB = decltype(nsub)::value, UNROLL = decltype(unroll)::value;
         const long long n = tiles_est * (N / (16 * NSUB));
-        hipLaunchKernelGGL((gemm_rows_kernel<EPI, GATHER, KS, NSUB, UNROLL>), dim3((unsigned)(n < 32768 ? n : 32768)), dim3(KS * 64), 0,
-                           st, (const uint16_t*)a, K, N, w, tiles, hdr, out, ld_out, row_token, row_gate, a_div);
+        const unsigned n_other = other ? (unsigned)(tiles_estimate(other_A, 1) * (other->N / (16 * NSUB))) : 0u;
+        hipLaunchKernelGGL((gemm_rows_kernel<EPI, GATHER, KS, NSUB, UNROLL>), dim3((unsigned)(n < 32768 ? n : 32768) + n_other), dim3(KS * 64), 0,
+                           st, main, other ? *other : main, n_other);
     };
     auto go_unroll = [&](auto ks, auto nsub) {
         // Slices per round of loads: eight, or six where that leaves fewer loads unused (K = 768:
         // 91 -> 76 us at 78 experts; K = 1408: 71 -> 60 us at 46).
-        const int per = (K / 32 + decltype(ks)::value - 1) / decltype(ks)::value;
+        const int per = (K / 64 + decltype(ks)::value - 1) / decltype(ks)::value * 2;
         if ((per + 5) / 6 * 6 < (per + 7) / 8 * 8) go(ks, nsub, std::integral_constant<int, 6>{});
         else go(ks, nsub, std::integral_constant<int, 8>{});
     };
@@ -230,16 +256,31 @@ int launch(const void* a, int A, int K, int N, int E, const void* const* w, cons
 
 int moe_launch_gemm_rows(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                          const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_token, const float* row_gate) {
-    if (epi == MOE_EPI_RELU) return launch<MOE_EPI_RELU, false>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st, nullptr, nullptr, 1);
-    if (epi == MOE_EPI_SWIGLU) return launch<MOE_EPI_SWIGLU, false>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st, nullptr, nullptr, 1);
-    if (epi == MOE_EPI_SCATTER)
-        return launch<MOE_EPI_SCATTER, false>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st, row_token, row_gate, 1);
-    return launch<MOE_EPI_STORE, false>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st, nullptr, nullptr, 1);
+    const bool scatter = epi == MOE_EPI_SCATTER;
+    const Job j = {(const uint16_t*)a, w, tiles, hdr, out, scatter ? row_token : nullptr, scatter ? row_gate : nullptr, K, N, ld_out, 1};
+    if (epi == MOE_EPI_RELU) return launch<MOE_EPI_RELU, false>(j, A, E, st);
+    if (epi == MOE_EPI_SWIGLU) return launch<MOE_EPI_SWIGLU, false>(j, A, E, st);
+    if (scatter) return launch<MOE_EPI_SCATTER, false>(j, A, E, st);
+    return launch<MOE_EPI_STORE, false>(j, A, E, st);
 }
 
 int moe_launch_gemm_rows_gather(int epi, const void* x, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                                 const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
-    if (epi == MOE_EPI_SWIGLU)
-        return launch<MOE_EPI_SWIGLU, true>(x, A, K, N, E, w, tiles, hdr, out, ld_out, st, row_src, nullptr, src_div);
-    return launch<MOE_EPI_RELU, true>(x, A, K, N, E, w, tiles, hdr, out, ld_out, st, row_src, nullptr, src_div);
+    const Job j = {(const uint16_t*)x, w, tiles, hdr, out, row_src, nullptr, K, N, ld_out, src_div};
+    if (epi == MOE_EPI_SWIGLU) return launch<MOE_EPI_SWIGLU, true>(j, A, E, st);
+    return launch<MOE_EPI_RELU, true>(j, A, E, st);
+}
+
+int moe_launch_gemm_rows_shared(int phase, const void* x, int T, int d, int F, int E, int k, const void* const* w, const moe_tile* tiles,
+                                const int32_t* hdr, void* h, float* y_perm, const int32_t* perm, int shared_F,
+                                const void* const* s_w, const moe_tile* s_tiles, const int32_t* s_hdr, void* s_h, float* s_y,
+                                hipStream_t st) {
+    if (phase == 1) {
+        const Job j = {(const uint16_t*)x, w, tiles, hdr, h, perm, nullptr, d, 2 * F, F, k};
+        const Job o = {(const uint16_t*)x, s_w, s_tiles, s_hdr, s_h, nullptr, nullptr, d, 2 * shared_F, shared_F, 1};
+        return launch<MOE_EPI_SWIGLU, true>(j, T * k, E, st, &o, T);
+    }
+    const Job j = {(const uint16_t*)h, w, tiles, hdr, y_perm, nullptr, nullptr, F, d, d, 1};
+    const Job o = {(const uint16_t*)s_h, s_w, s_tiles, s_hdr, s_y, nullptr, nullptr, shared_F, d, d, 1};
+    return launch<MOE_EPI_STORE, false>(j, T * k, E, st, &o, T);
 }

@@ -217,6 +217,14 @@ class MoELayer:
             args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
                     self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm,
                     stream)
+            if marks is None and self.shared_F:              # (k > 1: with a shared expert the combine is not folded)
+                s = self.shared
+                B.moe_grouped_ffn_shared(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
+                                         self.tiles, self.plan_hdr, self.tile_m, self.h, self.perm, self.y_perm, self.shared_F,
+                                         s.in_ptrs, s.out_ptrs, self.s_tiles, self.s_hdr, self.s_tile_m, self.s_h, self.s_y,
+                                         stream)
+                self.combine(True, stream)
+                return self.y
             if marks is None:
                 B.moe_grouped_ffn_fused(*args)
             else:

@@ -198,6 +198,14 @@ def test_pack_combine_copy_argument_errors():
     assert fused(T=0, perm=None, y=None) == B.MOE_OK
     assert status(B.moe_grouped_ffn_fused_phase, 0, FAKE, 8, 256, 512, 2, 1, B.MOE_RELU, B.MOE_BF16, FAKE, FAKE, FAKE, FAKE,
                   128, FAKE, FAKE, None, FAKE, 0) == B.MOE_ERR_ARG
+    shared = lambda dt=B.MOE_BF16, T=8, d=256, k=2, tile_m=128, s_tile_m=128, sF=512, y=FAKE, sy=FAKE, sh=FAKE: status(
+        B.moe_grouped_ffn_shared, FAKE, T, d, 512, 2, k, B.MOE_SWIGLU, dt, FAKE, FAKE, FAKE, FAKE, tile_m, FAKE, FAKE, y, sF,
+        FAKE, FAKE, FAKE, FAKE, s_tile_m, sh, sy, 0)
+    assert shared(dt=B.MOE_F32) == B.MOE_ERR_UNSUPPORTED and shared(k=1) == B.MOE_ERR_UNSUPPORTED
+    assert shared(d=192) == B.MOE_ERR_UNSUPPORTED and shared(sF=500) == B.MOE_ERR_UNSUPPORTED
+    assert shared(tile_m=64) == B.MOE_ERR_UNSUPPORTED and shared(s_tile_m=64) == B.MOE_ERR_UNSUPPORTED
+    assert shared(y=None) == B.MOE_ERR_ARG and shared(sy=None) == B.MOE_ERR_ARG and shared(sh=None) == B.MOE_ERR_ARG
+    assert shared(T=0) == B.MOE_OK
     assert status(B.moe_pack_w_out, None, 1, 8, 32, B.MOE_BF16, FAKE, 0) == B.MOE_ERR_ARG
     assert status(B.moe_pack_w_out, FAKE, 1, 8, 8, 7, FAKE, 0) == B.MOE_ERR_UNSUPPORTED
     assert status(B.moe_pack_w_out, None, 0, 8, 8, B.MOE_BF16, None, 0) == B.MOE_OK

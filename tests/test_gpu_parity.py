@@ -1457,6 +1457,42 @@ def test_ffn_top1_is_ffn_then_combine(torch_gpu, T, d, F, E, gate, skew, tile_m)
     assert int(L.plan_hdr[B.MOE_PLAN_HDR_CTR:].abs().sum()) == 0      # the work counters are back at zero
 
 
+# (contractions whose parts by four wavefronts end in the middle of a round or leave a wavefront without terms; one
+# row to four row groups of the shared expert, and one row too many for it; no few rows per expert; ReLU: no shared launch)
+@pytest.mark.parametrize("T,d,F,E,k,sF,act", [(1, 256, 64, 60, 4, 64, "swiglu"), (3, 2048, 192, 8, 2, 320, "swiglu"),
+                                              (33, 512, 1408, 24, 2, 1088, "swiglu"), (64, 320, 704, 60, 3, 2112, "swiglu"),
+                                              (65, 256, 192, 60, 2, 192, "swiglu"), (40, 256, 192, 4, 2, 256, "swiglu"),
+                                              (9, 256, 320, 16, 2, 448, "relu")])
+def test_ffn_shared_is_ffn_fused_then_ffn(torch_gpu, T, d, F, E, k, sF, act):
+    """moe_grouped_ffn_shared against its two separate calls (sums of the contraction in parts: 1e-5 of the
+    RMS before the hidden activations' rounding, which may then go the other way: 1e-3 as between
+    the stages and the oracle), and the layer that uses it against the oracle."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    wl = W.WORKLOADS["c3"].scaled(T=T, d=d, F=F, E=E, k=k, shared_F=sF, act=act)
+    _note("shared T=%d d=%d F=%d E=%d k=%d sF=%d %s" % (T, d, F, E, k, sF, act))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, inp)
+    x = layer_x(layer, inp)
+    for t in (layer.h, layer.s_h, layer.y_perm, layer.s_y):
+        t.fill_(float("nan"))
+    y = to_numpy(layer.forward(x).clone())
+    got = [to_numpy(layer.y_perm), to_numpy(layer.s_y)]
+    layer.y_perm.fill_(float("nan"))
+    layer.s_y.fill_(float("nan"))
+    g = layer.experts
+    B.moe_grouped_ffn_fused(x, T, d, F, E, k, layer.act, layer.dt, g.in_ptrs, g.out_ptrs, layer.tiles, layer.plan_hdr, layer.tile_m,
+                            layer.h, layer.perm, None, layer.y_perm)
+    layer.shared_ffn(x)
+    torch.cuda.synchronize()
+    for a, b in zip(got, (to_numpy(layer.y_perm), to_numpy(layer.s_y))):
+        assert max_err_over_rms(a, b) <= 1e-3
+    idx_o, w_o, _ = O.route_topk(inp["x"], inp["W_g"], inp["b"], wl.k, wl.renorm)
+    shared = {"Wg": inp["sWg"], "Wu": inp["sWu"], "Wd": inp["sWd"]}
+    y_o = O.moe_layer(inp["x"], idx_o, w_o, expert_dict(wl, inp), wl.act, shared=shared)
+    assert max_err_over_rms(y, y_o) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("T,d,F,E,k,act,skew", [(1500, 256, 512, 16, 1, "relu", "zipf"), (1500, 256, 512, 16, 2, "swiglu", "zipf"),
                                                  (4096, 768, 3072, 128, 1, "relu", "zipf"), (777, 320, 640, 5, 3, "relu", "hot"),
                                                  (300, 1024, 1024, 40, 1, "swiglu", "uniform"), (1, 256, 512, 4, 4, "relu", "uniform")])
