@@ -271,7 +271,7 @@ extern "C" int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int 
 
 // moe_grouped_ffn_fused and the shared expert's moe_grouped_ffn.  Where the few-row kernels serve both, each
 // product of the shared expert shares the launch of the routed experts' one (33 rows of 2048 x 1408, E = 60, and
-// 5632: 94 + 56 + 25 + 26 us in four launches, SHARED_US in two): one expert's product has too few items to keep
+// 5632: 94 + 56 + 25 + 26 us in four launches, 108 + 70 in two): one expert's product has too few items to keep
 // the memory busy by itself.  Everywhere else the calls follow one another.
 extern "C" int moe_grouped_ffn_shared(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
                                       const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
