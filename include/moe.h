@@ -394,6 +394,15 @@ MOE_API int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int d, 
                                         void* h_scratch, const int32_t* perm, const float* gate_w,
                                         float* y_out, void* stream);
 
+/* Steps 4 (the row gather) and 5 in fp32: the first product reads row r of the table's row space
+ * from x[perm[r] / k] (x [T,d] fp32, perm [T*k] from moe_permute or moe_permute_plan), so that no x_perm is
+ * needed.  y_perm as moe_grouped_ffn writes it, bit for bit; other arguments as there.  MOE_F32 only.
+ */
+MOE_API int moe_grouped_ffn_gather(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                   const void* const* w_in, const void* const* w_out,
+                                   const moe_tile* tiles, int32_t* plan_hdr, int tile_m,
+                                   void* h_scratch, const int32_t* perm, float* y_perm, void* stream);
+
 /* moe_grouped_ffn_fused for k >= 2 and, for the same tokens, the always-on shared expert:
  *
  *   moe_grouped_ffn_fused(x, ..., y_perm)

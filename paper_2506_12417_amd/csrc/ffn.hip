@@ -169,7 +169,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
     } else {
         if (phases & 1) {
             rc = moe_launch_gemm_f32(act == MOE_SWIGLU ? MOE_EPI_SWIGLU : MOE_EPI_RELU, x_perm, A, d, n1, E, w_in, tiles, plan_hdr,
-                                     h_scratch, F, st);
+                                     h_scratch, F, st, gather.on ? gather.perm : nullptr, gather.k);
             if (rc != MOE_OK) return rc;
         }
         if (phases & 2) {
@@ -267,6 +267,21 @@ extern "C" int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int 
                                            const int32_t* perm, const float* gate_w, float* y_out, void* stream) {
     MOE_REQUIRE(phase == 1 || phase == 2, MOE_ERR_ARG, "moe_grouped_ffn_fused_phase: phase %d", phase);
     return fused_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, gate_w, y_out, stream);
+}
+
+extern "C" int moe_grouped_ffn_gather(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                      const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                                      int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, void* stream) {
+    MOE_REQUIRE(dt == MOE_F32, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_gather: MOE_F32 only (dtype %d)", (int)dt);
+    MOE_REQUIRE(T >= 0 && k >= 1, MOE_ERR_ARG, "moe_grouped_ffn_gather: T=%d k=%d", T, k);
+    MOE_REQUIRE((long long)T * k < (1ll << 30), MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_gather: T*k too large");
+    MOE_REQUIRE(T == 0 || perm, MOE_ERR_ARG, "moe_grouped_ffn_gather: null pointer");
+    Gather g;
+    g.perm = perm;
+    g.x_rows = T;
+    g.k = k;
+    g.on = true;
+    return grouped_ffn_impl(3, x, T * k, d, F, E, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, y_perm, stream, Top1(), g);
 }
 
 // moe_grouped_ffn_fused and the shared expert's moe_grouped_ffn.  Where the few-row kernels serve both, each

@@ -15,10 +15,11 @@
 // (their sums meet in LDS), so that its items are half as large and still busy every SIMD.
 //
 // Bound by the matrix cores, and then by how evenly the items fall on the CUs: an item is a
-// work-group of its own, which the hardware starts where one has finished, and the XCDs get equal
-// contiguous runs of the plan's tiles (with the plan's bins, equal in rows but not in tiles, 28 %
-// of the CU time was idle).  3002 rows, d=768 F=2048 E=16 SwiGLU: 496 + 292 us with vector fma
-// tiles of 64 x 64, 245 + 134 here; 8192 rows in full tiles, d=1024 F=4096: 57 -> 121 TFLOP/s.
+// work-group of its own, which the hardware starts where one has finished; the plan's bins, equal in
+// rows but not in tiles, play no role (28 % of the CU time was idle with them; equal runs of tiles per XCD,
+// which differ in ragged tiles: 236 us for the first product below, every tile shared by all XCDs 220).
+// 3002 rows, d=768 F=2048 E=16 SwiGLU: 496 + 292 us with vector fma tiles of 64 x 64, 220 + 118 here; 12288
+// rows in full tiles, d=1024 F=4096: 128 TFLOP/s.
 //
 // LDS: a row holds 32 terms in eight 16-byte pieces, piece p at position p ^ ((row / 2) & 7): 16
 // consecutive rows' pieces touch every bank once.  Lane (l32, lhi) reads piece 2 q + lhi and feeds its
@@ -42,7 +43,8 @@ template <int EPI, int NWN, int KSP>
 __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float* __restrict__ a_mat, int K, int N,
                                                            const void* const* __restrict__ w_ptrs,
                                                            const moe_tile* __restrict__ tiles,
-                                                           const int32_t* __restrict__ hdr, float* __restrict__ out, int ld_out) {
+                                                           const int32_t* __restrict__ hdr, float* __restrict__ out, int ld_out,
+                                                           const int32_t* __restrict__ row_src, int src_div) {
     constexpr int NTH = NWN * KSP * 64, BN = 32 * NWN;
     constexpr int AL = BM * PIECES / NTH, BL = BN * PIECES / NTH;       // 16-byte pieces per thread and stage
     __shared__ f32x4 lds[2][(BM + BN) * PIECES];
@@ -56,16 +58,12 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
     const int rd_swz = (l32 >> 1) & 7;
     const int n_cb = (N + BN - 1) / BN, KT = (K + BK - 1) / BK;
 
-    // All items -- groups of eight tiles, in a group column block after column block, so that the
-    // work-groups of an XCD share both operands through its L2 -- cut into 8 equal runs: one per XCD
-    // (work-groups are dealt to the XCDs in turn).
-    const int n_tiles = hdr[0], n_items = n_tiles * n_cb, per_xcd = (n_items + 7) / 8;
-    for (int l = blockIdx.x / 8; l < per_xcd; l += gridDim.x / 8) {
-        const int item = (blockIdx.x % 8) * per_xcd + l;
-        if (item >= n_items) break;
-        const int grp = item / (8 * n_cb), in_grp = item - grp * 8 * n_cb;
-        const int size = n_tiles - grp * 8 < 8 ? n_tiles - grp * 8 : 8;
-        const int cb = in_grp / size, ti = grp * 8 + in_grp - cb * size;
+    // Items in the order of the plan's tiles, a tile's column blocks one after the other: the XCDs, to which
+    // work-groups are dealt in turn, share every tile's column blocks evenly, and each keeps the slices of
+    // an expert's weights that fall to it in its L2 from one of the expert's tiles to the next.
+    const int n_items = hdr[0] * n_cb;
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int ti = item / n_cb, cb = item - ti * n_cb;
         const moe_tile t = tiles[ti];
         const int rc = __builtin_amdgcn_readfirstlane(t.row_count < BM ? t.row_count : BM);
         if (rc <= 0) continue;
@@ -76,7 +74,9 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
 #pragma unroll
         for (int i = 0; i < AL; ++i) {
             const int r = ld_row + i * ROWS;
-            a_src[i] = a_mat + (size_t)(t.row_begin + (r < rc ? r : rc - 1)) * K;
+            int row = t.row_begin + (r < rc ? r : rc - 1);
+            if (row_src) row = (int)((unsigned)row_src[row] / (unsigned)src_div);     // (the rows of x brought into expert order here)
+            a_src[i] = a_mat + (size_t)row * K;
         }
 #pragma unroll
         for (int i = 0; i < BL; ++i) {
@@ -179,15 +179,26 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
     }
 }
 
+struct Args {
+    const void* a;
+    int A, K, N, E;
+    const void* const* w;
+    const moe_tile* tiles;
+    const int32_t* hdr;
+    void* out;
+    int ld_out;
+    const int32_t* row_src;
+    int src_div;
+};
+
 template <int EPI, int NWN, int KSP>
-int launch(const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
-           int ld_out, hipStream_t st) {
+int launch(const Args& g, hipStream_t st) {
     // one work-group per item of the tiles there usually are (the device alone knows; they loop if there are more)
-    const long long tiles_est = A < E + A / BM ? A : E + A / BM;
-    const long long items = tiles_est * ((N + 32 * NWN - 1) / (32 * NWN));
+    const long long tiles_est = g.A < g.E + g.A / BM ? g.A : g.E + g.A / BM;
+    const long long items = tiles_est * ((g.N + 32 * NWN - 1) / (32 * NWN));
     const unsigned grid = (unsigned)(items < (1 << 20) ? (items + 7) / 8 * 8 : 1 << 20);
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, NWN, KSP>), dim3(grid), dim3(NWN * KSP * 64), 0, st, (const float*)a, K, N, w, tiles, hdr,
-                       (float*)out, ld_out);
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, NWN, KSP>), dim3(grid), dim3(NWN * KSP * 64), 0, st, (const float*)g.a, g.K, g.N, g.w, g.tiles,
+                       g.hdr, (float*)g.out, g.ld_out, g.row_src, g.src_div);
     MOE_CHECK_LAUNCH("moe_grouped_ffn (fp32 GEMM)");
     return MOE_OK;
 }
@@ -195,17 +206,13 @@ int launch(const void* a, int A, int K, int N, int E, const void* const* w, cons
 }  // namespace
 
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
-                        const int32_t* hdr, void* out, int ld_out, hipStream_t st) {
+                        const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
     // Column blocks of 128 weight rows read the activations half as often; of 64 where 128 would
     // leave fewer than four items per CU.
+    const Args g = {a, A, K, N, E, w, tiles, hdr, out, ld_out, row_src, src_div};
     const long long tiles_est = (A + BM - 1) / BM + E / 2;
     const bool narrow = tiles_est * ((N + 127) / 128) < 4 * 256;
-    if (epi == MOE_EPI_SWIGLU)
-        return narrow ? launch<MOE_EPI_SWIGLU, 2, 2>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st)
-                      : launch<MOE_EPI_SWIGLU, 4, 1>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st);
-    if (epi == MOE_EPI_RELU)
-        return narrow ? launch<MOE_EPI_RELU, 2, 2>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st)
-                      : launch<MOE_EPI_RELU, 4, 1>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st);
-    return narrow ? launch<MOE_EPI_STORE, 2, 2>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st)
-                  : launch<MOE_EPI_STORE, 4, 1>(a, A, K, N, E, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_SWIGLU) return narrow ? launch<MOE_EPI_SWIGLU, 2, 2>(g, st) : launch<MOE_EPI_SWIGLU, 4, 1>(g, st);
+    if (epi == MOE_EPI_RELU) return narrow ? launch<MOE_EPI_RELU, 2, 2>(g, st) : launch<MOE_EPI_RELU, 4, 1>(g, st);
+    return narrow ? launch<MOE_EPI_STORE, 2, 2>(g, st) : launch<MOE_EPI_STORE, 4, 1>(g, st);
 }

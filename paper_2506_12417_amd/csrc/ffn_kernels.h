@@ -69,9 +69,10 @@ int moe_launch_gemm_rows_shared(int phase, const void* x, int T, int d, int F, i
                                 const void* const* s_w, const moe_tile* s_tiles, const int32_t* s_hdr, void* s_h, float* s_y,
                                 hipStream_t st);
 
-// The fp32 products (ffn_f32.hip; tiles of at most 64 rows, RELU / SWIGLU / STORE, all of fp32).
+// The fp32 products (ffn_f32.hip; tiles of at most 64 rows, RELU / SWIGLU / STORE, all of fp32).  row_src: row r
+// of the table's row space is row row_src[r] / src_div of a.
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
-                        const int32_t* hdr, void* out, int ld_out, hipStream_t st);
+                        const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src = nullptr, int src_div = 1);
 
 // MOE_OK if the current device is the GPU the persistent launches are laid out for (256 compute
 // units in 8 XCDs), else MOE_ERR_UNSUPPORTED.

@@ -111,6 +111,8 @@ class MoELayer:
         # the row gather inside the first product (moe_grouped_ffn_fused): where the library offers it
         can_fuse = (self.dt == B.MOE_BF16 and tall_ok and d >= 256 and d % 64 == 0 and F % 64 == 0
                     and T * d * 2 < 2 ** 32 and (k > 1 or self.fold_combine))
+        # in fp32 the first product can gather as well (moe_grouped_ffn_gather; where forward() records no stages)
+        can_fuse = can_fuse or (self.dt == B.MOE_F32 and T >= 1)
         self.fuse_gather = can_fuse if fuse_gather is None else (fuse_gather and can_fuse)
         if shared_F:
             # the always-on shared expert is one more group: E = 1, every token, rows in place
@@ -209,7 +211,7 @@ class MoELayer:
             return self._forward_staged(x, stages, routed)
         if not routed:
             self.route(x, None, stream)
-        if self.fuse_gather:
+        if self.fuse_gather and self.dt == B.MOE_BF16:
             # the first product gathers its rows from x itself (no x_perm); for top-1 the second one
             # also writes y directly
             self.permute_plan(stream)
@@ -235,6 +237,15 @@ class MoELayer:
                 marks[2].record()
             if self.k == 1:
                 return self.y
+            if self.shared_F:
+                self.shared_ffn(x, stream)
+            self.combine(True, stream)
+            return self.y
+        if self.fuse_gather and self.dt == B.MOE_F32 and marks is None:
+            self.permute_plan(stream)
+            g = self.experts
+            B.moe_grouped_ffn_gather(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
+                                     self.tiles, self.plan_hdr, self.tile_m, self.h, self.perm, self.y_perm, stream)
             if self.shared_F:
                 self.shared_ffn(x, stream)
             self.combine(True, stream)
@@ -281,7 +292,8 @@ class MoELayer:
         if not routed:
             self.route(x, None, None)
             mark("route")
-        if self.fuse_gather:
+        fused = self.fuse_gather and self.dt == B.MOE_BF16
+        if fused:
             self.permute_plan(None)
             mark("permute_plan")
         else:
@@ -289,7 +301,7 @@ class MoELayer:
             mark("permute")
             self.plan(None)
             mark("plan")
-        if self.fuse_gather:
+        if fused:
             args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
                     self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm, None)
             B.moe_grouped_ffn_fused_phase(1, *args)

@@ -198,6 +198,11 @@ def test_pack_combine_copy_argument_errors():
     assert fused(T=0, perm=None, y=None) == B.MOE_OK
     assert status(B.moe_grouped_ffn_fused_phase, 0, FAKE, 8, 256, 512, 2, 1, B.MOE_RELU, B.MOE_BF16, FAKE, FAKE, FAKE, FAKE,
                   128, FAKE, FAKE, None, FAKE, 0) == B.MOE_ERR_ARG
+    gather = lambda dt=B.MOE_F32, T=8, d=64, k=2, tile_m=64, perm=FAKE, y=FAKE: status(
+        B.moe_grouped_ffn_gather, FAKE, T, d, 512, 2, k, B.MOE_SWIGLU, dt, FAKE, FAKE, FAKE, FAKE, tile_m, FAKE, perm, y, 0)
+    assert gather(dt=B.MOE_BF16) == B.MOE_ERR_UNSUPPORTED and gather(tile_m=128) == B.MOE_ERR_UNSUPPORTED
+    assert gather(d=30) == B.MOE_ERR_UNSUPPORTED and gather(k=0) == B.MOE_ERR_ARG and gather(T=2 ** 30) == B.MOE_ERR_UNSUPPORTED
+    assert gather(perm=None) == B.MOE_ERR_ARG and gather(y=None) == B.MOE_ERR_ARG and gather(T=0, perm=None) == B.MOE_OK
     shared = lambda dt=B.MOE_BF16, T=8, d=256, k=2, tile_m=128, s_tile_m=128, sF=512, y=FAKE, sy=FAKE, sh=FAKE: status(
         B.moe_grouped_ffn_shared, FAKE, T, d, 512, 2, k, B.MOE_SWIGLU, dt, FAKE, FAKE, FAKE, FAKE, tile_m, FAKE, FAKE, y, sF,
         FAKE, FAKE, FAKE, FAKE, s_tile_m, sh, sy, 0)
