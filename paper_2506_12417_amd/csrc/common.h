@@ -68,6 +68,17 @@ __device__ __forceinline__ unsigned moe_wave_sum_u32(unsigned v) {
     return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
            __builtin_amdgcn_readlane(v, 48);
 }
+// Inclusive sum over the lanes (all 64 active): inside each row of 16 lanes by shifts, then the row totals
+// are passed on to the rows behind (row 1 and 3 take lane 15's and 47's, the upper half lane 31's).
+__device__ __forceinline__ unsigned moe_wave_scan_u32(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);    // row_shr:1
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);    // row_shr:2
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);    // row_shr:4
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);    // row_shr:8
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
 // max of non-negative floats (their bit patterns order like unsigned integers)
 __device__ __forceinline__ float moe_wave_max_nonneg(float v) {
     return __uint_as_float(moe_wave_max_u32(__float_as_uint(v)));

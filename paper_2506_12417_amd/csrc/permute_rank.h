@@ -29,6 +29,8 @@ __device__ __forceinline__ void count_experts(const int32_t* __restrict__ idx, i
         int4 v[NV];
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
+            v[j] = make_int4(-1, -1, -1, -1);
+            if (i0 + j * NTH * 4 >= A) continue;           // (uniform: a small call has few of the sixteen)
             const int i = i0 + (j * NTH + (int)threadIdx.x) * 4;
             if (i + 3 < A) {
                 __builtin_memcpy(&v[j], idx + i, sizeof v[j]);
@@ -41,6 +43,7 @@ __device__ __forceinline__ void count_experts(const int32_t* __restrict__ idx, i
         }
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
+            if (i0 + j * NTH * 4 >= A) continue;
             const int i = i0 + (j * NTH + (int)threadIdx.x) * 4;
             const int e4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
 #pragma unroll
@@ -53,6 +56,19 @@ __device__ __forceinline__ void count_experts(const int32_t* __restrict__ idx, i
     }
 }
 
+// Inclusive sum over the NTH threads of a work-group; tot: NTH / 64 words of LDS.  One barrier (a scan through
+// LDS, a barrier and a latency per doubling, took 1 us of a small plan's 10).
+__device__ __forceinline__ int block_scan(int v, int* tot) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    v = (int)moe_wave_scan_u32((unsigned)v);
+    if (lane == 63) tot[wave] = v;
+    __syncthreads();
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < NTH / 64; ++w) before += w < wave ? tot[w] : 0;
+    return v + before;
+}
+
 template <int MODE>
 __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A, int E, int nbits, int nb,
                                           const int32_t* __restrict__ block_hist,
@@ -60,7 +76,7 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
                                           int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
     extern __shared__ int chunk_hist[];   // [CHUNKS][E]
     __shared__ int start_of[MOE_MAX_EXPERTS];      // first position of this work-group's assignments of expert e
-    __shared__ int scan_buf[2][MOE_MAX_EXPERTS];
+    __shared__ int scan_buf[2][MOE_MAX_EXPERTS], scan_tot[NTH / 64];
     for (int i = threadIdx.x; i < CHUNKS * E; i += NTH) chunk_hist[i] = 0;
     // this thread's assignments: fetched first, all at once, so that their latency passes under the scan
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -89,7 +105,6 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
             __syncthreads();
             before = scan_buf[0][e];
             total = scan_buf[1][e];
-            __syncthreads();
         } else if (e < E)
             for (int b0 = 0; b0 < nb; b0 += 8) {           // eight loads in flight at a time
                 int v[8];
@@ -101,17 +116,7 @@ __device__ __forceinline__ void rank_body(const int32_t* __restrict__ idx, int A
                     total += v[j];
                 }
             }
-        // inclusive scan of the totals over the experts (Hillis-Steele, MOE_MAX_EXPERTS entries)
-        scan_buf[0][e] = e < E ? total : 0;
-        __syncthreads();
-        int cur = 0;
-        for (int step = 1; step < MOE_MAX_EXPERTS; step <<= 1) {
-            const int v = scan_buf[cur][e] + (e >= step ? scan_buf[cur][e - step] : 0);
-            scan_buf[cur ^ 1][e] = v;
-            cur ^= 1;
-            __syncthreads();
-        }
-        const int incl = scan_buf[cur][e];
+        const int incl = block_scan(e < E ? total : 0, scan_tot);      // inclusive, over the experts
         if (e < E) {
             start_of[e] = incl - total + before;
             if (blockIdx.x == 0) {
