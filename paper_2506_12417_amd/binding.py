@@ -97,8 +97,15 @@ def _p(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        # (the current stream's handle without a torch object for it: the search for one and the count
+        # of devices took half of a call's time on the host)
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream
