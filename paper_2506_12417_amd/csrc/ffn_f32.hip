@@ -11,8 +11,8 @@
 // the tile, so that a ragged tile leaves all wavefronts the same work (an empty block is
 // skipped), and one block of 32 weight rows; with SwiGLU a gate block and its up block lie on
 // neighbouring wavefronts, which meet in LDS at the end.  Four wavefronts: one per SIMD.  The narrow
-// form holds two blocks of weight rows and gives each wavefront half of every stage's terms
-// (their sums meet in LDS), so that its items are half as large and still busy every SIMD.
+// forms hold two blocks of weight rows, or one, and give each wavefront half (a quarter) of every stage's
+// terms (their sums meet in LDS), so that their items are smaller and still busy every SIMD.
 //
 // Bound by the matrix cores, and then by how evenly the items fall on the CUs: an item is a
 // work-group of its own, which the hardware starts where one has finished; the plan's bins, equal in
@@ -129,6 +129,8 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
                             acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[j], b[j], acc[1], 0, 0, 0);
                     }
                 }
+                // (the compiler asks for the next stage near the end of this one; pinning the loads or all fragment reads
+                // to its start was slower, 128 -> 107 - 120 TFLOP/s on full tiles, three work-groups on a CU covering the latency)
                 // (nothing of the store may move up: it would wait for loads that have this whole step to arrive)
                 __builtin_amdgcn_sched_barrier(0);
                 store(kt + 1);
@@ -138,16 +140,19 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
         else multiply(std::false_type{});
         // acc[m][r]: row 32 m + 8 (r / 4) + 4 lhi + r % 4, weight row l32 of the wavefront's block
         float* meet = (float*)&lds[0][0] + wn * (32 * 64);              // (the stages have been read)
+        static_assert((KSP - 1) * NWN * 32 * 64 * 4 <= (int)sizeof lds, "the parts meet in the stages' memory");
         if constexpr (KSP > 1) {
             __syncthreads();
             if (wk) {
 #pragma unroll
-                for (int r = 0; r < 32; ++r) meet[r * 64 + lane] = acc[r >> 4][r & 15];
+                for (int r = 0; r < 32; ++r) meet[(wk - 1) * (NWN * 32 * 64) + r * 64 + lane] = acc[r >> 4][r & 15];
             }
             __syncthreads();
             if (!wk) {
 #pragma unroll
-                for (int r = 0; r < 32; ++r) acc[r >> 4][r & 15] += meet[r * 64 + lane];
+                for (int p = 0; p < KSP - 1; ++p)
+#pragma unroll
+                    for (int r = 0; r < 32; ++r) acc[r >> 4][r & 15] += meet[p * (NWN * 32 * 64) + r * 64 + lane];
             }
         }
         if constexpr (EPI == MOE_EPI_SWIGLU) {
@@ -208,11 +213,15 @@ int launch(const Args& g, hipStream_t st) {
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                         const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
     // Column blocks of 128 weight rows read the activations half as often; of 64 where 128 would
-    // leave fewer than four items per CU.
+    // leave fewer than four items per CU; of 32, all four wavefronts on a stage's terms, where 64 would leave
+    // fewer than two (without SwiGLU, which needs a gate and an up block): 256 rows, second product of K = 512,
+    // N = 256 14.6 -> 10.9 us, first of K = 256, N = 512 9.3 -> 7.8; 1024 rows, K = 1024, N = 512 32.6 -> 26.1;
+    // with two to four items per CU it makes no difference (3002 rows, K = 2048, N = 768: 119 and 120).
     const Args g = {a, A, K, N, E, w, tiles, hdr, out, ld_out, row_src, src_div};
     const long long tiles_est = (A + BM - 1) / BM + E / 2;
-    const bool narrow = tiles_est * ((N + 127) / 128) < 4 * 256;
+    const bool narrow = tiles_est * ((N + 127) / 128) < 4 * 256, narrowest = tiles_est * ((N + 63) / 64) < 2 * 256;
     if (epi == MOE_EPI_SWIGLU) return narrow ? launch<MOE_EPI_SWIGLU, 2, 2>(g, st) : launch<MOE_EPI_SWIGLU, 4, 1>(g, st);
+    if (narrowest) return epi == MOE_EPI_RELU ? launch<MOE_EPI_RELU, 1, 4>(g, st) : launch<MOE_EPI_STORE, 1, 4>(g, st);
     if (epi == MOE_EPI_RELU) return narrow ? launch<MOE_EPI_RELU, 2, 2>(g, st) : launch<MOE_EPI_RELU, 4, 1>(g, st);
     return narrow ? launch<MOE_EPI_STORE, 2, 2>(g, st) : launch<MOE_EPI_STORE, 4, 1>(g, st);
 }

@@ -1457,6 +1457,20 @@ def test_ffn_top1_is_ffn_then_combine(torch_gpu, T, d, F, E, gate, skew, tile_m)
     assert int(L.plan_hdr[B.MOE_PLAN_HDR_CTR:].abs().sum()) == 0      # the work counters are back at zero
 
 
+# (column blocks of 32, 64 and 128 weight rows; contractions shorter than a stage, not a multiple of it, of several;
+# ragged column blocks, tiles of one row to two row blocks)
+# (d a multiple of 8: the router takes no other)
+@pytest.mark.parametrize("T,d,F,E,k,act", [(5, 8, 12, 3, 1, "relu"), (70, 24, 36, 2, 2, "relu"), (200, 104, 64, 5, 2, "relu"),
+                                           (65, 136, 160, 4, 1, "swiglu"), (900, 72, 100, 3, 2, "relu"), (2000, 264, 1024, 6, 2, "relu"),
+                                           (3000, 136, 1056, 4, 2, "swiglu")])
+def test_fp32_products_at_every_column_block(torch_gpu, T, d, F, E, k, act):
+    """The fp32 layer (rows gathered by the first product: bit for bit the separate calls) against the
+    oracle in 64 bits, with the bound of fp32 sums."""
+    wl = W.WORKLOADS["c1"].scaled(T=T, d=d, F=F, E=E, k=k, act=act)
+    _note("fp32 T=%d d=%d F=%d E=%d k=%d %s" % (T, d, F, E, k, act))
+    _stage_check(torch_gpu, wl, W.make_inputs(wl))
+
+
 # (contractions whose parts by four wavefronts end in the middle of a round or leave a wavefront without terms; one
 # row to four row groups of the shared expert, and one row too many for it; no few rows per expert; ReLU: no shared launch)
 @pytest.mark.parametrize("T,d,F,E,k,sF,act", [(1, 256, 64, 60, 4, 64, "swiglu"), (3, 2048, 192, 8, 2, 320, "swiglu"),
