@@ -67,6 +67,19 @@ static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
     return tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 
+// Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels.  An item of
+// 256 rows takes them 7/4 to 2 times what one of 128 rows takes the eight-wavefront kernels (the less the longer
+// the contraction); what decides are the rounds of items that the CUs need, and the contraction has to be long
+// enough for a work-group's longer way in and out.  Measured (one product, eight-wavefront kernels -> this;
+// rounds before, after): K=3520 (1.7, 0.9) 146 -> 105 us, K=1664 (1.5, 0.8) 66 -> 50, K=14336 (1.1, 0.7) 423 -> 360 and (3.6,
+// 1.9) 828 -> 737, K=4096 (25.4, 13.6) 1516 -> 1364; where the rule says no: K=14336 (2.3, 1.3) 614 -> 675, K=2048 (12.3, 6.8) 418 ->
+// 401 but 1 % more over the layer's pass, K=1408 (8.9, 4.9) 246 -> 246, K=640 (1.5, 0.9) 31 -> 42, K=704 (6.4, 3.5) 96 -> 114.
+static bool wide_pairs(int A, int E, int K, int N) {
+    const long long cb = (N + 255) / 256, grid = MOE_GEMM_GRID;
+    const long long before = (((long long)A / 128 + E / 2) * cb + grid - 1) / grid, after = (((long long)A / 256 + E / 2) * cb + grid - 1) / grid;
+    return (K >= 1408 && 2 * after <= before) || (K >= 4096 && 7 * after <= 4 * before);
+}
+
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
 // Measured with and without the hint (both products): 128 experts of 768 x 3072, Zipf 1.0: 8 rows
 // each 213 : 228 us, 16 rows 257 : 267, 32 rows 284 : 278; 60 of 2048 x 1408, Zipf 1.2: 13 rows 203 :
@@ -110,10 +123,14 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         const bool streaming = tile_m == 128 && g_kernel_mode == 2;
         auto stream = [&](int epi, int K) { return streaming && moe_gemm_stream_supports(epi, K); };
         auto stream_narrow = [&](int N) { return tiles_est * ((N + 255) / 256) < 4 * MOE_GEMM_GRID; };
-        // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
-        // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1).
-        auto wide = [&](int epi, int K) { return tile_m == 256 && g_kernel_mode != 1 && moe_gemm_wide_supports(epi, K); };
         const bool rows = few_rows_call(A, d, F, E, tile_m);
+        // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
+        // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1), 128-row
+        // tiles where taking them in pairs pays.
+        auto wide = [&](int epi, int K, int N) {
+            if (g_kernel_mode == 1 || !moe_gemm_wide_supports(epi, K)) return false;
+            return tile_m == 256 || (g_kernel_mode == 0 && !rows && wide_pairs(A, E, K, N));
+        };
         // (the eight XCDs' L2s hold 32 MB)
         auto cache = [&](long long weights, size_t out_bytes) {
             return moe_weights_once(A, E, weights * E * 2) ? MOE_CACHE_WEIGHTS_ONCE
@@ -131,8 +148,8 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
             else if (gather.on && stream(epi, d))
                 rc = moe_launch_gemm_stream_gather(stream_narrow(n1), x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr,
                                                    h_scratch, F, st, gather.perm, gather.k);
-            else if (gather.on && tile_m == 256)
-                // (fused_impl has checked that the four-wavefront kernels are in use and cover d)
+            else if (gather.on && wide(epi, d, n1))
+                // (with 256-row tiles fused_impl has checked that these kernels are in use and cover d)
                 rc = moe_launch_gemm_wide_gather(epi, x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
                                                  gather.perm, gather.k);
             else if (gather.on)
@@ -140,7 +157,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                                                  w_in, tiles, plan_hdr, h_scratch, F, st, gather.perm, gather.k);
             else if (stream(epi, d))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(n1), x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
-            else if (wide(epi, d))
+            else if (wide(epi, d, n1))
                 rc = moe_launch_gemm_wide(epi, x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else
                 rc = moe_launch_gemm_bf16(epi, tile_m, narrow(n1), cache_h, x_perm, d, n1,
@@ -155,7 +172,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
             else if (stream(epi, F))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(d), h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st,
                                             top1.perm, top1.gate_w, top1.on ? A : 0);
-            else if (wide(epi, F))
+            else if (wide(epi, F, d))
                 rc = moe_launch_gemm_wide(epi, h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
                                           top1.gate_w, top1.on ? A : 0);
             else if (top1.on)

@@ -39,7 +39,8 @@ int moe_launch_gemm_stream_gather(int narrow, const void* x, int x_rows, int K, 
                                   const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                   const int32_t* row_src, int src_div);
 
-// The same products for 256-row tiles by the kernels of ffn_wide.hip (four wavefronts of 128 x 128
+// The same products for 256-row tiles, or pairs of neighbouring 128-row tiles of an expert, by the kernels of
+// ffn_wide.hip (four wavefronts of 128 x 128
 // per work-group instead of eight of 128 x 64: less LDS traffic per multiply-add, which is what the
 // power-bound case pays for).  Same results, bit for bit; all four epilogues, and the first
 // product with the row gather folded in (arguments as for the launchers above).

@@ -62,7 +62,7 @@ struct WCfg {
     static constexpr int RING_BYTES = RING * STAGE_BYTES;
     static constexpr int MAX_BLK_TILES = 3068;            // tiles of a bin the block table can hold
     static constexpr int ROWINFO_BYTES = 2 * 2 * BM * 4;  // (token, gate) of a tile's rows, for two items
-    static constexpr size_t SMEM = (size_t)RING_BYTES + (size_t)MAX_BLK_TILES * 4 + 16 + ROWINFO_BYTES;
+    static constexpr size_t SMEM = (size_t)RING_BYTES + (size_t)MAX_BLK_TILES * 4 + 16 + ROWINFO_BYTES + (size_t)MAX_BLK_TILES * 2 + 8;
     static_assert(ROWS_PER_PASS % (WRAP * PPR) == 0 && 16 % (WRAP * PPR) == 0, "swizzle period");
     static_assert(RING == 2 && 2 * LPS <= 63, "vmcnt range");
     static_assert(SMEM <= 160 * 1024, "LDS ring too large");
@@ -80,6 +80,7 @@ struct Geo {
     const void* const* w_ptrs;
     const moe_tile* tiles;
     const uint32_t* blk;       // LDS: first tile and tile count of the block each tile of the bin belongs to
+    const uint16_t* first_of;  // LDS: a tile's first entry in the bin's table, 0x8000 if the next one belongs to it
     int K, N, KT, n_col_blocks, bin_start, n_tiles, n_items, stride;
     bool by_block;
     // gather (first product): row r of the table's row space is row row_token[r] / a_div of a_mat,
@@ -107,6 +108,15 @@ __device__ __forceinline__ void locate(const Geo& g, int it, int& tile_idx, int&
     }
 }
 
+// Tile ti of this launch: an entry of the table, or two neighbouring ones (Geo::first_of).
+__device__ __forceinline__ moe_tile tile_at(const Geo& g, int ti) {
+    if (!g.by_block) return g.tiles[g.bin_start + ti];
+    const int u = sgpr((int)g.first_of[ti]);
+    moe_tile t = g.tiles[g.bin_start + (u & 0x7fff)];
+    if (u & 0x8000) t.row_count += g.tiles[g.bin_start + (u & 0x7fff) + 1].row_count;
+    return t;
+}
+
 // The loader's place in the stream of stages.
 struct Loader {
     __amdgpu_buffer_rsrc_t ra, rb;   // the item's rows and its block of weight rows (exactly: the range check does the clipping)
@@ -122,7 +132,7 @@ struct Loader {
 __device__ __forceinline__ void fetch_rows(const Geo& g, int par, int it, int wave, int lane) {
     int cb, ti;
     locate(g, it, ti, cb);
-    const moe_tile t = g.tiles[g.bin_start + ti];
+    const moe_tile t = tile_at(g, ti);
     const int rc = t.row_count < C::BM ? t.row_count : C::BM;
     const __amdgpu_buffer_rsrc_t rt = make_rsrc(g.row_token + t.row_begin, (unsigned)(rc > 0 ? rc : 0) * 4u);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_void_t*)(g.rinfo + par * 2 * C::BM + wave * 64), 4,
@@ -133,7 +143,7 @@ template <bool GATHER>
 __device__ __forceinline__ void load_item(const Geo& g, Loader& L, int it, int wave, int lane, int ld_row, unsigned ld_piece) {
     int cb, ti;
     locate(g, it, ti, cb);
-    const moe_tile t = g.tiles[g.bin_start + ti];
+    const moe_tile t = tile_at(g, ti);
     const int rc = t.row_count < C::BM ? t.row_count : C::BM;
     const int n0 = cb * C::BN;
     const int nr = g.N - n0 < C::BN ? g.N - n0 : C::BN;
@@ -440,7 +450,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.row_gate = row_gate;
     g.out_rows = out_rows;
     g.a_div = a_div;
-    g.rinfo = (int*)(ring + C::SMEM - C::ROWINFO_BYTES);
+    g.rinfo = (int*)(ring + C::RING_BYTES + C::MAX_BLK_TILES * 4 + 16);
     g.K = K;
     g.N = N;
     g.KT = K / C::BK;                                        // (K is a multiple of 64)
@@ -450,27 +460,58 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.stride = ws.stride;
     g.bin_start = ws.bin_start;
     g.n_tiles = ws.n_tiles;
-    g.n_items = g.n_tiles * g.n_col_blocks;
-    if (first >= g.n_items) return;
-
+    // Tables of 128-row tiles: two neighbouring tiles of one expert are one tile here.  first_of[p]: see Geo;
     // blk[p] = first tile and tile count of the block (one expert's tiles on this bin, at most 256)
     // that tile p belongs to
     uint32_t* blk = (uint32_t*)(ring + C::RING_BYTES);
+    uint16_t* first_of = (uint16_t*)(ring + C::RING_BYTES + C::MAX_BLK_TILES * 4 + 16 + C::ROWINFO_BYTES);
     g.blk = blk;
+    g.first_of = first_of;
     g.by_block = g.n_tiles <= C::MAX_BLK_TILES;
     if (g.by_block) {
-        int* ex = (int*)ring;                              // the ring is still empty: expert of every tile
-        for (int p = tid; p < g.n_tiles; p += C::NTH) ex[p] = tiles[g.bin_start + p].expert;
+        // (the ring is still empty: expert of every entry, whether the one before ends where it begins, tiles so far)
+        int* ex = (int*)ring;
+        unsigned char* joins = ring + C::MAX_BLK_TILES * 4;
+        int* count = (int*)(ring + C::MAX_BLK_TILES * 8);
+        const int n = g.n_tiles;
+        for (int p = tid; p < n; p += C::NTH) {
+            const moe_tile t = tiles[g.bin_start + p];
+            ex[p] = t.expert;
+            bool j = false;
+            if (p > 0) {
+                const moe_tile u = tiles[g.bin_start + p - 1];
+                j = u.expert == t.expert && u.row_begin + u.row_count == t.row_begin && u.row_count == C::BM / 2 && t.row_count <= C::BM / 2;
+            }
+            joins[p] = j ? 1 : 0;
+        }
         __syncthreads();
+        if (wave == 0) {                                   // entries at odd places of a joined run go with the one before
+            int at = 0;
+            for (int p0 = 0; p0 < n; p0 += 64) {
+                const int p = p0 + lane;
+                int f = p;                                 // (runs are counted from every 64th entry: an even number)
+                while (p < n && f > p0 && joins[f]) --f;
+                const bool leads = p < n && ((p - f) & 1) == 0;
+                const bool pair = leads && p + 1 < n && lane < 63 && joins[p + 1];
+                const unsigned long long m = __ballot(leads);
+                if (leads) first_of[at + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(p | (pair ? 0x8000 : 0));
+                at += __popcll(m);
+            }
+            if (lane == 0) *count = at;
+        }
+        __syncthreads();
+        g.n_tiles = sgpr(*count);
         for (int p = tid; p < g.n_tiles; p += C::NTH) {
-            const int e = ex[p];
+            const int e = ex[first_of[p] & 0x7fff];
             int f = p, l = p;
-            while (f > 0 && (f & 255) != 0 && ex[f - 1] == e) --f;
-            while (l + 1 < g.n_tiles && ((l + 1) & 255) != 0 && ex[l + 1] == e) ++l;
+            while (f > 0 && (f & 255) != 0 && ex[first_of[f - 1] & 0x7fff] == e) --f;
+            while (l + 1 < g.n_tiles && ((l + 1) & 255) != 0 && ex[first_of[l + 1] & 0x7fff] == e) ++l;
             blk[p] = (uint32_t)f | ((uint32_t)(l - f + 1) << 16);
         }
     }
     __syncthreads();
+    g.n_items = g.n_tiles * g.n_col_blocks;
+    if (first >= g.n_items) return;
 
     Lane ln;
     ln.wave = wave;
@@ -520,7 +561,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     for (int item = first; item < g.n_items; item += g.stride, ++c_seq) {
         int cb, ti;
         locate(g, item, ti, cb);
-        const moe_tile tile = tiles[g.bin_start + ti];
+        const moe_tile tile = tile_at(g, ti);
         const int rc = sgpr(tile.row_count < C::BM ? tile.row_count : C::BM);
         const int col0 = cb * C::BN + wn * 128;
         // 32-row blocks of this wavefront that hold real rows (wave-uniform)

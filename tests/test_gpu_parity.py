@@ -1066,6 +1066,44 @@ def test_four_wavefront_kernels_give_the_bits_of_the_lds_ring_kernels(torch_gpu,
     assert max_err_over_rms(to_numpy(out[0][0]), y_o) <= TOL["bf16"]
 
 
+# (pairs, single tiles and ragged ends of 128-row tables on eight, three and one bins; the second product with and without the
+# combine folded in, the first with its gather)
+@pytest.mark.parametrize("T,d,F,E,k,act,skew,bins", [(4096, 2048, 1408, 4, 1, "relu", "zipf", 8), (2400, 1408, 2816, 3, 2, "swiglu", "hot", 8),
+                                                     (4000, 1536, 1472, 4, 2, "swiglu", "zipf", 3), (4096, 2048, 1408, 4, 1, "relu", "uniform", 1)])
+def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F, E, k, act, skew, bins):
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    wl = W.WORKLOADS["c4"].scaled(T=T, d=d, F=F, E=E, k=k, act=act, skew=skew)
+    _note("pairs T=%d d=%d F=%d E=%d k=%d %s %s bins=%d" % (T, d, F, E, k, act, skew, bins))
+    inp = W.make_inputs(wl)
+    before = B.moe_ffn_kernel_mode(-1)
+    out = {}
+    try:
+        for mode in (1, 0):
+            B.moe_ffn_kernel_mode(mode)
+            layer = make_layer(wl, inp, tile_m=128, n_bins=bins)
+            x = layer_x(layer, inp)
+            for plain in (False, True):
+                for t in (layer.h, layer.y, layer.y_perm):
+                    t.fill_(float("nan"))
+                if plain:                                 # the plain entry point
+                    layer.permute(x)
+                    layer.plan()
+                    layer.ffn()
+                    layer.combine(True)
+                else:
+                    layer.forward(x)
+                torch.cuda.synchronize()
+                out[mode, plain] = (layer.y.clone(), layer.h.clone())
+    finally:
+        B.moe_ffn_kernel_mode(before)
+    for key in ((1, True), (0, False), (0, True)):
+        for a, b, name in zip(out[1, False], out[key], ("y", "H")):
+            assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a.view(torch.int16),
+                               b.view(torch.int32) if b.dtype == torch.float32 else b.view(torch.int16)), (name, key)
+    assert torch.isfinite(out[0, False][0]).all()
+
+
 @pytest.mark.parametrize("T", [300000, 400000])
 def test_layer_with_very_many_tiles_in_a_bin(torch_gpu, T):
     """All rows on ONE bin in 128-row tiles.  400 000 rows: more than 3 100 tiles, beyond the per-bin
