@@ -18,6 +18,7 @@
 // Selection: eight or sixteen threads scan one token's logits from LDS, keep a sorted top-(k+1)
 // list in registers, and merge the lists with DPP exchanges inside their group of lanes.
 #include "common.h"
+#include "route_stage.h"
 #include <climits>
 #include <type_traits>
 
@@ -478,20 +479,15 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     for (int r = 0; r < 16; ++r) { acc64[r] = 0.0; acc[r] = 0.f; }
     static_assert(KACC == KC, "a chunk is what one fp32 accumulation holds");
 
-    // ---- staging.  Stage s holds the chunks s*KSP ... s*KSP+KSP-1: for each, 32 token rows, then
-    // for each EPT expert rows, every row one 128-byte line (64 terms) in eight 16-byte pieces,
-    // piece p of row r at position p ^ ((r / 2) & 7) (conflict-free fragment reads).  A load moves
-    // eight rows (lane = row * 8 + position).  With one or two wavefronts on a SIMD the loop is bound by
-    // the instructions a wavefront issues (one every five cycles), so a wavefront's loads are the
-    // same in every stage: XL of token rows and WL of expert rows, their per-lane offsets formed once,
-    // the stage only in the scalar offset.  (Deciding in every stage which rows a load brings took
-    // 0.6 us a stage.)  Chunks past the end bring the following terms, or zeros past the end of the
-    // matrix, and are not multiplied; past the last stage its loads go out again, so that the count of
-    // outstanding loads that guarantees a stage is a constant.
-    constexpr int SROWS = (TB + EPT) * KSP, STAGE = SROWS * 128;
-    constexpr int XL = (TB / 8 * KSP + NWV - 1) / NWV, WL = EPT / 8 * KSP / NWV, LPW = XL + WL;
-    constexpr int RING = ROUTE_RING;
-    static_assert(EPT / 8 * KSP % NWV == 0 && (TB / 8 * KSP % NWV == 0 || XL == 1), "loads dealt to the wavefronts");
+    // ---- staging (route_stage.h).  With one or two wavefronts on a SIMD the loop is bound by the instructions a
+    // wavefront issues (one every five cycles), so a wavefront's loads are the same in every stage, their
+    // per-lane offsets formed once, the stage only in the scalar offset.  (Deciding in every stage which rows
+    // a load brings took 0.6 us a stage.)  Chunks past the end bring earlier terms again and are not
+    // multiplied; past the last stage its loads go out again, so that the count of outstanding loads that
+    // guarantees a stage is a constant.
+    using S = RouteStage<NB, KSP>;
+    constexpr int STAGE = S::BYTES, LPW = S::LPW, RING = ROUTE_RING;
+    static_assert(S::TB == TB && S::EPT == EPT && S::CHUNK == KC * 2, "route_stage.h");
     static_assert(LPW * (RING - 1) < 64 && RING * STAGE + 1024 <= 150 * 1024, "staging ring");
     unsigned char* ring = smem;
     const int n_stages = (n_chunks + KSP - 1) / KSP;
@@ -499,25 +495,22 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wgt), 0, E * d * 2, 0x00020000);
-    const int ld_r = lane >> 3, ld_p = lane & 7;
-    unsigned voff[LPW], to[LPW];                             // byte offsets: in the matrix, and (scalar) in the stage
+    unsigned voff[LPW], to[LPW], last[LPW];                  // byte offsets: in the matrix, and (scalar) in the stage and at most
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-        const int per_chunk = i < XL ? TB / 8 : EPT / 8;     // loads of a chunk's token (expert) rows
-        const int L = wave + (i < XL ? i : i - XL) * NWV, sub = L / per_chunk, row = (L - sub * per_chunk) * 8;
-        const int rr = (i < XL ? 0 : TB) + row;              // row inside the chunk: tokens, then experts
-        const bool none = i < XL && L >= TB / 8 * KSP;       // (more wavefronts than loads of token rows)
-        voff[i] = (unsigned)(row + ld_r) * (unsigned)d * 2u + (unsigned)(sub * 128) + (unsigned)((ld_p ^ (((rr + ld_r) >> 1) & 7)) << 4);
-        to[i] = (unsigned)__builtin_amdgcn_readfirstlane((sub * (TB + EPT) + rr) * 128);
-        if (none) { voff[i] = 0x80000000u; to[i] = RING * STAGE; }   // (zeros to the 1 KB behind the ring)
+        voff[i] = S::lane_offset(wave, i, lane, d);
+        to[i] = (unsigned)__builtin_amdgcn_readfirstlane((int)S::lds(wave, i));
+        last[i] = (unsigned)__builtin_amdgcn_readfirstlane((int)S::last_offset(wave, i, n_chunks));
+        if (S::spare(wave, i)) { voff[i] = 0x80000000u; to[i] = RING * STAGE; }   // (zeros to the 1 KB behind the ring)
     }
     auto issue_stage = [&](int st) {
-        const unsigned buf = (unsigned)(st % RING) * STAGE, soff = (unsigned)(st < n_stages ? st : n_stages - 1) * (KSP * 128u);
+        const unsigned buf = (unsigned)(st % RING) * STAGE;
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const bool spare = XL * NWV > TB / 8 * KSP && i < XL;      // (its place does not move with the stage)
+            const bool spare = S::XL * NWV > TB / 8 * KSP && S::is_x(i);     // (its place does not move with the stage)
             lds_void_t* at = (lds_void_t*)(ring + (spare && to[i] == (unsigned)(RING * STAGE) ? to[i] : buf + to[i]));
-            if (i < XL) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, at, 16, voff[i], soff, 0, 0);
+            const unsigned soff = S::offset(st, last[i]);
+            if (S::is_x(i)) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, at, 16, voff[i], soff, 0, 0);
             else __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, at, 16, voff[i], soff, 0, 0);
         }
     };
@@ -568,7 +561,7 @@ __device__ __forceinline__ void route_packed_body(const uint16_t* __restrict__ x
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc64[r] += (double)acc[r];
-    MOE_WAIT_VMCNT(0);                                       // (the trailing empty loads still target this LDS)
+    MOE_WAIT_VMCNT(0);                                       // (the trailing loads, the last stage's again, still target this LDS)
     __syncthreads();                                         // the ring's memory is reused below
     route_finish<NB, KSP, RMAX, true>(smem, acc64, xsq, w2, mine, x, wgt, bias, T, d, E, k, renorm, idx_out, w_out, logits_out);
 }
