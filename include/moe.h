@@ -321,6 +321,10 @@ MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
  * it -- and returns the previous setting (a negative moe_status on a bad argument).  For
  * measurements and tests. */
 MOE_API int moe_ffn_kernel_mode(int mode);
+/* Whether mode 0 runs a product of A rows [A,K] x [K,N] over 128-row tiles of E experts by the four-wavefront kernels,
+ * two neighbouring tiles of an expert at a time (1), or not (0): it does where that leaves one round of items on the chip
+ * instead of two.  N counts weight rows: 2F for the first product of MOE_SWIGLU.  For measurements and tests. */
+MOE_API int moe_ffn_pairs(int A, int E, int K, int N);
 
 MOE_API int moe_grouped_ffn(const void* x_perm, int A, int d, int F, int E, moe_act act, moe_dtype dt,
                     const void* const* w_in, const void* const* w_out,

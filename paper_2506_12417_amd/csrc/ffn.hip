@@ -67,17 +67,26 @@ static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
     return tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 
-// Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels.  An item of
-// 256 rows takes them 7/4 to 2 times what one of 128 rows takes the eight-wavefront kernels (the less the longer
-// the contraction); what decides are the rounds of items that the CUs need, and the contraction has to be long
-// enough for a work-group's longer way in and out.  Measured (one product, eight-wavefront kernels -> this;
-// rounds before, after): K=3520 (1.7, 0.9) 146 -> 105 us, K=1664 (1.5, 0.8) 66 -> 50, K=14336 (1.1, 0.7) 423 -> 360 and (3.6,
-// 1.9) 828 -> 737, K=4096 (25.4, 13.6) 1516 -> 1364; where the rule says no: K=14336 (2.3, 1.3) 614 -> 675, K=2048 (12.3, 6.8) 418 ->
-// 401 but 1 % more over the layer's pass, K=1408 (8.9, 4.9) 246 -> 246, K=640 (1.5, 0.9) 31 -> 42, K=704 (6.4, 3.5) 96 -> 114.
+// Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels: where the
+// CUs then need one round of items instead of two.  An item of 256 rows takes them as long whether its second tile is
+// there or not, 7/4 to 2 times what one of 128 rows takes the eight-wavefront kernels; and a contraction of 1408 terms
+// is long enough for a work-group's longer way in and out.  The table is on the device: an expert whose rows are split over
+// bins, or are no multiple of 128, adds ragged tiles, one half per expert on average.  The bounds are a quarter and three
+// quarters (and of few experts at least the eight bins' share): over Zipf loads the table then has its second round, and
+// the pairs their one, where the rule says so.
+// Measured (one product, eight-wavefront kernels -> this; items per CU before, after): K=14336 (1.1, 0.7) 415 -> 359 us, (1.6,
+// 0.9) 550 -> 377; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=1472 (1.4, 0.8) 62 -> 50.  Where the rule says no: a single round before,
+// K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than one after, K=14336 (1.7, 1.1) 518 -> 630, K=4096 (28.9, 15.3) 1601 -> 1696,
+// K=2368 (4.1, 2.5) 209 -> 220; nothing to pair, 128 experts of 27 rows, K=3072 (1.6, 1.5) 138 -> 173.
 static bool wide_pairs(int A, int E, int K, int N) {
-    const long long cb = (N + 255) / 256, grid = MOE_GEMM_GRID;
-    const long long before = (((long long)A / 128 + E / 2) * cb + grid - 1) / grid, after = (((long long)A / 256 + E / 2) * cb + grid - 1) / grid;
-    return (K >= 1408 && 2 * after <= before) || (K >= 4096 && 7 * after <= 4 * before);
+    const long long cb = (N + 255) / 256, rows = A;
+    const int ragged = E == 1 ? 0 : E < 8 ? 7 : E - 1;
+    const long long before = (rows + 127) / 128 + (E - 1) / 4, after = (rows + 255) / 256 + 3 * ragged / 4;
+    return K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID;
+}
+
+extern "C" int moe_ffn_pairs(int A, int E, int K, int N) {
+    return A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N);
 }
 
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.

@@ -1067,14 +1067,17 @@ def test_four_wavefront_kernels_give_the_bits_of_the_lds_ring_kernels(torch_gpu,
 
 
 # (pairs, single tiles and ragged ends of 128-row tables on eight, three and one bins; the second product with and without the
-# combine folded in, the first with its gather)
-@pytest.mark.parametrize("T,d,F,E,k,act,skew,bins", [(4096, 2048, 1408, 4, 1, "relu", "zipf", 8), (2400, 1408, 2816, 3, 2, "swiglu", "hot", 8),
-                                                     (4000, 1536, 1472, 4, 2, "swiglu", "zipf", 3), (4096, 2048, 1408, 4, 1, "relu", "uniform", 1)])
-def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F, E, k, act, skew, bins):
+# combine folded in, the first with its gather and without; `paired`: the products that the library takes in pairs)
+@pytest.mark.parametrize("T,d,F,E,k,act,skew,bins,paired", [(4096, 2048, 1408, 4, 1, "relu", "zipf", 8, ()), (2400, 1408, 2816, 3, 2, "swiglu", "hot", 8, ()),
+                                                            (4000, 1536, 1472, 4, 2, "swiglu", "zipf", 3, (2,)), (4096, 2048, 1408, 4, 1, "relu", "uniform", 1, ()),
+                                                            (4500, 2048, 1408, 4, 1, "relu", "zipf", 8, (2,)), (4500, 2048, 1408, 4, 1, "relu", "uniform", 1, (2,)),
+                                                            (1600, 1408, 1408, 3, 2, "swiglu", "hot", 8, (1,)), (1600, 1408, 2816, 4, 2, "relu", "zipf", 8, (1,))])
+def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F, E, k, act, skew, bins, paired):
     torch = torch_gpu
     from paper_2506_12417_amd import binding as B
     wl = W.WORKLOADS["c4"].scaled(T=T, d=d, F=F, E=E, k=k, act=act, skew=skew)
     _note("pairs T=%d d=%d F=%d E=%d k=%d %s %s bins=%d" % (T, d, F, E, k, act, skew, bins))
+    assert paired == tuple(p for p, K, N in ((1, d, 2 * F if act == "swiglu" else F), (2, F, d)) if B.moe_ffn_pairs(T * k, E, K, N))
     inp = W.make_inputs(wl)
     before = B.moe_ffn_kernel_mode(-1)
     out = {}
@@ -1095,6 +1098,8 @@ def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F
                     layer.forward(x)
                 torch.cuda.synchronize()
                 out[mode, plain] = (layer.y.clone(), layer.h.clone())
+        table = to_numpy(layer.tiles)[:int(layer.plan_hdr[0])]
+        assert any(a[0] == b[0] and a[1] + a[2] == b[1] and a[2] == 128 for a, b in zip(table, table[1:]))
     finally:
         B.moe_ffn_kernel_mode(before)
     for key in ((1, True), (0, False), (0, True)):
