@@ -74,13 +74,13 @@ static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
 // bins, or are no multiple of 128, adds ragged tiles, one half per expert on average.  The bounds are a quarter and three
 // quarters (and of few experts at least the eight bins' share): over Zipf loads the table then has its second round, and
 // the pairs their one, where the rule says so.
-// Measured (one product, eight-wavefront kernels -> this; items per CU before, after): K=14336 (1.1, 0.7) 415 -> 359 us, (1.6,
-// 0.9) 550 -> 377; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=1472 (1.4, 0.8) 62 -> 50.  Where the rule says no: a single round before,
+// Measured (one product, eight-wavefront kernels -> this; items per CU before, after): K=14336 (1.1, 0.7) 418 -> 380 us, (1.3,
+// 0.8) 532 -> 366; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=3968 (1.1, 0.6) 125 -> 103; K=1472 (1.1, 0.7) 59 -> 50.  Where the rule says no: a single round before,
 // K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than one after, K=14336 (1.7, 1.1) 518 -> 630, K=4096 (28.9, 15.3) 1601 -> 1696,
 // K=2368 (4.1, 2.5) 209 -> 220; nothing to pair, 128 experts of 27 rows, K=3072 (1.6, 1.5) 138 -> 173.
 static bool wide_pairs(int A, int E, int K, int N) {
     const long long cb = (N + 255) / 256, rows = A;
-    const int ragged = E == 1 ? 0 : E < 8 ? 7 : E - 1;
+    const long long ragged = E == 1 ? 0 : E < 8 ? 8 : E;
     const long long before = (rows + 127) / 128 + (E - 1) / 4, after = (rows + 255) / 256 + 3 * ragged / 4;
     return K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID;
 }
@@ -159,7 +159,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                                                    h_scratch, F, st, gather.perm, gather.k);
             else if (gather.on && wide(epi, d, n1))
                 // (with 256-row tiles fused_impl has checked that these kernels are in use and cover d)
-                rc = moe_launch_gemm_wide_gather(epi, x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
+                rc = moe_launch_gemm_wide_gather(epi, tile_m, x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
                                                  gather.perm, gather.k);
             else if (gather.on)
                 rc = moe_launch_gemm_bf16_gather(epi, cache_h, x_perm, gather.x_rows, d, n1,
@@ -167,7 +167,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
             else if (stream(epi, d))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(n1), x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else if (wide(epi, d, n1))
-                rc = moe_launch_gemm_wide(epi, x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
+                rc = moe_launch_gemm_wide(epi, tile_m, x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else
                 rc = moe_launch_gemm_bf16(epi, tile_m, narrow(n1), cache_h, x_perm, d, n1,
                                           w_in, tiles, plan_hdr, h_scratch, F, st);
@@ -182,7 +182,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                 rc = moe_launch_gemm_stream(epi, stream_narrow(d), h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st,
                                             top1.perm, top1.gate_w, top1.on ? A : 0);
             else if (wide(epi, F, d))
-                rc = moe_launch_gemm_wide(epi, h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
+                rc = moe_launch_gemm_wide(epi, tile_m, h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
                                           top1.gate_w, top1.on ? A : 0);
             else if (top1.on)
                 rc = moe_launch_gemm_bf16(MOE_EPI_SCATTER, tile_m, narrow(d), cache_y, h_scratch, F, d, w_out, tiles, plan_hdr,

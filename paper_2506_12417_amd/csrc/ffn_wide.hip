@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
                                                         const moe_tile* __restrict__ tiles,
                                                         const int32_t* __restrict__ hdr, void* __restrict__ out,
                                                         int ld_out, const int32_t* __restrict__ row_token,
-                                                        const float* __restrict__ row_gate, int out_rows, int a_div) {
+                                                        const float* __restrict__ row_gate, int out_rows, int a_div, int pairs) {
     static_assert(!GATHER || EPI == MOE_EPI_RELU || EPI == MOE_EPI_SWIGLU, "gather: first product");
     constexpr bool SCAT = EPI == MOE_EPI_SCATTER;
     constexpr bool HALF_IN = EPI == MOE_EPI_STORE || SCAT;  // the second product: half operands, fp32 results
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.N = N;
     g.KT = K / C::BK;                                        // (K is a multiple of 64)
     g.n_col_blocks = (N + C::BN - 1) / C::BN;
-    const WorkShare ws = work_share(hdr, g.n_col_blocks);
+    const WorkShare ws = work_share(hdr, g.n_col_blocks, pairs);
     const int first = ws.first;
     g.stride = ws.stride;
     g.bin_start = ws.bin_start;
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
 }
 
 template <int EPI, bool GATHER = false>
-int launch_wide(const void* a, int K, int N, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
+int launch_wide(int tile_m, const void* a, int K, int N, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
                 int ld_out, hipStream_t st, const int32_t* row_token = nullptr, const float* row_gate = nullptr,
                 int out_rows = 0, int a_div = 1) {
     const int dev_ok = moe_check_gemm_device();
@@ -599,7 +599,7 @@ int launch_wide(const void* a, int K, int N, const void* const* w, const moe_til
                                        (int)C::SMEM);
     if (e != hipSuccess) return moe_fail(MOE_ERR_HIP, "moe_grouped_ffn: shared memory attribute: %s", hipGetErrorString(e));
     hipLaunchKernelGGL(kern, dim3(MOE_GEMM_GRID), dim3(C::NTH), C::SMEM, st, (const uint16_t*)a, K, N, w, tiles, hdr, out,
-                       ld_out, row_token, row_gate, out_rows, a_div);
+                       ld_out, row_token, row_gate, out_rows, a_div, tile_m == 128 ? 1 : 0);
     MOE_CHECK_LAUNCH("moe_grouped_ffn (bf16 GEMM, four wavefronts)");
     return MOE_OK;
 }
@@ -610,21 +610,21 @@ bool moe_gemm_wide_supports(int epi, int K) {
     return epi >= MOE_EPI_RELU && epi <= MOE_EPI_SCATTER && K % 64 == 0 && K >= 256;
 }
 
-int moe_launch_gemm_wide(int epi, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
+int moe_launch_gemm_wide(int epi, int tile_m, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
                          const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_token,
                          const float* row_gate, int out_rows) {
-    if (epi == MOE_EPI_RELU) return launch_wide<MOE_EPI_RELU>(a, K, N, w, tiles, hdr, out, ld_out, st);
-    if (epi == MOE_EPI_SWIGLU) return launch_wide<MOE_EPI_SWIGLU>(a, K, N, w, tiles, hdr, out, ld_out, st);
-    if (epi == MOE_EPI_STORE) return launch_wide<MOE_EPI_STORE>(a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_RELU) return launch_wide<MOE_EPI_RELU>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_SWIGLU) return launch_wide<MOE_EPI_SWIGLU>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_STORE) return launch_wide<MOE_EPI_STORE>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
     if (epi == MOE_EPI_SCATTER)
-        return launch_wide<MOE_EPI_SCATTER>(a, K, N, w, tiles, hdr, out, ld_out, st, row_token, row_gate, out_rows);
+        return launch_wide<MOE_EPI_SCATTER>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st, row_token, row_gate, out_rows);
     return moe_fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: epilogue %d in the four-wavefront kernel", epi);
 }
 
-int moe_launch_gemm_wide_gather(int epi, const void* x, int x_rows, int K, int N, const void* const* w,
+int moe_launch_gemm_wide_gather(int epi, int tile_m, const void* x, int x_rows, int K, int N, const void* const* w,
                                 const moe_tile* tiles, const int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div) {
     if (epi == MOE_EPI_SWIGLU)
-        return launch_wide<MOE_EPI_SWIGLU, true>(x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
-    return launch_wide<MOE_EPI_RELU, true>(x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
+        return launch_wide<MOE_EPI_SWIGLU, true>(tile_m, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
+    return launch_wide<MOE_EPI_RELU, true>(tile_m, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
 }
