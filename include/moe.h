@@ -280,7 +280,10 @@ MOE_API int moe_pack_w_out(const void* w, int n, int F, int d, moe_dtype dt, voi
  *           gate/up interleaved by moe_pack_weights)
  *   w_out : device array of E device pointers; w_out[e] = packed [d,F] from moe_pack_w_out
  *   tiles, plan_hdr : from moe_plan_tiles with the same E and A; tile_m as given to the plan:
- *           moe_ffn_tile_m(dt), or for bf16 128 or 256 (moe_ffn_pick_tile_m).  The bf16 kernels
+ *           moe_ffn_tile_m(dt), or for bf16 128 or 256 (moe_ffn_pick_tile_m), to which MOE_TILE_WHOLE_PLAN
+ *           may be added where the plan covers all A rows (moe_plan_tiles, moe_permute_plan; not
+ *           moe_plan_tiles_subset): the choice of the kernels then goes by the tiles that A rows and E
+ *           experts make, as moe_ffn_pairs says.  The results are the same bits.  The bf16 kernels
  *           hand the tiles of a bin to its work-groups through the counters at
  *           plan_hdr[MOE_PLAN_HDR_CTR ...]: they must be zero on entry (moe_plan_tiles leaves
  *           them so) and are zero again when the call's kernels have finished, so a plan can be
@@ -296,6 +299,7 @@ MOE_API int moe_pack_w_out(const void* w, int n, int F, int d, moe_dtype dt, voi
  * are persistent launches laid out for the whole MI355X (256 compute units in 8 XCDs):
  * MOE_ERR_UNSUPPORTED on a device that reports another count.
  */
+#define MOE_TILE_WHOLE_PLAN 0x10000
 MOE_API int moe_ffn_tile_m(moe_dtype dt);
 /* bf16 has two tile heights, 128 and 256 rows; this picks one from the mean rows per expert
  * (256 once A/E >= 1024: under skewed routing most experts hold far fewer rows than the mean, and
@@ -321,10 +325,11 @@ MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
  * it -- and returns the previous setting (a negative moe_status on a bad argument).  For
  * measurements and tests. */
 MOE_API int moe_ffn_kernel_mode(int mode);
-/* Whether mode 0 runs a product of A rows [A,K] x [K,N] over 128-row tiles of E experts by the four-wavefront kernels,
- * two neighbouring tiles of an expert at a time (1), or not (0): it does where that leaves one round of items on the chip
- * instead of two.  N counts weight rows: 2F for the first product of MOE_SWIGLU.  For measurements and tests. */
-MOE_API int moe_ffn_pairs(int A, int E, int K, int N);
+/* Whether mode 0, given this tile_m (see moe_grouped_ffn), runs a product of A rows [A,K] x [K,N] over the tiles of E
+ * experts by the four-wavefront kernels, two neighbouring 128-row tiles of an expert at a time (1), or not (0): it does where
+ * that leaves one round of items on the chip instead of two.  N counts weight rows: 2F for the first product of MOE_SWIGLU.
+ * For measurements and tests. */
+MOE_API int moe_ffn_pairs(int tile_m, int A, int E, int K, int N);
 
 MOE_API int moe_grouped_ffn(const void* x_perm, int A, int d, int F, int E, moe_act act, moe_dtype dt,
                     const void* const* w_in, const void* const* w_out,

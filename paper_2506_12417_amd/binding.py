@@ -29,6 +29,7 @@ MOE_PLAN_HDR_INTS = MOE_PLAN_HDR_CTR + MOE_MAX_BINS + 1
 MOE_OP_PERMUTE = 1
 MOE_PERMUTE_STATIC_BYTES = 1 << 20
 MOE_PERMUTE_PLAN_MAX = 32768
+MOE_TILE_WHOLE_PLAN = 0x10000
 
 EXPORTS = [
     "moe_route_topk", "moe_pack_router", "moe_route_topk_packed", "moe_permute", "moe_permute_static", "moe_plan_capacity", "moe_plan_tiles", "moe_permute_plan", "moe_plan_tiles_subset", "moe_rebalance", "moe_pack_weights", "moe_pack_w_out",
@@ -53,7 +54,7 @@ lib.moe_pack_w_out.argtypes = [_vp, _i, _i, _i, _i, _vp, _vp]
 lib.moe_ffn_tile_m.argtypes = [_i]
 lib.moe_ffn_pick_tile_m.argtypes = [_i, _i, _i]
 lib.moe_ffn_kernel_mode.argtypes = [_i]
-lib.moe_ffn_pairs.argtypes = [_i, _i, _i, _i]
+lib.moe_ffn_pairs.argtypes = [_i, _i, _i, _i, _i]
 lib.moe_grouped_ffn.argtypes = [_vp, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp]
 lib.moe_grouped_ffn_phase.argtypes = [_i, _vp, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp]
 lib.moe_grouped_ffn_top1.argtypes = [_vp, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp, _vp]
@@ -176,8 +177,8 @@ def moe_ffn_kernel_mode(mode: int) -> int:
     return r
 
 
-def moe_ffn_pairs(A: int, E: int, K: int, N: int) -> bool:
-    return bool(lib.moe_ffn_pairs(A, E, K, N))
+def moe_ffn_pairs(tile_m: int, A: int, E: int, K: int, N: int) -> bool:
+    return bool(lib.moe_ffn_pairs(tile_m, A, E, K, N))
 
 
 def moe_permute_static(x, expert_idx, T, d, E, k, dt, counts, offsets, perm, inv_perm, x_perm, stream=None):

@@ -63,12 +63,16 @@ static bool few_rows_per_expert(int A, int E) {
     return A <= 64 * E && (long long)A * E <= 32ll * (8 - E) * E;
 }
 
+// the plan's tile height of a tile_m argument
+static int tile_height(int tile_m) { return tile_m & ~MOE_TILE_WHOLE_PLAN; }
+
 static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
-    return tile_m == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
+    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 
 // Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels: where the
-// CUs then need one round of items instead of two.  An item of 256 rows takes them as long whether its second tile is
+// CUs then need one round of items instead of two.  (For a plan of all A rows only, MOE_TILE_WHOLE_PLAN: four of 32 experts,
+// judged by all 12000 rows, took 41 us by single tiles and 64 in pairs.)  An item of 256 rows takes them as long whether its second tile is
 // there or not, 7/4 to 2 times what one of 128 rows takes the eight-wavefront kernels; and a contraction of 1408 terms
 // is long enough for a work-group's longer way in and out.  The table is on the device: an expert whose rows are split over
 // bins, or are no multiple of 128, adds ragged tiles, one half per expert on average.  The bounds are a quarter and three
@@ -85,8 +89,8 @@ static bool wide_pairs(int A, int E, int K, int N) {
     return K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID;
 }
 
-extern "C" int moe_ffn_pairs(int A, int E, int K, int N) {
-    return A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N);
+extern "C" int moe_ffn_pairs(int tile_m, int A, int E, int K, int N) {
+    return tile_m == (128 | MOE_TILE_WHOLE_PLAN) && A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N);
 }
 
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
@@ -103,7 +107,9 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
     MOE_REQUIRE(moe_dtype_ok(dt), MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: dtype %d", (int)dt);
     MOE_REQUIRE(act == MOE_RELU || act == MOE_SWIGLU, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: activation %d", (int)act);
     MOE_REQUIRE(A >= 0 && d >= 1 && F >= 1 && E >= 1, MOE_ERR_ARG, "moe_grouped_ffn: A=%d d=%d F=%d E=%d", A, d, F, E);
+    const bool whole_plan = tile_m & MOE_TILE_WHOLE_PLAN;
     if (dt == MOE_BF16) {
+        tile_m = tile_height(tile_m);
         MOE_REQUIRE(tile_m == 128 || tile_m == 256, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: bf16 tile_m=%d, must be 128 or 256", tile_m);
         MOE_REQUIRE(d % 64 == 0 && F % 64 == 0, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: bf16 needs d and F multiples of 64 (d=%d F=%d)", d, F);
     } else {
@@ -138,7 +144,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // tiles where taking them in pairs pays.
         auto wide = [&](int epi, int K, int N) {
             if (g_kernel_mode == 1 || !moe_gemm_wide_supports(epi, K)) return false;
-            return tile_m == 256 || (g_kernel_mode == 0 && !rows && wide_pairs(A, E, K, N));
+            return tile_m == 256 || (whole_plan && g_kernel_mode == 0 && !rows && wide_pairs(A, E, K, N));
         };
         // (the eight XCDs' L2s hold 32 MB)
         auto cache = [&](long long weights, size_t out_bytes) {
@@ -255,8 +261,9 @@ static int fused_impl(int phases, const void* x, int T, int d, int F, int E, int
     MOE_REQUIRE(dt == MOE_BF16, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_fused: MOE_BF16 only (dtype %d)", (int)dt);
     MOE_REQUIRE(T >= 0 && k >= 1, MOE_ERR_ARG, "moe_grouped_ffn_fused: T=%d k=%d", T, k);
     MOE_REQUIRE((long long)T * k < (1ll << 30), MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_fused: T*k too large");
-    MOE_REQUIRE(tile_m == 128 || tile_m == 256, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_fused: bf16 tile_m=%d, must be 128 or 256", tile_m);
-    MOE_REQUIRE(tile_m == 128 || (g_kernel_mode != 1 && moe_gemm_wide_supports(MOE_EPI_RELU, d)), MOE_ERR_UNSUPPORTED,
+    const int height = tile_height(tile_m);
+    MOE_REQUIRE(height == 128 || height == 256, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_fused: bf16 tile_m=%d, must be 128 or 256", height);
+    MOE_REQUIRE(height == 128 || (g_kernel_mode != 1 && moe_gemm_wide_supports(MOE_EPI_RELU, d)), MOE_ERR_UNSUPPORTED,
                 "moe_grouped_ffn_fused: with 256-row tiles the row gather is done by the four-wavefront kernels only "
                 "(moe_ffn_kernel_mode %d, d=%d)", g_kernel_mode, d);
     MOE_REQUIRE(d >= 256, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_fused: needs d >= 256 (d=%d)", d);

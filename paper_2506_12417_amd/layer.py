@@ -79,6 +79,9 @@ class MoELayer:
         self.n_bins, self.policy = n_bins, policy
         self.q_tokens = q_tokens if q_tokens is not None else default_q_tokens(self.dt)
         self.tile_m = tile_m if tile_m is not None else B.moe_ffn_pick_tile_m(self.dt, self.A, E)
+        # what the products are told: the plan holds all rows
+        whole = B.MOE_TILE_WHOLE_PLAN if self.dt == B.MOE_BF16 else 0
+        self.ffn_tile_m = self.tile_m | whole
         self.device = torch.device(device)
         dev, A = self.device, self.A
         i32, f32 = torch.int32, torch.float32
@@ -120,6 +123,7 @@ class MoELayer:
             self.s_counts = torch.tensor([T], dtype=i32).to(dev)
             self.s_offsets = torch.tensor([0, T], dtype=i32).to(dev)
             self.s_tile_m = B.moe_ffn_pick_tile_m(self.dt, T, 1)
+            self.s_ffn_tile_m = self.s_tile_m | whole
             self.s_capacity = B.moe_plan_capacity(T, 1, self.s_tile_m, n_bins)
             self.s_tiles = torch.empty((self.s_capacity, 4), dtype=i32, device=dev)
             self.s_hdr = torch.empty(B.MOE_PLAN_HDR_INTS, dtype=i32, device=dev)
@@ -181,17 +185,17 @@ class MoELayer:
     def ffn(self, stream=None):
         g = self.experts
         B.moe_grouped_ffn(self.x_perm, self.A, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs, g.out_ptrs,
-                          self.tiles, self.plan_hdr, self.tile_m, self.h, self.y_perm, stream)
+                          self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.y_perm, stream)
 
     def ffn_phase(self, phase: int, stream=None):
         g = self.experts
         B.moe_grouped_ffn_phase(phase, self.x_perm, self.A, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs,
-                                g.out_ptrs, self.tiles, self.plan_hdr, self.tile_m, self.h, self.y_perm, stream)
+                                g.out_ptrs, self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.y_perm, stream)
 
     def shared_ffn(self, x, stream=None):
         g = self.shared
         B.moe_grouped_ffn(x, self.T, self.d, self.shared_F, 1, B.MOE_SWIGLU, self.dt, g.in_ptrs, g.out_ptrs,
-                          self.s_tiles, self.s_hdr, self.s_tile_m, self.s_h, self.s_y, stream)
+                          self.s_tiles, self.s_hdr, self.s_ffn_tile_m, self.s_h, self.s_y, stream)
 
     def combine(self, use_gate: bool = True, stream=None):
         B.moe_unpermute_combine(self.y_perm, self.inv_perm, self.gate_w if use_gate else None,
@@ -217,13 +221,13 @@ class MoELayer:
             self.permute_plan(stream)
             g = self.experts
             args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm,
+                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm,
                     stream)
             if marks is None and self.shared_F:              # (k > 1: with a shared expert the combine is not folded)
                 s = self.shared
                 B.moe_grouped_ffn_shared(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
-                                         self.tiles, self.plan_hdr, self.tile_m, self.h, self.perm, self.y_perm, self.shared_F,
-                                         s.in_ptrs, s.out_ptrs, self.s_tiles, self.s_hdr, self.s_tile_m, self.s_h, self.s_y,
+                                         self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.y_perm, self.shared_F,
+                                         s.in_ptrs, s.out_ptrs, self.s_tiles, self.s_hdr, self.s_ffn_tile_m, self.s_h, self.s_y,
                                          stream)
                 self.combine(True, stream)
                 return self.y
@@ -245,7 +249,7 @@ class MoELayer:
             self.permute_plan(stream)
             g = self.experts
             B.moe_grouped_ffn_gather(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
-                                     self.tiles, self.plan_hdr, self.tile_m, self.h, self.perm, self.y_perm, stream)
+                                     self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.y_perm, stream)
             if self.shared_F:
                 self.shared_ffn(x, stream)
             self.combine(True, stream)
@@ -256,7 +260,7 @@ class MoELayer:
             # top-1: the second product writes y directly (no y_perm round trip, no combine kernel)
             g = self.experts
             args = (self.x_perm, self.T, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y, stream)
+                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y, stream)
             if marks is None:
                 B.moe_grouped_ffn_top1(*args)
             else:
@@ -303,7 +307,7 @@ class MoELayer:
             mark("plan")
         if fused:
             args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm, None)
+                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm, None)
             B.moe_grouped_ffn_fused_phase(1, *args)
             mark("g1")
             B.moe_grouped_ffn_fused_phase(2, *args)
@@ -312,7 +316,7 @@ class MoELayer:
                 return self.y
         elif self.fold_combine:
             args = (self.x_perm, self.T, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.tile_m, self.h, self.perm, self.gate_w, self.y, None)
+                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y, None)
             B.moe_grouped_ffn_top1_phase(1, *args)
             mark("g1")
             B.moe_grouped_ffn_top1_phase(2, *args)

@@ -155,6 +155,9 @@ def test_ffn_argument_errors():
     assert call(act=2) == B.MOE_ERR_UNSUPPORTED
     assert call(E=0) == B.MOE_ERR_ARG
     assert call(tile_m=64) == B.MOE_ERR_UNSUPPORTED        # bf16 tiles are 128 or 256 rows
+    whole = B.MOE_TILE_WHOLE_PLAN
+    assert call(A=0, tile_m=128 | whole) == B.MOE_OK and call(tile_m=64 | whole) == B.MOE_ERR_UNSUPPORTED
+    assert call(dt=B.MOE_F32, tile_m=64 | whole) == B.MOE_ERR_UNSUPPORTED
     assert call(d=96) == B.MOE_ERR_UNSUPPORTED             # bf16 needs multiples of 64
     assert call(dt=B.MOE_F32, tile_m=128) == B.MOE_ERR_UNSUPPORTED
     assert call(dt=B.MOE_F32, tile_m=64, d=30) == B.MOE_ERR_UNSUPPORTED

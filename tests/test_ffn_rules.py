@@ -12,6 +12,7 @@ from paper_2506_12417_amd import binding as B
 from paper_2506_12417_amd.layer import XCDS, default_q_tokens
 
 GRID = 256                       # compute units
+WHOLE = 128 | B.MOE_TILE_WHOLE_PLAN
 
 
 def table(T, E, k, zipf, rng):
@@ -59,12 +60,12 @@ def test_pairs_are_taken_only_where_they_save_a_round(E, k, products, tokens):
     rng, said, wrong = np.random.default_rng(E), 0, []
     for _ in range(300):
         T = int(round(math.exp(rng.uniform(math.log(tokens[0]), math.log(tokens[1])))))
-        if not any(B.moe_ffn_pairs(T * k, E, K, N) for K, N in products):
+        if not any(B.moe_ffn_pairs(WHOLE, T * k, E, K, N) for K, N in products):
             continue
         tiles, starts = table(T, E, k, rng.uniform(0, 2.0 if E == 8 else 1.5), rng)
         for K, N in products:
             cb = (N + 255) // 256
-            if B.moe_ffn_pairs(T * k, E, K, N):
+            if B.moe_ffn_pairs(WHOLE, T * k, E, K, N):
                 said += 1
                 if rounds(tiles, starts, cb)[0] < 2 or rounds(tiles, starts, cb)[1] != 1:
                     wrong.append((T, K, N, rounds(tiles, starts, cb)))
@@ -74,10 +75,19 @@ def test_pairs_are_taken_only_where_they_save_a_round(E, k, products, tokens):
 
 def test_nothing_is_paired_where_every_expert_has_one_tile_or_the_items_fit_one_round():
     for A in range(1, 641):
-        assert not B.moe_ffn_pairs(A, 1, 2048, 11264) and not B.moe_ffn_pairs(A, 1, 5632, 2048), A
+        assert not B.moe_ffn_pairs(WHOLE, A, 1, 2048, 11264) and not B.moe_ffn_pairs(WHOLE, A, 1, 5632, 2048), A
     for T in range(1, 400):
-        assert not B.moe_ffn_pairs(4 * T, 60, 1408, 2048), T
+        assert not B.moe_ffn_pairs(WHOLE, 4 * T, 60, 1408, 2048), T
     for T in range(1, 16385, 7):
-        assert not B.moe_ffn_pairs(T, 128, 3072, 768), T
-    assert not B.moe_ffn_pairs(1792, 24, 2560, 2560)
-    assert B.moe_ffn_pairs(768, 1, 2048, 11264) and B.moe_ffn_pairs(1023, 1, 2048, 11264)
+        assert not B.moe_ffn_pairs(WHOLE, T, 128, 3072, 768), T
+    assert not B.moe_ffn_pairs(WHOLE, 1792, 24, 2560, 2560)
+    assert B.moe_ffn_pairs(WHOLE, 768, 1, 2048, 11264) and B.moe_ffn_pairs(WHOLE, 1023, 1, 2048, 11264)
+
+
+def test_a_plan_over_some_of_the_experts_is_never_paired():
+    """A call that does not say that its plan covers all rows (a group of experts, moe_plan_tiles_subset) cannot be judged by them."""
+    for A in range(64, 32769, 64):
+        for E in (1, 8, 32):
+            for K, N in ((2048, 11264), (3072, 768), (14336, 4096)):
+                assert not B.moe_ffn_pairs(128, A, E, K, N) and not B.moe_ffn_pairs(256 | B.MOE_TILE_WHOLE_PLAN, A, E, K, N)
+    assert B.moe_ffn_pairs(WHOLE, 12000, 32, 3072, 768)

@@ -1077,7 +1077,6 @@ def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F
     from paper_2506_12417_amd import binding as B
     wl = W.WORKLOADS["c4"].scaled(T=T, d=d, F=F, E=E, k=k, act=act, skew=skew)
     _note("pairs T=%d d=%d F=%d E=%d k=%d %s %s bins=%d" % (T, d, F, E, k, act, skew, bins))
-    assert paired == tuple(p for p, K, N in ((1, d, 2 * F if act == "swiglu" else F), (2, F, d)) if B.moe_ffn_pairs(T * k, E, K, N))
     inp = W.make_inputs(wl)
     before = B.moe_ffn_kernel_mode(-1)
     out = {}
@@ -1085,6 +1084,8 @@ def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F
         for mode in (1, 0):
             B.moe_ffn_kernel_mode(mode)
             layer = make_layer(wl, inp, tile_m=128, n_bins=bins)
+            assert paired == tuple(p for p, K, N in ((1, d, 2 * F if act == "swiglu" else F), (2, F, d))
+                                   if B.moe_ffn_pairs(layer.ffn_tile_m, T * k, E, K, N))
             x = layer_x(layer, inp)
             for plain in (False, True):
                 for t in (layer.h, layer.y, layer.y_perm):
