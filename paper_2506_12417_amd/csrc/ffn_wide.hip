@@ -82,7 +82,7 @@ struct Geo {
     const uint32_t* blk;       // LDS: first tile and tile count of the block each tile of the bin belongs to
     const uint16_t* first_of;  // LDS: a tile's first entry in the bin's table, 0x8000 if the next one belongs to it
     int K, N, KT, n_col_blocks, bin_start, n_tiles, n_items, stride;
-    bool by_block;
+    bool by_block, pairs;      // pairs: 128-row entries are taken two at a time (with by_block)
     // gather (first product): row r of the table's row space is row row_token[r] / a_div of a_mat,
     // which has out_rows rows.  scatter (second product, top-1): row r goes to row row_token[r] of
     // the output (out_rows rows), times row_gate[that row] (1 if null).
@@ -110,7 +110,7 @@ __device__ __forceinline__ void locate(const Geo& g, int it, int& tile_idx, int&
 
 // Tile ti of this launch: an entry of the table, or two neighbouring ones (Geo::first_of).
 __device__ __forceinline__ moe_tile tile_at(const Geo& g, int ti) {
-    if (!g.by_block) return g.tiles[g.bin_start + ti];
+    if (!g.pairs) return g.tiles[g.bin_start + ti];
     const int u = sgpr((int)g.first_of[ti]);
     moe_tile t = g.tiles[g.bin_start + (u & 0x7fff)];
     if (u & 0x8000) t.row_count += g.tiles[g.bin_start + (u & 0x7fff) + 1].row_count;
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.stride = ws.stride;
     g.bin_start = ws.bin_start;
     g.n_tiles = ws.n_tiles;
-    // Tables of 128-row tiles: two neighbouring tiles of one expert are one tile here.  first_of[p]: see Geo;
+    // Tables of 128-row tiles (pairs): two neighbouring tiles of one expert are one tile here.  first_of[p]: see Geo;
     // blk[p] = first tile and tile count of the block (one expert's tiles on this bin, at most 256)
     // that tile p belongs to
     uint32_t* blk = (uint32_t*)(ring + C::RING_BYTES);
@@ -468,6 +468,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.blk = blk;
     g.first_of = first_of;
     g.by_block = g.n_tiles <= C::MAX_BLK_TILES;
+    g.pairs = pairs && g.by_block;
     if (g.by_block) {
         // (the ring is still empty: expert of every entry, whether the one before ends where it begins, tiles so far)
         int* ex = (int*)ring;
@@ -477,35 +478,40 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
         for (int p = tid; p < n; p += C::NTH) {
             const moe_tile t = tiles[g.bin_start + p];
             ex[p] = t.expert;
-            bool j = false;
-            if (p > 0) {
-                const moe_tile u = tiles[g.bin_start + p - 1];
-                j = u.expert == t.expert && u.row_begin + u.row_count == t.row_begin && u.row_count == C::BM / 2 && t.row_count <= C::BM / 2;
+            if (g.pairs) {
+                bool j = false;
+                if (p > 0) {
+                    const moe_tile u = tiles[g.bin_start + p - 1];
+                    j = u.expert == t.expert && u.row_begin + u.row_count == t.row_begin && u.row_count == C::BM / 2 && t.row_count <= C::BM / 2;
+                }
+                joins[p] = j ? 1 : 0;
             }
-            joins[p] = j ? 1 : 0;
         }
         __syncthreads();
-        if (wave == 0) {                                   // entries at odd places of a joined run go with the one before
-            int at = 0;
-            for (int p0 = 0; p0 < n; p0 += 64) {
-                const int p = p0 + lane;
-                int f = p;                                 // (runs are counted from every 64th entry: an even number)
-                while (p < n && f > p0 && joins[f]) --f;
-                const bool leads = p < n && ((p - f) & 1) == 0;
-                const bool pair = leads && p + 1 < n && lane < 63 && joins[p + 1];
-                const unsigned long long m = __ballot(leads);
-                if (leads) first_of[at + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(p | (pair ? 0x8000 : 0));
-                at += __popcll(m);
+        if (g.pairs) {
+            if (wave == 0) {                               // entries at odd places of a joined run go with the one before
+                int at = 0;
+                for (int p0 = 0; p0 < n; p0 += 64) {
+                    const int p = p0 + lane;
+                    int f = p;                             // (runs are counted from every 64th entry: an even number)
+                    while (p < n && f > p0 && joins[f]) --f;
+                    const bool leads = p < n && ((p - f) & 1) == 0;
+                    const bool pair = leads && p + 1 < n && lane < 63 && joins[p + 1];
+                    const unsigned long long m = __ballot(leads);
+                    if (leads) first_of[at + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(p | (pair ? 0x8000 : 0));
+                    at += __popcll(m);
+                }
+                if (lane == 0) *count = at;
             }
-            if (lane == 0) *count = at;
+            __syncthreads();
+            g.n_tiles = sgpr(*count);
         }
-        __syncthreads();
-        g.n_tiles = sgpr(*count);
+        auto expert = [&](int p) { return ex[g.pairs ? first_of[p] & 0x7fff : p]; };
         for (int p = tid; p < g.n_tiles; p += C::NTH) {
-            const int e = ex[first_of[p] & 0x7fff];
+            const int e = expert(p);
             int f = p, l = p;
-            while (f > 0 && (f & 255) != 0 && ex[first_of[f - 1] & 0x7fff] == e) --f;
-            while (l + 1 < g.n_tiles && ((l + 1) & 255) != 0 && ex[first_of[l + 1] & 0x7fff] == e) ++l;
+            while (f > 0 && (f & 255) != 0 && expert(f - 1) == e) --f;
+            while (l + 1 < g.n_tiles && ((l + 1) & 255) != 0 && expert(l + 1) == e) ++l;
             blk[p] = (uint32_t)f | ((uint32_t)(l - f + 1) << 16);
         }
     }
