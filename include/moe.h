@@ -411,6 +411,11 @@ MOE_API int moe_grouped_ffn_gather(const void* x, int T, int d, int F, int E, in
                                    const void* const* w_in, const void* const* w_out,
                                    const moe_tile* tiles, int32_t* plan_hdr, int tile_m,
                                    void* h_scratch, const int32_t* perm, float* y_perm, void* stream);
+/* One of its two products on its own, like moe_grouped_ffn_phase (phase 2 does not read x). */
+MOE_API int moe_grouped_ffn_gather_phase(int phase, const void* x, int T, int d, int F, int E, int k, moe_act act,
+                                         moe_dtype dt, const void* const* w_in, const void* const* w_out,
+                                         const moe_tile* tiles, int32_t* plan_hdr, int tile_m,
+                                         void* h_scratch, const int32_t* perm, float* y_perm, void* stream);
 
 /* moe_grouped_ffn_fused for k >= 2 and, for the same tokens, the always-on shared expert:
  *
@@ -428,6 +433,16 @@ MOE_API int moe_grouped_ffn_shared(const void* x, int T, int d, int F, int E, in
                                    const void* const* s_w_in, const void* const* s_w_out,
                                    const moe_tile* s_tiles, int32_t* s_plan_hdr, int s_tile_m,
                                    void* s_h_scratch, float* s_y, void* stream);
+/* A part of its launches, with all its arguments; the three in order are the whole call.  Phase 1: the routed experts' first
+ * product; phase 2: their second; where the shared expert's products share launches they are in these.  Phase 3: the
+ * shared expert's own launches (none where it has none). */
+MOE_API int moe_grouped_ffn_shared_phase(int phase, const void* x, int T, int d, int F, int E, int k, moe_act act,
+                                         moe_dtype dt, const void* const* w_in, const void* const* w_out,
+                                         const moe_tile* tiles, int32_t* plan_hdr, int tile_m,
+                                         void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
+                                         const void* const* s_w_in, const void* const* s_w_out,
+                                         const moe_tile* s_tiles, int32_t* s_plan_hdr, int s_tile_m,
+                                         void* s_h_scratch, float* s_y, void* stream);
 
 /* ------------------------------------------------------------------------------------------
  * Step 6 (Alg. 1 "reconstruct"; section 2: the experts' outputs are weighted by the router's

@@ -33,7 +33,7 @@ MOE_TILE_WHOLE_PLAN = 0x10000
 
 EXPORTS = [
     "moe_route_topk", "moe_pack_router", "moe_route_topk_packed", "moe_permute", "moe_permute_static", "moe_plan_capacity", "moe_plan_tiles", "moe_permute_plan", "moe_plan_tiles_subset", "moe_rebalance", "moe_pack_weights", "moe_pack_w_out",
-    "moe_ffn_tile_m", "moe_ffn_pick_tile_m", "moe_ffn_kernel_mode", "moe_ffn_pairs", "moe_grouped_ffn", "moe_grouped_ffn_phase", "moe_grouped_ffn_top1", "moe_grouped_ffn_top1_phase", "moe_grouped_ffn_fused", "moe_grouped_ffn_fused_phase", "moe_grouped_ffn_shared", "moe_grouped_ffn_gather", "moe_unpermute_combine", "moe_prefetch_create",
+    "moe_ffn_tile_m", "moe_ffn_pick_tile_m", "moe_ffn_kernel_mode", "moe_ffn_pairs", "moe_grouped_ffn", "moe_grouped_ffn_phase", "moe_grouped_ffn_top1", "moe_grouped_ffn_top1_phase", "moe_grouped_ffn_fused", "moe_grouped_ffn_fused_phase", "moe_grouped_ffn_shared", "moe_grouped_ffn_shared_phase", "moe_grouped_ffn_gather", "moe_grouped_ffn_gather_phase", "moe_unpermute_combine", "moe_prefetch_create",
     "moe_prefetch_experts", "moe_set_expert_pointers", "moe_prefetch_wait", "moe_prefetch_release", "moe_prefetch_reset", "moe_prefetch_destroy",
     "moe_token_threshold", "moe_workspace_bytes", "moe_copy_bytes", "moe_last_error", "moe_version",
 ]
@@ -63,6 +63,8 @@ lib.moe_grouped_ffn_fused.argtypes = [_vp, _i, _i, _i, _i, _i, _i, _i, _vp, _vp,
 lib.moe_grouped_ffn_fused_phase.argtypes = [_i, _vp, _i, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp, _vp]
 lib.moe_grouped_ffn_gather.argtypes = [_vp, _i, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp]
 lib.moe_grouped_ffn_shared.argtypes = [_vp, _i, _i, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp]
+lib.moe_grouped_ffn_gather_phase.argtypes = [_i] + lib.moe_grouped_ffn_gather.argtypes
+lib.moe_grouped_ffn_shared_phase.argtypes = [_i] + lib.moe_grouped_ffn_shared.argtypes
 lib.moe_unpermute_combine.argtypes = [_vp, _vp, _vp, _vp, _i, _i, _i, _vp, _vp]
 lib.moe_prefetch_create.argtypes = [C.POINTER(_vp), _i, _sz, _vp]
 lib.moe_prefetch_experts.argtypes = [_vp, C.POINTER(C.c_int32), _i, C.POINTER(_vp), _sz, C.POINTER(_vp)]
@@ -260,6 +262,19 @@ def moe_grouped_ffn_shared(x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_h
     _check(lib.moe_grouped_ffn_shared(_p(x), T, d, F, E, k, act, dt, _p(w_in), _p(w_out), _p(tiles), _p(plan_hdr), tile_m,
                                       _p(h_scratch), _p(perm), _p(y_perm), shared_F, _p(s_w_in), _p(s_w_out), _p(s_tiles),
                                       _p(s_plan_hdr), s_tile_m, _p(s_h_scratch), _p(s_y), _stream(stream)))
+
+
+def moe_grouped_ffn_gather_phase(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm,
+                                 stream=None):
+    _check(lib.moe_grouped_ffn_gather_phase(phase, _p(x), T, d, F, E, k, act, dt, _p(w_in), _p(w_out), _p(tiles), _p(plan_hdr), tile_m,
+                                            _p(h_scratch), _p(perm), _p(y_perm), _stream(stream)))
+
+
+def moe_grouped_ffn_shared_phase(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm, shared_F,
+                                 s_w_in, s_w_out, s_tiles, s_plan_hdr, s_tile_m, s_h_scratch, s_y, stream=None):
+    _check(lib.moe_grouped_ffn_shared_phase(phase, _p(x), T, d, F, E, k, act, dt, _p(w_in), _p(w_out), _p(tiles), _p(plan_hdr), tile_m,
+                                            _p(h_scratch), _p(perm), _p(y_perm), shared_F, _p(s_w_in), _p(s_w_out), _p(s_tiles),
+                                            _p(s_plan_hdr), s_tile_m, _p(s_h_scratch), _p(s_y), _stream(stream)))
 
 
 def moe_grouped_ffn_phase(phase, x_perm, A, d, F, E, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch,

@@ -302,49 +302,82 @@ extern "C" int moe_grouped_ffn_fused_phase(int phase, const void* x, int T, int 
     return fused_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, gate_w, y_out, stream);
 }
 
-extern "C" int moe_grouped_ffn_gather(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
-                                      const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
-                                      int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, void* stream) {
+static int gather_impl(int phases, const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                       const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                       int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, void* stream) {
     MOE_REQUIRE(dt == MOE_F32, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_gather: MOE_F32 only (dtype %d)", (int)dt);
     MOE_REQUIRE(T >= 0 && k >= 1, MOE_ERR_ARG, "moe_grouped_ffn_gather: T=%d k=%d", T, k);
     MOE_REQUIRE((long long)T * k < (1ll << 30), MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_gather: T*k too large");
-    MOE_REQUIRE(T == 0 || perm, MOE_ERR_ARG, "moe_grouped_ffn_gather: null pointer");
+    MOE_REQUIRE(T == 0 || !(phases & 1) || perm, MOE_ERR_ARG, "moe_grouped_ffn_gather: null pointer");
     Gather g;
     g.perm = perm;
     g.x_rows = T;
     g.k = k;
     g.on = true;
-    return grouped_ffn_impl(3, x, T * k, d, F, E, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, y_perm, stream, Top1(), g);
+    return grouped_ffn_impl(phases, x, T * k, d, F, E, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, y_perm, stream, Top1(), g);
+}
+
+extern "C" int moe_grouped_ffn_gather(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                      const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                                      int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, void* stream) {
+    return gather_impl(3, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm, stream);
+}
+
+extern "C" int moe_grouped_ffn_gather_phase(int phase, const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                            const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                                            int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, void* stream) {
+    MOE_REQUIRE(phase == 1 || phase == 2, MOE_ERR_ARG, "moe_grouped_ffn_gather_phase: phase %d", phase);
+    return gather_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm, stream);
 }
 
 // moe_grouped_ffn_fused and the shared expert's moe_grouped_ffn.  Where the few-row kernels serve both, each
 // product of the shared expert shares the launch of the routed experts' one (33 rows of 2048 x 1408, E = 60, and
 // 5632: 94 + 56 + 25 + 26 us in four launches, 108 + 70 in two): one expert's product has too few items to keep
-// the memory busy by itself.  Everywhere else the calls follow one another.
+// the memory busy by itself.  Everywhere else the calls follow one another.  phases: bits of moe_grouped_ffn_shared_phase.
+static int shared_impl(int phases, const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                       const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                       int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
+                       const void* const* s_w_in, const void* const* s_w_out, const moe_tile* s_tiles,
+                       int32_t* s_plan_hdr, int s_tile_m, void* s_h_scratch, float* s_y, void* stream) {
+    MOE_REQUIRE(k >= 2, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_shared: needs k >= 2 (k=%d)", k);
+    const bool rows = dt == MOE_BF16 && act == MOE_SWIGLU && T >= 1 && E >= 1 && k >= 2 && (long long)T * k < (1ll << 30) &&
+                      few_rows_call(T * k, d, F, E, tile_m) && few_rows_call(T, d, shared_F, 1, s_tile_m);
+    MOE_REQUIRE(T <= 0 || (x && w_in && w_out && y_perm && s_w_in && s_w_out && s_y), MOE_ERR_ARG, "moe_grouped_ffn_shared: null pointer");
+    auto routed = [&](int p) {
+        return fused_impl(p, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, nullptr, y_perm, stream);
+    };
+    auto shared = [&](int p) {
+        return grouped_ffn_impl(p, x, T, d, shared_F, 1, MOE_SWIGLU, dt, s_w_in, s_w_out, s_tiles, s_plan_hdr, s_tile_m, s_h_scratch, s_y,
+                                stream);
+    };
+    // (phase 0 checks the other arguments and enqueues nothing)
+    int rc = routed(0);
+    if (rc == MOE_OK) rc = shared(0);
+    for (int p = 1; p <= 2 && rc == MOE_OK; ++p) {
+        if (!(phases & p)) continue;
+        rc = rows ? moe_launch_gemm_rows_shared(p, x, T, d, F, E, k, p == 1 ? w_in : w_out, tiles, plan_hdr, h_scratch, y_perm, perm, shared_F,
+                                                p == 1 ? s_w_in : s_w_out, s_tiles, s_plan_hdr, s_h_scratch, s_y, (hipStream_t)stream)
+                  : routed(p);
+    }
+    if (rc == MOE_OK && (phases & 4) && !rows) rc = shared(3);
+    return rc;
+}
+
 extern "C" int moe_grouped_ffn_shared(const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
                                       const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
                                       int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
                                       const void* const* s_w_in, const void* const* s_w_out, const moe_tile* s_tiles,
                                       int32_t* s_plan_hdr, int s_tile_m, void* s_h_scratch, float* s_y, void* stream) {
-    MOE_REQUIRE(k >= 2, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_shared: needs k >= 2 (k=%d)", k);
-    const bool rows = dt == MOE_BF16 && act == MOE_SWIGLU && T >= 1 && E >= 1 && k >= 2 && (long long)T * k < (1ll << 30) &&
-                      few_rows_call(T * k, d, F, E, tile_m) && few_rows_call(T, d, shared_F, 1, s_tile_m);
-    MOE_REQUIRE(T <= 0 || (x && w_in && w_out && y_perm && s_w_in && s_w_out && s_y), MOE_ERR_ARG, "moe_grouped_ffn_shared: null pointer");
-    // (phase 0 checks the other arguments and enqueues nothing)
-    for (int phase = 0; phase <= 3; phase += 3) {
-        if (phase && rows) break;
-        int rc = fused_impl(phase, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, nullptr, y_perm, stream);
-        if (rc == MOE_OK)
-            rc = grouped_ffn_impl(phase, x, T, d, shared_F, 1, MOE_SWIGLU, dt, s_w_in, s_w_out, s_tiles, s_plan_hdr, s_tile_m,
-                                  s_h_scratch, s_y, stream);
-        if (rc != MOE_OK) return rc;
-    }
-    if (!rows) return MOE_OK;
-    for (int phase = 1; phase <= 2; ++phase) {
-        const int rc = moe_launch_gemm_rows_shared(phase, x, T, d, F, E, k, phase == 1 ? w_in : w_out, tiles, plan_hdr, h_scratch, y_perm,
-                                                   perm, shared_F, phase == 1 ? s_w_in : s_w_out, s_tiles, s_plan_hdr, s_h_scratch,
-                                                   s_y, (hipStream_t)stream);
-        if (rc != MOE_OK) return rc;
-    }
-    return MOE_OK;
+    return shared_impl(7, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm, shared_F, s_w_in,
+                       s_w_out, s_tiles, s_plan_hdr, s_tile_m, s_h_scratch, s_y, stream);
+}
+
+extern "C" int moe_grouped_ffn_shared_phase(int phase, const void* x, int T, int d, int F, int E, int k, moe_act act, moe_dtype dt,
+                                            const void* const* w_in, const void* const* w_out, const moe_tile* tiles, int32_t* plan_hdr,
+                                            int tile_m, void* h_scratch, const int32_t* perm, float* y_perm, int shared_F,
+                                            const void* const* s_w_in, const void* const* s_w_out, const moe_tile* s_tiles,
+                                            int32_t* s_plan_hdr, int s_tile_m, void* s_h_scratch, float* s_y, void* stream) {
+    MOE_REQUIRE(phase >= 1 && phase <= 3, MOE_ERR_ARG, "moe_grouped_ffn_shared_phase: phase %d", phase);
+    return shared_impl(1 << (phase - 1), x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, y_perm,
+                       shared_F, s_w_in, s_w_out, s_tiles, s_plan_hdr, s_tile_m, s_h_scratch, s_y, stream);
 }

@@ -114,7 +114,7 @@ class MoELayer:
         # the row gather inside the first product (moe_grouped_ffn_fused): where the library offers it
         can_fuse = (self.dt == B.MOE_BF16 and tall_ok and d >= 256 and d % 64 == 0 and F % 64 == 0
                     and T * d * 2 < 2 ** 32 and (k > 1 or self.fold_combine))
-        # in fp32 the first product can gather as well (moe_grouped_ffn_gather; where forward() records no stages)
+        # in fp32 the first product can gather as well (moe_grouped_ffn_gather)
         can_fuse = can_fuse or (self.dt == B.MOE_F32 and T >= 1)
         self.fuse_gather = can_fuse if fuse_gather is None else (fuse_gather and can_fuse)
         if shared_F:
@@ -201,6 +201,32 @@ class MoELayer:
         B.moe_unpermute_combine(self.y_perm, self.inv_perm, self.gate_w if use_gate else None,
                                 self.s_y if self.shared_F else None, self.T, self.d, self.k, self.y, stream)
 
+    def _products(self, x, stream):
+        """The calls of step 5: the whole call, its form by parts, their arguments and the parts' names."""
+        g = self.experts
+        table = (g.in_ptrs, g.out_ptrs, self.tiles, self.plan_hdr, self.ffn_tile_m, self.h)
+        shape = (self.T, self.d, self.F, self.E)
+        kinds = (self.act, self.dt)
+        if self.fuse_gather and self.dt == B.MOE_F32:
+            return (B.moe_grouped_ffn_gather, B.moe_grouped_ffn_gather_phase,
+                    (x, *shape, self.k, *kinds, *table, self.perm, self.y_perm, stream), ("g1", "g2"))
+        if self.fuse_gather and self.shared_F:                   # (k > 1: with a shared expert the combine is not folded)
+            s = self.shared
+            return (B.moe_grouped_ffn_shared, B.moe_grouped_ffn_shared_phase,
+                    (x, *shape, self.k, *kinds, *table, self.perm, self.y_perm, self.shared_F, s.in_ptrs, s.out_ptrs,
+                     self.s_tiles, self.s_hdr, self.s_ffn_tile_m, self.s_h, self.s_y, stream), ("g1", "g2", "shared"))
+        if self.fuse_gather:
+            # the first product gathers its rows from x itself (no x_perm); for top-1 the second one
+            # also writes y directly
+            return (B.moe_grouped_ffn_fused, B.moe_grouped_ffn_fused_phase,
+                    (x, *shape, self.k, *kinds, *table, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm, stream), ("g1", "g2"))
+        if self.fold_combine:
+            # top-1: the second product writes y directly (no y_perm round trip, no combine kernel)
+            return (B.moe_grouped_ffn_top1, B.moe_grouped_ffn_top1_phase,
+                    (self.x_perm, *shape, *kinds, *table, self.perm, self.gate_w, self.y, stream), ("g1", "g2"))
+        return (B.moe_grouped_ffn, B.moe_grouped_ffn_phase,
+                (self.x_perm, self.A, *shape[1:], *kinds, *table, self.y_perm, stream), ("g1", "g2"))
+
     def forward(self, x: torch.Tensor, stream=None, marks=None, routed: bool = False, stages=None) -> torch.Tensor:
         """Enqueues the whole layer on the current (or given) stream; returns the output buffer.
         A bf16 token's last bits depend on the number of tokens the layer is made for: calls with a
@@ -210,128 +236,56 @@ class MoELayer:
         grouped GEMMs (for per-kernel timing).  routed: expert_idx and gate_w are already set
         (a router that samples ids, section 5.1's synthetic skew): step 1 is skipped.
         stages: optional list that receives (name, event) after every stage of the path, starting
-        with ("start", event) (per-stage timing; the events are recorded on the current stream)."""
+        with ("start", event) (per-stage timing; the events are recorded on the current stream).  With
+        either the same launches run in the same order, the products by their *_phase calls; in calls
+        with few rows the shared expert's products share the launches of g1 and g2."""
+        mark = None
         if stages is not None:
-            return self._forward_staged(x, stages, routed)
+            stream = None
+
+            def mark(name):
+                ev = torch.cuda.Event(enable_timing=True)
+                ev.record()
+                stages.append((name, ev))
+
+            mark("start")
+        elif marks is not None:
+            def mark(name):
+                at = {"plan": 0, "permute_plan": 0, "g1": 1, "g2": 2}.get(name)
+                if at is not None:
+                    marks[at].record()
+
         if not routed:
             self.route(x, None, stream)
-        if self.fuse_gather and self.dt == B.MOE_BF16:
-            # the first product gathers its rows from x itself (no x_perm); for top-1 the second one
-            # also writes y directly
+            if mark:
+                mark("route")
+        if self.fuse_gather:
             self.permute_plan(stream)
-            g = self.experts
-            args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm,
-                    stream)
-            if marks is None and self.shared_F:              # (k > 1: with a shared expert the combine is not folded)
-                s = self.shared
-                B.moe_grouped_ffn_shared(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
-                                         self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.y_perm, self.shared_F,
-                                         s.in_ptrs, s.out_ptrs, self.s_tiles, self.s_hdr, self.s_ffn_tile_m, self.s_h, self.s_y,
-                                         stream)
-                self.combine(True, stream)
-                return self.y
-            if marks is None:
-                B.moe_grouped_ffn_fused(*args)
-            else:
-                marks[0].record()
-                B.moe_grouped_ffn_fused_phase(1, *args)
-                marks[1].record()
-                B.moe_grouped_ffn_fused_phase(2, *args)
-                marks[2].record()
-            if self.k == 1:
-                return self.y
-            if self.shared_F:
-                self.shared_ffn(x, stream)
-            self.combine(True, stream)
-            return self.y
-        if self.fuse_gather and self.dt == B.MOE_F32 and marks is None:
-            self.permute_plan(stream)
-            g = self.experts
-            B.moe_grouped_ffn_gather(x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs,
-                                     self.tiles, self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.y_perm, stream)
-            if self.shared_F:
-                self.shared_ffn(x, stream)
-            self.combine(True, stream)
-            return self.y
-        self.permute(x, stream)
-        self.plan(stream)
+            if mark:
+                mark("permute_plan")
+        else:
+            self.permute(x, stream)
+            if mark:
+                mark("permute")
+            self.plan(stream)
+            if mark:
+                mark("plan")
+        whole, part, args, names = self._products(x, stream)
+        if mark is None:
+            whole(*args)
+        else:
+            for p, name in enumerate(names):
+                part(p + 1, *args)
+                mark(name)
         if self.fold_combine:
-            # top-1: the second product writes y directly (no y_perm round trip, no combine kernel)
-            g = self.experts
-            args = (self.x_perm, self.T, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y, stream)
-            if marks is None:
-                B.moe_grouped_ffn_top1(*args)
-            else:
-                marks[0].record()
-                B.moe_grouped_ffn_top1_phase(1, *args)
-                marks[1].record()
-                B.moe_grouped_ffn_top1_phase(2, *args)
-                marks[2].record()
             return self.y
-        if marks is None:
-            self.ffn(stream)
-        else:
-            marks[0].record()
-            self.ffn_phase(1, stream)
-            marks[1].record()
-            self.ffn_phase(2, stream)
-            marks[2].record()
-        if self.shared_F:
+        if self.shared_F and len(names) == 2:
             self.shared_ffn(x, stream)
+            if mark:
+                mark("shared")
         self.combine(True, stream)
-        return self.y
-
-
-    def _forward_staged(self, x: torch.Tensor, stages: list, routed: bool) -> torch.Tensor:
-        """forward() with an event after every stage: the same calls in the same order."""
-        def mark(name):
-            ev = torch.cuda.Event(enable_timing=True)
-            ev.record()
-            stages.append((name, ev))
-
-        g = self.experts
-        mark("start")
-        if not routed:
-            self.route(x, None, None)
-            mark("route")
-        fused = self.fuse_gather and self.dt == B.MOE_BF16
-        if fused:
-            self.permute_plan(None)
-            mark("permute_plan")
-        else:
-            self.permute(x, None)
-            mark("permute")
-            self.plan(None)
-            mark("plan")
-        if fused:
-            args = (x, self.T, self.d, self.F, self.E, self.k, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y if self.k == 1 else self.y_perm, None)
-            B.moe_grouped_ffn_fused_phase(1, *args)
-            mark("g1")
-            B.moe_grouped_ffn_fused_phase(2, *args)
-            mark("g2")
-            if self.k == 1:
-                return self.y
-        elif self.fold_combine:
-            args = (self.x_perm, self.T, self.d, self.F, self.E, self.act, self.dt, g.in_ptrs, g.out_ptrs, self.tiles,
-                    self.plan_hdr, self.ffn_tile_m, self.h, self.perm, self.gate_w, self.y, None)
-            B.moe_grouped_ffn_top1_phase(1, *args)
-            mark("g1")
-            B.moe_grouped_ffn_top1_phase(2, *args)
-            mark("g2")
-            return self.y
-        else:
-            self.ffn_phase(1, None)
-            mark("g1")
-            self.ffn_phase(2, None)
-            mark("g2")
-        if self.shared_F:
-            self.shared_ffn(x, None)
-            mark("shared")
-        self.combine(True, None)
-        mark("combine")
+        if mark:
+            mark("combine")
         return self.y
 
 

@@ -214,6 +214,12 @@ def test_pack_combine_copy_argument_errors():
     assert shared(tile_m=64) == B.MOE_ERR_UNSUPPORTED and shared(s_tile_m=64) == B.MOE_ERR_UNSUPPORTED
     assert shared(y=None) == B.MOE_ERR_ARG and shared(sy=None) == B.MOE_ERR_ARG and shared(sh=None) == B.MOE_ERR_ARG
     assert shared(T=0) == B.MOE_OK
+    for phase, ok in ((0, False), (1, True), (2, True), (3, False)):
+        assert (status(B.moe_grouped_ffn_gather_phase, phase, FAKE, 0, 64, 512, 2, 2, B.MOE_SWIGLU, B.MOE_F32, FAKE, FAKE, FAKE, FAKE, 64,
+                       FAKE, FAKE, FAKE, 0) == B.MOE_OK) == ok
+    for phase, ok in ((0, False), (1, True), (3, True), (4, False)):
+        assert (status(B.moe_grouped_ffn_shared_phase, phase, FAKE, 0, 256, 512, 2, 2, B.MOE_SWIGLU, B.MOE_BF16, FAKE, FAKE, FAKE, FAKE, 128,
+                       FAKE, FAKE, FAKE, 512, FAKE, FAKE, FAKE, FAKE, 128, FAKE, FAKE, 0) == B.MOE_OK) == ok
     assert status(B.moe_pack_w_out, None, 1, 8, 32, B.MOE_BF16, FAKE, 0) == B.MOE_ERR_ARG
     assert status(B.moe_pack_w_out, FAKE, 1, 8, 8, 7, FAKE, 0) == B.MOE_ERR_UNSUPPORTED
     assert status(B.moe_pack_w_out, None, 0, 8, 8, B.MOE_BF16, None, 0) == B.MOE_OK

@@ -1128,7 +1128,8 @@ def test_layer_with_very_many_tiles_in_a_bin(torch_gpu, T):
 
 
 @pytest.mark.parametrize("name,over", [("c2", dict(T=3000, d=256, F=512, E=24)), ("c3", dict(T=700, d=256, F=192, E=12, shared_F=320)),
-                                       ("c4", dict(T=4200, d=256, F=512, E=2, k=1)), ("c1", {})])
+                                       ("c4", dict(T=4200, d=256, F=512, E=2, k=1)), ("c1", {}),
+                                       ("c3", dict(T=20, d=512, F=256, E=20, k=2, shared_F=2048))])   # few rows: shared launches
 def test_forward_in_two_timed_halves_gives_the_same_output(torch_gpu, name, over):
     """forward(marks=...) runs the two grouped GEMMs through the *_phase entry points with events
     between them (what bench.py times); the output is that of the single call, bit for bit."""
@@ -1145,6 +1146,28 @@ def test_forward_in_two_timed_halves_gives_the_same_output(torch_gpu, name, over
     torch.cuda.synchronize()
     assert torch.equal(y, ref)
     assert marks[0].elapsed_time(marks[1]) > 0 and marks[1].elapsed_time(marks[2]) > 0
+
+
+@pytest.mark.parametrize("name,over,stages", [("c1", {}, "permute_plan g1 g2 combine"), ("c2", dict(T=3000, d=256, F=512, E=24), "permute_plan g1 g2"),
+                                              ("c3", dict(T=20, d=512, F=256, E=20, k=2, shared_F=2048), "permute_plan g1 g2 shared combine"),
+                                              ("c3", dict(T=700, d=256, F=192, E=12, shared_F=320), "permute_plan g1 g2 shared combine"),
+                                              ("c3", dict(T=90, d=192, F=192, E=12, shared_F=320), "permute plan g1 g2 shared combine")])
+def test_forward_with_stages_is_the_same_launches(torch_gpu, name, over, stages):
+    """forward(stages=...) runs what forward runs, with an event after every stage: the same output bits, and the row
+    gather stays where forward has it (x_perm is written only by a layer that permutes by itself)."""
+    torch = torch_gpu
+    wl = W.WORKLOADS[name].scaled(**over)
+    layer = make_layer(wl, inp := W.make_inputs(wl))
+    x = layer_x(layer, inp)
+    ref = layer.forward(x).clone()
+    seen = []
+    layer.y.fill_(float("nan"))
+    layer.x_perm.fill_(float("nan"))
+    y = layer.forward(x, stages=seen)
+    torch.cuda.synchronize()
+    assert torch.equal(y, ref)
+    assert " ".join(n for n, _ in seen) == "start route " + stages
+    assert bool(torch.isnan(layer.x_perm.float()).all()) == ("permute_plan" in stages)
 
 
 @pytest.mark.parametrize("T,d,k,gated,with_shared", [(1, 4, 1, True, False), (77, 1032, 3, False, True), (300, 260, 8, True, False),
