@@ -306,12 +306,13 @@ MOE_API int moe_ffn_tile_m(moe_dtype dt);
  * their tiles are mostly empty at 256 rows).  Plan and FFN must be given the same value. */
 MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
 
-/* Each bf16 tile height has two families of kernels that compute the same bits.
+/* Each bf16 tile height has families of kernels that compute the same bits.
  * 128 rows: one stages both operands through an LDS ring (eight wavefronts), the other streams
  * the weights straight into registers (meant for experts with few rows, where a product costs
  * the fetch of its weights: section 4.4's regime below q; it covers the ReLU first product and
- * the second product, the scatter form from F >= 512 on).  The LDS ring is the default: it is
- * the faster one on every workload measured so far.
+ * the second product, the scatter form from F >= 512 on).  The LDS ring is the default of the two: it is
+ * the faster one on every workload measured so far.  Where it pays (moe_ffn_pairs) the
+ * default takes neighbouring tiles two at a time by the four-wavefront kernels named next.
  * 256 rows: the LDS ring with eight wavefronts of 128 x 64 outputs each, and four wavefronts of
  * 128 x 128 (a third less LDS traffic per multiply-add, which is what the arithmetic-bound case
  * pays for; d and F multiples of 64, at least 256).  The four wavefronts are the default; only
@@ -319,15 +320,16 @@ MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
  * Calls with a handful of rows per expert (decode steps) go, by default and with 128-row tiles, to
  * a third family that shares an expert's weights out over the whole chip whatever the plan's bins;
  * it sums the contraction in parts, so its last bits differ from the other two: a row's last bits
- * depend on whether the call it is in has that few rows.  (Modes 1 and 2 do not use this family.)
+ * depend on whether the call it is in has that few rows.  (Modes 1 and 2 use neither this family nor pairs.)
  * moe_ffn_kernel_mode sets the choice for the process -- 0 default, 1 the LDS ring with eight
- * wavefronts at both heights, 2 the streaming kernels wherever they cover the call, -1 leaves
- * it -- and returns the previous setting (a negative moe_status on a bad argument).  For
+ * wavefronts at both heights, 2 the streaming kernels wherever they cover a call of 128-row tiles and else
+ * the LDS ring (256 rows as by default), -1 leaves it -- and returns the previous setting (a negative moe_status on a bad argument).  For
  * measurements and tests. */
 MOE_API int moe_ffn_kernel_mode(int mode);
 /* Whether mode 0, given this tile_m (see moe_grouped_ffn), runs a product of A rows [A,K] x [K,N] over the tiles of E
  * experts by the four-wavefront kernels, two neighbouring 128-row tiles of an expert at a time (1), or not (0): it does where
- * that leaves one round of items on the chip instead of two.  N counts weight rows: 2F for the first product of MOE_SWIGLU.
+ * that leaves one round of items on the chip instead of two, and where there are many rounds of a long contraction and nearly
+ * every tile has a partner.  N counts weight rows: 2F for the first product of MOE_SWIGLU.
  * For measurements and tests. */
 MOE_API int moe_ffn_pairs(int tile_m, int A, int E, int K, int N);
 

@@ -37,8 +37,9 @@ struct Gather {
 };
 
 // which 16-bit kernels run: 0 the default (128-row tiles: the few-row kernels where they serve the
-// call, else the LDS-ring kernels; 256-row tiles: the four-wavefront kernels), 1 the LDS-ring
-// kernels, 2 the default with 128-row tiles by the register-streaming kernels wherever they cover the call
+// call, the four-wavefront kernels two tiles at a time where wide_pairs says so, else the LDS-ring kernels; 256-row
+// tiles: the four-wavefront kernels), 1 the LDS-ring kernels, 2 the four-wavefront kernels for 256-row
+// tiles and for 128-row tiles the register-streaming kernels wherever they cover the call, else the LDS-ring kernels
 static int g_kernel_mode = 0;
 
 extern "C" int moe_ffn_kernel_mode(int mode) {
@@ -70,27 +71,33 @@ static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
     return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 
-// Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels: where the
-// CUs then need one round of items instead of two.  (For a plan of all A rows only, MOE_TILE_WHOLE_PLAN: four of 32 experts,
-// judged by all 12000 rows, took 41 us by single tiles and 64 in pairs.)  An item of 256 rows takes them as long whether its second tile is
-// there or not, 7/4 to 2 times what one of 128 rows takes the eight-wavefront kernels; and a contraction of 1408 terms
-// is long enough for a work-group's longer way in and out.  The table is on the device: an expert whose rows are split over
-// bins, or are no multiple of 128, adds ragged tiles, one half per expert on average.  The bounds are a quarter and three
-// quarters (and of few experts at least the eight bins' share): over Zipf loads the table then has its second round, and
-// the pairs their one, where the rule says so.
-// Measured (one product, eight-wavefront kernels -> this; items per CU before, after): K=14336 (1.1, 0.7) 418 -> 380 us, (1.3,
-// 0.8) 532 -> 366; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=3968 (1.1, 0.6) 125 -> 103; K=1472 (1.1, 0.7) 59 -> 50.  Where the rule says no: a single round before,
-// K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than one after, K=14336 (1.7, 1.1) 518 -> 630, K=4096 (28.9, 15.3) 1601 -> 1696,
-// K=2368 (4.1, 2.5) 209 -> 220; nothing to pair, 128 experts of 27 rows, K=3072 (1.6, 1.5) 138 -> 173.
-static bool wide_pairs(int A, int E, int K, int N) {
+// Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels (for a plan of all A
+// rows only, MOE_TILE_WHOLE_PLAN: four of 32 experts, judged by all 12000 rows, took 41 us by single tiles and 64 in pairs).
+// An item of 256 rows takes them as long whether its second tile is there or not, 1.5 to 2 times what one of 128 rows takes
+// the eight-wavefront kernels, and a contraction of 1408 terms is long enough for a work-group's longer way in and out.
+//   MOE_PAIRS_ONE_ROUND  the CUs then need one round of items instead of two
+//   MOE_PAIRS_MANY       many rounds of a long contraction, nearly every tile with a partner: the matrix cores then run at
+//                        their power limit, where a multiply-add of a larger tile is cheaper
+// The table is on the device: an expert whose rows are split over bins, or are no multiple of 128, adds ragged tiles, one
+// half per expert on average.  The bounds are a quarter and three quarters (and of few experts at least the eight
+// bins' share): over Zipf loads the table then has its second round, and the pairs their one, where the rule says so.
+// Measured (one product, eight-wavefront kernels -> this; items per CU before, after): one round K=14336 (1.1, 0.7) 418 -> 380 us, (1.3,
+// 0.8) 532 -> 366; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=3968 (1.1, 0.6) 125 -> 103; K=1472 (1.1, 0.7) 59 -> 50.  Many rounds,
+// launches one after the other, K=4096, 8 experts, means over Zipf 0 - 2: 650 rows each (20, 11) 0.97 of the time, 750 (23, 13) 0.93,
+// 960 (29, 16) 0.92.  Where the rule says no: a single round before, K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than
+// one after, K=14336 (1.7, 1.1) 510 -> 630, (3.7, 2.1) 868 -> 903, K=3200 (4.7, 2.9) 325 -> 370; nothing to pair, 128 experts of 27 rows,
+// K=3072 (1.6, 1.5) 138 -> 173.
+static int wide_pairs(int A, int E, int K, int N) {
     const long long cb = (N + 255) / 256, rows = A;
     const long long ragged = E == 1 ? 0 : E < 8 ? 8 : E;
-    const long long before = (rows + 127) / 128 + (E - 1) / 4, after = (rows + 255) / 256 + 3 * ragged / 4;
-    return K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID;
+    const long long before = (rows + 127) / 128 + E / 4, after = (rows + 255) / 256 + 3 * ragged / 4;
+    if (K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID) return MOE_PAIRS_ONE_ROUND;
+    if (K >= 4096 && rows >= 640ll * E && rows / 128 + E <= MOE_PAIRS_MAX_TILES && after * cb >= 8 * MOE_GEMM_GRID) return MOE_PAIRS_MANY;
+    return 0;
 }
 
 extern "C" int moe_ffn_pairs(int tile_m, int A, int E, int K, int N) {
-    return tile_m == (128 | MOE_TILE_WHOLE_PLAN) && A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N);
+    return tile_m == (128 | MOE_TILE_WHOLE_PLAN) && A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N) != 0;
 }
 
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
@@ -142,9 +149,11 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1), 128-row
         // tiles where taking them in pairs pays.
+        auto pairs = [&](int K, int N) {
+            return tile_m == 128 && whole_plan && g_kernel_mode == 0 && !rows ? wide_pairs(A, E, K, N) : 0;
+        };
         auto wide = [&](int epi, int K, int N) {
-            if (g_kernel_mode == 1 || !moe_gemm_wide_supports(epi, K)) return false;
-            return tile_m == 256 || (whole_plan && g_kernel_mode == 0 && !rows && wide_pairs(A, E, K, N));
+            return g_kernel_mode != 1 && moe_gemm_wide_supports(epi, K) && (tile_m == 256 || pairs(K, N));
         };
         // (the eight XCDs' L2s hold 32 MB)
         auto cache = [&](long long weights, size_t out_bytes) {
@@ -165,7 +174,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                                                    h_scratch, F, st, gather.perm, gather.k);
             else if (gather.on && wide(epi, d, n1))
                 // (with 256-row tiles fused_impl has checked that these kernels are in use and cover d)
-                rc = moe_launch_gemm_wide_gather(epi, tile_m, x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
+                rc = moe_launch_gemm_wide_gather(epi, pairs(d, n1), x_perm, gather.x_rows, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st,
                                                  gather.perm, gather.k);
             else if (gather.on)
                 rc = moe_launch_gemm_bf16_gather(epi, cache_h, x_perm, gather.x_rows, d, n1,
@@ -173,7 +182,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
             else if (stream(epi, d))
                 rc = moe_launch_gemm_stream(epi, stream_narrow(n1), x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else if (wide(epi, d, n1))
-                rc = moe_launch_gemm_wide(epi, tile_m, x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
+                rc = moe_launch_gemm_wide(epi, pairs(d, n1), x_perm, d, n1, w_in, tiles, plan_hdr, h_scratch, F, st);
             else
                 rc = moe_launch_gemm_bf16(epi, tile_m, narrow(n1), cache_h, x_perm, d, n1,
                                           w_in, tiles, plan_hdr, h_scratch, F, st);
@@ -188,7 +197,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
                 rc = moe_launch_gemm_stream(epi, stream_narrow(d), h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st,
                                             top1.perm, top1.gate_w, top1.on ? A : 0);
             else if (wide(epi, F, d))
-                rc = moe_launch_gemm_wide(epi, tile_m, h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
+                rc = moe_launch_gemm_wide(epi, pairs(F, d), h_scratch, F, d, w_out, tiles, plan_hdr, (void*)y_perm, d, st, top1.perm,
                                           top1.gate_w, top1.on ? A : 0);
             else if (top1.on)
                 rc = moe_launch_gemm_bf16(MOE_EPI_SCATTER, tile_m, narrow(d), cache_y, h_scratch, F, d, w_out, tiles, plan_hdr,

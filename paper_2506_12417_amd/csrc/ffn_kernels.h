@@ -39,15 +39,17 @@ int moe_launch_gemm_stream_gather(int narrow, const void* x, int x_rows, int K, 
                                   const moe_tile* tiles, int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                   const int32_t* row_src, int src_div);
 
-// The same products for 256-row tiles, or (tile_m = 128) pairs of neighbouring 128-row tiles of an expert, by the
+// The same products for 256-row tiles, or (pairs) neighbouring 128-row tiles of an expert taken two at a time, by the
 // kernels of ffn_wide.hip (four wavefronts of 128 x 128 per work-group instead of eight of 128 x 64: less
 // LDS traffic per multiply-add, which is what the power-bound case pays for).  Same results, bit for bit; all four epilogues, and the first
 // product with the row gather folded in (arguments as for the launchers above).
+enum { MOE_PAIRS_ONE_ROUND = 1, MOE_PAIRS_MANY = 2 };
+constexpr int MOE_PAIRS_MAX_TILES = 3068;      // single tiles of a work-group's share that can be paired
 bool moe_gemm_wide_supports(int epi, int K);
-int moe_launch_gemm_wide(int epi, int tile_m, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
+int moe_launch_gemm_wide(int epi, int pairs, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
                          const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_token = nullptr,
                          const float* row_gate = nullptr, int out_rows = 0);
-int moe_launch_gemm_wide_gather(int epi, int tile_m, const void* x, int x_rows, int K, int N, const void* const* w,
+int moe_launch_gemm_wide_gather(int epi, int pairs, const void* x, int x_rows, int K, int N, const void* const* w,
                                 const moe_tile* tiles, const int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div);
 

@@ -1,5 +1,5 @@
-// Grouped 16-bit GEMM for 256-row tiles by FOUR wavefronts, each holding a 128 x 128 block of the
-// 256 x 256 output tile (section 4.4: x W1 W2 over rows grouped by expert, driven by the tile
+// Grouped 16-bit GEMM for 256-row tiles, or pairs of neighbouring 128-row tiles of an expert, by FOUR wavefronts, each
+// holding a 128 x 128 block of the 256 x 256 output tile (section 4.4: x W1 W2 over rows grouped by expert, driven by the tile
 // table).  Same products, same operand layouts, same results bit for bit as the kernels of
 // ffn_bf16.hip; what differs is where the energy goes.
 //
@@ -60,7 +60,7 @@ struct WCfg {
     static constexpr int ROWS_PER_PASS = NTH / PPR;
     static constexpr int MI = 4, NI = 4;                  // 32 x 32 blocks of a wavefront's 128 x 128
     static constexpr int RING_BYTES = RING * STAGE_BYTES;
-    static constexpr int MAX_BLK_TILES = 3068;            // tiles of a bin the block table can hold
+    static constexpr int MAX_BLK_TILES = MOE_PAIRS_MAX_TILES;   // tiles of a bin the block table can hold
     static constexpr int ROWINFO_BYTES = 2 * 2 * BM * 4;  // (token, gate) of a tile's rows, for two items
     static constexpr size_t SMEM = (size_t)RING_BYTES + (size_t)MAX_BLK_TILES * 4 + 16 + ROWINFO_BYTES + (size_t)MAX_BLK_TILES * 2 + 8;
     static_assert(ROWS_PER_PASS % (WRAP * PPR) == 0 && 16 % (WRAP * PPR) == 0, "swizzle period");
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.N = N;
     g.KT = K / C::BK;                                        // (K is a multiple of 64)
     g.n_col_blocks = (N + C::BN - 1) / C::BN;
-    const WorkShare ws = work_share(hdr, g.n_col_blocks, pairs);
+    const WorkShare ws = work_share(hdr, g.n_col_blocks, pairs == MOE_PAIRS_ONE_ROUND);
     const int first = ws.first;
     g.stride = ws.stride;
     g.bin_start = ws.bin_start;
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     g.blk = blk;
     g.first_of = first_of;
     g.by_block = g.n_tiles <= C::MAX_BLK_TILES;
-    g.pairs = pairs && g.by_block;
+    g.pairs = pairs != 0 && g.by_block;
     if (g.by_block) {
         // (the ring is still empty: expert of every entry, whether the one before ends where it begins, tiles so far)
         int* ex = (int*)ring;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
     Acc acc;
     int stores = 0;
 
-    // ---- prologue: all RING stages on their way; stage 0 read into set 0; stage 1 landed
+    // ---- prologue: both stages on their way; the first half of stage 0 read into set 0 (stage 1 is waited for in step 0)
     Loader L;
     L.item = first;
     L.kt = 0;
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint16_t* __restri
 }
 
 template <int EPI, bool GATHER = false>
-int launch_wide(int tile_m, const void* a, int K, int N, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
+int launch_wide(int pairs, const void* a, int K, int N, const void* const* w, const moe_tile* tiles, const int32_t* hdr, void* out,
                 int ld_out, hipStream_t st, const int32_t* row_token = nullptr, const float* row_gate = nullptr,
                 int out_rows = 0, int a_div = 1) {
     const int dev_ok = moe_check_gemm_device();
@@ -605,7 +605,7 @@ int launch_wide(int tile_m, const void* a, int K, int N, const void* const* w, c
                                        (int)C::SMEM);
     if (e != hipSuccess) return moe_fail(MOE_ERR_HIP, "moe_grouped_ffn: shared memory attribute: %s", hipGetErrorString(e));
     hipLaunchKernelGGL(kern, dim3(MOE_GEMM_GRID), dim3(C::NTH), C::SMEM, st, (const uint16_t*)a, K, N, w, tiles, hdr, out,
-                       ld_out, row_token, row_gate, out_rows, a_div, tile_m == 128 ? 1 : 0);
+                       ld_out, row_token, row_gate, out_rows, a_div, pairs);
     MOE_CHECK_LAUNCH("moe_grouped_ffn (bf16 GEMM, four wavefronts)");
     return MOE_OK;
 }
@@ -616,21 +616,21 @@ bool moe_gemm_wide_supports(int epi, int K) {
     return epi >= MOE_EPI_RELU && epi <= MOE_EPI_SCATTER && K % 64 == 0 && K >= 256;
 }
 
-int moe_launch_gemm_wide(int epi, int tile_m, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
+int moe_launch_gemm_wide(int epi, int pairs, const void* a, int K, int N, const void* const* w, const moe_tile* tiles,
                          const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_token,
                          const float* row_gate, int out_rows) {
-    if (epi == MOE_EPI_RELU) return launch_wide<MOE_EPI_RELU>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
-    if (epi == MOE_EPI_SWIGLU) return launch_wide<MOE_EPI_SWIGLU>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
-    if (epi == MOE_EPI_STORE) return launch_wide<MOE_EPI_STORE>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_RELU) return launch_wide<MOE_EPI_RELU>(pairs, a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_SWIGLU) return launch_wide<MOE_EPI_SWIGLU>(pairs, a, K, N, w, tiles, hdr, out, ld_out, st);
+    if (epi == MOE_EPI_STORE) return launch_wide<MOE_EPI_STORE>(pairs, a, K, N, w, tiles, hdr, out, ld_out, st);
     if (epi == MOE_EPI_SCATTER)
-        return launch_wide<MOE_EPI_SCATTER>(tile_m, a, K, N, w, tiles, hdr, out, ld_out, st, row_token, row_gate, out_rows);
+        return launch_wide<MOE_EPI_SCATTER>(pairs, a, K, N, w, tiles, hdr, out, ld_out, st, row_token, row_gate, out_rows);
     return moe_fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn: epilogue %d in the four-wavefront kernel", epi);
 }
 
-int moe_launch_gemm_wide_gather(int epi, int tile_m, const void* x, int x_rows, int K, int N, const void* const* w,
+int moe_launch_gemm_wide_gather(int epi, int pairs, const void* x, int x_rows, int K, int N, const void* const* w,
                                 const moe_tile* tiles, const int32_t* hdr, void* out, int ld_out, hipStream_t st,
                                 const int32_t* row_src, int src_div) {
     if (epi == MOE_EPI_SWIGLU)
-        return launch_wide<MOE_EPI_SWIGLU, true>(tile_m, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
-    return launch_wide<MOE_EPI_RELU, true>(tile_m, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
+        return launch_wide<MOE_EPI_SWIGLU, true>(pairs, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
+    return launch_wide<MOE_EPI_RELU, true>(pairs, x, K, N, w, tiles, hdr, out, ld_out, st, row_src, nullptr, x_rows, src_div);
 }

@@ -43,13 +43,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsig
 // to four if it is fewer by two fifths; beyond, sharing an XCD's L2 is worth more than the idle CUs.
 // One expert of 2048 x 5632 (both products): 512 rows 259 -> 94 us, 1100 rows 530 -> 179; four
 // experts, 1024 rows 230 -> 154, 2048 rows (6 rounds against 4) 232 by bins, 242 flat.
-// pairs: the launch takes the tiles two at a time, which is done where the whole chip then has one round: by bins
+// one_round_of_pairs: the launch takes the tiles two at a time, and the whole chip then has one round: by bins
 // if the fullest one has too (its tiles count for five eighths, some having no partner), else flat.  32 experts, 12000 rows
 // of 768 x 3072, second product: 94 us by bins, 106 flat; 16000 rows (two rounds by bins): 162 and 122.
 struct WorkShare {
     int bin, first, stride, bin_start, n_tiles;   // bin: whose work counter hands out the items
 };
-__device__ __forceinline__ WorkShare work_share(const int32_t* __restrict__ hdr, int n_col_blocks, bool pairs = false) {
+__device__ __forceinline__ WorkShare work_share(const int32_t* __restrict__ hdr, int n_col_blocks, bool one_round_of_pairs = false) {
     // (the bins' starts are fetched with the number of bins, not after it: one memory latency)
     const int grid = (int)gridDim.x, lane = threadIdx.x & 63;
     const int at = lane < MOE_MAX_BINS ? lane : MOE_MAX_BINS - 1;
@@ -57,8 +57,8 @@ __device__ __forceinline__ WorkShare work_share(const int32_t* __restrict__ hdr,
     const int G = hdr[1];
     const int fullest = (int)moe_wave_max_u32(lane < G ? (unsigned)(end - start) : 0u);
     const int first_tile = __builtin_amdgcn_readlane(start, 0), all = __builtin_amdgcn_readlane(end, G - 1) - first_tile;
-    const int rounds_flat = pairs ? 1 : (all * n_col_blocks + grid - 1) / grid;
-    const int per_bin = grid / G, rounds_bin = ((pairs ? (5 * fullest + 7) / 8 : fullest) * n_col_blocks + per_bin - 1) / per_bin;
+    const int rounds_flat = one_round_of_pairs ? 1 : (all * n_col_blocks + grid - 1) / grid;
+    const int per_bin = grid / G, rounds_bin = ((one_round_of_pairs ? (5 * fullest + 7) / 8 : fullest) * n_col_blocks + per_bin - 1) / per_bin;
     WorkShare w;
     if (rounds_flat < rounds_bin && (rounds_flat <= 2 || (rounds_flat <= 4 && 3 * rounds_bin >= 5 * rounds_flat))) {
         w.bin = 0;

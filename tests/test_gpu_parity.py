@@ -1068,8 +1068,8 @@ def test_four_wavefront_kernels_give_the_bits_of_the_lds_ring_kernels(torch_gpu,
 
 # (pairs, single tiles and ragged ends of 128-row tables on eight, three and one bins; the second product with and without the
 # combine folded in, the first with its gather and without; `paired`: the products that the library takes in pairs)
-@pytest.mark.parametrize("T,d,F,E,k,act,skew,bins,paired", [(4096, 2048, 1408, 4, 1, "relu", "zipf", 8, ()), (2400, 1408, 2816, 3, 2, "swiglu", "hot", 8, ()),
-                                                            (4000, 1536, 1472, 4, 2, "swiglu", "zipf", 3, (2,)), (4096, 2048, 1408, 4, 1, "relu", "uniform", 1, ()),
+@pytest.mark.parametrize("T,d,F,E,k,act,skew,bins,paired", [(4096, 2048, 1408, 4, 1, "relu", "zipf", 8, (2,)), (2400, 1408, 2816, 3, 2, "swiglu", "hot", 8, ()),
+                                                            (4000, 1536, 1472, 4, 2, "swiglu", "zipf", 3, (2,)), (4096, 2048, 1408, 4, 1, "relu", "uniform", 1, (2,)),
                                                             (4500, 2048, 1408, 4, 1, "relu", "zipf", 8, (2,)), (4500, 2048, 1408, 4, 1, "relu", "uniform", 1, (2,)),
                                                             (1600, 1408, 1408, 3, 2, "swiglu", "hot", 8, (1,)), (1600, 1408, 2816, 4, 2, "relu", "zipf", 8, (1,))])
 def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F, E, k, act, skew, bins, paired):
@@ -1108,6 +1108,46 @@ def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F
             assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a.view(torch.int16),
                                b.view(torch.int32) if b.dtype == torch.float32 else b.view(torch.int16)), (name, key)
     assert torch.isfinite(out[0, False][0]).all()
+
+
+@pytest.mark.parametrize("act,F,counts,bins", [("relu", 29184, [1500, 130, 256, 1130], 8), ("swiglu", 14592, [1500, 130, 256, 1130], 3),
+                                               ("swiglu", 14592, [0, 1, 3000, 15], 1)])
+def test_many_rounds_of_pairs_give_the_bits_of_single_tiles(torch_gpu, act, F, counts, bins):
+    """A first product with many items of paired tiles per work-group, with its row gather and without, against the
+    LDS-ring kernels bit for bit (weights drawn on the GPU; H is what the product writes)."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import MoELayer
+    E, k, d, A = 4, 2, 4096, sum(counts)
+    _note("many rounds of pairs %s F=%d %s bins=%d" % (act, F, counts, bins))
+    layer = MoELayer(A // k, d, F, E, k, act, "bf16", 0, n_bins=bins, tile_m=128)
+    assert layer.fuse_gather and B.moe_ffn_pairs(layer.ffn_tile_m, A, E, d, layer.experts.rows_in)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    layer.experts.w_in.normal_(0, d ** -0.5, generator=gen)
+    layer.experts.w_out.view(torch.float16).normal_(0, F ** -0.5, generator=gen)
+    x = torch.empty((A // k, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    ids = np.random.default_rng(3).permutation(np.repeat(np.arange(E), counts)).astype(np.int32)
+    layer.expert_idx.copy_(torch.from_numpy(ids).view(A // k, k))
+    layer.gate_w.fill_(0.5)
+    before, out = B.moe_ffn_kernel_mode(-1), []
+    try:
+        for mode, plain in ((1, False), (0, False), (0, True)):
+            B.moe_ffn_kernel_mode(mode)
+            layer.h.fill_(float("nan"))
+            if plain:
+                layer.permute(x)
+                layer.plan()
+                layer.ffn()
+                layer.combine(True)
+            else:
+                layer.forward(x, routed=True)
+            torch.cuda.synchronize()
+            out.append((layer.h.view(torch.int16).clone(), layer.y.clone().view(torch.int32)))
+    finally:
+        B.moe_ffn_kernel_mode(before)
+    for h, y in out[1:]:
+        assert torch.equal(h, out[0][0]) and torch.equal(y, out[0][1])
+    assert torch.isfinite(layer.y).all()
 
 
 @pytest.mark.parametrize("T", [300000, 400000])
