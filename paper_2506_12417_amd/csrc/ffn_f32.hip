@@ -18,7 +18,7 @@
 // work-group of its own, which the hardware starts where one has finished; the plan's bins, equal in
 // rows but not in tiles, play no role (28 % of the CU time was idle with them; equal runs of tiles per XCD,
 // which differ in ragged tiles: 236 us for the first product below, every tile shared by all XCDs 220).
-// 3002 rows, d=768 F=2048 E=16 SwiGLU: 496 + 292 us with vector fma tiles of 64 x 64, 220 + 118 here; 12288
+// 3002 rows, d=768 F=2048 E=16 SwiGLU: 496 + 292 us with vector fma tiles of 64 x 64, 207 + 120 here (layer after layer); 12288
 // rows in full tiles, d=1024 F=4096: 128 TFLOP/s.
 //
 // LDS: a row holds 32 terms in eight 16-byte pieces, piece p at position p ^ ((row / 2) & 7): 16
@@ -59,8 +59,8 @@ __global__ __launch_bounds__(NWN * KSP * 64, 3) void gemm_f32_kernel(const float
     const int n_cb = (N + BN - 1) / BN, KT = (K + BK - 1) / BK;
 
     // Items in the order of the plan's tiles, a tile's column blocks one after the other: the XCDs, to which
-    // work-groups are dealt in turn, share every tile's column blocks evenly, and each keeps the slices of
-    // an expert's weights that fall to it in its L2 from one of the expert's tiles to the next.
+    // work-groups are dealt in turn, share every tile's column blocks evenly.  (With a multiple of eight column blocks
+    // each XCD meets the same slices of an expert's weights in all of its tiles.)
     const int n_items = hdr[0] * n_cb;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
         const int ti = item / n_cb, cb = item - ti * n_cb;

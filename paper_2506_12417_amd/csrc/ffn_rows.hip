@@ -115,7 +115,8 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(Job main, Job oth
     const int a_div = second ? other.a_div : main.a_div;
     const int n_cb = N / COLS;                   // (N is a multiple of 64)
     // (whole lines: a wavefront's part is an even number of 64-byte slices, K being a multiple of 64.  K = 1408 by
-    // four wavefronts in parts of 11 slices read 20 % more than the weights.)
+    // four wavefronts in parts of 11 slices read 20 % more than the weights: 315 MB from memory for the second product of
+    // 33 rows and E = 60; with the shared expert's 23 MB it reads 287 now.)
     const int n_slices = K / 32, per = (n_slices / 2 + KS - 1) / KS * 2;
     const int s0 = wave * per < n_slices ? wave * per : n_slices, s1 = s0 + per < n_slices ? s0 + per : n_slices;
     const unsigned w_off = ((unsigned)l16 * (unsigned)K + (unsigned)lq * 8u) * 2u;

@@ -26,7 +26,8 @@
 // A work-group's items form one stream of stages: the loads cross item boundaries, and past the last
 // item they go on with empty descriptors.
 // Measured (16384 rows, 4096 x 14336, stages of 32 terms in a ring of four with a barrier per step -> this):
-// one expert 2850 -> 2620 us (1470 TFLOP/s) and 1590 -> 1470, eight Zipf(2) experts 3290 -> 2990 and 1825 -> 1740 (layer 5195 -> 4852);
+// one expert 2850 -> 2620 us (1470 TFLOP/s) and 1590 -> 1470, eight Zipf(2) experts 3290 -> 2990 and 1825 -> 1740 (layer 5195 -> 4860 - 4930
+// by the run);
 // 8192 rows, 2048 x 5632: 320 -> 292 and 151 -> 134.  What is left: a power limit (the clock falls with the
 // energy of a multiply-add), loads that miss the L2 (second product with every load hitting: 1290 us), and
 // ragged tiles, which cost nearly a full one (their weights' loads take as long).
