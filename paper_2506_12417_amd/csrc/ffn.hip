@@ -79,20 +79,21 @@ static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
 //   MOE_PAIRS_MANY       many rounds of a long contraction, nearly every tile with a partner: the matrix cores then run at
 //                        their power limit, where a multiply-add of a larger tile is cheaper
 // The table is on the device: an expert whose rows are split over bins, or are no multiple of 128, adds ragged tiles, one
-// half per expert on average.  The bounds are a quarter and three quarters (and of few experts at least the eight
-// bins' share): over Zipf loads the table then has its second round, and the pairs their one, where the rule says so.
+// half per expert on average.  The bounds (three eighths for the table, five eighths for the pairs, and there of few experts
+// at least the eight bins' share) are where the gain over Zipf loads of 2 to 48 experts is largest: seven or more of
+// eight tables that the rule picks then have their second round, and their pairs one.
 // Measured (one product, eight-wavefront kernels -> this; items per CU before, after): one round K=14336 (1.1, 0.7) 418 -> 380 us, (1.3,
 // 0.8) 532 -> 366; K=2048 (1.2, 0.7) 77 -> 58, one expert; K=3968 (1.1, 0.6) 125 -> 103; K=1472 (1.1, 0.7) 59 -> 50.  Many rounds,
-// launches one after the other, K=4096, 8 experts, means over Zipf 0 - 2: 650 rows each (20, 11) 0.97 of the time, 750 (23, 13) 0.93,
-// 960 (29, 16) 0.92.  Where the rule says no: a single round before, K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than
+// launches one after the other, K=4096, 8 experts, means over Zipf 0 - 2: 425 rows each (14, 8) 1.02 of the time, 525 (17, 10) 0.98,
+// 650 (20, 11) 0.97, 750 (23, 13) 0.93, 960 (29, 16) 0.92.  Where the rule says no: a single round before, K=2048 (0.2, 0.2) 38 -> 51, K=5632 (0.2, 0.2) 60 -> 124; more than
 // one after, K=14336 (1.7, 1.1) 510 -> 630, (3.7, 2.1) 868 -> 903, K=3200 (4.7, 2.9) 325 -> 370; nothing to pair, 128 experts of 27 rows,
 // K=3072 (1.6, 1.5) 138 -> 173.
 static int wide_pairs(int A, int E, int K, int N) {
     const long long cb = (N + 255) / 256, rows = A;
     const long long ragged = E == 1 ? 0 : E < 8 ? 8 : E;
-    const long long before = (rows + 127) / 128 + E / 4, after = (rows + 255) / 256 + 3 * ragged / 4;
+    const long long before = (rows + 127) / 128 + 3ll * E / 8, after = (rows + 255) / 256 + 5 * ragged / 8;
     if (K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID) return MOE_PAIRS_ONE_ROUND;
-    if (K >= 4096 && rows >= 640ll * E && rows / 128 + E <= MOE_PAIRS_MAX_TILES && after * cb >= 8 * MOE_GEMM_GRID) return MOE_PAIRS_MANY;
+    if (K >= 4096 && rows >= 500ll * E && rows / 128 + E <= MOE_PAIRS_MAX_TILES && after * cb >= 8 * MOE_GEMM_GRID) return MOE_PAIRS_MANY;
     return 0;
 }
 

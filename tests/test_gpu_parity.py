@@ -1110,8 +1110,8 @@ def test_pairs_of_128_row_tiles_give_the_bits_of_single_tiles(torch_gpu, T, d, F
     assert torch.isfinite(out[0, False][0]).all()
 
 
-@pytest.mark.parametrize("act,F,counts,bins", [("relu", 29184, [1500, 130, 256, 1130], 8), ("swiglu", 14592, [1500, 130, 256, 1130], 3),
-                                               ("swiglu", 14592, [0, 1, 3000, 15], 1)])
+@pytest.mark.parametrize("act,F,counts,bins", [("relu", 31232, [1500, 130, 256, 1130], 8), ("swiglu", 15616, [1500, 130, 256, 1130], 3),
+                                               ("swiglu", 15616, [0, 1, 3000, 15], 1)])
 def test_many_rounds_of_pairs_give_the_bits_of_single_tiles(torch_gpu, act, F, counts, bins):
     """A first product with many items of paired tiles per work-group, with its row gather and without, against the
     LDS-ring kernels bit for bit (weights drawn on the GPU; H is what the product writes)."""
