@@ -50,10 +50,16 @@ extern "C" int moe_prefetch_create(moe_prefetch** h, int n_slots, size_t slot_by
     return MOE_OK;
 }
 
+// The slot an expert is in: the one that holds it unreleased, else the one that was released last.  (With slots to spare
+// an expert that was released and fetched again is named by its old slot too.)
 static int find_slot(const moe_prefetch* p, int expert_id) {
-    for (int s = 0; s < p->n_slots; ++s)
-        if (p->expert[s] == expert_id) return s;
-    return -1;
+    int at = -1;
+    for (int s = 0; s < p->n_slots; ++s) {
+        if (p->expert[s] != expert_id) continue;
+        if (!p->released[s]) return s;
+        if (at < 0 || p->release_seq[s] > p->release_seq[at]) at = s;
+    }
+    return at;
 }
 
 extern "C" int moe_prefetch_experts(moe_prefetch* h, const int32_t* expert_ids, int n, const void* const* host_w,

@@ -1264,7 +1264,8 @@ def _share(torch, wl, inp, n_local, n_slots, group=None):
 
 
 @pytest.mark.parametrize("n_slots,group,d,F", [(7, None, 128, 256), (3, None, 128, 256), (2, 1, 128, 256), (1, 1, 128, 256),
-                                               (7, None, 256, 512), (2, None, 256, 512)])
+                                               (7, None, 256, 512), (2, None, 256, 512),
+                                               (9, None, 128, 256), (16, None, 256, 512), (8, 1, 256, 512)])   # slots to spare
 def test_prefetch_overwrite_matches_all_resident(torch_gpu, n_slots, group, d, F):
     """The pre-routed share (rows arrive with their expert ids, some experts live in pinned host
     memory): with every expert resident, with a slot per host expert, and with fewer slots than
