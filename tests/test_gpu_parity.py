@@ -979,6 +979,59 @@ def test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, polic
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
 
 
+@pytest.mark.parametrize("rows,d,F,act", [([40, 70], 100, 4096, "relu"), ([300, 17], 68, 4096, "swiglu"), ([64], 36, 160, "swiglu")])
+def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
+    """Infinities, NaN, the largest values and very small ones come out of the products as fp32 arithmetic has them, and leave the
+    other rows alone (the kernels multiply by bf16 parts where the values allow it)."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    wl = W.WORKLOADS["c1"].scaled(T=A, d=d, F=F, E=E, k=1, act=act, skew="uniform")
+    _note("fp32 extremes A=%d d=%d F=%d %s" % (A, d, F, act))
+    inp = W.make_inputs(wl)
+    layer = make_layer(wl, {n: v for n, v in inp.items() if n != "W_g"})
+    ids = _few(rows).reshape(A, 1)
+    p = O.permute(ids, E)
+    xp = O.gather_rows(inp["x"], p["perm"], 1)
+    xp[1, 3] = np.inf
+    xp[5] = np.nan
+    xp[9] *= np.float32(2.0 ** -100)
+    xp[20] = np.float32(3.4e38) / np.float32(64) * np.sign(xp[20])
+    xp[21] = 0
+    xp[21, 0] = np.float32(3.4028234e38)
+    xp[22] *= np.float32(2.0 ** -128)
+    for dst, src in ((layer.expert_idx, ids), (layer.x_perm, xp), (layer.counts, p["counts"]), (layer.offsets, p["offsets"])):
+        dst.copy_(to_device(src, layer.device))
+    layer.plan()
+    layer.ffn()
+    torch.cuda.synchronize()
+    # the first product as the kernels have stored it: bound of an fp32 sum of d terms on the absolute products, and of bits
+    # below the smallest normal number
+    h = to_numpy(layer.h)
+    e = np.repeat(np.arange(E), rows)
+    ex = {n: np.asarray(v, dtype=np.float64) for n, v in expert_dict(wl, inp).items()}
+    x64 = xp.astype(np.float64)
+    with np.errstate(all="ignore"):
+        prod = {n: np.stack([x64[i] @ ex[n][e[i]] for i in range(A)]) for n in ex if n in ("W1", "Wg", "Wu")}
+        size = {n: np.stack([np.abs(x64[i]) @ np.abs(ex[n][e[i]]) for i in range(A)]) for n in prod}
+    first = "W1" if act == "relu" else "Wg"
+    if act == "relu":
+        fits = np.abs(size["W1"]) < 3e38
+        want, room = np.maximum(prod["W1"], 0), d * 2.0 ** -23 * size["W1"] + 2.0 ** -126
+        assert (np.abs(h[fits] - want[fits]) <= room[fits]).all()
+        assert (h[1][prod["W1"][1] > 0] == np.inf).all() and (h[1][prod["W1"][1] < 0] == 0).all()
+    assert np.isnan(h[5]).all() or act == "relu"       # (fmax(NaN, 0) is 0)
+    normal = np.isfinite(x64).all(axis=1) & (np.abs(x64).max(axis=1) < 100) & (np.abs(x64).max(axis=1) > 1e-3)
+    yp = O.grouped_ffn(xp[normal], np.concatenate([[0], np.cumsum([normal[e == i].sum() for i in range(E)])]), expert_dict(wl, inp), act)
+    assert max_err_over_rms(to_numpy(layer.y_perm)[normal], yp) <= TOL["f32"]
+    # small activations: the products by their own size (row 9 far above the smallest normal number, row 22 below it)
+    if act == "relu":
+        assert (np.abs(h[9] - want[9]) <= d * 2.0 ** -23 * size["W1"][9]).all()
+    else:
+        z = prod[first][9] * prod["Wu"][9] / 2           # silu(z) = z / 2 for tiny z; the product is below fp32's range
+        assert (np.abs(h[9] - z) <= 2.0 ** -126).all()
+
+
 @pytest.mark.parametrize("rows,d,F,tile_m,bins", [([300], 256, 1024, 128, 8), ([700, 10], 256, 512, 128, 8), ([900], 256, 512, 256, 8),
                                                   ([520, 33, 260], 320, 704, 128, 3), ([300, 0, 40], 512, 256, 256, 16)])
 def test_small_calls_shared_by_all_work_groups(torch_gpu, rows, d, F, tile_m, bins):
