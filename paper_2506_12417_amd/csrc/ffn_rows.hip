@@ -8,16 +8,19 @@
 // kernels give an expert to one XCD (its bin) and 128 or 256 weight rows to a work-group: with
 // eight active experts most of the chip idles.  Here a work item is 32 weight rows of one tile,
 // whatever its bin: a work-group of KS wavefronts takes it, each wavefront a KS-th of the
-// contraction; its weights go from global memory straight to registers in the matrix
-// instruction's fragment layout (16 rows x 64 bytes per load, UNROLL slices in flight per wavefront,
-// sixteen wavefronts per CU), the few activation rows come through L1/L2.  The KS partial sums
+// contraction.  Weights and activation rows are fetched in whole 128-byte lines, eight rows a load, UNROLL slices
+// in flight per wavefront and sixteen wavefronts per CU, and turned into the matrix instruction's fragment layout in a piece
+// of LDS of the wavefront's own (no barrier: a wavefront's LDS accesses keep their order).  The KS partial sums
 // are added in a fixed order through LDS.  No item shares weights with another one, so XCDs and
 // bins play no role and the grid is plain: the hardware hands out work-groups as CUs become free.
 //
-// Measured (tile kernels -> this one): d=4096 F=14336, one row on each of two experts 208 + 105 ->
-// 87 + 50 us (5.4 and 4.7 TB/s of weights); d=2048 F=1408, 46 experts of 1..23 rows 121 + 62 ->
-// 102 + 61 us; d=768 F=3072, six experts 18 + 30 -> 12 + 12 us; one expert F=5632 with 33 rows
-// 55 + 47 -> 24 + 25 us.
+// Fetched straight into fragment registers, 16 rows x 64 bytes a load, the four lanes that the vector cache serves
+// together lay on four rows: 64 look-ups a load instead of 16, which held a CU to 11 - 13 bytes a clock and the chip to
+// 5.3 TB/s at best, less wherever the items fell unevenly or an expert had more than a few rows.
+//
+// Measured (fragments from global memory -> lines through LDS): d=2048 F=1408, 46 experts of 1..23 rows and a shared expert
+// F=5632 with 33 rows 107 + 69 -> 93 + 57 us (6.2 and 5.0 TB/s of weights); d=4096 F=14336, three rows' experts 116 + 75 -> 105 + 60
+// (6.5 and 5.5); d=768 F=3072, six experts 11 + 11.5 -> 9.4 + 8.7; four experts d=1024 F=2048 of 32 rows each 10.7 + 12.6 -> 9.2 + 7.6.
 //
 // A matrix instruction takes 16 activation rows; lanes past the tile's last row load that row
 // again (rows of the product are independent, nothing is stored for them).
@@ -37,11 +40,14 @@ __device__ __forceinline__ bf16x8 load_frag(const void* base, unsigned offset) {
 
 // acc[g][h] = (16 activation rows of group g) x (16 weight rows of block h) over the slices [s0, s1)
 // of 32 terms, UNROLL slices at a time: all their loads, then their products (the other wavefronts
-// of the SIMD keep the memory busy meanwhile).
+// of the SIMD keep the memory busy meanwhile).  turn: 16 NSUB rows of 128 bytes of the wavefront's own.
 template <bool HALF_IN, int RG, int NSUB, int UNROLL>
-__device__ __forceinline__ void rows_product(const uint16_t* __restrict__ a_mat, const unsigned (&a_off)[RG],
-                                             const uint16_t* w, size_t w_step, unsigned w_off, int s0, int s1,
-                                             f32x4 (&acc)[RG][NSUB]) {
+__device__ __forceinline__ void rows_product(const uint16_t* __restrict__ a_mat, const unsigned (&a_off)[RG][2],
+                                             const uint16_t* w, size_t w_step, unsigned w_off, size_t w_eight, int s0, int s1,
+                                             f32x4 (&acc)[RG][NSUB], bf16x8* turn) {
+    static_assert(UNROLL % 2 == 0, "a line holds two slices");
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+    const int st_at = (lane >> 3) * 8 + ((lane & 7) ^ (lane >> 3)), rd_at = l16 * 8 + (lq ^ (l16 & 7));
 #pragma unroll
     for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -49,27 +55,49 @@ __device__ __forceinline__ void rows_product(const uint16_t* __restrict__ a_mat,
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[g][h][r] = 0.f;
     for (int s = s0; s < s1; s += UNROLL) {
-        bf16x8 wf[UNROLL][NSUB], af[UNROLL][RG];
+        bf16x8 wl[UNROLL / 2][NSUB][2], al[UNROLL / 2][RG][2];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int at = (s + u < s1 ? s + u : s1 - 1) * 32;   // (past the end: the last slice again, not multiplied)
+        for (int u = 0; u < UNROLL; u += 2) {
+            const int at = (s + u < s1 ? s + u : s1 - 2) * 32;   // (past the end: the last line again, not multiplied)
 #pragma unroll
-            for (int h = 0; h < NSUB; ++h) wf[u][h] = load_frag(w + h * w_step + at, w_off);
+            for (int h = 0; h < NSUB; ++h)
 #pragma unroll
-            for (int g = 0; g < RG; ++g) af[u][g] = load_frag(a_mat + at, a_off[g]);
+                for (int i = 0; i < 2; ++i) wl[u / 2][h][i] = load_frag(w + h * w_step + i * w_eight + at, w_off);
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) al[u / 2][g][i] = load_frag(a_mat + at, a_off[g][i]);
         }
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
+        for (int u = 0; u < UNROLL; u += 2) {
             if (s + u < s1) {
 #pragma unroll
-                for (int g = 0; g < RG; ++g)
+                for (int h = 0; h < NSUB; ++h)
 #pragma unroll
-                    for (int h = 0; h < NSUB; ++h)
-                        if constexpr (HALF_IN)
-                            acc[g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, af[u][g]),
-                                                                               __builtin_bit_cast(f16x8, wf[u][h]), acc[g][h], 0, 0, 0);
-                        else
-                            acc[g][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][g], wf[u][h], acc[g][h], 0, 0, 0);
+                    for (int i = 0; i < 2; ++i) turn[(h * 16 + i * 8) * 8 + st_at] = wl[u / 2][h][i];
+                bf16x8 wf[2][NSUB];
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int h = 0; h < NSUB; ++h) wf[v][h] = turn[h * 16 * 8 + (rd_at ^ (4 * v))];
+                // (two groups' lines side by side where the wavefront's piece holds them)
+#pragma unroll
+                for (int g = 0; g < RG; ++g) {
+                    bf16x8* const at = turn + 16 * NSUB * 8 + (NSUB == 2 ? g & 1 : 0) * 16 * 8;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) at[i * 8 * 8 + st_at] = al[u / 2][g][i];
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) {
+                        const bf16x8 af = at[rd_at ^ (4 * v)];
+#pragma unroll
+                        for (int h = 0; h < NSUB; ++h)
+                            if constexpr (HALF_IN)
+                                acc[g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, af),
+                                                                                   __builtin_bit_cast(f16x8, wf[v][h]), acc[g][h], 0, 0, 0);
+                            else
+                                acc[g][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wf[v][h], acc[g][h], 0, 0, 0);
+                    }
+                }
             }
         }
     }
@@ -119,7 +147,11 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(Job main, Job oth
     // 33 rows and E = 60; with the shared expert's 23 MB it reads 287 now.)
     const int n_slices = K / 32, per = (n_slices / 2 + KS - 1) / KS * 2;
     const int s0 = wave * per < n_slices ? wave * per : n_slices, s1 = s0 + per < n_slices ? s0 + per : n_slices;
-    const unsigned w_off = ((unsigned)l16 * (unsigned)K + (unsigned)lq * 8u) * 2u;
+    const unsigned w_off = ((unsigned)(lane >> 3) * (unsigned)K + (unsigned)(lane & 7) * 8u) * 2u;      // eight rows' lines a load
+    // (a wavefront's lines turn where its sums will be.  Rows of eight 16-byte pieces, piece p of row r at position p ^ (r & 7):
+    // no bank conflicts either way)
+    bf16x8* const turn = (bf16x8*)&part[wave][0][0];
+    static_assert(sizeof part[0] >= (16 * NSUB + 16 * NSUB) * 128 && sizeof part[0] % 16 == 0, "");
 
     // (The tile is read after the number of tiles, although both latencies pass before the weights can
     // be asked for: a table kept by its owner may end with its last tile.)
@@ -140,18 +172,20 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(Job main, Job oth
             const int left = rc - r0;
             auto multiply = [&](auto groups, auto unroll) __attribute__((always_inline)) {
                 constexpr int RG = decltype(groups)::value;
-                unsigned a_off[RG];
+                unsigned a_off[RG][2];
 #pragma unroll
-                for (int g = 0; g < RG; ++g) {
-                    const int r = g * 16 + l16 < left ? g * 16 + l16 : left - 1;
-                    unsigned src = (unsigned)(row0 + r0 + r);
-                    if constexpr (GATHER) {
-                        if (row_token) src = (unsigned)row_token[src] / (unsigned)a_div;
+                for (int g = 0; g < RG; ++g)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int at = g * 16 + i * 8 + (lane >> 3), r = at < left ? at : left - 1;
+                        unsigned src = (unsigned)(row0 + r0 + r);
+                        if constexpr (GATHER) {
+                            if (row_token) src = (unsigned)row_token[src] / (unsigned)a_div;
+                        }
+                        a_off[g][i] = (src * (unsigned)K + (unsigned)(lane & 7) * 8u) * 2u;
                     }
-                    a_off[g] = (src * (unsigned)K + (unsigned)lq * 8u) * 2u;
-                }
                 f32x4 acc[RG][NSUB];
-                rows_product<HALF_IN, RG, NSUB, decltype(unroll)::value>(a_mat, a_off, w, w_step, w_off, s0, s1, acc);
+                rows_product<HALF_IN, RG, NSUB, decltype(unroll)::value>(a_mat, a_off, w, w_step, w_off, (size_t)8 * K, s0, s1, acc, turn);
 #pragma unroll
                 for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -160,9 +194,9 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_rows_kernel(Job main, Job oth
                         for (int r = 0; r < 4; ++r) part[wave][g * 16 + 4 * lq + r][h * 16 + l16] = acc[g][h][r];
             };
             if (left <= 16) multiply(std::integral_constant<int, 1>{}, std::integral_constant<int, UNROLL>{});
-            else if (left <= 32) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, UNROLL / 2>{});
-            else if (left <= 48) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, UNROLL / 2>{});
-            else multiply(std::integral_constant<int, 4>{}, std::integral_constant<int, UNROLL / 2>{});
+            else if (left <= 32) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, UNROLL / 4 * 2>{});
+            else if (left <= 48) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, UNROLL / 4 * 2>{});
+            else multiply(std::integral_constant<int, 4>{}, std::integral_constant<int, UNROLL / 4 * 2>{});
             // (fetched while the other wavefronts finish: the place of this thread's first row)
             const int rows = left < RGMAX * 16 ? left : RGMAX * 16;
             unsigned tok = 0;
