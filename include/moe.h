@@ -317,10 +317,10 @@ MOE_API int moe_ffn_pick_tile_m(moe_dtype dt, int A, int E);
  * 128 x 128 (a third less LDS traffic per multiply-add, which is what the arithmetic-bound case
  * pays for; d and F multiples of 64, at least 256).  The four wavefronts are the default; only
  * they offer the row gather of moe_grouped_ffn_fused at this height.
- * Calls with a handful of rows per expert (decode steps) go, by default and with 128-row tiles, to
- * a third family that shares an expert's weights out over the whole chip whatever the plan's bins;
+ * Calls with a handful of rows per expert (decode steps), or of few multiply-adds altogether, go, by default and with
+ * 128-row tiles, to a third family that shares an expert's weights out over the whole chip whatever the plan's bins;
  * it sums the contraction in parts, so its last bits differ from the other two: a row's last bits
- * depend on whether the call it is in has that few rows.  (Modes 1 and 2 use neither this family nor pairs.)
+ * depend on whether the call it is in is that small.  (Modes 1 and 2 use neither this family nor pairs.)
  * moe_ffn_kernel_mode sets the choice for the process -- 0 default, 1 the LDS ring with eight
  * wavefronts at both heights, 2 the streaming kernels wherever they cover a call of 128-row tiles and else
  * the LDS ring (256 rows as by default), -1 leaves it -- and returns the previous setting (a negative moe_status on a bad argument).  For

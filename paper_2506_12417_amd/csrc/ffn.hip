@@ -50,25 +50,28 @@ extern "C" int moe_ffn_kernel_mode(int mode) {
 }
 
 // Whether the few-row kernels (ffn_rows.hip) serve a plan of 128-row tiles.  A product is then the
-// fetch of the active experts' weights; the tile kernels fetch an expert through one XCD, the
-// few-row kernels through the whole chip, but these read the rows again for every 32 weight rows.
-// Measured (both products, few-row against tile kernels): with more experts than XCDs they win up
-// to about three rows per expert (d=2048 F=1408 E=60: 163 : 184 us at 2.2 rows, 197 : 197 at 4.3;
-// d=768 F=3072 E=128: 158 : 171 at 2, 210 : 193 at 4), with one expert per XCD up to two (d=4096
-// F=14336 E=8: 347 : 348 us at 2, 490 : 445 at 4), and with fewer experts than XCDs up to the row
-// count at which the idle XCDs are made up for (d=2048 F=5632, E=4: 98 : 112 us at 32 rows, 141 :
-// 121 at 64; E=1: 64 : 102 us at 64 rows, 124 : 113 at 128).
-static bool few_rows_per_expert(int A, int E) {
-    if (A <= (E >= 16 ? 3 : 2) * E) return true;
-    if (E >= 8) return false;
-    return A <= 64 * E && (long long)A * E <= 32ll * (8 - E) * E;
+// fetch of the active experts' weights; the tile kernels fetch an expert through one XCD and one stage after the
+// other, the few-row kernels through the whole chip, but these read the rows again for every 32 weight rows.
+// What that costs grows with the multiply-adds of a call, what the tile kernels lose is 15 - 20 us a product where the
+// weights are small; where both stream at the memory's rate the rows per expert decide.  flops: of both products.
+// Measured (both products, few-row against tile kernels):
+//   flops      1024 x 2048, E=16: 2.1 GFLOP (16 rows each) 36 : 45 us, 4.3 46 : 49, 6.4 52 : 51; 512 x 1024 SwiGLU, E=48: 3.8 44 : 45,
+//              5.7 50 : 47; 1024 x 1024, E=100: 1.7 69 : 90, 6.7 94 : 97; 2560 x 512, E=24: 1.0 36 : 59; 1536 x 4096 SwiGLU, E=8: 7.5 74 :
+//              79, 11 87 : 81; 1024 x 2048, E=4: 4.3 (128 rows each) 35 : 45, 8.6 47 : 50; one expert 2048 x 5632: 2.3 27 : 69,
+//              8.9 52 : 81
+//   rows       768 x 3072, E=128: 3 rows 165 : 173, 4 183 : 183, 6 208 : 197; 2048 x 1408 SwiGLU, E=60: 8 rows 181 : 198, 17 202 : 201;
+//              4096 x 14336 SwiGLU, E=8: 8 rows 468 : 470, 12 474 : 457
+static bool few_rows_per_expert(int A, int E, double flops, bool glu) {
+    return flops <= (E <= 8 ? 8e9 : 4.5e9) || A <= (long long)(glu ? 8 : 3) * E;
 }
 
 // the plan's tile height of a tile_m argument
 static int tile_height(int tile_m) { return tile_m & ~MOE_TILE_WHOLE_PLAN; }
 
-static bool few_rows_call(int A, int d, int F, int E, int tile_m) {
-    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E) && (long long)A * (d > F ? d : F) < (1ll << 31);
+static bool few_rows_call(int A, int d, int F, int E, moe_act act, int tile_m) {
+    const bool glu = act == MOE_SWIGLU;
+    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E, 2.0 * A * d * F * (glu ? 3 : 2), glu) &&
+           (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 
 // Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels (for a plan of all A
@@ -98,7 +101,7 @@ static int wide_pairs(int A, int E, int K, int N) {
 }
 
 extern "C" int moe_ffn_pairs(int tile_m, int A, int E, int K, int N) {
-    return tile_m == (128 | MOE_TILE_WHOLE_PLAN) && A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && !few_rows_per_expert(A, E) && wide_pairs(A, E, K, N) != 0;
+    return tile_m == (128 | MOE_TILE_WHOLE_PLAN) && A >= 1 && E >= 1 && K % 64 == 0 && N >= 1 && wide_pairs(A, E, K, N) != 0;
 }
 
 // Whether nearly every expert fits one 128-row tile, so that the tile kernels read its weights once.
@@ -146,7 +149,7 @@ static int grouped_ffn_impl(int phases, const void* x_perm, int A, int d, int F,
         const bool streaming = tile_m == 128 && g_kernel_mode == 2;
         auto stream = [&](int epi, int K) { return streaming && moe_gemm_stream_supports(epi, K); };
         auto stream_narrow = [&](int N) { return tiles_est * ((N + 255) / 256) < 4 * MOE_GEMM_GRID; };
-        const bool rows = few_rows_call(A, d, F, E, tile_m);
+        const bool rows = few_rows_call(A, d, F, E, act, tile_m);
         // 256-row tiles (many rows per expert: the arithmetic-bound case) go to the four-wavefront
         // kernels of ffn_wide.hip unless the LDS-ring kernels are asked for (moe_ffn_kernel_mode 1), 128-row
         // tiles where taking them in pairs pays.
@@ -351,7 +354,7 @@ static int shared_impl(int phases, const void* x, int T, int d, int F, int E, in
                        int32_t* s_plan_hdr, int s_tile_m, void* s_h_scratch, float* s_y, void* stream) {
     MOE_REQUIRE(k >= 2, MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_shared: needs k >= 2 (k=%d)", k);
     const bool rows = dt == MOE_BF16 && act == MOE_SWIGLU && T >= 1 && E >= 1 && k >= 2 && (long long)T * k < (1ll << 30) &&
-                      few_rows_call(T * k, d, F, E, tile_m) && few_rows_call(T, d, shared_F, 1, s_tile_m);
+                      few_rows_call(T * k, d, F, E, act, tile_m) && few_rows_call(T, d, shared_F, 1, MOE_SWIGLU, s_tile_m);
     MOE_REQUIRE(T <= 0 || (x && w_in && w_out && y_perm && s_w_in && s_w_out && s_y), MOE_ERR_ARG, "moe_grouped_ffn_shared: null pointer");
     auto routed = [&](int p) {
         return fused_impl(p, x, T, d, F, E, k, act, dt, w_in, w_out, tiles, plan_hdr, tile_m, h_scratch, perm, nullptr, y_perm, stream);

@@ -1032,6 +1032,43 @@ def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
         assert (np.abs(h[9] - z) <= 2.0 ** -126).all()
 
 
+@pytest.mark.parametrize("rows,d,F,act", [([300], 256, 1024, "relu"), ([700, 10], 256, 512, "relu"), ([520, 33, 260], 320, 704, "swiglu"),
+                                          ([128, 127, 65, 0, 129, 17, 48, 1, 64], 192, 576, "swiglu"), ([40] * 20, 256, 256, "relu")])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_small_calls_by_either_family(torch_gpu, rows, d, F, act, mode):
+    """Calls of few multiply-adds with more than a handful of rows per expert: the few-row kernels, which take them by default
+    (several passes of 64 rows, full tiles), and the tile kernels (mode 1) against the oracle; fused against separate calls."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    wl = W.WORKLOADS["c2"].scaled(T=A, d=d, F=F, E=E, k=1, act=act, skew="uniform")
+    _note("small calls rows %s d=%d F=%d %s mode %d" % (rows, d, F, act, mode))
+    inp = W.make_inputs(wl)
+    before = B.moe_ffn_kernel_mode(-1)
+    try:
+        B.moe_ffn_kernel_mode(mode)
+        layer = make_layer(wl, inp, tile_m=128)
+        ids = _few(rows).reshape(A, 1)
+        layer.expert_idx.copy_(to_device(ids, layer.device))
+        layer.gate_w.fill_(1.0)
+        x = layer_x(layer, inp)
+        y = layer.forward(x, routed=True).clone()
+        layer.permute(x)
+        layer.plan()
+        layer.y_perm.fill_(float("nan"))
+        layer.ffn()
+        layer.combine()
+        torch.cuda.synchronize()
+    finally:
+        B.moe_ffn_kernel_mode(before)
+    p = O.permute(ids, E)
+    yp = O.grouped_ffn(O.gather_rows(inp["x"], p["perm"], 1), p["offsets"], expert_dict(wl, inp), act, h_round="f16")
+    assert max_err_over_rms(to_numpy(layer.y_perm), yp) <= 1e-3      # (as in _stage_check)
+    assert torch.equal(y, layer.y)
+    assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
+
+
 @pytest.mark.parametrize("rows,d,F,tile_m,bins", [([300], 256, 1024, 128, 8), ([700, 10], 256, 512, 128, 8), ([900], 256, 512, 256, 8),
                                                   ([520, 33, 260], 320, 704, 128, 3), ([300, 0, 40], 512, 256, 256, 16)])
 def test_small_calls_shared_by_all_work_groups(torch_gpu, rows, d, F, tile_m, bins):
