@@ -5,8 +5,8 @@
 //
 // Two kernels.  gemm_f32_split_kernel multiplies by bf16 matrix instructions, which run at 16 times the rate of the fp32 ones:
 // every operand is cut into three bf16 parts that add up to it exactly, and six of the nine products of parts are summed in
-// fp32 (the other three are below 2^-26 of a term).  gemm_f32_kernel, for items too few and small for that, multiplies by
-// v_mfma_f32_32x32x2_f32 like an fma chain.
+// fp32 (the other three are below 2^-26 of a term).  gemm_f32_rows_kernel, for calls too small for that, multiplies by
+// v_mfma_f32_16x16x4_f32, the contraction in four or eight parts.
 //
 // Items in both: a tile and a block of weight rows, one work-group each, which the hardware starts where one has finished; the
 // plan's bins, equal in rows but not in tiles, play no role (28 % of the CU time was idle with them).
@@ -18,7 +18,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
@@ -26,32 +25,43 @@ constexpr int BM = 64, BK = 32, PIECES = BK / 4;
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
-// Items of 32 weight rows whose stages of 32 terms are shared by four wavefronts, a quarter of the terms each (their sums meet in
-// LDS): for products whose wider items would leave CUs idle, where a stage's latency is what counts.  A stage is held in two
-// LDS buffers, the next one on its way in registers; one barrier per stage.  A wavefront takes both 32-row blocks of the tile.
+// Few multiply-adds, or few rows per expert: a call's time is the latency of one item, or the fetch of the weights.  An item is
+// 16 NSUB weight rows of a tile; its KS wavefronts share the contraction out, a run of whole 128-byte lines each, UNROLL lines
+// of every operand row in flight and sixteen wavefronts on a CU.  The lines are turned into the matrix instruction's fragments
+// in a piece of LDS of the wavefront's own (no barrier), and the partial sums meet in LDS in a fixed order.
+// (A work-group that staged 32 terms of all rows at a time, the next ones on their way, spent 0.55 us a stage however little was
+// in it.  Measured, that -> this: one token, d=296 F=1984, E=8, k=2: 8.5 + 30 -> 4.9 + 7.5 us; 79 tokens, d=72 F=1408, E=4 7.2 + 29
+// -> 6.5 + 13; 200 tokens, d=1024 F=2048, E=8 39 + 57 -> 31 + 31; 12 tokens, d=816 F=576, E=4, SwiGLU 18 + 12.6 -> 8.2 + 4.8.)
+// Bound by latency in small calls; with tens of rows per expert by the fp32 instructions, 45 - 50 TFLOP/s.  Tried: sixteen
+// wavefronts per item, tiles in parts of 16 or 32 rows: no faster, twice as slow where there are many items.
+// Error of a layer against 64 bits 1.2 - 2.0e-7 of the result's norm; by a single chain of each wavefront's terms 1.5 - 3e-7.
 //
-// LDS: a row holds 32 terms in eight 16-byte pieces, piece p at position p ^ ((row / 2) & 7): 16
-// consecutive rows' pieces touch every bank once.  Lane (l32, lhi) reads piece 2 q + lhi and feeds its
-// four terms to four matrix instructions: which term goes to which of the two k slots is free as
-// long as both operands agree.
-template <int EPI>
-__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restrict__ a_mat, int K, int N,
-                                                           const void* const* __restrict__ w_ptrs,
-                                                           const moe_tile* __restrict__ tiles,
-                                                           const int32_t* __restrict__ hdr, float* __restrict__ out, int ld_out,
-                                                           const int32_t* __restrict__ row_src, int src_div) {
-    constexpr int KSP = 4, NTH = KSP * 64, BN = 32;
-    constexpr int AL = BM * PIECES / NTH, BL = BN * PIECES / NTH;       // 16-byte pieces per thread and stage
-    __shared__ f32x4 lds[2][(BM + BN) * PIECES];
+// LDS: a row's line is eight 16-byte pieces, piece p at position p ^ (row & 7) (no bank conflicts).  Lane (l16, lq) reads pieces
+// lq and 4 + lq and feeds their four terms to four matrix instructions each (both operands agree on the order of the terms).
+template <int EPI, int KS, int NSUB>
+__global__ __launch_bounds__(KS * 64, 4) void gemm_f32_rows_kernel(const float* __restrict__ a_mat, int K, int N,
+                                                                   const void* const* __restrict__ w_ptrs,
+                                                                   const moe_tile* __restrict__ tiles,
+                                                                   const int32_t* __restrict__ hdr, float* __restrict__ out, int ld_out,
+                                                                   const int32_t* __restrict__ row_src, int src_div) {
+    constexpr bool GLU = EPI == MOE_EPI_SWIGLU;
+    constexpr int NTH = KS * 64, COLS = 16 * NSUB, OUT = GLU ? 16 : COLS;
+    static_assert(!GLU || NSUB == 2, "a gate and an up block");
+    // (a wave-uniform base and 32-bit byte offsets: the launch sees to it that they suffice)
+    auto fetch = [](const float* base, unsigned offset) __attribute__((always_inline)) {
+        typedef const __attribute__((address_space(1))) unsigned char* gbytes;
+        return *(const __attribute__((address_space(1))) f32x4*)((gbytes)(uintptr_t)base + offset);
+    };
+    __shared__ __attribute__((aligned(16))) float part[KS][BM][COLS + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, lhi = lane >> 5;
-    const int wk = wave;
-    const int ld_row = tid / PIECES, ld_p = tid % PIECES;               // pass i: row ld_row + i * NTH / PIECES
-    constexpr int ROWS = NTH / PIECES;
-    static_assert(ROWS % 16 == 0, "the swizzle repeats every 16 rows");
-    const int st_at = ld_row * PIECES + (ld_p ^ ((ld_row >> 1) & 7));
-    const int rd_swz = (l32 >> 1) & 7;
-    const int n_cb = (N + BN - 1) / BN, KT = (K + BK - 1) / BK;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int st_row = lane >> 3, st_p = lane & 7, st_at = st_row * PIECES + (st_p ^ st_row), rd_at = l16 * PIECES + (lq ^ (l16 & 7));
+    f32x4* const turn = (f32x4*)&part[wave][0][0];
+    static_assert(sizeof part[0] >= (16 * NSUB + 16) * 128 && sizeof part[0] % 16 == 0, "a wavefront's lines turn where its sums will be");
+    const int n_cb = GLU ? N / 32 : (N + COLS - 1) / COLS;
+    const int n_lines = (K + BK - 1) / BK, per = (n_lines + KS - 1) / KS;
+    const int s0 = wave * per < n_lines ? wave * per : n_lines, s1 = s0 + per < n_lines ? s0 + per : n_lines;
+    const bool ragged = K % BK != 0;
 
     const int n_items = hdr[0] * n_cb;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
@@ -59,101 +69,127 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restric
         const moe_tile t = tiles[ti];
         const int rc = __builtin_amdgcn_readfirstlane(t.row_count < BM ? t.row_count : BM);
         if (rc <= 0) continue;
-        const int n0 = cb * BN;
-        // (rows past the tile's end and weight rows past N are the last ones again: never stored)
-        const float* a_src[AL];
-        const float* b_src[BL];
+        // SwiGLU: blocks of 32 gate and 32 up rows alternate; an item takes a half of each
+        const int p0 = GLU ? (cb >> 1) * 64 + (cb & 1) * 16 : cb * COLS, w_step = GLU ? 32 : 16;
+        const float* w_mat = (const float*)w_ptrs[__builtin_amdgcn_readfirstlane(t.expert)];
+        unsigned w_src[NSUB][2];
 #pragma unroll
-        for (int i = 0; i < AL; ++i) {
-            const int r = ld_row + i * ROWS;
-            int row = t.row_begin + (r < rc ? r : rc - 1);
-            if (row_src) row = (int)((unsigned)row_src[row] / (unsigned)src_div);     // (the rows of x brought into expert order here)
-            a_src[i] = a_mat + (size_t)row * K;
-        }
+        for (int h = 0; h < NSUB; ++h)
 #pragma unroll
-        for (int i = 0; i < BL; ++i) {
-            const int r = n0 + ld_row + i * ROWS;
-            b_src[i] = (const float*)w_ptrs[t.expert] + (size_t)(r < N ? r : N - 1) * K;
-        }
-        f32x4 av[AL], bv[BL];
-        auto load = [&](int kt) __attribute__((always_inline)) {
-            const int k = kt * BK + ld_p * 4, at = k < K ? k : K - 4;   // (K is a multiple of 4)
-#pragma unroll
-            for (int i = 0; i < AL; ++i) av[i] = *(const __attribute__((address_space(1))) f32x4*)(uintptr_t)(a_src[i] + at);
-#pragma unroll
-            for (int i = 0; i < BL; ++i) bv[i] = *(const __attribute__((address_space(1))) f32x4*)(uintptr_t)(b_src[i] + at);
-        };
-        auto store = [&](int kt) __attribute__((always_inline)) {
-            f32x4* buf = lds[kt & 1];
-            if (kt + 1 == KT && kt * BK + ld_p * 4 >= K) {              // (terms past K count as zero on both sides)
-                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < AL; ++i) av[i] = zero;
-#pragma unroll
-                for (int i = 0; i < BL; ++i) bv[i] = zero;
+            for (int i = 0; i < 2; ++i) {
+                const int r = p0 + h * w_step + i * 8 + st_row;
+                w_src[h][i] = (unsigned)(r < N ? r : N - 1) * (unsigned)K * 4u;
             }
+        auto multiply = [&](auto groups, auto unroll) __attribute__((always_inline)) {
+            constexpr int RG = decltype(groups)::value, UNROLL = decltype(unroll)::value;
+            unsigned a_src[RG][2];
 #pragma unroll
-            for (int i = 0; i < AL; ++i) buf[st_at + i * ROWS * PIECES] = av[i];
+            for (int g = 0; g < RG; ++g)
 #pragma unroll
-            for (int i = 0; i < BL; ++i) buf[(BM + i * ROWS) * PIECES + st_at] = bv[i];
-        };
-        f32x16 acc[2];
+                for (int i = 0; i < 2; ++i) {
+                    const int r = g * 16 + i * 8 + st_row;
+                    int row = t.row_begin + (r < rc ? r : rc - 1);
+                    if (row_src) row = (int)((unsigned)row_src[row] / (unsigned)src_div);
+                    a_src[g][i] = (unsigned)row * (unsigned)K * 4u;
+                }
+            f32x4 acc[RG][NSUB];
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+            for (int g = 0; g < RG; ++g)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
-        load(0);
-        store(0);
-        auto multiply = [&](auto second) __attribute__((always_inline)) {
-            for (int kt = 0; kt < KT; ++kt) {
-                __syncthreads();                                        // stage kt is complete, stage kt - 1 has been read
-                load(kt + 1 < KT ? kt + 1 : kt);                        // (without a condition: the last step's is not used)
-                const f32x4* buf = lds[kt & 1];
+                for (int h = 0; h < NSUB; ++h)
 #pragma unroll
-                for (int q0 = 0; q0 < PIECES / 2 / KSP; ++q0) {
-                    const int at = (2 * (wk * (PIECES / 2 / KSP) + q0) + lhi) ^ rd_swz;
-                    const f32x4 b = buf[(BM + l32) * PIECES + at];
-                    const f32x4 a0 = buf[l32 * PIECES + at], a1 = buf[(32 + l32) * PIECES + at];
+                    for (int r = 0; r < 4; ++r) acc[g][h][r] = 0.f;
+            for (int s = s0; s < s1; s += UNROLL) {
+                f32x4 wl[UNROLL][NSUB][2], al[UNROLL][RG][2];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[j], b[j], acc[0], 0, 0, 0);
-                        if constexpr (decltype(second)::value)
-                            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[j], b[j], acc[1], 0, 0, 0);
+                for (int u = 0; u < UNROLL; ++u) {
+                    const int line = s + u < s1 ? s + u : s1 - 1;       // (past the end: the last line again, not multiplied)
+                    const int k = line * BK + st_p * 4, at = (k < K ? k : K - 4) * 4;
+#pragma unroll
+                    for (int h = 0; h < NSUB; ++h)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) wl[u][h][i] = fetch(w_mat, w_src[h][i] + (unsigned)at);
+#pragma unroll
+                    for (int g = 0; g < RG; ++g)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) al[u][g][i] = fetch(a_mat, a_src[g][i] + (unsigned)at);
+                }
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u) {
+                    if (s + u >= s1) continue;
+                    if (ragged && s + u + 1 == n_lines) {               // (terms past K count as zero on both sides)
+                        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                        const bool past = (s + u) * BK + st_p * 4 >= K;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                            for (int h = 0; h < NSUB; ++h) wl[u][h][i] = past ? zero : wl[u][h][i];
+#pragma unroll
+                            for (int g = 0; g < RG; ++g) al[u][g][i] = past ? zero : al[u][g][i];
+                        }
+                    }
+#pragma unroll
+                    for (int h = 0; h < NSUB; ++h)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) turn[(h * 16 + i * 8) * PIECES + st_at] = wl[u][h][i];
+                    f32x4 wf[2][NSUB];
+#pragma unroll
+                    for (int v = 0; v < 2; ++v)
+#pragma unroll
+                        for (int h = 0; h < NSUB; ++h) wf[v][h] = turn[h * 16 * PIECES + (rd_at ^ (4 * v))];
+#pragma unroll
+                    for (int g = 0; g < RG; ++g) {
+                        f32x4* const at = turn + 16 * NSUB * PIECES + (NSUB == 2 ? g & 1 : 0) * 16 * PIECES;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) at[i * 8 * PIECES + st_at] = al[u][g][i];
+#pragma unroll
+                        for (int v = 0; v < 2; ++v) {
+                            // (16 terms at a time, added to the sum as one: half the rounding error of a single chain)
+                            const f32x4 af = at[rd_at ^ (4 * v)];
+                            f32x4 sixteen[NSUB];
+#pragma unroll
+                            for (int h = 0; h < NSUB; ++h) sixteen[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                                for (int h = 0; h < NSUB; ++h)
+                                    sixteen[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[j], wf[v][h][j], sixteen[h], 0, 0, 0);
+#pragma unroll
+                            for (int h = 0; h < NSUB; ++h)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) acc[g][h][r] += sixteen[h][r];
+                        }
                     }
                 }
-                // (nothing of the store may move up: it would wait for loads that have this whole step to arrive)
-                __builtin_amdgcn_sched_barrier(0);
-                store(kt + 1);
             }
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int h = 0; h < NSUB; ++h)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part[wave][g * 16 + 4 * lq + r][h * 16 + l16] = acc[g][h][r];
         };
-        if (rc > 32) multiply(std::true_type{});                        // (the second 32-row block holds rows)
-        else multiply(std::false_type{});
-        // acc[m][r]: row 32 m + 8 (r / 4) + 4 lhi + r % 4, weight row l32
-        float* meet = (float*)&lds[0][0];                               // (the stages have been read)
-        static_assert((KSP - 1) * 32 * 64 * 4 <= (int)sizeof lds, "the parts meet in the stages' memory");
+        // (lines in flight as the registers allow: 128 of them, with sixteen wavefronts on a CU)
+        constexpr int ONE = NSUB == 1;
+        if (rc <= 16) multiply(std::integral_constant<int, 1>{}, std::integral_constant<int, 3 + ONE>{});
+        else if (rc <= 32) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, 2 + ONE>{});
+        else if (rc <= 48) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, 1 + ONE>{});
+        else multiply(std::integral_constant<int, 4>{}, std::integral_constant<int, 1 + ONE>{});
         __syncthreads();
-        if (wk) {
+        auto total = [&](int r, int c) __attribute__((always_inline)) {
+            float v = part[0][r][c];
 #pragma unroll
-            for (int r = 0; r < 32; ++r) meet[(wk - 1) * (32 * 64) + r * 64 + lane] = acc[r >> 4][r & 15];
+            for (int p = 1; p < KS; ++p) v += part[p][r][c];
+            return v;
+        };
+        for (int i = tid; i < rc * OUT; i += NTH) {
+            const int r = i / OUT, c = i % OUT, col = GLU ? cb * 16 + c : p0 + c;
+            float v = total(r, c);
+            if constexpr (GLU) v = silu_f(v) * total(r, 16 + c);
+            else if constexpr (EPI == MOE_EPI_RELU) v = fmaxf(v, 0.f);
+            if (GLU || col < N) out[(size_t)(t.row_begin + r) * ld_out + col] = v;
         }
         __syncthreads();
-        if (!wk) {
-#pragma unroll
-            for (int p = 0; p < KSP - 1; ++p)
-#pragma unroll
-                for (int r = 0; r < 32; ++r) acc[r >> 4][r & 15] += meet[p * (32 * 64) + r * 64 + lane];
-        }
-        if (n0 + l32 < N && !wk) {
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = m * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-                    if (row < rc)
-                        out[(size_t)(t.row_begin + row) * ld_out + n0 + l32] = EPI == MOE_EPI_RELU ? fmaxf(acc[m][r], 0.f) : acc[m][r];
-                }
-        }
-        __syncthreads();                                                // the next item refills the first buffer
     }
 }
 
@@ -431,9 +467,9 @@ struct Args {
 };
 
 // one work-group per item of the tiles there usually are (the device alone knows; they loop if there are more)
+long long tiles_there_are(const Args& g) { return g.A < g.E + g.A / BM ? g.A : g.E + g.A / BM; }
 unsigned grid_of(const Args& g, int bn) {
-    const long long tiles_est = g.A < g.E + g.A / BM ? g.A : g.E + g.A / BM;
-    const long long items = tiles_est * ((g.N + bn - 1) / bn);
+    const long long items = tiles_there_are(g) * ((g.N + bn - 1) / bn);
     return (unsigned)(items < (1 << 20) ? (items + 7) / 8 * 8 : 1 << 20);
 }
 
@@ -446,9 +482,28 @@ int launch_split(const Args& g, hipStream_t st) {
 }
 
 template <int EPI>
-int launch_fma(const Args& g, hipStream_t st) {
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI>), dim3(grid_of(g, 32)), dim3(256), 0, st, (const float*)g.a, g.K, g.N, g.w, g.tiles,
-                       g.hdr, (float*)g.out, g.ld_out, g.row_src, g.src_div);
+int launch_rows(const Args& g, hipStream_t st) {
+    auto go = [&](auto ks, auto nsub) {
+        constexpr int KS = decltype(ks)::value, NSUB = decltype(nsub)::value;
+        hipLaunchKernelGGL((gemm_f32_rows_kernel<EPI, KS, NSUB>), dim3(grid_of(g, 16 * NSUB)), dim3(KS * 64), 0, st, (const float*)g.a, g.K, g.N,
+                           g.w, g.tiles, g.hdr, (float*)g.out, g.ld_out, g.row_src, g.src_div);
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    const std::integral_constant<int, 4> four{};
+    const std::integral_constant<int, 8> eight{};
+    // Items of 32 weight rows where those of 16 would be four per CU and more (304 tokens, K = 80, N = 1600 13.4 us by 16, 10.6 by 32;
+    // 306 items of K = 1696 25 by 32, 19 by 16).  Eight wavefronts where they have two lines each at least and few items (19 items,
+    // K = 1984: 7.9 and 6.8; N = 64, K = 2048: 14.0 and 11.3) or SwiGLU's wide items (K = 1000: 57 and 55; K = 256: 30 and 39).
+    if constexpr (EPI == MOE_EPI_SWIGLU) {
+        if (g.K >= 512) go(eight, two);
+        else go(four, two);
+    } else {
+        const long long items = tiles_there_are(g) * ((g.N + 15) / 16);
+        if (items < 64 && g.K >= 1024) go(eight, one);
+        else if (items < 4 * 256) go(four, one);
+        else go(four, two);
+    }
     MOE_CHECK_LAUNCH("moe_grouped_ffn (fp32 GEMM)");
     return MOE_OK;
 }
@@ -458,14 +513,21 @@ int launch_fma(const Args& g, hipStream_t st) {
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                         const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
     // Column blocks of 128 weight rows read the activations half as often; of 64 where 128 would leave fewer than four items
-    // per CU; of 32 by fp32 instructions where 64 would leave fewer than two (without SwiGLU, which needs a gate and an up block): 256
-    // rows, second product of K = 512, N = 256 14.6 us by 64 weight rows, 10.9 by 32; 60 rows of 32 experts, K = 512, N = 504
-    // 18 us by the split kernel with 32 weight rows, 13; 400 tokens twice, K = 1024, N = 512 36 and 34.
+    // per CU.  The few-row kernel where 64 would leave fewer than two (one with SwiGLU), or the experts hold few rows.  By the split
+    // kernel and by it, in us: 600 tokens, K = N = 1024, E = 4, k = 2 (320 items of 64) 51 and 42; 2000 tokens, K = 1024, N = 128 27 and 23;
+    // 1300 tokens, K = N = 1024, E = 8 37 and 40; 1000 tokens of 32 experts, K = 2048, N = 512 65 and 45; 2000 tokens twice, K = 256, N = 512,
+    // E = 16 (250 rows per expert) 18 and 20.  With SwiGLU (N: gate and up) 250 tokens, K = 1024, N = 1024, E = 4 27 and 16; 40 tokens
+    // twice, K = 1024, N = 4096, E = 32 102 and 73; 120 twice, K = 1000, N = 3072, E = 16 53 and 56; 2000, K = 512, N = 640, E = 8 (360 items) 23 and 28.
     const Args g = {a, A, K, N, E, w, tiles, hdr, out, ld_out, row_src, src_div};
-    const long long tiles_est = (A + BM - 1) / BM + E / 2;
-    const bool narrow = tiles_est * ((N + 127) / 128) < 4 * 256, narrowest = tiles_est * ((N + 63) / 64) < 2 * 256;
-    if (epi == MOE_EPI_SWIGLU) return narrow ? launch_split<MOE_EPI_SWIGLU, 1>(g, st) : launch_split<MOE_EPI_SWIGLU, 2>(g, st);
-    if (narrowest) return epi == MOE_EPI_RELU ? launch_fma<MOE_EPI_RELU>(g, st) : launch_fma<MOE_EPI_STORE>(g, st);
+    const long long tiles_est = (A + BM - 1) / BM + E / 2, items = tiles_est * ((N + 63) / 64);
+    const bool glu = epi == MOE_EPI_SWIGLU, narrow = tiles_est * ((N + 127) / 128) < 4 * 256;
+    const bool in_reach = (long long)A * K < 1ll << 30 && (long long)N * K < 1ll << 30;     // of its 32-bit byte offsets
+    const bool rows = in_reach && (glu ? items < 256 || A <= 8ll * E : items < 2 * 256 || A <= 32ll * E);
+    if (rows) {
+        if (glu) return launch_rows<MOE_EPI_SWIGLU>(g, st);
+        return epi == MOE_EPI_RELU ? launch_rows<MOE_EPI_RELU>(g, st) : launch_rows<MOE_EPI_STORE>(g, st);
+    }
+    if (glu) return narrow ? launch_split<MOE_EPI_SWIGLU, 1>(g, st) : launch_split<MOE_EPI_SWIGLU, 2>(g, st);
     if (epi == MOE_EPI_RELU) return narrow ? launch_split<MOE_EPI_RELU, 1>(g, st) : launch_split<MOE_EPI_RELU, 2>(g, st);
     return narrow ? launch_split<MOE_EPI_STORE, 1>(g, st) : launch_split<MOE_EPI_STORE, 2>(g, st);
 }

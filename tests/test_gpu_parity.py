@@ -979,7 +979,25 @@ def test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, polic
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
 
 
-@pytest.mark.parametrize("rows,d,F,act", [([40, 70], 100, 4096, "relu"), ([300, 17], 68, 4096, "swiglu"), ([64], 36, 160, "swiglu")])
+F32_FEW_CASES = [
+    # every number of 16-row groups and their edges, contractions that end inside a line, weight blocks cut short, idle
+    # wavefronts; items of 16 weight rows by four and by eight wavefronts, of 32 by four; both of SwiGLU's; tiles of two kernels
+    ([1, 16, 17, 48, 49, 64, 65], 1, 1028, 300, "relu", 1),
+    ([3, 0, 2], 1, 2052, 20, "relu", 1),
+    ([5, 20, 33] * 8, 1, 132, 1604, "relu", 1),
+    ([33, 31, 2], 1, 100, 160, "swiglu", 1),
+    ([40, 16, 1, 47], 2, 516, 96, "swiglu", 3),
+    ([300, 500, 64], 1, 260, 1024, "swiglu", 1),
+]
+
+
+@pytest.mark.parametrize("rows,k,d,F,act,policy", F32_FEW_CASES)
+def test_f32_products_of_small_calls(torch_gpu, rows, k, d, F, act, policy):
+    test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, policy)
+
+
+@pytest.mark.parametrize("rows,d,F,act", [([40, 70], 100, 4096, "relu"), ([300, 17], 68, 4096, "swiglu"), ([64], 36, 160, "swiglu"),
+                                          ([400, 700], 100, 4096, "relu"), ([17, 40], 1028, 512, "relu")])
 def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
     """Infinities, NaN, the largest values and very small ones come out of the products as fp32 arithmetic has them, and leave the
     other rows alone (the kernels multiply by bf16 parts where the values allow it)."""
