@@ -118,6 +118,14 @@ __device__ __forceinline__ void row_best_f64(double& v, int& e, bool all) {
     }
 }
 
+// exp(v) = 2^t for t = v log2(e), with what the rounding of t took away put back (v is up to tens, so t alone costs several
+// units in the last place of the result).
+__device__ __forceinline__ float gate_exp(float v) {
+    constexpr float L = 1.44269504088896340736f, L_REST = (float)(1.44269504088896340736 - (double)L), LN2 = 0.69314718055994530942f;
+    const float t = v * L, rest = fmaf(v, L_REST, fmaf(v, L, -t)), e = __builtin_amdgcn_exp2f(t);
+    return e > 0.f ? fmaf(e, rest * LN2, e) : e;     // (rest is no number for an infinite v)
+}
+
 // LDS of the phases after the product (it reuses the memory of the operand staging).
 template <int NB, int KSP>
 struct RouteLds {
@@ -127,7 +135,7 @@ struct RouteLds {
     static constexpr int SLAB = KSP > 1 ? KSP * TB * EPT * 8 : 0;
     static constexpr int CAND = NWV * LIST * 12;
     static constexpr int REGION0 = SLAB > CAND ? SLAB : CAND;
-    static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 4 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
+    static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 5 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
 };
 
 // What a thread needs of the bias: fetched before the product, so that its latency passes under it.
@@ -167,7 +175,8 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     float* flag_thr = reinterpret_cast<float*>(flag_tok + TB);
     float* flag_max = flag_thr + TB;
     float* flag_den = flag_max + TB;
-    float* red = flag_den + TB;                      // [2 * NWV]
+    float* flag_tau = flag_den + TB;
+    float* red = flag_tau + TB;                      // [2 * NWV]
     int* n_cand = reinterpret_cast<int*>(red + 2 * NWV);         // [NWV]
     int* n_flag = n_cand + NWV;
 
@@ -266,10 +275,10 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
             }
         }
         m = group_max<TPT>(m);
-        float s = 0.f;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};                       // (four short sums: half the rounding of one)
 #pragma unroll
-        for (int j = 0; j < CPT; ++j) s += sub * CPT + j < E ? __expf(mine[j] - m) : 0.f;
-        const float denom = group_sum<TPT>(s);
+        for (int j = 0; j < CPT; ++j) s[j & 3] += sub * CPT + j < E ? gate_exp(mine[j] - m) : 0.f;
+        const float denom = group_sum<TPT>((s[0] + s[1]) + (s[2] + s[3]));
         float sel_v[RMAX];
         int sel_e[RMAX];
 #pragma unroll
@@ -302,7 +311,7 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 float p[RMAX], tot = 0.f;
 #pragma unroll
                 for (int r = 0; r < RMAX; ++r)
-                    if (r < k) { p[r] = __expf(sel_v[r] - m) / denom; tot += p[r]; }
+                    if (r < k) { p[r] = gate_exp(sel_v[r] - m) / denom; tot += p[r]; }
 #pragma unroll
                 for (int r = 0; r < RMAX; ++r)
                     if (r < k) {
@@ -310,12 +319,13 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                         w_out[(size_t)t * k + r] = renorm ? p[r] / tot : p[r];
                     }
             } else {
-                float last = sel_v[0];
+                float last = sel_v[0];                           // the k-th choice: what lies tau below it cannot be among them
 #pragma unroll
-                for (int r = 1; r < RMAX; ++r) if (r < rounds) last = sel_v[r];
+                for (int r = 1; r < RMAX; ++r) if (r < k) last = sel_v[r];
                 const int f = atomicAdd(n_flag, 1);
                 flag_tok[f] = tok;
                 flag_thr[f] = last - tau;
+                flag_tau[f] = tau;
                 flag_max[f] = m;
                 flag_den[f] = denom;
             }
@@ -323,14 +333,15 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     }
     __syncthreads();
 
-    // ---- exact path for the flagged tokens: every expert whose fp32 logit could still reach the top
-    // k is recomputed in fp64.  A round takes as many flagged tokens as there are wavefronts: each
-    // wavefront lists one token's candidates, then all of them share out the (token, candidate)
-    // pairs -- a work-group has a flagged token or two, and left to one wavefront its nine or ten
-    // candidates follow one another, a memory latency each -- and each selects for its token.  What it costs
-    // is a chain of latencies (256 experts, k = 8: 16 - 20 us of a work-group's 45 when a token is flagged), so the
-    // sums and the choices go through the vector unit's lane exchanges (through LDS: 8 us more).  Sharing a
-    // candidate's terms out over the wavefronts as well was slower (44 -> 57 us: 64-lane sums for everybody).
+    // ---- exact path for the flagged tokens: of the experts whose fp32 logit could still reach the top k, those with another one
+    // within tau are recomputed in fp64 (the others' places are certain: a token has two or three to recompute, not k + 1).
+    // A round takes as many flagged tokens as there are wavefronts: each wavefront lists one token's candidates, then all of them
+    // share out the (token, candidate) pairs, a memory latency each, and each selects for its token: up to 64 candidates a lane
+    // each, which counts those that beat its own.  What it costs is a chain of latencies, about 6 us of a work-group's time
+    // and 4 more for 1032 terms of a W_g as given, so the sums go through the vector unit's lane exchanges (through LDS: 8 us more).
+    // Sharing a candidate's terms out over the wavefronts was slower (64-lane sums for everybody), and so were 32 instead of
+    // 16 loads in flight (20011 tokens, E = 256: 94 us, 78 now).  (All candidates recomputed, the choices made one after the other ->
+    // this: 20011 x 1032, E = 256, k = 8 107 -> 78 us; 619 x 1792, E = 83, k = 6 72 -> 44; 5000 x 1032, E = 60, k = 4 34 -> 25.)
     constexpr int CJ = (MOE_MAX_EXPERTS + 63) / 64;
     double* cand_v = slab;                                       // [NWV][LIST]
     int* cand_e = reinterpret_cast<int*>(slab + NWV * L::LIST);  // [NWV][LIST]
@@ -349,7 +360,25 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 nc += __popcll(mask);
             }
         }
-        if (lane == 0) n_cand[wave] = nc;
+        int n_near = nc;
+        if (nc <= 64) {                                          // those with a neighbour come first
+            const int e = lane < nc ? cand_e[wave * L::LIST + lane] : 0;
+            const float l = ls[flag_tok[f < nf ? f : f0] * PL + e], tau = flag_tau[f < nf ? f : f0];
+            bool near = !(fabsf(l) < __builtin_huge_valf());
+            for (int j = 0; j < nc; ++j) {
+                const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), j));
+                near = near || (j != lane && fabsf(l - o) < tau);
+            }
+            const unsigned long long here = (1ull << lane) - 1ull, in = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
+            const unsigned long long first = __ballot(near) & in, rest = in & ~first;
+            n_near = __popcll(first);
+            if (lane < nc) {
+                const int at = wave * L::LIST + (near ? __popcll(first & here) : n_near + __popcll(rest & here));
+                cand_e[at] = e;
+                cand_v[at] = (double)l;
+            }
+        }
+        if (lane == 0) n_cand[wave] = n_near;
         __syncthreads();
         for (int s = 0, p = wave; s < NWV; ++s) {
             const int n = __builtin_amdgcn_readfirstlane(n_cand[s]);
@@ -397,7 +426,22 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
             p -= n;
         }
         __syncthreads();
-        if (f < nf) {
+        if (f < nf && nc <= 64) {                                // a candidate's place: how many beat it
+            const int t = t0 + flag_tok[f], at = wave * L::LIST + (lane < nc ? lane : 0);
+            const double v = cand_v[at];
+            const int e = cand_e[at];
+            int place = 0;
+            for (int j = 0; j < nc; ++j) place += beats(lane_f64(v, j), __builtin_amdgcn_readlane(e, j), v, e) ? 1 : 0;
+            const bool chosen = lane < nc && place < k;
+            const double p = exp(v - (double)flag_max[f]) / (double)flag_den[f];
+            if (chosen) cand_v[wave * L::LIST + place] = p;      // (every lane has read its own)
+            double tot = 0.0;
+            for (int r = 0; r < k; ++r) tot += cand_v[wave * L::LIST + r];
+            if (chosen) {
+                idx_out[(size_t)t * k + place] = e;
+                w_out[(size_t)t * k + place] = (float)(renorm ? p / tot : p);
+            }
+        } else if (f < nf) {
             const int t = t0 + flag_tok[f];
             double cv[CJ];
             int ce_[CJ];

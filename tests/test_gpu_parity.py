@@ -143,6 +143,33 @@ def test_route_error_bound_covers_every_term(torch_gpu, E):
         assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
 
 
+@pytest.mark.parametrize("E,same,k", [(40, 2, 4), (100, 3, 6), (200, 2, 8), (200, 63, 8), (200, 64, 1), (200, 65, 5), (200, 130, 8)])
+def test_route_experts_with_and_without_a_neighbour(torch_gpu, E, same, k):
+    """Tokens whose first choices lie apart (their fp32 logits decide) beside `same` experts with the same or nearly the same logits
+    (recomputed in 64 bits), few and more than a wavefront has lanes for."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    T, d = 150, 192
+    r = np.random.default_rng(E + same)
+    xf = r.standard_normal((T, d)).astype(np.float32)
+    Wf = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    group = r.permutation(E)[:same]
+    Wf[:, group] = Wf[:, group[:1]]
+    b = r.standard_normal(E).astype(np.float32)
+    b[group] = 1.5
+    x, Wg = W.f32_to_bf16_bits(xf), W.f32_to_bf16_bits(Wf)
+    Wg[5, group[-1]] ^= 1                      # one bf16 ulp in one coefficient
+    wl = W.WORKLOADS["c2"].scaled(T=T, d=d, E=E, k=k, renorm=1)
+    idx_o, w_o, _ = O.route_topk(x, Wg, b, k, 1)
+    for packed in (False, True):
+        layer = make_layer(wl, {})
+        layer.load_router(Wg, b, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), "packed=%s" % packed
+        assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
+
+
 # (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
 # of the stage; every block and contraction split; E < 8: the general kernel)
 @pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
