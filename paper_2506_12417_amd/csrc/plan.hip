@@ -87,11 +87,12 @@ __global__ __launch_bounds__(NTH) void plan_kernel(const int32_t* __restrict__ c
     if (tid < G) { load[tid] = 0; bin_blocks[tid] = 0; bin_cursor[tid] = 0; bin_tiles[tid] = 0; }
     if (MERGED) {
         // this work-group's own count of every expert (cnt) and its first row (row0: exclusive prefix)
-        cnt[tid] = 0;
+        __shared__ moe_rank::Counters of_all;
+        moe_rank::clear(of_all);
         __syncthreads();
-        moe_rank::count_experts(ra.idx, A, E, 0, nullptr, cnt);
+        moe_rank::count_experts(ra.idx, A, E, 0, nullptr, of_all);
         __syncthreads();
-        const int total = tid < E ? cnt[tid] : 0;
+        const int total = tid < E ? moe_rank::sum_of(of_all, tid) : 0;
         const int first = moe_rank::block_scan(total, order) - total;    // (order[] is not in use yet)
         if (tid < E) {
             const int c = ((mask.w[tid >> 5] >> (tid & 31)) & 1u) ? total : 0;
