@@ -427,12 +427,14 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
         }
         __syncthreads();
         if (f < nf && nc <= 64) {                                // a candidate's place: how many beat it
-            const int t = t0 + flag_tok[f], at = wave * L::LIST + (lane < nc ? lane : 0);
-            const double v = cand_v[at];
-            const int e = cand_e[at];
+            const int t = t0 + flag_tok[f], at = wave * L::LIST + lane;
+            const double v = lane < nc ? cand_v[at] : -__builtin_huge_val();
+            const int e = lane < nc ? cand_e[at] : INT_MAX;
             int place = 0;
             for (int j = 0; j < nc; ++j) place += beats(lane_f64(v, j), __builtin_amdgcn_readlane(e, j), v, e) ? 1 : 0;
-            const bool chosen = lane < nc && place < k;
+            // (logits that are no numbers are no candidates: with fewer than k others, the places behind them name no expert)
+            if (lane >= nc) place = lane;
+            const bool chosen = place < k;
             const double p = exp(v - (double)flag_max[f]) / (double)flag_den[f];
             if (chosen) cand_v[wave * L::LIST + place] = p;      // (every lane has read its own)
             double tot = 0.0;

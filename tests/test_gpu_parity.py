@@ -170,6 +170,45 @@ def test_route_experts_with_and_without_a_neighbour(torch_gpu, E, same, k):
         assert np.abs(to_numpy(layer.gate_w) - w_o).max() <= 2e-6
 
 
+def _nan_bias_router(E, k, n_num, tied, seed):
+    """Tokens and a router of which only n_num experts have logits that are numbers, the first two of them equal where tied."""
+    T, d = 96, 64
+    r = np.random.default_rng(seed)
+    xf = r.standard_normal((T, d)).astype(np.float32)
+    Wf = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    num = np.sort(r.permutation(E)[:n_num])
+    b = np.full(E, np.nan, dtype=np.float32)
+    b[num] = np.arange(n_num) * (0 if tied else 64)
+    if tied:
+        Wf[:, num] = Wf[:, num[:1]]
+    x, Wg = W.f32_to_bf16_bits(xf), W.f32_to_bf16_bits(Wf)
+    b0 = np.where(np.isnan(b), np.float32(-1e30), b)
+    idx_o, _, _ = O.route_topk(x, Wg, b0, k, 1)
+    idx_o[:, n_num:] = 2 ** 31 - 1
+    return x, Wg, b, idx_o
+
+
+@pytest.mark.parametrize("E,k,n_num", [(8, 4, 3), (40, 8, 2), (200, 8, 7), (100, 3, 2)])
+@pytest.mark.parametrize("tied", [True, False])
+def test_route_writes_all_choices_of_a_token_with_few_numbers(torch_gpu, E, k, n_num, tied):
+    """Fewer logits that are numbers than choices: what is left of the choices names no expert, whatever the outputs held before,
+    and the gates are no numbers, as the softmax over all logits is none."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    x, Wg, b, idx_o = _nan_bias_router(E, k, n_num, tied, E + k)
+    for renorm in (0, 1):
+        for packed in (False, True):
+            layer = make_layer(W.WORKLOADS["c2"].scaled(T=x.shape[0], d=x.shape[1], E=E, k=k, renorm=renorm), {})
+            layer.load_router(Wg, b, packed=packed)
+            layer.expert_idx.fill_(1)
+            layer.gate_w.fill_(0.25)
+            layer.route(to_device(x, layer.device))
+            torch.cuda.synchronize()
+            assert np.array_equal(to_numpy(layer.expert_idx), idx_o), "renorm=%d packed=%s" % (renorm, packed)
+            if tied:
+                assert np.isnan(to_numpy(layer.gate_w)).all(), "renorm=%d packed=%s" % (renorm, packed)
+
+
 # (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
 # of the stage; every block and contraction split; E < 8: the general kernel)
 @pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
