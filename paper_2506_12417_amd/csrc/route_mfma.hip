@@ -312,11 +312,12 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
 #pragma unroll
                 for (int r = 0; r < RMAX; ++r)
                     if (r < k) { p[r] = gate_exp(sel_v[r] - m); tot += p[r]; }
+                const float over = renorm && denom == denom ? tot : denom;     // (a logit that is no number: nor is any gate)
 #pragma unroll
                 for (int r = 0; r < RMAX; ++r)
                     if (r < k) {
                         idx_out[(size_t)t * k + r] = sel_e[r];
-                        w_out[(size_t)t * k + r] = p[r] / (renorm ? tot : denom);     // (one rounding; the sum over all cancels)
+                        w_out[(size_t)t * k + r] = p[r] / over;     // (one rounding; renormalised, the sum over all cancels)
                     }
             } else {
                 float last = sel_v[0];                           // the k-th choice: what lies tau below it cannot be among them

@@ -209,6 +209,25 @@ def test_route_writes_all_choices_of_a_token_with_few_numbers(torch_gpu, E, k, n
                 assert np.isnan(to_numpy(layer.gate_w)).all(), "renorm=%d packed=%s" % (renorm, packed)
 
 
+@pytest.mark.parametrize("dtype,E,k,n_num", [("c2", 8, 4, 5), ("c2", 40, 1, 39), ("c2", 200, 8, 60), ("c2", 6, 2, 3), ("c1", 40, 4, 9)])
+@pytest.mark.parametrize("tied", [True, False])
+def test_route_gates_beside_a_logit_that_is_no_number(torch_gpu, dtype, E, k, n_num, tied):
+    """A softmax over logits of which one is no number has no values: the gates are NaN, near ties or not, renormalised or not."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    x, Wg, b, idx_o = _nan_bias_router(E, k, n_num, tied, E)
+    if dtype == "c1":
+        x, Wg = O.to_f64(x).astype(np.float32), O.to_f64(Wg).astype(np.float32)
+    for renorm in (0, 1):
+        for packed in (False, True):
+            layer = make_layer(W.WORKLOADS[dtype].scaled(T=x.shape[0], d=x.shape[1], E=E, k=k, renorm=renorm), {})
+            layer.load_router(Wg, b, packed=packed)
+            layer.route(to_device(x, layer.device))
+            torch.cuda.synchronize()
+            assert np.array_equal(to_numpy(layer.expert_idx), idx_o), "renorm=%d packed=%s" % (renorm, packed)
+            assert np.isnan(to_numpy(layer.gate_w)).all(), "renorm=%d packed=%s" % (renorm, packed)
+
+
 # (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
 # of the stage; every block and contraction split; E < 8: the general kernel)
 @pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
