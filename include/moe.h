@@ -65,8 +65,8 @@ typedef enum { MOE_RELU = 0, MOE_SWIGLU = 1 } moe_act;
  *   gate_w[t,j] = value of expert_idx[t,j]; renorm != 0 divides the k values by their sum
  *
  * The top-k decision is taken as if the logits were computed in float64: MOE_F32 computes them so;
- * the MOE_BF16 kernels work in fp32 with a rigorous error bound and recompute in fp64 the experts of a
- * token that lie inside that bound of one another.
+ * the MOE_BF16 kernels work in fp32 with a rigorous error bound and recompute in fp64 every token
+ * whose decision gaps are inside that bound.
  *
  *   x       [T,d]  dtype dt        w_gate [d,E] dtype dt       bias [E] fp32, may be NULL
  *   expert_idx [T,k] int32 out     gate_w [T,k] fp32 out

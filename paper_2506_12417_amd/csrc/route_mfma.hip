@@ -6,9 +6,9 @@
 // into fp64 accumulators, so only the rounding inside a chunk counts: |error| <= c * |x_t| * |w_e|
 // with c = (2*KACC+6) * 2^-24 (two roundings per term allowed for, since the accumulation order
 // inside the instruction is not specified).  A token whose deciding gaps are all wider than twice
-// that bound keeps its fp32 selection; in the others, of the experts that could still reach the top k, those with
-// another one as near as that get their logits recomputed in fp64, so expert indices and their order are those of
-// exact arithmetic (ties to the lower index).
+// that bound keeps its fp32 selection; the others get the logits of every expert that could still
+// reach the top k recomputed in fp64, so expert indices and their order are those of exact
+// arithmetic (ties to the lower index).
 //
 // The wavefronts of a work-group split the experts into blocks of 32 (NB blocks) and, when there
 // are fewer than four blocks, also the contraction (KSP parts); the partial sums of the parts are
@@ -135,7 +135,7 @@ struct RouteLds {
     static constexpr int SLAB = KSP > 1 ? KSP * TB * EPT * 8 : 0;
     static constexpr int CAND = NWV * LIST * 12;
     static constexpr int REGION0 = SLAB > CAND ? SLAB : CAND;
-    static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 5 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
+    static constexpr size_t BYTES = REGION0 + (size_t)TB * PL * 4 + KSP * TB * 4 + 4 * TB * 4 + 2 * NWV * 4 + NWV * 4 + 16;
 };
 
 // What a thread needs of the bias: fetched before the product, so that its latency passes under it.
@@ -175,8 +175,7 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     float* flag_thr = reinterpret_cast<float*>(flag_tok + TB);
     float* flag_max = flag_thr + TB;
     float* flag_den = flag_max + TB;
-    float* flag_tau = flag_den + TB;
-    float* red = flag_tau + TB;                      // [2 * NWV]
+    float* red = flag_den + TB;                      // [2 * NWV]
     int* n_cand = reinterpret_cast<int*>(red + 2 * NWV);         // [NWV]
     int* n_flag = n_cand + NWV;
 
@@ -326,7 +325,6 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 const int f = atomicAdd(n_flag, 1);
                 flag_tok[f] = tok;
                 flag_thr[f] = last - tau;
-                flag_tau[f] = tau;
                 flag_max[f] = m;
                 flag_den[f] = denom;
             }
@@ -334,15 +332,16 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
     }
     __syncthreads();
 
-    // ---- exact path for the flagged tokens: of the experts whose fp32 logit could still reach the top k, those with another one
-    // within tau are recomputed in fp64 (the others' places are certain: a token has two or three to recompute, not k + 1).
-    // A round takes as many flagged tokens as there are wavefronts: each wavefront lists one token's candidates, then all of them
-    // share out the (token, candidate) pairs, a memory latency each, and each selects for its token: up to 64 candidates a lane
-    // each, which counts those that beat its own.  What it costs is a chain of latencies, about 6 us of a work-group's time
-    // and 4 more for 1032 terms of a W_g as given, so the sums go through the vector unit's lane exchanges (through LDS: 8 us more).
-    // Sharing a candidate's terms out over the wavefronts was slower (64-lane sums for everybody), and so were 32 instead of
-    // 16 loads in flight (20011 tokens, E = 256: 94 us, 78 now).  (All candidates recomputed, the choices made one after the other ->
-    // this: 20011 x 1032, E = 256, k = 8 107 -> 78 us; 619 x 1792, E = 83, k = 6 72 -> 44; 5000 x 1032, E = 60, k = 4 34 -> 25.)
+    // ---- exact path for the flagged tokens: every expert whose fp32 logit could still reach the top k is recomputed in fp64, for
+    // the decision and for its gate.  A round takes as many flagged tokens as there are wavefronts: each wavefront lists one token's
+    // candidates, then all of them share out the (token, candidate) pairs, a memory latency each, and each selects for its token: up
+    // to 64 candidates a lane each, which counts those that beat its own.  What it costs is a chain of latencies (256 experts, k = 8: 20
+    // to 30 us of a work-group's time where a token is flagged), so the sums go through the vector unit's lane exchanges
+    // (through LDS: 8 us more).  Sharing a candidate's terms out over the wavefronts was slower (64-lane sums for everybody), and so
+    // were 32 instead of 16 loads in flight (20011 tokens, E = 256: 17 us more).  (Candidates down from the k-th instead of the k + 1-th
+    // choice, chosen at once instead of one after the other: 20011 x 1032, E = 256, k = 8 112 -> 102 us; 619 x 1792, E = 83, k = 6 71 -> 64;
+    // 8192 x 2048, E = 256, k = 8, W_g prepared, 45 -> 41.  Recomputing only the candidates with another one within tau, which decide
+    // just as well, takes 82, 44 and 36, but leaves the other choices' gates to fp32 logits.)
     constexpr int CJ = (MOE_MAX_EXPERTS + 63) / 64;
     double* cand_v = slab;                                       // [NWV][LIST]
     int* cand_e = reinterpret_cast<int*>(slab + NWV * L::LIST);  // [NWV][LIST]
@@ -361,25 +360,7 @@ __device__ __forceinline__ void route_finish(unsigned char* smem, const double (
                 nc += __popcll(mask);
             }
         }
-        int n_near = nc;
-        if (nc <= 64) {                                          // those with a neighbour come first
-            const int e = lane < nc ? cand_e[wave * L::LIST + lane] : 0;
-            const float l = ls[flag_tok[f < nf ? f : f0] * PL + e], tau = flag_tau[f < nf ? f : f0];
-            bool near = !(fabsf(l) < __builtin_huge_valf());
-            for (int j = 0; j < nc; ++j) {
-                const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), j));
-                near = near || (j != lane && fabsf(l - o) < tau);
-            }
-            const unsigned long long here = (1ull << lane) - 1ull, in = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
-            const unsigned long long first = __ballot(near) & in, rest = in & ~first;
-            n_near = __popcll(first);
-            if (lane < nc) {
-                const int at = wave * L::LIST + (near ? __popcll(first & here) : n_near + __popcll(rest & here));
-                cand_e[at] = e;
-                cand_v[at] = (double)l;
-            }
-        }
-        if (lane == 0) n_cand[wave] = n_near;
+        if (lane == 0) n_cand[wave] = nc;
         __syncthreads();
         for (int s = 0, p = wave; s < NWV; ++s) {
             const int n = __builtin_amdgcn_readfirstlane(n_cand[s]);
@@ -628,7 +609,7 @@ __global__ __launch_bounds__(NB * KSP * 64, 2) void route_packed_kernel(const ui
 // thread fetches eight terms of eight neighbouring experts (eight 16-byte loads), swaps them into
 // eight runs of eight terms with byte permutes, and writes those as 16-byte pieces.  (Two-byte
 // loads and LDS writes, one term of one expert each, kept the kernel at 1257 us for 20011 tokens x
-// 1032, E = 256; this takes 78 us, 64 of them before the exact path.)  A stage is 128 terms per contraction part of the 32 tokens and
+// 1032, E = 256; this takes 102 us, 64 of them before the exact path.)  A stage is 128 terms per contraction part of the 32 tokens and
 // all experts; its loads are in flight while the previous stage is multiplied.
 //
 // LDS rows hold 16 pieces (128 terms); piece p of row r sits at position p ^ swz(r), chosen so that

@@ -228,6 +228,36 @@ def test_route_gates_beside_a_logit_that_is_no_number(torch_gpu, dtype, E, k, n_
             assert np.isnan(to_numpy(layer.gate_w)).all(), "renorm=%d packed=%s" % (renorm, packed)
 
 
+@pytest.mark.parametrize("E,k", [(16, 3), (40, 4), (100, 6), (200, 8)])
+def test_route_gates_of_near_tied_tokens_come_from_64_bits(torch_gpu, E, k):
+    """A token with a near tie among its first choices has the logits of all its choices recomputed, not only those of the tie: its
+    renormalised gates are exact to their own rounding, where fp32 logits (300 and more, 2^-16 apart) give 2^-17 at best."""
+    torch = torch_gpu
+    from paper_2506_12417_amd.layer import to_device
+    T, d = 150, 192
+    r = np.random.default_rng(E)
+    xf = r.standard_normal((T, d)).astype(np.float32)
+    Wf = (r.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    tie = r.permutation(E)[:2]
+    Wf[:, tie[1]] = Wf[:, tie[0]]
+    b = (300 + r.standard_normal(E)).astype(np.float32)
+    b[tie] = 303
+    x, Wg = W.f32_to_bf16_bits(xf), W.f32_to_bf16_bits(Wf)
+    idx_o, _, l_o = O.route_topk(x, Wg, b, k, 1)
+    gate = np.exp(np.take_along_axis(l_o, idx_o.astype(np.int64), axis=1) - l_o.max(axis=1, keepdims=True))
+    gate /= gate.sum(axis=1, keepdims=True)
+    tied = (idx_o == tie.min()).any(axis=1)
+    assert tied.sum() > T // 4
+    for packed in (False, True):
+        layer = make_layer(W.WORKLOADS["c2"].scaled(T=T, d=d, E=E, k=k, renorm=1), {})
+        layer.load_router(Wg, b, packed=packed)
+        layer.route(to_device(x, layer.device))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_numpy(layer.expert_idx), idx_o), "packed=%s" % packed
+        # one rounding to fp32, and the rounding of 64-bit sums of logits of 300 (2^-44)
+        assert (np.abs(to_numpy(layer.gate_w).astype(np.float64) - gate)[tied] <= 1.01 * 2.0 ** -24 * gate[tied]).all(), "packed=%s" % packed
+
+
 # (odd and small E: rows of W_g at every alignment, the matrix's end inside a load; d not a multiple
 # of the stage; every block and contraction split; E < 8: the general kernel)
 @pytest.mark.parametrize("T,d,E,k", [(33, 8, 8, 8), (1, 24, 9, 3), (70, 136, 63, 4), (40, 1032, 255, 8), (64, 128, 256, 8),
