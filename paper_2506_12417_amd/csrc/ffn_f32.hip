@@ -193,15 +193,16 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_f32_rows_kernel(const float* 
     }
 }
 
-// Eight fp32 values as three bf16 parts, v = part[0] + part[1] + part[2] exactly (round to nearest, then the same of what is
-// left: 8 + 8 + 8 bits of 24; parts below bf16's 2^-133 are lost).  Converted and subtracted by plain vector instructions, which
+// Eight fp32 values times 2^32 as three bf16 parts, v 2^32 = part[0] + part[1] + part[2] exactly (round to nearest, then the same of
+// what is left: 8 + 8 + 8 bits of 24).  The factor lifts fp32's last bit, 2^-149, to 2^-117, so that no part of any value is below
+// bf16's smallest numbers; values from 2^95 on become infinite.  Converted and subtracted by plain vector instructions, which
 // run beside matrix instructions; v_dot2_f32_bf16 would subtract in one instead of two, but takes the matrix cores' time.
 __device__ __forceinline__ void split3(f32x4 lo, f32x4 hi, bf16x8 (&part)[3]) {
     float v[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        v[i] = lo[i];
-        v[4 + i] = hi[i];
+        v[i] = lo[i] * 0x1p32f;
+        v[4 + i] = hi[i] * 0x1p32f;
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p)
@@ -230,9 +231,9 @@ __device__ const float zeros[4] = {0.f, 0.f, 0.f, 0.f};
 // rounded once per 32 terms.  Error of an fp32 layer (1501 x 768, F = 2048) against 64 bits: 3.8e-7 of the result's norm; the
 // fp32 instructions' chain has 9.5e-7, a single sum of all six products 8.2e-7.
 //
-// An infinity or NaN, or an operand that rounds to a bf16 infinity, makes NaNs of the parts' products, and parts below 2^-133
-// are lost: a wavefront with a sum that is not finite, or not zero and below 2^-60, does its block again by fp32 matrix
-// instructions from global memory, so that such values come out as they do in fp32.
+// The sums are of values times 2^64 (split3).  An infinity or NaN, an operand of 2^95 or more and a sum of 2^64 or more make
+// infinities or NaNs of them: a wavefront with a sum that is not finite does its block again by fp32 matrix instructions from global
+// memory, so that such values come out as they do in fp32.  Everything else is exact in its parts, however small.
 //
 // Bound by issue and latency more than by the matrix cores: cutting takes as many vector instructions as the products take
 // matrix instructions' cycles.  Full tiles (6144 rows, K = 768, N = 4096) 150 TFLOP/s of fp32 work, 1.0 PFLOP/s of bf16, 1.3 within
@@ -387,9 +388,8 @@ __global__ __launch_bounds__(256, CB == 2 ? 2 : 3) void gemm_f32_split_kernel(co
             for (int h = 0; h < CB; ++h)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    acc[m][h][r] += low[m][h][r];
-                    const float v = __builtin_fabsf(acc[m][h][r]);
-                    redo = redo || !(v < __builtin_inff()) || (v < 0x1p-60f && v > 0.f);
+                    acc[m][h][r] = (acc[m][h][r] + low[m][h][r]) * 0x1p-64f;
+                    redo = redo || !(__builtin_fabsf(acc[m][h][r]) < __builtin_inff());
                 }
         if (__any(redo)) {
 #pragma unroll

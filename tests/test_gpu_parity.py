@@ -1165,6 +1165,68 @@ def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
         assert (np.abs(h[9] - z) <= 2.0 ** -126).all()
 
 
+def _f32_first_product(torch, rows, d, F, act, xp, weights):
+    """The first product of an fp32 layer with rows[e] rows of expert e, as the kernels have stored it; the sums in 64 bits
+    and the sums of the absolute terms of every matrix."""
+    from paper_2506_12417_amd.layer import to_device
+    A, E = sum(rows), len(rows)
+    wl = W.WORKLOADS["c1"].scaled(T=A, d=d, F=F, E=E, k=1, act=act, skew="uniform")
+    layer = make_layer(wl, weights)
+    p = O.permute(_few(rows).reshape(A, 1), E)
+    for dst, src in ((layer.x_perm, xp), (layer.counts, p["counts"]), (layer.offsets, p["offsets"])):
+        dst.copy_(to_device(src, layer.device))
+    layer.h.fill_(float("nan"))
+    layer.plan()
+    layer.ffn()
+    torch.cuda.synchronize()
+    off = np.concatenate([[0], np.cumsum(rows)])
+    x64 = xp.astype(np.float64)
+    def sums(m):
+        return np.concatenate([x64[off[e]:off[e + 1]] @ m[e].astype(np.float64) for e in range(E)])
+    def sizes(m):
+        return np.concatenate([np.abs(x64[off[e]:off[e + 1]]) @ np.abs(m[e]).astype(np.float64) for e in range(E)])
+    names = ("W1",) if act == "relu" else ("Wg", "Wu")
+    return to_numpy(layer.h).astype(np.float64), {n: sums(weights[n]) for n in names}, {n: sizes(weights[n]) for n in names}
+
+
+def _f32_weights(rows, d, F, act, scale, seed):
+    r = np.random.default_rng(seed)
+    shapes = {"W1": (d, F), "W2": (F, d)} if act == "relu" else {"Wg": (d, F), "Wu": (d, F), "Wd": (F, d)}
+    return {n: (r.standard_normal((len(rows),) + s) * s[0] ** -0.5).astype(np.float32) * np.float32(1 if n in ("W2", "Wd") else scale)
+            for n, s in shapes.items()}
+
+
+# (first products by either width of the column blocks, one and several tiles, and by the few-row kernel)
+F32_RANGE_SHAPES = [([400, 700], 100, 4096, "relu"), ([1000, 1090], 68, 4096, "relu"), ([800, 340], 132, 2048, "swiglu"), ([1000, 1090], 36, 2048, "swiglu"),
+                    ([40, 70], 100, 512, "relu")]
+
+
+@pytest.mark.parametrize("rows,d,F,act", F32_RANGE_SHAPES)
+@pytest.mark.parametrize("rows_at,weights_at", [((-118, -124, -130, -140), 60), ((-118, -124, -130, -140), 110), ((60, 80, 90, 100), -118),
+                                                ((40, 60, 80, 118), -136)])
+def test_fp32_products_of_tiny_values_with_large_ones(torch_gpu, rows, d, F, act, rows_at, weights_at):
+    """Operands of which only a few bits, or no normal number, are left, against operands so large that the sums are ordinary: the
+    products have all bits that the operands have."""
+    A = sum(rows)
+    _note("fp32 tiny with large A=%d d=%d F=%d %s rows %s weights %d" % (A, d, F, act, rows_at, weights_at))
+    weights = _f32_weights(rows, d, F, act, 2.0 ** weights_at, d)
+    xp = (np.random.default_rng(A).standard_normal((A, d)) * np.exp2(np.array(rows_at)[np.arange(A) % 4])[:, None]).astype(np.float32)
+    h, prod, size = _f32_first_product(torch_gpu, rows, d, F, act, xp, weights)
+    # an fp32 sum of d terms, and bits below the smallest number
+    room = {n: (d + 2) * 2.0 ** -23 * size[n] + 2.0 ** -148 for n in prod}
+    if act == "relu":
+        assert (np.abs(h - np.maximum(prod["W1"], 0)) <= room["W1"]).all()
+    else:
+        z, u = prod["Wg"], prod["Wu"]
+        ok = np.abs(z) < 60                          # (an exponential that fp32 holds)
+        silu = z / (1 + np.exp(-np.where(ok, z, 0)))
+        fits = ok & (np.abs(silu * u) < 1e38)
+        assert fits.sum() > A * F // 8
+        # silu's slope is below 1.1; its exponential has a relative error of 2^-22 (1 + |z|)
+        far = 1.1 * room["Wg"] * (np.abs(u) + room["Wu"]) + np.abs(silu) * room["Wu"] + (1 + np.abs(z)) * 2.0 ** -21 * np.abs(silu * u) + 2.0 ** -148
+        assert (np.abs(h - silu * u) <= far)[fits].all()
+
+
 @pytest.mark.parametrize("rows,d,F,act", [([300], 256, 1024, "relu"), ([700, 10], 256, 512, "relu"), ([520, 33, 260], 320, 704, "swiglu"),
                                           ([128, 127, 65, 0, 129, 17, 48, 1, 64], 192, 576, "swiglu"), ([40] * 20, 256, 256, "relu")])
 @pytest.mark.parametrize("mode", [0, 1])
