@@ -4,9 +4,9 @@
 //   out[r, n] = epilogue( sum_k a[r, k] * w_e[n, k] )      r in a tile of expert e
 //
 // Two kernels.  gemm_f32_split_kernel multiplies by bf16 matrix instructions, which run at 16 times the rate of the fp32 ones:
-// every operand is cut into three bf16 parts that add up to it exactly, and six of the nine products of parts are summed in
-// fp32 (the other three are below 2^-26 of a term).  gemm_f32_rows_kernel, for calls too small for that, multiplies by
-// v_mfma_f32_16x16x4_f32, the contraction in four or eight parts.
+// every operand is cut into three bf16 parts that add up to it exactly, and eight of the nine products of parts are summed in
+// fp32 (the ninth, of the smallest parts, is below 2^-33 of a term).  gemm_f32_rows_kernel, for calls too small for that,
+// multiplies by v_mfma_f32_16x16x4_f32, the contraction in four or eight parts.
 //
 // Items in both: a tile and a block of weight rows, one work-group each, which the hardware starts where one has finished; the
 // plan's bins, equal in rows but not in tiles, play no role (28 % of the CU time was idle with them).
@@ -32,8 +32,9 @@ __device__ __forceinline__ float silu_f(float z) { return z / (1.f + __expf(-z))
 // (A work-group that staged 32 terms of all rows at a time, the next ones on their way, spent 0.55 us a stage however little was
 // in it.  Measured, that -> this: one token, d=296 F=1984, E=8, k=2: 8.5 + 30 -> 4.9 + 7.5 us; 79 tokens, d=72 F=1408, E=4 7.2 + 29
 // -> 6.5 + 13; 200 tokens, d=1024 F=2048, E=8 39 + 57 -> 31 + 31; 12 tokens, d=816 F=576, E=4, SwiGLU 18 + 12.6 -> 8.2 + 4.8.)
-// Bound by latency in small calls; with tens of rows per expert by the fp32 instructions, 45 - 50 TFLOP/s.  Tried: sixteen
-// wavefronts per item, tiles in parts of 16 or 32 rows: no faster, twice as slow where there are many items.
+// Bound by latency in small calls; with tens of rows per expert by the fp32 instructions on ragged tiles, 58 TFLOP/s (full tiles, 6144
+// rows of K = 768 and of 4096: 119 and 125).  Tried: sixteen wavefronts per item, tiles in parts of 16 or 32 rows: no faster, twice as
+// slow where there are many items.
 // Error of a layer against 64 bits 1.2 - 2.0e-7 of the result's norm; by a single chain of each wavefront's terms 1.5 - 3e-7.
 //
 // LDS: a row's line is eight 16-byte pieces, piece p at position p ^ (row & 7) (no bank conflicts).  Lane (l16, lq) reads pieces
@@ -227,21 +228,23 @@ __device__ const float zeros[4] = {0.f, 0.f, 0.f, 0.f};
 // LDS of the wavefront's own and cut in registers.  While a stage is multiplied, the next one is cut and the one after it
 // is on its way; one barrier per stage.
 //
-// The term's large products (first parts) and its five small ones are summed apart and added at the end: the large sum is
-// rounded once per 32 terms.  Error of an fp32 layer (1501 x 768, F = 2048) against 64 bits: 3.8e-7 of the result's norm; the
-// fp32 instructions' chain has 9.5e-7, a single sum of all six products 8.2e-7.
+// The term's large products (first parts) and its seven small ones are summed apart and added at the end: the large sum is
+// rounded once per 32 terms, and a sum of one term once.  (Without the products of second and third parts, 2^-25 of a term each at
+// most, single terms were off by up to 2^-24 more than their rounding; the products of 1501 x 768, F = 2048 took 252 us, 275 now.)
+// Error of an fp32 layer (1501 x 768, F = 2048) against 64 bits: 3.85e-7 of the result's norm; the fp32 instructions' chain has 9.5e-7, a single
+// sum of all products 8.2e-7.
 //
 // The sums are of values times 2^64 (split3).  An infinity or NaN, an operand of 2^95 or more and a sum of 2^64 or more make
 // infinities or NaNs of them: a wavefront with a sum that is not finite does its block again by fp32 matrix instructions from global
 // memory, so that such values come out as they do in fp32.  Everything else is exact in its parts, however small.
 //
-// Bound by issue and latency more than by the matrix cores: cutting takes as many vector instructions as the products take
-// matrix instructions' cycles.  Full tiles (6144 rows, K = 768, N = 4096) 150 TFLOP/s of fp32 work, 1.0 PFLOP/s of bf16, 1.3 within
-// the stages of an item: a quarter goes into an item's way in (header, tile, addresses, first stage) and out.  Measured
-// (fp32 instructions -> this): 3002 rows, d=768 F=2048 E=16 SwiGLU 208 + 124 -> 160 + 97 us; 4000 rows, d=1000 F=2048 E=8
-// 181 + 191 -> 133 + 145; 400 tokens, d=512 F=1024 E=16, first product 40 -> 28; 1000 rows of 32 experts 1024 x 2048 97 + 104 -> 84 + 92.
+// Bound by issue and latency as much as by the matrix cores: cutting takes as many vector instructions as the products take
+// matrix instructions' cycles.  Full tiles (6144 rows, K = 768, N = 4096) 148 TFLOP/s of fp32 work, 1.2 PFLOP/s of bf16; a quarter goes into
+// an item's way in (header, tile, addresses, first stage) and out.  Measured (fp32 instructions -> this): 3002 rows, d=768 F=2048 E=16
+// SwiGLU 208 + 124 -> 183 + 114 us; 4000 rows, d=1000 F=2048 E=8 181 + 191 -> 138 + 159; 1501 tokens twice, d=768 F=2048 E=16, SwiGLU, a
+// layer 348 -> 290.
 // Tried, all within 3 %: weights' parts shared through LDS too, two tiles of an expert at a time (twice the registers), the
-// next two stages in flight.  v_dot2_f32_bf16 would take a part off in one instruction instead of two, but runs on the matrix
+// next two stages in flight, two blocks of rows multiplied at a time.  v_dot2_f32_bf16 would take a part off in one instruction instead of two, but runs on the matrix
 // cores: no faster.
 //
 // LDS: a row's 32 terms are four groups of 8 (terms 4 g .. 4 g + 3 and 16 + 4 g .. 16 + 4 g + 3: fetched as two pieces of 16 bytes), group g of
@@ -352,8 +355,10 @@ __global__ __launch_bounds__(256, CB == 2 ? 2 : 3) void gemm_f32_split_kernel(co
 #pragma unroll
                         for (int h = 0; h < CB; ++h) c[m][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pa], b[h][pb], c[m][h], 0, 0, 0);
                     };
-                    mul(2, 0, low);
+                    mul(2, 1, low);
                     mul(0, 0, acc);
+                    mul(1, 2, low);
+                    mul(2, 0, low);
                     mul(1, 1, low);
                     mul(0, 2, low);
                     mul(1, 0, low);
@@ -514,15 +519,17 @@ int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, cons
                         const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
     // Column blocks of 128 weight rows read the activations half as often; of 64 where 128 would leave fewer than four items
     // per CU.  The few-row kernel where 64 would leave fewer than two (one with SwiGLU), or the experts hold few rows.  By the split
-    // kernel and by it, in us: 600 tokens, K = N = 1024, E = 4, k = 2 (320 items of 64) 51 and 42; 2000 tokens, K = 1024, N = 128 27 and 23;
-    // 1300 tokens, K = N = 1024, E = 8 37 and 40; 1000 tokens of 32 experts, K = 2048, N = 512 65 and 45; 2000 tokens twice, K = 256, N = 512,
-    // E = 16 (250 rows per expert) 18 and 20.  With SwiGLU (N: gate and up) 250 tokens, K = 1024, N = 1024, E = 4 27 and 16; 40 tokens
-    // twice, K = 1024, N = 4096, E = 32 102 and 73; 120 twice, K = 1000, N = 3072, E = 16 53 and 56; 2000, K = 512, N = 640, E = 8 (360 items) 23 and 28.
+    // kernel and by it, in us: 600 tokens, K = N = 1024, E = 4, k = 2 (320 items of 64) 55 and 42; 2000 tokens twice, K = 1024, N = 128, E = 4 28 and 25;
+    // 1300 tokens, K = N = 1024, E = 8 38 and 38; 1501 tokens twice, K = 2048, N = 768, E = 16 (660 items) 112 and 118.  Rows per expert:
+    // 1000 tokens of 32 experts, K = 1024, N = 2048 89 and 74; 900 of 16, K = 768, N = 1536 39 and 33; 2048 of 32 (64 rows each), K = 512, N = 2048 56 and
+    // 58; 4096 of 32, K = N = 1024 100 and 102.  With SwiGLU (N: gate and up) 250 tokens, K = 1024, N = 1024, E = 4 27 and 15; 40 tokens twice, K = 1024,
+    // N = 4096, E = 32 110 and 74; 300 of 16 77 and 57, 600 85 and 77; 240 tokens twice, K = 1000, N = 3072, E = 16 74 and 66; 2000, K = 512, N = 640, E = 8
+    // (360 items) 23 and 22; 1501 twice, K = 768, N = 4096, E = 16 177 and 211.
     const Args g = {a, A, K, N, E, w, tiles, hdr, out, ld_out, row_src, src_div};
     const long long tiles_est = (A + BM - 1) / BM + E / 2, items = tiles_est * ((N + 63) / 64);
     const bool glu = epi == MOE_EPI_SWIGLU, narrow = tiles_est * ((N + 127) / 128) < 4 * 256;
     const bool in_reach = (long long)A * K < 1ll << 30 && (long long)N * K < 1ll << 30;     // of its 32-bit byte offsets
-    const bool rows = in_reach && (glu ? items < 256 || A <= 8ll * E : items < 2 * 256 || A <= 32ll * E);
+    const bool rows = in_reach && (glu ? items < 256 || A <= 32ll * E : items < 2 * 256 || A <= 48ll * E);
     if (rows) {
         if (glu) return launch_rows<MOE_EPI_SWIGLU>(g, st);
         return epi == MOE_EPI_RELU ? launch_rows<MOE_EPI_RELU>(g, st) : launch_rows<MOE_EPI_STORE>(g, st);

@@ -1227,6 +1227,23 @@ def test_fp32_products_of_tiny_values_with_large_ones(torch_gpu, rows, d, F, act
         assert (np.abs(h - silu * u) <= far)[fits].all()
 
 
+@pytest.mark.parametrize("rows,d,F", [([400, 700], 100, 4096), ([1000, 1090], 68, 4096), ([40, 70], 100, 512)])
+def test_fp32_products_of_single_terms_are_rounded_once(torch_gpu, rows, d, F):
+    """Rows with one nonzero entry: every element is one product of two fp32 values, and comes out as its nearest fp32 number (up to
+    the 2^-32 of it that sums of parts may lose)."""
+    A = sum(rows)
+    _note("fp32 single terms A=%d d=%d F=%d" % (A, d, F))
+    weights = _f32_weights(rows, d, F, "relu", 1.0, d)
+    weights["W1"] = np.abs(weights["W1"])
+    r = np.random.default_rng(A)
+    xp = np.zeros((A, d), dtype=np.float32)
+    xp[np.arange(A), r.integers(0, d, A)] = np.abs(r.standard_normal(A)).astype(np.float32) + np.float32(0.01)
+    h, prod, _ = _f32_first_product(torch_gpu, rows, d, F, "relu", xp, weights)
+    want = prod["W1"]
+    half = 0.5 * np.spacing(want.astype(np.float32)).astype(np.float64)
+    assert (np.abs(h - want) <= half + 2.0 ** -29 * want).all()
+
+
 @pytest.mark.parametrize("rows,d,F,act", [([300], 256, 1024, "relu"), ([700, 10], 256, 512, "relu"), ([520, 33, 260], 320, 704, "swiglu"),
                                           ([128, 127, 65, 0, 129, 17, 48, 1, 64], 192, 576, "swiglu"), ([40] * 20, 256, 256, "relu")])
 @pytest.mark.parametrize("mode", [0, 1])
