@@ -49,28 +49,32 @@ extern "C" int moe_ffn_kernel_mode(int mode) {
     return before;
 }
 
-// Whether the few-row kernels (ffn_rows.hip) serve a plan of 128-row tiles.  A product is then the
-// fetch of the active experts' weights; the tile kernels fetch an expert through one XCD and one stage after the
-// other, the few-row kernels through the whole chip, but these read the rows again for every 32 weight rows.
-// What that costs grows with the multiply-adds of a call, what the tile kernels lose is 15 - 20 us a product where the
-// weights are small; where both stream at the memory's rate the rows per expert decide.  flops: of both products.
-// Measured (both products, few-row against tile kernels):
-//   flops      1024 x 2048, E=16: 2.1 GFLOP (16 rows each) 36 : 45 us, 4.3 46 : 49, 6.4 52 : 51; 512 x 1024 SwiGLU, E=48: 3.8 44 : 45,
-//              5.7 50 : 47; 1024 x 1024, E=100: 1.7 69 : 90, 6.7 94 : 97; 2560 x 512, E=24: 1.0 36 : 59; 1536 x 4096 SwiGLU, E=8: 7.5 74 :
-//              79, 11 87 : 81; 1024 x 2048, E=4: 4.3 (128 rows each) 35 : 45, 8.6 47 : 50; one expert 2048 x 5632: 2.3 27 : 69,
-//              8.9 52 : 81
-//   rows       768 x 3072, E=128: 3 rows 165 : 173, 4 183 : 183, 6 208 : 197; 2048 x 1408 SwiGLU, E=60: 8 rows 181 : 198, 17 202 : 201;
-//              4096 x 14336 SwiGLU, E=8: 8 rows 468 : 470, 12 474 : 457
-static bool few_rows_per_expert(int A, int E, double flops, bool glu) {
-    return flops <= (E <= 8 ? 8e9 : 4.5e9) || A <= (long long)(glu ? 8 : 3) * E;
+// Whether the few-row kernels (ffn_rows.hip) serve a plan of 128-row tiles.  The tile kernels fetch an expert through one XCD, one
+// stage of 64 terms after the other: both products last about (d + F) / 64 stages of 0.35 us, however small they are.  The few-row
+// kernels fetch it through the whole chip, but read the rows again for every 32 weight rows and the weights for every 64 rows: beyond the
+// fetch of the weights they take 360 TFLOP/s.  So they serve calls that they multiply within those stages, 2 MFLOP per term of d + F;
+// where both stream the weights at the memory's rate, calls of few rows per expert (a few hot ones make up for the bins); and with
+// fewer experts than XCDs, up to the rows at which the idle XCDs are made up for.  flops: of both products.
+// Measured (both products in us, few-row against tile kernels; the line in GFLOP or rows):
+//   flops   256 x 512 (1.5): E=4 2.0 GFLOP 21 : 22, E=8 SwiGLU 4.0 28 : 25, E=16 3.0 23 : 23, E=64 3.0 27 : 24; 512 x 1024 (3.1): E=2 2.0 21 : 27, 4.0 38 : 27,
+//           E=8 2.0 22 : 25, 4.0 28 : 26, E=32 3.0 23 : 27, 4.5 32 : 29; 768 x 768 (3.1): E=1 2.0 18 : 27, E=4 4.0 24 : 26, 6.0 34 : 28; 1024 x 1024
+//           (4.1): E=2 4.0 25 : 33, 6.0 38 : 31, E=4 SwiGLU 4.0 27 : 32, 12 39 : 35; 1024 x 2048 (6.1): E=10 4.5 28 : 35, 8.0 45 : 37, E=16 6.0 34 : 37,
+//           8.0 41 : 38; 2048 x 1408 (6.9): E=10 6.0 32 : 37, 8.0 45 : 39; 2048 x 5632 SwiGLU (15): E=4 13 63 : 81, E=8 13 110 : 114
+//   rows    768 x 3072 SwiGLU, E=128, Zipf 0.7 and 1.2: 4.5 rows 1.00 and 0.78 of the tile kernels' time, 8 1.07 and 0.82; 2048 x 1408 SwiGLU, E=64: 8 rows
+//           0.96 and 0.83; 2560 x 2560, E=64 1.09 and 0.95
+//   XCDs    4096 x 14336 SwiGLU: one expert of 64 rows 111 : 175, 128 198 : 210; two of 64 177 : 212, 96 287 : 234; three of 48 257 : 297, 64 325 : 304;
+//           four of 32 280 : 328, 64 416 : 341; six of 8 357 : 364, 32 422 : 408
+static bool few_rows_per_expert(int A, int d, int F, int E, bool glu) {
+    const double flops = 2.0 * A * d * F * (glu ? 3 : 2);
+    if (flops <= 2e6 * ((double)d + F) || A <= (long long)(glu ? 8 : 3) * E) return true;
+    return E < 8 && A <= 64 * E && A <= 32 * (8 - E);
 }
 
 // the plan's tile height of a tile_m argument
 static int tile_height(int tile_m) { return tile_m & ~MOE_TILE_WHOLE_PLAN; }
 
 static bool few_rows_call(int A, int d, int F, int E, moe_act act, int tile_m) {
-    const bool glu = act == MOE_SWIGLU;
-    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, E, 2.0 * A * d * F * (glu ? 3 : 2), glu) &&
+    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, d, F, E, act == MOE_SWIGLU) &&
            (long long)A * (d > F ? d : F) < (1ll << 31);
 }
 

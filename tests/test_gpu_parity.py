@@ -1281,6 +1281,42 @@ def test_small_calls_by_either_family(torch_gpu, rows, d, F, act, mode):
     assert not to_numpy(layer.plan_hdr)[B.MOE_PLAN_HDR_CTR:].any()
 
 
+@pytest.mark.parametrize("rows,d,F,act,few", [
+    # on both sides of the line: multiply-adds within the tile kernels' chain of d + F terms or not, few experts or many
+    ([200], 1024, 1024, "relu", True), ([100] * 16, 512, 1024, "relu", False), ([50] * 16, 512, 1024, "swiglu", True),
+    ([953, 953], 512, 1024, "relu", False), ([500, 500], 512, 1024, "relu", True), ([600] * 8, 256, 512, "relu", False),
+    ([300] * 8, 768, 768, "relu", False), ([7] * 8, 1152, 2560, "swiglu", True), ([90] * 3, 1024, 1024, "swiglu", True),
+    # few experts of few rows and many multiply-adds
+    ([64], 2048, 12288, "swiglu", True), ([40, 50], 2048, 9216, "swiglu", True), ([60] * 6, 1344, 12288, "swiglu", False)])
+def test_which_family_serves_a_small_call(torch_gpu, rows, d, F, act, few):
+    """The few-row kernels add a contraction in parts, so their bits are not the tile kernels' (mode 1)."""
+    torch = torch_gpu
+    from paper_2506_12417_amd import binding as B
+    from paper_2506_12417_amd.layer import MoELayer, to_device
+    A, E = sum(rows), len(rows)
+    _note("family of rows %s d=%d F=%d %s" % (rows, d, F, act))
+    layer = MoELayer(A, d, F, E, 1, act, "bf16", 0, tile_m=128)
+    torch.manual_seed(A)
+    layer.experts.w_in.normal_(0.0, d ** -0.5)
+    layer.experts.w_out.view(torch.float16).normal_(0.0, F ** -0.5)
+    layer.expert_idx.copy_(to_device(_few(rows).reshape(A, 1), layer.device))
+    layer.gate_w.fill_(1.0)
+    layer.permute(torch.randn((A, d), device=layer.device).to(torch.bfloat16))
+    got, before = [], B.moe_ffn_kernel_mode(-1)
+    try:
+        for mode in (0, 1):
+            B.moe_ffn_kernel_mode(mode)
+            layer.plan()
+            layer.y_perm.fill_(float("nan"))
+            layer.ffn()
+            got.append(layer.y_perm.clone())
+    finally:
+        B.moe_ffn_kernel_mode(before)
+    torch.cuda.synchronize()
+    assert max_err_over_rms(to_numpy(got[0]), to_numpy(got[1])) <= 1e-2     # (a rounding of h to half the other way)
+    assert torch.equal(got[0], got[1]) != few
+
+
 @pytest.mark.parametrize("rows,d,F,tile_m,bins", [([300], 256, 1024, 128, 8), ([700, 10], 256, 512, 128, 8), ([900], 256, 512, 256, 8),
                                                   ([520, 33, 260], 320, 704, 128, 3), ([300, 0, 40], 512, 256, 256, 16)])
 def test_small_calls_shared_by_all_work_groups(torch_gpu, rows, d, F, tile_m, bins):
