@@ -58,7 +58,7 @@ __global__ __launch_bounds__(KS * 64, 4) void gemm_f32_rows_kernel(const float* 
     const int l16 = lane & 15, lq = lane >> 4;
     const int st_row = lane >> 3, st_p = lane & 7, st_at = st_row * PIECES + (st_p ^ st_row), rd_at = l16 * PIECES + (lq ^ (l16 & 7));
     f32x4* const turn = (f32x4*)&part[wave][0][0];
-    static_assert(sizeof part[0] >= (16 * NSUB + 16) * 128 && sizeof part[0] % 16 == 0, "a wavefront's lines turn where its sums will be");
+    static_assert(sizeof part[0] >= 16 * 2 * NSUB * 128 && sizeof part[0] % 16 == 0, "a wavefront's lines turn where its sums will be");
     const int n_cb = GLU ? N / 32 : (N + COLS - 1) / COLS;
     const int n_lines = (K + BK - 1) / BK, per = (n_lines + KS - 1) / KS;
     const int s0 = wave * per < n_lines ? wave * per : n_lines, s1 = s0 + per < n_lines ? s0 + per : n_lines;
