@@ -220,7 +220,7 @@ __device__ __forceinline__ void split3(f32x4 lo, f32x4 hi, bf16x8 (&part)[3]) {
         }
 }
 
-__device__ const float zeros[4] = {0.f, 0.f, 0.f, 0.f};
+__device__ const f32x4 zeros = {0.f, 0.f, 0.f, 0.f};      // (fetched as one piece of 16 bytes, and aligned to it)
 
 // An item is a tile and BN = 64 CB weight rows: each of the four wavefronts multiplies all rows of the tile with 16 CB weight rows of
 // its own, in blocks of 16 x 16; blocks of 16 rows past the tile's end are left out.  Stages of 32 terms.  The rows' parts are made
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256, CB == 2 ? 2 : 3) void gemm_f32_split_kernel(co
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int k = kt * BK + j * 16 + ld_g * 4;
-                    av[i][j] = fetch(k < K ? a_src[i] + k : zeros);
+                    av[i][j] = fetch(k < K ? a_src[i] + k : (const float*)&zeros);
                 }
             const int k = kt * BK + w_p * 4;
 #pragma unroll
