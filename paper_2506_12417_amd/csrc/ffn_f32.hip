@@ -13,6 +13,7 @@
 #include <type_traits>
 #include "common.h"
 #include "ffn_kernels.h"
+#include "ffn_f32_rule.h"
 
 namespace {
 
@@ -517,20 +518,11 @@ int launch_rows(const Args& g, hipStream_t st) {
 
 int moe_launch_gemm_f32(int epi, const void* a, int A, int K, int N, int E, const void* const* w, const moe_tile* tiles,
                         const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div) {
-    // Column blocks of 128 weight rows read the activations half as often; of 64 where 128 would leave fewer than four items
-    // per CU.  The few-row kernel where 64 would leave fewer than two (one with SwiGLU), or the experts hold few rows.  By the split
-    // kernel and by it, in us: 600 tokens, K = N = 1024, E = 4, k = 2 (320 items of 64) 55 and 42; 2000 tokens twice, K = 1024, N = 128, E = 4 28 and 25;
-    // 1300 tokens, K = N = 1024, E = 8 38 and 38; 1501 tokens twice, K = 2048, N = 768, E = 16 (660 items) 112 and 118.  Rows per expert:
-    // 1000 tokens of 32 experts, K = 1024, N = 2048 89 and 74; 900 of 16, K = 768, N = 1536 39 and 33; 2048 of 32 (64 rows each), K = 512, N = 2048 56 and
-    // 58; 4096 of 32, K = N = 1024 100 and 102.  With SwiGLU (N: gate and up) 250 tokens, K = 1024, N = 1024, E = 4 27 and 15; 40 tokens twice, K = 1024,
-    // N = 4096, E = 32 110 and 74; 300 of 16 77 and 57, 600 85 and 77; 240 tokens twice, K = 1000, N = 3072, E = 16 74 and 66; 2000, K = 512, N = 640, E = 8
-    // (360 items) 23 and 22; 1501 twice, K = 768, N = 4096, E = 16 177 and 211.
     const Args g = {a, A, K, N, E, w, tiles, hdr, out, ld_out, row_src, src_div};
-    const long long tiles_est = (A + BM - 1) / BM + E / 2, items = tiles_est * ((N + 63) / 64);
-    const bool glu = epi == MOE_EPI_SWIGLU, narrow = tiles_est * ((N + 127) / 128) < 4 * 256;
-    const bool in_reach = (long long)A * K < 1ll << 30 && (long long)N * K < 1ll << 30;     // of its 32-bit byte offsets
-    const bool rows = in_reach && (glu ? items < 256 || A <= 32ll * E : items < 2 * 256 || A <= 48ll * E);
-    if (rows) {
+    const bool glu = epi == MOE_EPI_SWIGLU;
+    const int kernel = moe_f32_kernel(glu, A, K, N, E);
+    const bool narrow = kernel == MOE_F32_SPLIT_64;
+    if (kernel == MOE_F32_ROWS) {
         if (glu) return launch_rows<MOE_EPI_SWIGLU>(g, st);
         return epi == MOE_EPI_RELU ? launch_rows<MOE_EPI_RELU>(g, st) : launch_rows<MOE_EPI_STORE>(g, st);
     }

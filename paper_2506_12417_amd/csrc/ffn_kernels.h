@@ -64,8 +64,7 @@ int moe_launch_gemm_rows_gather(int epi, const void* x, int A, int K, int N, int
                                 const int32_t* hdr, void* out, int ld_out, hipStream_t st, const int32_t* row_src, int src_div);
 
 // The same for the routed SwiGLU experts (rows gathered from x, k > 1) and a shared SwiGLU expert over all
-// T rows of x (one expert's plan) in one launch per product (phase 1, 2); the shared expert has
-// the same d and holds at most 128 rows.
+// T rows of x (one expert's plan) in one launch per product (phase 1, 2); the shared expert has the same d.
 int moe_launch_gemm_rows_shared(int phase, const void* x, int T, int d, int F, int E, int k, const void* const* w, const moe_tile* tiles,
                                 const int32_t* hdr, void* h, float* y_perm, const int32_t* perm, int shared_F,
                                 const void* const* s_w, const moe_tile* s_tiles, const int32_t* s_hdr, void* s_h, float* s_y,

@@ -145,8 +145,8 @@ def test_route_error_bound_covers_every_term(torch_gpu, E):
 
 @pytest.mark.parametrize("E,same,k", [(40, 2, 4), (100, 3, 6), (200, 2, 8), (200, 63, 8), (200, 64, 1), (200, 65, 5), (200, 130, 8)])
 def test_route_experts_with_and_without_a_neighbour(torch_gpu, E, same, k):
-    """Tokens whose first choices lie apart (their fp32 logits decide) beside `same` experts with the same or nearly the same logits
-    (recomputed in 64 bits), few and more than a wavefront has lanes for."""
+    """Tokens whose first choices lie apart beside `same` experts with the same or nearly the same logits, among the first choices or
+    behind them, few and more than a wavefront has lanes for."""
     torch = torch_gpu
     from paper_2506_12417_amd.layer import to_device
     T, d = 150, 192
@@ -1063,6 +1063,12 @@ F32_CASES = [
     ([400, 300, 500, 77], 1, 128, 4100, "relu", 1),
     ([900, 31, 600], 1, 64, 4096, "swiglu", 1),
     ([9] * 24, 1, 32, 64, "relu", 3),
+    # second products of both widths, first ones of the wider, by bf16 parts
+    ([1500, 1301], 1, 740, 100, "relu", 1),
+    ([2000, 1999, 1], 1, 2052, 68, "relu", 1),
+    ([2100, 1900], 1, 36, 2052, "relu", 1),
+    ([1901, 2037], 1, 100, 1056, "swiglu", 1),
+    ([610, 390, 500], 2, 132, 992, "swiglu", 1),
 ]
 
 
@@ -1111,8 +1117,11 @@ def test_f32_products_of_small_calls(torch_gpu, rows, k, d, F, act, policy):
     test_f32_products_agree_with_the_oracle(torch_gpu, rows, k, d, F, act, policy)
 
 
-@pytest.mark.parametrize("rows,d,F,act", [([40, 70], 100, 4096, "relu"), ([300, 17], 68, 4096, "swiglu"), ([64], 36, 160, "swiglu"),
-                                          ([400, 700], 100, 4096, "relu"), ([17, 40], 1028, 512, "relu")])
+F32_EXTREME_CASES = [([40, 70], 100, 4096, "relu"), ([300, 17], 68, 4096, "swiglu"), ([64], 36, 160, "swiglu"), ([400, 700], 100, 4096, "relu"),
+                     ([17, 40], 1028, 512, "relu"), ([1000, 1090], 68, 4096, "relu"), ([1000, 1090], 36, 2048, "swiglu")]
+
+
+@pytest.mark.parametrize("rows,d,F,act", F32_EXTREME_CASES)
 def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
     """Infinities, NaN, the largest values and very small ones come out of the products as fp32 arithmetic has them, and leave the
     other rows alone (the kernels multiply by bf16 parts where the values allow it)."""
@@ -1139,7 +1148,7 @@ def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
     layer.ffn()
     torch.cuda.synchronize()
     # the first product as the kernels have stored it: bound of an fp32 sum of d terms on the absolute products, and of bits
-    # below the smallest normal number
+    # below the smallest number
     h = to_numpy(layer.h)
     e = np.repeat(np.arange(E), rows)
     ex = {n: np.asarray(v, dtype=np.float64) for n, v in expert_dict(wl, inp).items()}
@@ -1147,22 +1156,26 @@ def test_fp32_products_of_extreme_values(torch_gpu, rows, d, F, act):
     with np.errstate(all="ignore"):
         prod = {n: np.stack([x64[i] @ ex[n][e[i]] for i in range(A)]) for n in ex if n in ("W1", "Wg", "Wu")}
         size = {n: np.stack([np.abs(x64[i]) @ np.abs(ex[n][e[i]]) for i in range(A)]) for n in prod}
-    first = "W1" if act == "relu" else "Wg"
-    if act == "relu":
-        fits = np.abs(size["W1"]) < 3e38
-        want, room = np.maximum(prod["W1"], 0), d * 2.0 ** -23 * size["W1"] + 2.0 ** -126
-        assert (np.abs(h[fits] - want[fits]) <= room[fits]).all()
-        assert (h[1][prod["W1"][1] > 0] == np.inf).all() and (h[1][prod["W1"][1] < 0] == 0).all()
-    assert np.isnan(h[5]).all() or act == "relu"       # (fmax(NaN, 0) is 0)
+        if act == "relu":
+            fits = np.abs(size["W1"]) < 3e38
+            want, room = np.maximum(prod["W1"], 0), d * 2.0 ** -23 * size["W1"] + d * 2.0 ** -149
+            assert (np.abs(h[fits] - want[fits]) <= room[fits]).all() and fits[[9, 21, 22]].all()
+            assert (h[1][prod["W1"][1] > 0] == np.inf).all() and (h[1][prod["W1"][1] < 0] == 0).all()
+            assert (h[5] == 0).all()                         # (the larger one of NaN and 0 is 0)
+            assert (np.abs(want[[9, 22]]) > 4 * room[[9, 22]]).mean() > 0.3      # (what is stored matters)
+        else:
+            # rows whose gates are infinite, no numbers or far outside the exponential's range: 0, an infinity or NaN
+            far = [1, 5, 20, 21]
+            z, u = prod["Wg"][far], prod["Wu"][far]
+            silu = z / (1 + np.exp(-z))
+            want = (silu * u).astype(np.float32)
+            assert np.array_equal(np.isnan(h[far]), np.isnan(want)) and np.isnan(want[1]).all()
+            kept = ~np.isnan(want)
+            assert np.isinf(want[kept]).any() and (want[kept][~np.isinf(want[kept])] == 0).all()
+            assert np.array_equal(h[far][kept], want[kept])
     normal = np.isfinite(x64).all(axis=1) & (np.abs(x64).max(axis=1) < 100) & (np.abs(x64).max(axis=1) > 1e-3)
     yp = O.grouped_ffn(xp[normal], np.concatenate([[0], np.cumsum([normal[e == i].sum() for i in range(E)])]), expert_dict(wl, inp), act)
     assert max_err_over_rms(to_numpy(layer.y_perm)[normal], yp) <= TOL["f32"]
-    # small activations: the products by their own size (row 9 far above the smallest normal number, row 22 below it)
-    if act == "relu":
-        assert (np.abs(h[9] - want[9]) <= d * 2.0 ** -23 * size["W1"][9]).all()
-    else:
-        z = prod[first][9] * prod["Wu"][9] / 2           # silu(z) = z / 2 for tiny z; the product is below fp32's range
-        assert (np.abs(h[9] - z) <= 2.0 ** -126).all()
 
 
 def _f32_first_product(torch, rows, d, F, act, xp, weights):
@@ -1227,7 +1240,10 @@ def test_fp32_products_of_tiny_values_with_large_ones(torch_gpu, rows, d, F, act
         assert (np.abs(h - silu * u) <= far)[fits].all()
 
 
-@pytest.mark.parametrize("rows,d,F", [([400, 700], 100, 4096), ([1000, 1090], 68, 4096), ([40, 70], 100, 512)])
+F32_SINGLE_TERM_SHAPES = [([400, 700], 100, 4096), ([1000, 1090], 68, 4096), ([40, 70], 100, 512)]
+
+
+@pytest.mark.parametrize("rows,d,F", F32_SINGLE_TERM_SHAPES)
 def test_fp32_products_of_single_terms_are_rounded_once(torch_gpu, rows, d, F):
     """Rows with one nonzero entry: every element is one product of two fp32 values, and comes out as its nearest fp32 number (up to
     the 2^-32 of it that sums of parts may lose)."""
