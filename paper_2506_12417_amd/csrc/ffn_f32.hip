@@ -238,6 +238,8 @@ __device__ const f32x4 zeros = {0.f, 0.f, 0.f, 0.f};      // (fetched as one pie
 // The sums are of values times 2^64 (split3).  An infinity or NaN, an operand of 2^95 or more and a sum of 2^64 or more make
 // infinities or NaNs of them: a wavefront with a sum that is not finite does its block again by fp32 matrix instructions from global
 // memory, so that such values come out as they do in fp32.  Everything else is exact in its parts, however small.
+// (2048 tokens twice, d=1024 F=2048 E=16, both products: 335 us, with one infinite token 413, all of them 848; by fp32 instructions alone
+// 393 always.  Fetching four bytes a lane and term, that second pass took 822 and 2740.)
 //
 // Bound by issue and latency as much as by the matrix cores: cutting takes as many vector instructions as the products take
 // matrix instructions' cycles.  Full tiles (6144 rows, K = 768, N = 4096) 148 TFLOP/s of fp32 work, 1.2 PFLOP/s of bf16; a quarter goes into
@@ -404,18 +406,36 @@ __global__ __launch_bounds__(256, CB == 2 ? 2 : 3) void gemm_f32_split_kernel(co
                 for (int h = 0; h < CB; ++h)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[m][h][r] = 0.f;
-            typedef const __attribute__((address_space(1))) float* gptr;
-            gptr a[RB], w[CB];
+            const float *a[RB], *w[CB];
 #pragma unroll
-            for (int m = 0; m < RB; ++m) a[m] = (gptr)(uintptr_t)row_of(m * 16 + l16);
+            for (int m = 0; m < RB; ++m) a[m] = row_of(m * 16 + l16) + lq * 4;
 #pragma unroll
-            for (int h = 0; h < CB; ++h) w[h] = (gptr)(uintptr_t)weights_of(h * 16 + l16);
-            for (int k = lq; k < K; k += 4)
+            for (int h = 0; h < CB; ++h) w[h] = weights_of(h * 16 + l16) + lq * 4;
+            // (16 terms at a time, four of a lane's to four instructions each, the next 16 on their way; past K both sides count as zero)
+            f32x4 an[RB], wn[CB];
+            auto ask = [&](int k) __attribute__((always_inline)) {
+                const bool in = k + lq * 4 < K;
 #pragma unroll
-                for (int m = 0; m < RB; ++m)
+                for (int m = 0; m < RB; ++m) an[m] = fetch(in ? a[m] + k : (const float*)&zeros);
 #pragma unroll
-                    for (int h = 0; h < CB; ++h)
-                        acc[m][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][k], w[h][k], acc[m][h], 0, 0, 0);
+                for (int h = 0; h < CB; ++h) wn[h] = fetch(in ? w[h] + k : (const float*)&zeros);
+            };
+            ask(0);
+            for (int k = 0; k < K; k += 16) {
+                f32x4 av[RB], wv[CB];
+#pragma unroll
+                for (int m = 0; m < RB; ++m) av[m] = an[m];
+#pragma unroll
+                for (int h = 0; h < CB; ++h) wv[h] = wn[h];
+                ask(k + 16);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int m = 0; m < RB; ++m)
+#pragma unroll
+                        for (int h = 0; h < CB; ++h)
+                            acc[m][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[m][j], wv[h][j], acc[m][h], 0, 0, 0);
+            }
         }
         // acc[m][h][r]: row 16 m + 4 lq + r, weight row 16 h + l16 of the wavefront's
         bool keep = true;
