@@ -73,11 +73,6 @@ static bool few_rows_per_expert(int A, int d, int F, int E, bool glu) {
 // the plan's tile height of a tile_m argument
 static int tile_height(int tile_m) { return tile_m & ~MOE_TILE_WHOLE_PLAN; }
 
-static bool few_rows_call(int A, int d, int F, int E, moe_act act, int tile_m) {
-    return tile_height(tile_m) == 128 && g_kernel_mode == 0 && few_rows_per_expert(A, d, F, E, act == MOE_SWIGLU) &&
-           (long long)A * (d > F ? d : F) < (1ll << 31);
-}
-
 // Whether a product over 128-row tiles is better done two tiles at a time by the four-wavefront kernels (for a plan of all A
 // rows only, MOE_TILE_WHOLE_PLAN: four of 32 experts, judged by all 12000 rows, took 41 us by single tiles and 64 in pairs).
 // An item of 256 rows takes them as long whether its second tile is there or not, 1.5 to 2 times what one of 128 rows takes
@@ -102,6 +97,15 @@ static int wide_pairs(int A, int E, int K, int N) {
     if (K >= 1408 && before * cb > MOE_GEMM_GRID && after * cb <= MOE_GEMM_GRID) return MOE_PAIRS_ONE_ROUND;
     if (K >= 4096 && rows >= 500ll * E && rows / 128 + E <= MOE_PAIRS_MAX_TILES && after * cb >= 8 * MOE_GEMM_GRID) return MOE_PAIRS_MANY;
     return 0;
+}
+
+// (A product that moe_ffn_pairs says is taken in pairs is: 130 rows of one expert on very wide matrices could be either's.  With
+// MOE_TILE_WHOLE_PLAN or without, so that it changes no bits.)
+static bool few_rows_call(int A, int d, int F, int E, moe_act act, int tile_m) {
+    if (tile_height(tile_m) != 128 || g_kernel_mode != 0 || (long long)A * (d > F ? d : F) >= (1ll << 31)) return false;
+    const int n1 = act == MOE_SWIGLU ? 2 * F : F;
+    if (wide_pairs(A, E, d, n1) || wide_pairs(A, E, F, d)) return false;
+    return few_rows_per_expert(A, d, F, E, act == MOE_SWIGLU);
 }
 
 extern "C" int moe_ffn_pairs(int tile_m, int A, int E, int K, int N) {

@@ -1303,7 +1303,9 @@ def test_small_calls_by_either_family(torch_gpu, rows, d, F, act, mode):
     ([953, 953], 512, 1024, "relu", False), ([500, 500], 512, 1024, "relu", True), ([600] * 8, 256, 512, "relu", False),
     ([300] * 8, 768, 768, "relu", False), ([7] * 8, 1152, 2560, "swiglu", True), ([90] * 3, 1024, 1024, "swiglu", True),
     # few experts of few rows and many multiply-adds
-    ([64], 2048, 12288, "swiglu", True), ([40, 50], 2048, 9216, "swiglu", True), ([60] * 6, 1344, 12288, "swiglu", False)])
+    ([64], 2048, 12288, "swiglu", True), ([40, 50], 2048, 9216, "swiglu", True), ([60] * 6, 1344, 12288, "swiglu", False),
+    # two tiles of matrices so wide that they are taken as a pair, within the line of multiply-adds
+    ([130], 1408, 16448, "swiglu", False)])
 def test_which_family_serves_a_small_call(torch_gpu, rows, d, F, act, few):
     """The few-row kernels add a contraction in parts, so their bits are not the tile kernels' (mode 1)."""
     torch = torch_gpu
@@ -1331,6 +1333,8 @@ def test_which_family_serves_a_small_call(torch_gpu, rows, d, F, act, few):
     torch.cuda.synchronize()
     assert max_err_over_rms(to_numpy(got[0]), to_numpy(got[1])) <= 1e-2     # (a rounding of h to half the other way)
     assert torch.equal(got[0], got[1]) != few
+    pairs = [B.moe_ffn_pairs(layer.ffn_tile_m, A, E, K, N) for K, N in ((d, layer.experts.rows_in), (F, d))]
+    assert not (few and any(pairs)) and (any(pairs) or rows != [130])
 
 
 @pytest.mark.parametrize("rows,d,F,tile_m,bins", [([300], 256, 1024, 128, 8), ([700, 10], 256, 512, 128, 8), ([900], 256, 512, 256, 8),
