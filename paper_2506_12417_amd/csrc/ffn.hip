@@ -52,7 +52,9 @@ extern "C" int moe_ffn_kernel_mode(int mode) {
 // Whether the few-row kernels (ffn_rows.hip) serve a plan of 128-row tiles.  The tile kernels fetch an expert through one XCD, one
 // stage of 64 terms after the other: both products last about (d + F) / 64 stages of 0.35 us, however small they are.  The few-row
 // kernels fetch it through the whole chip, but read the rows again for every 32 weight rows and the weights for every 64 rows: beyond the
-// fetch of the weights they take 360 TFLOP/s.  So they serve calls that they multiply within those stages, 2 MFLOP per term of d + F;
+// fetch of the weights they take 360 TFLOP/s.  So they serve calls that they multiply within those stages, 2 MFLOP per term of d + F,
+// unless as many experts as XCDs have matrices of 32 MB and more, whose fetch outlasts the stages (4096 x 14336, E=8, SwiGLU 12 rows each 475 : 473,
+// ReLU 12 rows 315 : 297; 3072 x 8192, E=16 8 rows 303 : 273);
 // where both stream the weights at the memory's rate, calls of few rows per expert (a few hot ones make up for the bins); and with
 // fewer experts than XCDs, up to the rows at which the idle XCDs are made up for.  flops: of both products.
 // Measured (both products in us, few-row against tile kernels; the line in GFLOP or rows):
@@ -66,7 +68,7 @@ extern "C" int moe_ffn_kernel_mode(int mode) {
 //           four of 32 280 : 328, 64 416 : 341; six of 8 357 : 364, 32 422 : 408
 static bool few_rows_per_expert(int A, int d, int F, int E, bool glu) {
     const double flops = 2.0 * A * d * F * (glu ? 3 : 2);
-    if (flops <= 2e6 * ((double)d + F) || A <= (long long)(glu ? 8 : 3) * E) return true;
+    if ((flops <= 2e6 * ((double)d + F) && (E < 8 || (long long)d * F < (1 << 24))) || A <= (long long)(glu ? 8 : 3) * E) return true;
     return E < 8 && A <= 64 * E && A <= 32 * (8 - E);
 }
 

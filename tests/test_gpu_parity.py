@@ -1302,6 +1302,7 @@ def test_small_calls_by_either_family(torch_gpu, rows, d, F, act, mode):
     ([200], 1024, 1024, "relu", True), ([100] * 16, 512, 1024, "relu", False), ([50] * 16, 512, 1024, "swiglu", True),
     ([953, 953], 512, 1024, "relu", False), ([500, 500], 512, 1024, "relu", True), ([600] * 8, 256, 512, "relu", False),
     ([300] * 8, 768, 768, "relu", False), ([7] * 8, 1152, 2560, "swiglu", True), ([90] * 3, 1024, 1024, "swiglu", True),
+    ([12] * 8, 2048, 8192, "swiglu", False), ([12] * 8, 1984, 8192, "swiglu", True),
     # few experts of few rows and many multiply-adds
     ([64], 2048, 12288, "swiglu", True), ([40, 50], 2048, 9216, "swiglu", True), ([60] * 6, 1344, 12288, "swiglu", False),
     # two tiles of matrices so wide that they are taken as a pair, within the line of multiply-adds
